@@ -366,6 +366,15 @@ __global__ __launch_bounds__(256) void gemm_splitk_reduce_kernel(const float *__
     *(uint2 *)(Y + (size_t)t * ldy + n0 + n) = o.u;
 }
 
+hipError_t launch_splitk_reduce(const float *partial, int k_split, int T, int n0, int width, const paro_half_t *bias,
+                                paro_half_t *Y, int64_t ldy, hipStream_t s)
+{
+    const long quads = (long)T * (width / 4);
+    hipLaunchKernelGGL(gemm_splitk_reduce_kernel, dim3((unsigned)((quads + 255) / 256)), dim3(256), 0, s, partial, k_split, T, n0,
+                       width, (const _Float16 *)bias, (_Float16 *)Y, ldy);
+    return hipGetLastError();
+}
+
 // Block slots of a launch over m_tiles x n_tiles tiles: the XCD patches are rounded up to whole
 // rounds of 8 (see the kernel's block numbering); slots without a tile exit at once.
 void gemm_patches(int m_tiles, int n_tiles, int &patch_m, int &patch_n, int &blocks)
@@ -494,6 +503,24 @@ bool gemm_supported(const paro_w4_weight &w, int64_t ldx, int64_t ldy, int T)
 // streaming decode kernel at moderate token counts (see plan_gemm for the model).
 double gemm_estimate_us(const paro_w4_weight &w, int T) { return plan_gemm(w, T).est_us; }
 
+// The same for the choice between either and the kernel of linear_tile.hip: fitted to 700 timings (58 shapes, 33 to 2048
+// tokens), 6 % off in the mean for unsplit launches, 8 and 14 % for split ones.  (plan_gemm's model ranks its own
+// choices, but is 24 % off as a time.)
+double gemm_fitted_us(const paro_w4_weight &w, int T)
+{
+    const GemmPlan p = plan_gemm(w, T);
+    const double n_ks = w.c_in / kBK, out_mb = (double)T * w.c_out * 2.0 / 1.0e6;
+    if (p.big_split > 1) return 1.303 * p.big_steps + 0.378 * 4.0 * p.big_split * out_mb - 3.6;
+    if (p.n_192 > 0) return 1.2 + 1.678 * 0.8 * n_ks + 0.34 * out_mb;
+    if (p.n_main == 0) {
+        if (p.k_split > 1) return 7.9 + 0.906 * p.k_steps + 0.213 * 4.0 * p.k_split * out_mb;
+        const long tiles = (long)((T + 127) / 128) * p.n_all;
+        return 2.8 + 0.846 * n_ks * (double)((tiles + 255) / 256) + 0.374 * out_mb;
+    }
+    const long rounds = ((long)p.m_big * p.n_main + 255) / 256;
+    return 1.2 + 1.678 * n_ks * ((double)rounds + (p.n_small ? 0.6 : 0.0)) + 0.34 * out_mb;
+}
+
 // output tiles [n_tile0, n_tile0 + n_count) x all token tiles
 template <int MI, int NI, int WM, int WN, bool SPLITK = false>
 static hipError_t launch_gemm_cfg(GemmArgs &a, int n_tile0, int n_count, hipStream_t s)
@@ -533,10 +560,7 @@ hipError_t launch_gemm(const paro_w4_weight &w, const paro_half_t *X, int64_t ld
     const GemmPlan p = plan_gemm(w, T);
     if (p.n_192 > 0) return launch_gemm_cfg<2, 3, 4, 2>(a, 0, p.n_192, s);
     auto reduce = [&](int k_split) {
-        const long quads = (long)T * (a.part_w / 4);
-        hipLaunchKernelGGL(gemm_splitk_reduce_kernel, dim3((unsigned)((quads + 255) / 256)), dim3(256), 0, s,
-                           (const float *)scratch, k_split, T, a.part_n0, a.part_w, (const _Float16 *)w.bias, (_Float16 *)Y, ldy);
-        return hipGetLastError();
+        return launch_splitk_reduce((const float *)scratch, k_split, T, a.part_n0, a.part_w, w.bias, Y, ldy, s);
     };
     const bool have_scratch = scratch && scratch_bytes >= p.scratch && ((uintptr_t)scratch % 16) == 0;
     if (p.big_split > 1) {

@@ -183,9 +183,28 @@ hipError_t launch_mxfp4_linear(const paro_mxfp4_weight &w, const uint32_t *x_cod
 hipError_t launch_quantize_act_mxfp4(const paro_rotation &rot, const paro_half_t *X, int64_t ldx, int T, uint32_t *codes,
                                      uint8_t *scales, hipStream_t s);
 
+// Weights in the interchange layout, up to 32 tokens (linear_rows.hip).  scratch: room for the partial sums of K split
+// between blocks (any contents before and after); without it the call runs unsplit.
+bool linear_rows_supported(const paro_w4_weight &w, int64_t ldx, int T);
+size_t linear_rows_scratch_bytes(const paro_w4_weight &w, int T);
+hipError_t launch_linear_rows(const paro_w4_weight &w, const paro_half_t *X, int64_t ldx, paro_half_t *Y, int64_t ldy,
+                              int T, void *scratch, size_t scratch_bytes, hipStream_t s);
+
+// Tiled linear with the weights in registers (linear_tile.hip), repacked or interchange layout; scratch as above.
+bool linear_tile_supported(const paro_w4_weight &w, bool interchange);
+double linear_tile_estimate_us(const paro_w4_weight &w, int T);
+size_t linear_tile_scratch_bytes(const paro_w4_weight &w, int T);
+hipError_t launch_linear_tile(const paro_w4_weight &w, bool interchange, const paro_half_t *X, int64_t ldx, paro_half_t *Y,
+                              int64_t ldy, int T, void *scratch, size_t scratch_bytes, hipStream_t s);
+
+// Y[t][n0 + n] = fp16(sum over k_split of partial[k][t][n] + bias[n0 + n]), slices in index order (gemm.hip)
+hipError_t launch_splitk_reduce(const float *partial, int k_split, int T, int n0, int width, const paro_half_t *bias,
+                                paro_half_t *Y, int64_t ldy, hipStream_t s);
+
 // Prefill-side linear (MFMA GEMM on the repacked weight), any T.
 bool gemm_supported(const paro_w4_weight &w, int64_t ldx, int64_t ldy, int T);
 double gemm_estimate_us(const paro_w4_weight &w, int T);
+double gemm_fitted_us(const paro_w4_weight &w, int T);
 // scratch: room for split-K partial tiles (gemm_scratch_bytes; any contents before and after);
 // without it the call runs unsplit.
 size_t gemm_scratch_bytes(const paro_w4_weight &w, int T);

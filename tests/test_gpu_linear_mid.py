@@ -1,0 +1,82 @@
+"""The W4A16 linear between the streaming decode kernels and the GEMM (linear_tile.hip) and on weights in the interchange
+layout (linear_rows.hip up to 32 tokens, linear_tile.hip above), against the oracle's contraction of the same fp16
+activations.
+
+Both kernels multiply q - z exactly, apply the group's scale to fp32 sums and round once, so every output must lie within
+half an fp16 ulp of the oracle's fp64 value plus the fp32 rounding of its sums:
+    |err| <= 2^-11 |y| 1.001 + (C + 64) 2^-24 sum |x w^| + 2^-25
+(one rounding of at most 2^-24 of the running sum per accumulated product, per group scale and per combined partial sum)."""
+import numpy as np
+import pytest
+
+import oracle
+import paro_inputs as pin
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def P():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU visible")
+    import paper_2511_10645_amd as paro
+    return paro
+
+
+def _weight(P, li, bias, form):
+    import torch
+    w = P.W4Weight(li.qweight, li.scales, li.qzeros, bias=bias)
+    if form == "packed":
+        P.paro_w4_repack(w)
+        w.drop_interchange()
+    elif form == "scales_odd":                        # scales not 4-byte aligned: the kernels' dword loads do not apply
+        buf = torch.zeros(w.scales.numel() + 1, dtype=torch.float16, device="cuda")
+        buf[1:] = w.scales.flatten()
+        w.scales = buf[1:].view(w.scales.shape)
+        w.c.scales = w.scales.data_ptr()
+    return w
+
+
+CASES = [
+    # interchange layout: blocks of 16 tokens, the last group of a round missing, outputs that end inside a block
+    (1, 640, 48, "plain"), (1, 11008, 272, "plain"), (16, 128, 16, "plain"), (17, 1920, 80, "plain"), (32, 640, 528, "plain"),
+    (24, 2176, 4112, "plain"), (33, 128, 16, "plain"), (33, 640, 144, "plain"), (64, 1152, 2064, "plain"),
+    (65, 1920, 272, "plain"), (129, 4096, 1040, "plain"), (200, 2176, 1296, "plain"), (5, 640, 80, "scales_odd"), (40, 640, 80, "scales_odd"),
+    # repacked: 64- and 128-token tiles, K split and not, ragged tokens and outputs
+    (33, 4096, 4112, "packed"), (64, 4096, 6144, "packed"), (64, 512, 16400, "packed"), (80, 2048, 2064, "packed"),
+    (128, 4096, 2048, "packed"), (129, 1536, 4112, "packed"), (193, 4096, 1552, "packed"), (40, 13824, 1040, "packed"),
+]
+
+
+@pytest.mark.parametrize("T,c_in,c_out,form", CASES)
+@pytest.mark.parametrize("rotated", [False, True])
+def test_linear_against_oracle(P, T, c_in, c_out, form, rotated):
+    import torch
+    print(f"linear T={T} {c_in}->{c_out} {form} rotated={rotated}", flush=True)
+    li = pin.make_custom(4000 + T + c_in, T, c_in, c_out, n_outlier=2)
+    bias = pin.make_bias(8, 8, c_out) if T % 2 else None
+    w = _weight(P, li, bias, form)
+    rot = None
+    if rotated:
+        rot = P.Rotation(li.pairs, li.theta, li.ch_scale)
+        P.paro_rotation_plan_build(rot)
+    ws = P.Workspace(P.paro_workspace_bytes(rot, w, T))
+    x = torch.as_tensor(li.x).cuda()
+    ybuf = torch.full((T, c_out + 24), 7.0, dtype=torch.float16, device="cuda")
+    if rotated:
+        P.paro_rotated_linear(rot, w, x, ws, Y=ybuf[:, 8:8 + c_out])
+        u = P.paro_rotate_scale(rot, x).cpu().numpy().astype(np.float64) if T > 4 or form != "packed" else None   # what the linear read
+    else:
+        P.paro_w4a16_linear(w, x, ws if ws.nbytes else None, Y=ybuf[:, 8:8 + c_out])
+        u = li.x.astype(np.float64)
+    got = ybuf.cpu().numpy().astype(np.float64)
+    assert (got[:, :8] == 7.0).all() and (got[:, 8 + c_out:] == 7.0).all()      # padding untouched
+    y = oracle.linear(u, li.qweight, li.scales, li.qzeros, bias)
+    g = c_in // 128
+    what = (li.codes.reshape(c_out, g, 128).astype(np.float64) - li.zeros.T[:, :, None]) * li.scales.T.astype(np.float64)[:, :, None]
+    mass = np.abs(u) @ np.abs(what.reshape(c_out, c_in)).T
+    allowed = 2.0 ** -11 * np.abs(y) * 1.001 + (c_in + 64) * 2.0 ** -24 * mass + 2.0 ** -25
+    worst = float((np.abs(got[:, 8:8 + c_out] - y) / allowed).max())
+    print(f"  worst err/allowed = {worst:.3f}", flush=True)
+    assert worst <= 1.0
