@@ -1,340 +1,322 @@
-// Weight side of the method, offline: the equivalent transform of Eq. 8 applied to every output
-// row of a dense fp16 weight, then the round-to-nearest INT4 quantiser of Eq. 1 with one
-// (scale, zero) per 128 input channels (Section 2.1), written in the interchange layout that
-// paro_w4_repack and the linear kernels consume.
+// Quantisers of transformed rows: the weight side of the method, offline (the equivalent transform of Eq. 8 applied to every
+// output row of a dense fp16 weight, then the round-to-nearest INT4 quantiser of Eq. 1 with one (scale, zero) per 128
+// input channels, Section 2.1), the activation side of the W4A4 extension (App. A.3: Y' = Q(X T^-1) . Q(T W) + b: the
+// transformed activations quantised while they are still in the wave's registers), and both with a microscaling FP4
+// quantiser (MXFP4 of the OCP Microscaling Formats specification, the 4-bit type the matrix cores of this chip take).
 //
-//      w'_n = R_K ... R_1 . diag(1 / ch_scale) . w_n          (scale_order 0; Eq. 8, weight side)
-//      s = (max - min) / 15,  z = -round(min / s),  q = clamp(round(w' / s) + z, 0, 15)
+//   weight       w'_n = R_K ... R_1 . diag(1 / ch_scale) . w_n      (scale_order 0; the plan's multipliers are reciprocated)
+//   activations  x'   = R_K ... R_1 . diag(ch_scale) . x
+//   INT4         s = (max - min) / 15,  z = -round(min / s),  q = clamp(round(v / s) + z, 0, 15) per row and group; the
+//                decisions in fp32 with the fp16-rounded scale that is stored (IEEE division, round-half-to-even), scale
+//                floor 2^-14, zero point clamped to 0..15.  The paper names no activation quantiser of its own: the
+//                same decisions per token and group.
+//   MXFP4        32 consecutive channels share 2^e, e = floor(log2(max |v|)) - 2 (>= -127), stored as e + 127; every value
+//                becomes the E2M1 code of v / 2^e, to nearest, ties to the even code, saturated at 6.
+// so that  sum_c (q - z) s . x'_c  ~  w_n . x  for the activations x' that paro_rotate_scale produces (Eq. 2).
 //
-// so that  sum_c (q - z) s . x'_c  ~  w_n . x  for the activations x' = R_K ... R_1 . S . x that
-// paro_rotate_scale produces (Eq. 2).  One wavefront per (row, group), exactly as the
-// activation kernel: the lane's two fp32 registers hold the pair being rotated; the group's
-// minimum and maximum are wave reductions.  The integer decisions are taken in fp32 with the
-// fp16-rounded scale that is stored (IEEE division, round-half-to-even); the scale has the
-// floor 2^-14; the zero point is clamped to 0..15.  A block handles 8 consecutive rows of one
-// group, so that their 8 zero points fill one output word.
+// One wavefront owns a channel group and a run of rows, four rows at a time, with the lane plan and layer loop of the
+// activation kernel (rotate_lane.h): the plan (7.4 KB at K = 8, 29 times a row's group) is read once per run, the four
+// rows' chains of multiply-adds and permutes are independent, and rows go through a wave-private LDS area as
+// [channel][4 rows].  What bounds it is the vector pipes: 38 instructions per (row, group) of rotation, and the rest was
+// made small against that -
+//   - INT4: minimum and maximum of the four rows are reduced together, each swap of half waves merging two rows, so that
+//     every 16 lanes end up with one row's and the scale, its reciprocal and the zero point are computed once for all
+//     four; v / s is the correctly rounded quotient from the correctly rounded reciprocal and one residual;
+//   - MXFP4: the rotated values are read back in channel order, 8 per lane, so that a block's maximum is two steps within
+//     four lanes and the codes are four instructions of the FP4 converter (equal to the thresholds of the format on
+//     every tie and its neighbours over the whole range of exponents).
+// Measured (before: one row of INT4 weights per wave, plan re-read for each; MXFP4 one row at a time, 14 instructions of
+// thresholds per value): INT4 weight 28672 x 4096 395 -> 142 us (448 -> 140 repeated on one weight), MXFP4 activations
+// 2048 x 4096 21.0 -> 12.8, 2048 x 14336 55.8 -> 36.4 us, INT4 activations 25.4 -> 15.1 and 80.3 -> 40.3 us; the same bits
+// throughout.
 #include "paro_internal.h"
 #include "rotate_lane.h"
+#include <type_traits>
 
 namespace paro {
 
-constexpr int kQuantRows = 8;      // rows (waves) per block = zero points per packed word
+constexpr int kQuantWaves = 4;       // waves per block
+constexpr int kQuantRows = 4;        // rows side by side
+constexpr int kQuantBatches = 8;     // most batches of kQuantRows rows per wave (unrolled, see rotate.hip)
+constexpr int kQuantPad = kGroup + 4;
 
-// K >= 0: rotation with K layers from the plan; K < 0: no transform (plain RTN).
-template <int K>
-__global__ __launch_bounds__(kQuantRows * 64) void quantize_rows_kernel(const uint32_t *__restrict__ plan,
-                                                                         const _Float16 *__restrict__ W, int64_t ldw,
-                                                                         int N, int C, uint32_t *__restrict__ qweight,
-                                                                         _Float16 *__restrict__ scales,
-                                                                         uint32_t *__restrict__ qzeros)
+enum QuantKind { kW4Weight, kA4Act, kMxAct, kMxWeight };
+
+struct QuantArgs {
+    const uint32_t *plan;
+    const _Float16 *X; int64_t ldx;
+    int T, C, rows_per_wave;         // rows; rows_per_wave: a multiple of kQuantRows (of 8 for kW4Weight)
+    uint32_t *codes;                 // [T][C/8]
+    _Float16 *scales;                // kW4Weight: [C/128][T], kA4Act: [T][C/128]
+    uint32_t *qzeros;                // kW4Weight: [C/128][T/8]
+    uint8_t *bytes;                  // kA4Act: zero points [T][C/128]; MXFP4: scales [T][C/32]
+};
+
+template <int N, class F, int I = 0>
+__device__ __forceinline__ void quant_while(F &&f)
 {
-    __shared__ _Float16 s_stage[kQuantRows][kGroup];
-    __shared__ uint8_t s_codes[kQuantRows][kGroup];
-    __shared__ uint32_t s_z[kQuantRows];
-    __shared__ _Float16 s_s[kQuantRows];
-    const int g = blockIdx.x;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int n = blockIdx.y * kQuantRows + wave;      // N is a multiple of 8
-
-    // the row's 128 channels of this group, two per lane in channel order
-    const uint32_t raw = *((const uint32_t *)(W + (size_t)n * ldw + (size_t)g * kGroup) + lane);
-    float va, vb;
-    int ch_a, ch_b;
-    if constexpr (K >= 0) {
-        LanePlan<K> P;
-        load_lane_plan<K>(plan + (size_t)g * plan_group_dwords(K), lane, P);
-        *(uint32_t *)&s_stage[wave][2 * lane] = raw;
-        __builtin_amdgcn_wave_barrier();
-        // the plan carries the activation-side multipliers; the weights take their reciprocals
-        float a[1] = {(float)s_stage[wave][P.in_a] * (1.0f / P.sia)};
-        float b[1] = {(float)s_stage[wave][P.in_b] * (1.0f / P.sib)};
-        rotate_layers<K, 1>(P, a, b);
-        va = a[0] * (1.0f / P.soa); vb = b[0] * (1.0f / P.sob);
-        ch_a = P.out_a; ch_b = P.out_b;
-    } else {
-        union { uint32_t u; _Float16 h[2]; } c; c.u = raw;
-        va = (float)c.h[0]; vb = (float)c.h[1];
-        ch_a = 2 * lane; ch_b = 2 * lane + 1;
-    }
-
-    // Eq. 1 on the group
-    float mn = fminf(va, vb), mx = fmaxf(va, vb);
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) {
-        mn = fminf(mn, __shfl_xor(mn, off, 64));
-        mx = fmaxf(mx, __shfl_xor(mx, off, 64));
-    }
-    float s32 = (mx - mn) / 15.0f;
-    if (!(s32 >= 6.103515625e-05f)) s32 = 6.103515625e-05f;
-    const _Float16 s16 = (_Float16)s32;
-    const float s = (float)s16;
-    float zf = -rintf(mn / s);
-    zf = fminf(fmaxf(zf, 0.0f), 15.0f);
-    const float qa = fminf(fmaxf(rintf(va / s) + zf, 0.0f), 15.0f);
-    const float qb = fminf(fmaxf(rintf(vb / s) + zf, 0.0f), 15.0f);
-    s_codes[wave][ch_a] = (uint8_t)qa;
-    s_codes[wave][ch_b] = (uint8_t)qb;
-    if (lane == 0) { s_z[wave] = (uint32_t)zf; s_s[wave] = s16; }
-    __syncthreads();
-
-    if (lane < kGroup / 8) {        // 16 words of 8 codes, code k of a word in bits 4k..4k+3
-        uint32_t word = 0;
-#pragma unroll
-        for (int k = 0; k < 8; ++k) word |= (uint32_t)s_codes[wave][lane * 8 + k] << (4 * k);
-        qweight[(size_t)n * (C / 8) + (size_t)g * (kGroup / 8) + lane] = word;
-    }
-    if (threadIdx.x < kQuantRows) scales[(size_t)g * N + (size_t)blockIdx.y * kQuantRows + threadIdx.x] = s_s[threadIdx.x];
-    if (threadIdx.x == 0) {
-        uint32_t word = 0;
-#pragma unroll
-        for (int k = 0; k < kQuantRows; ++k) word |= s_z[k] << (4 * k);
-        qzeros[(size_t)g * (N / 8) + blockIdx.y] = word;
+    if constexpr (I < N) {
+        if (f(std::integral_constant<int, I>{})) quant_while<N, F, I + 1>(static_cast<F &&>(f));
     }
 }
 
-template <int K>
-static hipError_t launch_quantize_k(const uint32_t *plan, const paro_half_t *W, int64_t ldw, int N, int C,
-                                    uint32_t *qweight, paro_half_t *scales, uint32_t *qzeros, hipStream_t s)
+// v of another lane of the same 16 (DPP control word CTRL)
+template <int CTRL>
+__device__ __forceinline__ float dpp(float v)
 {
-    hipLaunchKernelGGL(quantize_rows_kernel<K>, dim3(C / kGroup, N / kQuantRows), dim3(kQuantRows * 64), 0, s, plan,
-                       (const _Float16 *)W, ldw, N, C, qweight, (_Float16 *)scales, qzeros);
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, true));
+}
+constexpr int kQuadXor1 = 0xB1, kQuadXor2 = 0x4E, kHalfMirror = 0x141, kMirror = 0x140;
+
+// Maximum over the wave of four values per lane; lanes 0-15 return that of v[0], 16-31 of v[2], 32-47 of v[1], 48-63 of v[3].
+__device__ __forceinline__ float wave_max4(const float (&v)[4])
+{
+    typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+    auto merge32 = [](float a, float b) {
+        const u32x2 t = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+        return fmaxf(__uint_as_float(t[0]), __uint_as_float(t[1]));
+    };
+    const u32x2 t = __builtin_amdgcn_permlane16_swap(__float_as_uint(merge32(v[0], v[1])), __float_as_uint(merge32(v[2], v[3])), false, false);
+    float m = fmaxf(__uint_as_float(t[0]), __uint_as_float(t[1]));
+    m = fmaxf(m, dpp<kQuadXor1>(m));
+    m = fmaxf(m, dpp<kQuadXor2>(m));
+    m = fmaxf(m, dpp<kHalfMirror>(m));
+    return fmaxf(m, dpp<kMirror>(m));
+}
+constexpr int kRowLane[4] = {0, 32, 16, 48};         // a lane that holds row u's maximum
+__device__ __forceinline__ int row_of_lane(int lane) { return ((lane >> 5) & 1) | ((lane >> 3) & 2); }
+__device__ __forceinline__ float from_lane(float v, int lane) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), lane)); }
+
+// rotate_layers with the order of the two products of every sum written out (the one that is there first is rounded, the
+// later one joins it in a fused multiply-add): a code on a rounding tie must not depend on how the compiler schedules.
+template <int K>
+__device__ __forceinline__ void quant_rotate(const LanePlan<K> &P, float (&a)[kQuantRows], float (&b)[kQuantRows])
+{
+#pragma unroll
+    for (int l = 0; l < K; ++l)
+#pragma unroll
+        for (int u = 0; u < kQuantRows; ++u) {
+            const float na = l == 0 ? fmaf(P.m00[l], a[u], P.m01[l] * b[u]) : fmaf(P.m01[l], b[u], P.m00[l] * a[u]);
+            const float nb = l == 0 ? fmaf(P.m10[l], a[u], P.m11[l] * b[u]) : fmaf(P.m11[l], b[u], P.m10[l] * a[u]);
+            a[u] = na;
+            b[u] = (l + 1 < K) ? __int_as_float(__builtin_amdgcn_ds_bpermute(P.src[l], __float_as_int(nb))) : nb;
+        }
+}
+
+// K < 0: no transform (rows quantised as they are).
+template <int K, int KIND>
+__global__ __launch_bounds__(kQuantWaves * 64) void quantize_kernel(QuantArgs a)
+{
+    constexpr bool WSIDE = KIND == kW4Weight || KIND == kMxWeight, INT4 = KIND == kW4Weight || KIND == kA4Act;
+    __shared__ __attribute__((aligned(16))) uint32_t s_stage[kQuantWaves][kGroup * 2];                   // [channel][4 rows] fp16
+    __shared__ __attribute__((aligned(16))) uint32_t s_out[kQuantWaves][INT4 ? kGroup : 4 * kQuantPad];  // codes [channel][4 rows], or values [4 rows][channel]
+    const int g = blockIdx.x, G = a.C / kGroup;
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int64_t t0 = ((int64_t)blockIdx.y * kQuantWaves + wave) * a.rows_per_wave;
+    if (t0 >= a.T) return;
+    const int n_rows = (int)(a.T - t0 < a.rows_per_wave ? a.T - t0 : a.rows_per_wave);
+
+    // the wave's rows from one uniform address each (row strides of weights are not limited); rows beyond the run repeat
+    // its last one and are not written
+    const _Float16 *x0 = a.X + t0 * a.ldx + (size_t)g * kGroup;
+    auto load_row = [&](int r) { return *((const uint32_t *)(x0 + (int64_t)(r < n_rows ? r : n_rows - 1) * a.ldx) + lane); };
+    uint32_t cur[kQuantRows], nxt[kQuantRows];
+#pragma unroll
+    for (int u = 0; u < kQuantRows; ++u) cur[u] = load_row(u);
+
+    LanePlan<(K > 0 ? K : 0)> P;
+    float ia = 1.f, ib = 1.f, oa = 1.f, ob = 1.f;
+    int ch_a = 2 * lane, ch_b = 2 * lane + 1;
+    if constexpr (K >= 0) {
+        load_lane_plan<K>(a.plan + (size_t)g * plan_group_dwords(K), lane, P);
+        // the plan carries the activation-side multipliers; the weights take their reciprocals
+        ia = WSIDE ? 1.0f / P.sia : P.sia; ib = WSIDE ? 1.0f / P.sib : P.sib;
+        oa = WSIDE ? 1.0f / P.soa : P.soa; ob = WSIDE ? 1.0f / P.sob : P.sob;
+        ch_a = P.out_a; ch_b = P.out_b;
+    }
+    typedef _Float16 half4v __attribute__((ext_vector_type(4)));
+    typedef uint32_t u32x4v __attribute__((ext_vector_type(4)));
+    char *sp = (char *)s_stage[wave];
+    auto lo_pair = [](uint32_t x, uint32_t y) { return (x & 0xffffu) | (y << 16); };
+    auto hi_pair = [](uint32_t x, uint32_t y) { return (x >> 16) | (y & 0xffff0000u); };
+    const int orow = lane >> 4, oword = lane & 15;       // the row of a batch and its 8 channels this lane writes out
+    uint32_t zword = 0;
+
+    quant_while<kQuantBatches>([&](auto I) {
+        constexpr int t = I * kQuantRows;
+        if (t >= n_rows) return false;
+#pragma unroll
+        for (int u = 0; u < kQuantRows; ++u) nxt[u] = load_row(t + kQuantRows + u);
+        float va[kQuantRows], vb[kQuantRows];
+        if constexpr (K >= 0) {
+            const u32x4v in = {lo_pair(cur[0], cur[1]), lo_pair(cur[2], cur[3]), hi_pair(cur[0], cur[1]), hi_pair(cur[2], cur[3])};
+            *(u32x4v *)(sp + lane * 16) = in;
+            __builtin_amdgcn_wave_barrier();
+            const half4v ha = *(const half4v *)(sp + P.in_a * 8), hb = *(const half4v *)(sp + P.in_b * 8);
+#pragma unroll
+            for (int u = 0; u < kQuantRows; ++u) { va[u] = (float)ha[u] * ia; vb[u] = (float)hb[u] * ib; }
+            quant_rotate<K>(P, va, vb);
+#pragma unroll
+            for (int u = 0; u < kQuantRows; ++u) { va[u] *= oa; vb[u] *= ob; }
+        } else {
+#pragma unroll
+            for (int u = 0; u < kQuantRows; ++u) {
+                union { uint32_t u; _Float16 h[2]; } c; c.u = cur[u];
+                va[u] = (float)c.h[0]; vb[u] = (float)c.h[1];
+            }
+        }
+        const int64_t row = t0 + t + orow;               // the row this lane writes out
+        const bool live = t + orow < n_rows;
+        if constexpr (INT4) {
+            float mx[4], nmn[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) { mx[u] = fmaxf(va[u], vb[u]); nmn[u] = fmaxf(-va[u], -vb[u]); }
+            const float mxv = wave_max4(mx), mnv = -wave_max4(nmn);
+            float s32 = (mxv - mnv) / 15.0f;
+            if (!(s32 >= 6.103515625e-05f)) s32 = 6.103515625e-05f;
+            const _Float16 s16 = (_Float16)s32;
+            const float s = (float)s16, rs = 1.0f / s;
+            float zf = -rintf(mnv / s);
+            zf = fminf(fmaxf(zf, 0.0f), 15.0f);
+            uint32_t ca = 0, cb = 0;
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const float su = from_lane(s, kRowLane[u]), ru = from_lane(rs, kRowLane[u]), zu = from_lane(zf, kRowLane[u]);
+                float qa, qb;
+                if (su < __builtin_inff()) {             // (uniform)
+                    const float a0 = va[u] * ru, b0 = vb[u] * ru;
+                    qa = fmaf(fmaf(-su, a0, va[u]), ru, a0);
+                    qb = fmaf(fmaf(-su, b0, vb[u]), ru, b0);
+                } else {
+                    qa = va[u] / su; qb = vb[u] / su;
+                }
+                ca = __builtin_amdgcn_cvt_pk_u8_f32(fminf(fmaxf(rintf(qa) + zu, 0.0f), 15.0f), u, ca);
+                cb = __builtin_amdgcn_cvt_pk_u8_f32(fminf(fmaxf(rintf(qb) + zu, 0.0f), 15.0f), u, cb);
+                if constexpr (KIND == kW4Weight) zword |= (uint32_t)zu << (4 * (t % 8 + u));
+            }
+            s_out[wave][ch_a] = ca;
+            s_out[wave][ch_b] = cb;
+            __builtin_amdgcn_wave_barrier();
+            uint32_t d[8], word = 0;
+            *(u32x4v *)&d[0] = *(const u32x4v *)&s_out[wave][oword * 8];
+            *(u32x4v *)&d[4] = *(const u32x4v *)&s_out[wave][oword * 8 + 4];
+#pragma unroll
+            for (int k = 0; k < 8; ++k) word |= ((d[k] >> (8 * orow)) & 15u) << (4 * k);
+            if (live) a.codes[(size_t)row * (a.C / 8) + (size_t)g * (kGroup / 8) + oword] = word;
+            const int64_t prow = t0 + t + row_of_lane(lane);         // the row whose scale this lane holds
+            if (oword == 0 && t + row_of_lane(lane) < n_rows) {
+                if constexpr (KIND == kW4Weight) a.scales[(size_t)g * a.T + prow] = s16;
+                else { a.scales[(size_t)prow * G + g] = s16; a.bytes[(size_t)prow * G + g] = (uint8_t)zf; }
+            }
+            if constexpr (KIND == kW4Weight && t % 8 == 4) {
+                if (lane == 0) a.qzeros[(size_t)g * (a.T / 8) + (t0 + t) / 8] = zword;
+                zword = 0;
+            }
+        } else {
+            float v[8];
+            if constexpr (K >= 0) {
+                float *so = (float *)s_out[wave];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) { so[u * kQuantPad + ch_a] = va[u]; so[u * kQuantPad + ch_b] = vb[u]; }
+                __builtin_amdgcn_wave_barrier();
+                *(float4 *)&v[0] = *(const float4 *)(so + orow * kQuantPad + oword * 8);
+                *(float4 *)&v[4] = *(const float4 *)(so + orow * kQuantPad + oword * 8 + 4);
+            } else {
+                uint32_t *so = s_out[wave];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) so[u * kQuantPad + lane] = cur[u];
+                __builtin_amdgcn_wave_barrier();
+                union { u32x4v u; _Float16 h[8]; } c; c.u = *(const u32x4v *)(so + orow * kQuantPad + oword * 4);
+#pragma unroll
+                for (int k = 0; k < 8; ++k) v[k] = (float)c.h[k];
+            }
+            float amax = 0.f;
+#pragma unroll
+            for (int k = 0; k < 8; ++k) amax = fmaxf(amax, fabsf(v[k]));
+            amax = fmaxf(amax, dpp<kQuadXor1>(amax));
+            amax = fmaxf(amax, dpp<kQuadXor2>(amax));
+            int e = (int)(__float_as_uint(amax) >> 23) - 127 - 2;
+            if (e < -127) e = -127;
+            const float sc = __uint_as_float(e > -127 ? (uint32_t)(e + 127) << 23 : 0x00400000u);       // 2^e
+            uint32_t word = 0;
+            word = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(word, v[0], v[1], sc, 0);
+            word = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(word, v[2], v[3], sc, 1);
+            word = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(word, v[4], v[5], sc, 2);
+            word = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(word, v[6], v[7], sc, 3);
+            if (live) {
+                a.codes[(size_t)row * (a.C / 8) + (size_t)g * (kGroup / 8) + oword] = word;
+                if ((lane & 3) == 0) a.bytes[(size_t)row * (a.C / 32) + (size_t)g * (kGroup / 32) + (oword >> 2)] = (uint8_t)(e + 127);
+            }
+        }
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (int u = 0; u < kQuantRows; ++u) cur[u] = nxt[u];
+        return true;
+    });
+}
+
+template <int K, int KIND>
+static hipError_t launch_quant_k(QuantArgs &a, hipStream_t s)
+{
+    // runs of up to 32 rows per wave, shorter while that leaves fewer than ~4096 waves
+    const int G = a.C / kGroup, least = KIND == kW4Weight ? 2 * kQuantRows : kQuantRows;
+    int rpw = kQuantBatches * kQuantRows;
+    while (rpw > least && (int64_t)G * ((a.T + rpw - 1) / rpw) < 4096) rpw >>= 1;
+    a.rows_per_wave = rpw;
+    const int waves_t = (a.T + rpw - 1) / rpw;
+    hipLaunchKernelGGL((quantize_kernel<K, KIND>), dim3(G, (waves_t + kQuantWaves - 1) / kQuantWaves), dim3(kQuantWaves * 64), 0, s, a);
     return hipGetLastError();
+}
+
+template <int KIND>
+static hipError_t launch_quant(const paro_rotation *rot, QuantArgs &a, hipStream_t s)
+{
+    if (!rot) {
+        if constexpr (KIND == kW4Weight || KIND == kMxWeight) return launch_quant_k<-1, KIND>(a, s);
+        return hipErrorInvalidValue;
+    }
+    a.plan = (const uint32_t *)rot->plan;
+    switch (rot->n_layers) {
+    case 0: return launch_quant_k<0, KIND>(a, s);
+    case 1: return launch_quant_k<1, KIND>(a, s);
+    case 2: return launch_quant_k<2, KIND>(a, s);
+    case 3: return launch_quant_k<3, KIND>(a, s);
+    case 4: return launch_quant_k<4, KIND>(a, s);
+    case 5: return launch_quant_k<5, KIND>(a, s);
+    case 6: return launch_quant_k<6, KIND>(a, s);
+    case 7: return launch_quant_k<7, KIND>(a, s);
+    default: return launch_quant_k<8, KIND>(a, s);
+    }
 }
 
 hipError_t launch_quantize(const paro_rotation *rot, const paro_half_t *W, int64_t ldw, int N, int C, uint32_t *qweight,
                            paro_half_t *scales, uint32_t *qzeros, hipStream_t s)
 {
-    if (!rot) return launch_quantize_k<-1>(nullptr, W, ldw, N, C, qweight, scales, qzeros, s);
-    const uint32_t *plan = (const uint32_t *)rot->plan;
-    switch (rot->n_layers) {
-    case 0: return launch_quantize_k<0>(plan, W, ldw, N, C, qweight, scales, qzeros, s);
-    case 1: return launch_quantize_k<1>(plan, W, ldw, N, C, qweight, scales, qzeros, s);
-    case 2: return launch_quantize_k<2>(plan, W, ldw, N, C, qweight, scales, qzeros, s);
-    case 3: return launch_quantize_k<3>(plan, W, ldw, N, C, qweight, scales, qzeros, s);
-    case 4: return launch_quantize_k<4>(plan, W, ldw, N, C, qweight, scales, qzeros, s);
-    case 5: return launch_quantize_k<5>(plan, W, ldw, N, C, qweight, scales, qzeros, s);
-    case 6: return launch_quantize_k<6>(plan, W, ldw, N, C, qweight, scales, qzeros, s);
-    case 7: return launch_quantize_k<7>(plan, W, ldw, N, C, qweight, scales, qzeros, s);
-    default: return launch_quantize_k<8>(plan, W, ldw, N, C, qweight, scales, qzeros, s);
-    }
-}
-
-// ------------------------------------------------------------------------------------------
-// Activation side of the W4A4 extension (App. A.3: Y' = Q(X T^-1) . Q(T W) + b): the transformed
-// activations are quantised to INT4 right after the rotation, while they are still in the
-// wave's registers.  The paper names no activation quantiser of its own, so Eq. 1 (b = 4) is
-// applied per token and 128-channel group, with the same decisions as on the weight side.
-// One wavefront per (token, group); outputs per token: codes [c_in/8] words, scale and zero
-// point per group.
-// ------------------------------------------------------------------------------------------
-constexpr int kActWaves = 4;
-
-template <int K>
-__global__ __launch_bounds__(kActWaves * 64) void quantize_act_kernel(const uint32_t *__restrict__ plan,
-                                                                       const _Float16 *__restrict__ X, int64_t ldx, int T,
-                                                                       int C, int rows_per_wave, uint32_t *__restrict__ codes,
-                                                                       _Float16 *__restrict__ scales,
-                                                                       uint8_t *__restrict__ zeros)
-{
-    __shared__ _Float16 s_stage[kActWaves][kGroup];
-    __shared__ uint8_t s_codes[kActWaves][kGroup];
-    const int g = blockIdx.x, G = C / kGroup;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int t0 = (blockIdx.y * kActWaves + wave) * rows_per_wave;
-    if (t0 >= T) return;
-    const int t1 = min(T, t0 + rows_per_wave);
-
-    // the group's plan once per wave, then a run of tokens
-    LanePlan<K> P;
-    load_lane_plan<K>(plan + (size_t)g * plan_group_dwords(K), lane, P);
-    uint32_t raw = *((const uint32_t *)(X + (size_t)t0 * ldx + (size_t)g * kGroup) + lane);
-    for (int t = t0; t < t1; ++t) {
-        *(uint32_t *)&s_stage[wave][2 * lane] = raw;
-        if (t + 1 < t1) raw = *((const uint32_t *)(X + (size_t)(t + 1) * ldx + (size_t)g * kGroup) + lane);
-        __builtin_amdgcn_wave_barrier();
-        float a[1] = {(float)s_stage[wave][P.in_a] * P.sia};
-        float b[1] = {(float)s_stage[wave][P.in_b] * P.sib};
-        rotate_layers<K, 1>(P, a, b);
-        const float va = a[0] * P.soa, vb = b[0] * P.sob;
-
-        float mn = fminf(va, vb), mx = fmaxf(va, vb);
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) {
-            mn = fminf(mn, __shfl_xor(mn, off, 64));
-            mx = fmaxf(mx, __shfl_xor(mx, off, 64));
-        }
-        float s32 = (mx - mn) / 15.0f;
-        if (!(s32 >= 6.103515625e-05f)) s32 = 6.103515625e-05f;
-        const _Float16 s16 = (_Float16)s32;
-        const float s = (float)s16;
-        float zf = -rintf(mn / s);
-        zf = fminf(fmaxf(zf, 0.0f), 15.0f);
-        s_codes[wave][P.out_a] = (uint8_t)fminf(fmaxf(rintf(va / s) + zf, 0.0f), 15.0f);
-        s_codes[wave][P.out_b] = (uint8_t)fminf(fmaxf(rintf(vb / s) + zf, 0.0f), 15.0f);
-        __builtin_amdgcn_wave_barrier();
-        if (lane < kGroup / 8) {
-            uint32_t word = 0;
-#pragma unroll
-            for (int k = 0; k < 8; ++k) word |= (uint32_t)s_codes[wave][lane * 8 + k] << (4 * k);
-            codes[(size_t)t * (C / 8) + (size_t)g * (kGroup / 8) + lane] = word;
-        }
-        if (lane == 0) { scales[(size_t)t * G + g] = s16; zeros[(size_t)t * G + g] = (uint8_t)zf; }
-        __builtin_amdgcn_wave_barrier();
-    }
-}
-
-template <int K>
-static hipError_t launch_quantize_act_k(const paro_rotation &rot, const paro_half_t *X, int64_t ldx, int T,
-                                        uint32_t *codes, paro_half_t *scales, uint8_t *zeros, hipStream_t s)
-{
-    // runs of up to 32 tokens per wave, shorter while that leaves fewer than ~4096 waves
-    const int G = rot.c_in / kGroup;
-    int rpw = 32;
-    while (rpw > 1 && (int64_t)G * ((T + rpw - 1) / rpw) < 4096) rpw >>= 1;
-    const int waves_t = (T + rpw - 1) / rpw;
-    hipLaunchKernelGGL(quantize_act_kernel<K>, dim3(G, (waves_t + kActWaves - 1) / kActWaves), dim3(kActWaves * 64), 0, s,
-                       (const uint32_t *)rot.plan, (const _Float16 *)X, ldx, T, rot.c_in, rpw, codes, (_Float16 *)scales, zeros);
-    return hipGetLastError();
+    QuantArgs a{nullptr, (const _Float16 *)W, ldw, N, C, 0, qweight, (_Float16 *)scales, qzeros, nullptr};
+    return launch_quant<kW4Weight>(rot, a, s);
 }
 
 hipError_t launch_quantize_act(const paro_rotation &rot, const paro_half_t *X, int64_t ldx, int T, uint32_t *codes,
                                paro_half_t *scales, uint8_t *zeros, hipStream_t s)
 {
-    switch (rot.n_layers) {
-    case 0: return launch_quantize_act_k<0>(rot, X, ldx, T, codes, scales, zeros, s);
-    case 1: return launch_quantize_act_k<1>(rot, X, ldx, T, codes, scales, zeros, s);
-    case 2: return launch_quantize_act_k<2>(rot, X, ldx, T, codes, scales, zeros, s);
-    case 3: return launch_quantize_act_k<3>(rot, X, ldx, T, codes, scales, zeros, s);
-    case 4: return launch_quantize_act_k<4>(rot, X, ldx, T, codes, scales, zeros, s);
-    case 5: return launch_quantize_act_k<5>(rot, X, ldx, T, codes, scales, zeros, s);
-    case 6: return launch_quantize_act_k<6>(rot, X, ldx, T, codes, scales, zeros, s);
-    case 7: return launch_quantize_act_k<7>(rot, X, ldx, T, codes, scales, zeros, s);
-    default: return launch_quantize_act_k<8>(rot, X, ldx, T, codes, scales, zeros, s);
-    }
-}
-
-// ------------------------------------------------------------------------------------------
-// The same activation side with a microscaling FP4 quantiser (MXFP4 of the OCP Microscaling
-// Formats specification, the 4-bit type the matrix cores of this chip take directly): 32
-// consecutive channels share a power-of-two scale 2^e, e = floor(log2(max|v|)) - 2 (>= -127),
-// stored as the byte e + 127; each value becomes the E2M1 code of v / 2^e, rounded to nearest
-// with ties to the even code and saturated at 6.  Everything after the rotation is exact.
-// ------------------------------------------------------------------------------------------
-__device__ __forceinline__ uint32_t e2m1_code(float r)
-{
-    const float a = fabsf(r);
-    uint32_t c = a <= 0.25f ? 0u : a < 0.75f ? 1u : a <= 1.25f ? 2u : a < 1.75f ? 3u
-               : a <= 2.5f ? 4u : a < 3.5f ? 5u : a <= 5.0f ? 6u : 7u;
-    return c | ((__float_as_uint(r) >> 28) & 8u);
-}
-
-// WSIDE: the rows are output rows of a dense weight and take the weight side of the transform
-// (the reciprocals of the activation-side multipliers, as in quantize_rows_kernel): Q(T W) of
-// App. A.3.  K < 0: no transform at all (rows quantised as they are).
-template <int K, bool WSIDE>
-__global__ __launch_bounds__(kActWaves * 64) void quantize_act_mxfp4_kernel(const uint32_t *__restrict__ plan,
-                                                                             const _Float16 *__restrict__ X, int64_t ldx,
-                                                                             int T, int C, int rows_per_wave,
-                                                                             uint32_t *__restrict__ codes,
-                                                                             uint8_t *__restrict__ scales)
-{
-    __shared__ _Float16 s_stage[kActWaves][kGroup];
-    __shared__ float s_val[kActWaves][kGroup];
-    __shared__ __attribute__((aligned(4))) uint8_t s_codes[kActWaves][kLanes];
-    const int g = blockIdx.x;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int t0 = (blockIdx.y * kActWaves + wave) * rows_per_wave;
-    if (t0 >= T) return;
-    const int t1 = min(T, t0 + rows_per_wave);
-
-    // The group's plan once per wave, then a run of rows: the plan is 7.4 KB at K = 8, re-reading it per row would
-    // outweigh the row itself 30 times.  (Rotating four rows at a time as the activation kernel does was measured
-    // and is no faster here: the conversion, not the permute latency, is what a row costs.)
-    LanePlan<K> P;
-    float ia = 1.f, ib = 1.f, oa = 1.f, ob = 1.f;
-    if constexpr (K >= 0) {
-        load_lane_plan<K>(plan + (size_t)g * plan_group_dwords(K), lane, P);
-        ia = WSIDE ? 1.0f / P.sia : P.sia; ib = WSIDE ? 1.0f / P.sib : P.sib;
-        oa = WSIDE ? 1.0f / P.soa : P.soa; ob = WSIDE ? 1.0f / P.sob : P.sob;
-    }
-    uint32_t raw = *((const uint32_t *)(X + (size_t)t0 * ldx + (size_t)g * kGroup) + lane);
-    for (int t = t0; t < t1; ++t) {
-        const uint32_t cur = raw;
-        if (t + 1 < t1) raw = *((const uint32_t *)(X + (size_t)(t + 1) * ldx + (size_t)g * kGroup) + lane);
-        float2 v;
-        if constexpr (K >= 0) {
-            *(uint32_t *)&s_stage[wave][2 * lane] = cur;
-            __builtin_amdgcn_wave_barrier();
-            float a[1] = {(float)s_stage[wave][P.in_a] * ia};
-            float b[1] = {(float)s_stage[wave][P.in_b] * ib};
-            rotate_layers<K, 1>(P, a, b);
-            s_val[wave][P.out_a] = a[0] * oa;
-            s_val[wave][P.out_b] = b[0] * ob;
-            __builtin_amdgcn_wave_barrier();
-            // channel order from here: lane l holds channels 2l, 2l+1; 16 lanes = one 32-channel block
-            v = *(const float2 *)&s_val[wave][2 * lane];
-        } else {
-            union { uint32_t u; _Float16 h[2]; } c; c.u = cur;
-            v = make_float2((float)c.h[0], (float)c.h[1]);
-        }
-        float amax = fmaxf(fabsf(v.x), fabsf(v.y));
-#pragma unroll
-        for (int off = 8; off > 0; off >>= 1) amax = fmaxf(amax, __shfl_xor(amax, off, 64));
-        int e = (int)(__float_as_uint(amax) >> 23) - 127 - 2;
-        if (e < -127) e = -127;
-        const uint32_t byte = e2m1_code(ldexpf(v.x, -e)) | (e2m1_code(ldexpf(v.y, -e)) << 4);
-        s_codes[wave][lane] = (uint8_t)byte;
-        __builtin_amdgcn_wave_barrier();
-        if (lane < kGroup / 8) codes[(size_t)t * (C / 8) + (size_t)g * (kGroup / 8) + lane] = *(const uint32_t *)&s_codes[wave][4 * lane];
-        if ((lane & 15) == 0) scales[(size_t)t * (C / 32) + (size_t)g * (kGroup / 32) + (lane >> 4)] = (uint8_t)(e + 127);
-        __builtin_amdgcn_wave_barrier();
-    }
-}
-
-template <int K, bool WSIDE>
-static hipError_t launch_quantize_mxfp4_k(const uint32_t *plan, int C, const paro_half_t *X, int64_t ldx, int T,
-                                          uint32_t *codes, uint8_t *scales, hipStream_t s)
-{
-    // runs of up to 32 rows per wave, shorter while that leaves fewer than ~4096 waves
-    const int G = C / kGroup;
-    int rpw = 32;
-    while (rpw > 1 && (int64_t)G * ((T + rpw - 1) / rpw) < 4096) rpw >>= 1;
-    const int waves_t = (T + rpw - 1) / rpw;
-    hipLaunchKernelGGL((quantize_act_mxfp4_kernel<K, WSIDE>), dim3(G, (waves_t + kActWaves - 1) / kActWaves),
-                       dim3(kActWaves * 64), 0, s, plan, (const _Float16 *)X, ldx, T, C, rpw, codes, scales);
-    return hipGetLastError();
-}
-
-template <bool WSIDE>
-static hipError_t launch_quantize_mxfp4_side(const paro_rotation *rot, int C, const paro_half_t *X, int64_t ldx, int T,
-                                             uint32_t *codes, uint8_t *scales, hipStream_t s)
-{
-    if (!rot) return launch_quantize_mxfp4_k<-1, WSIDE>(nullptr, C, X, ldx, T, codes, scales, s);
-    const uint32_t *plan = (const uint32_t *)rot->plan;
-    switch (rot->n_layers) {
-    case 0: return launch_quantize_mxfp4_k<0, WSIDE>(plan, C, X, ldx, T, codes, scales, s);
-    case 1: return launch_quantize_mxfp4_k<1, WSIDE>(plan, C, X, ldx, T, codes, scales, s);
-    case 2: return launch_quantize_mxfp4_k<2, WSIDE>(plan, C, X, ldx, T, codes, scales, s);
-    case 3: return launch_quantize_mxfp4_k<3, WSIDE>(plan, C, X, ldx, T, codes, scales, s);
-    case 4: return launch_quantize_mxfp4_k<4, WSIDE>(plan, C, X, ldx, T, codes, scales, s);
-    case 5: return launch_quantize_mxfp4_k<5, WSIDE>(plan, C, X, ldx, T, codes, scales, s);
-    case 6: return launch_quantize_mxfp4_k<6, WSIDE>(plan, C, X, ldx, T, codes, scales, s);
-    case 7: return launch_quantize_mxfp4_k<7, WSIDE>(plan, C, X, ldx, T, codes, scales, s);
-    default: return launch_quantize_mxfp4_k<8, WSIDE>(plan, C, X, ldx, T, codes, scales, s);
-    }
+    QuantArgs a{nullptr, (const _Float16 *)X, ldx, T, rot.c_in, 0, codes, (_Float16 *)scales, nullptr, zeros};
+    return launch_quant<kA4Act>(&rot, a, s);
 }
 
 hipError_t launch_quantize_act_mxfp4(const paro_rotation &rot, const paro_half_t *X, int64_t ldx, int T, uint32_t *codes,
                                      uint8_t *scales, hipStream_t s)
 {
-    return launch_quantize_mxfp4_side<false>(&rot, rot.c_in, X, ldx, T, codes, scales, s);
+    QuantArgs a{nullptr, (const _Float16 *)X, ldx, T, rot.c_in, 0, codes, nullptr, nullptr, scales};
+    return launch_quant<kMxAct>(&rot, a, s);
 }
 
 // rows of a dense weight [N][ldw]; rot == nullptr: no transform
 hipError_t launch_quantize_weight_mxfp4(const paro_rotation *rot, const paro_half_t *W, int64_t ldw, int N, int C,
                                         uint32_t *codes, uint8_t *scales, hipStream_t s)
 {
-    return launch_quantize_mxfp4_side<true>(rot, C, W, ldw, N, codes, scales, s);
+    QuantArgs a{nullptr, (const _Float16 *)W, ldw, N, C, 0, codes, nullptr, nullptr, scales};
+    return launch_quant<kMxWeight>(rot, a, s);
 }
 
 }  // namespace paro
