@@ -153,14 +153,15 @@ paro_status paro_w4_repack(const paro_w4_weight *w, void *packed_out, void *stre
  *     of the buffer as given by ws_bytes (rounded down to 256): transformed activations when the
  *     rotation runs as a pass of its own (T > 4, no plan / no repacked weight, or a shape on
  *     which two launches are faster than the exchange of the fused kernel), and fp32
- *     partial tiles where the GEMM splits K (some tens to hundreds of tokens).  No requirement
+ *     partial tiles where K is split between blocks (some tens to hundreds of tokens).  No requirement
  *     before a call, any contents after it.
  * paro_workspace_bytes() is the sum: enough for a buffer that only serves calls of that one shape.
  * A buffer shared by calls of several shapes must hold the largest exchange part plus the largest
  * scratch part of all of them, so that no call's scratch reaches into another's exchange part;
  * pass its full size as ws_bytes.  Calls that share a workspace must not overlap in time.
  * The bare linear needs no workspace (0 bytes, ws may be NULL) where it neither splits K between
- * blocks nor runs the GEMM's split. */
+ * blocks nor runs the GEMM's split.  A call whose buffer lacks only room for what makes it faster (the partial
+ * tiles of the kernels between streaming and GEMM) is not refused: it takes the routes that fit. */
 size_t paro_workspace_error_offset(void);
 size_t paro_workspace_partials_offset(void);
 size_t paro_workspace_bytes(const paro_rotation *rot, const paro_w4_weight *w, int32_t T);

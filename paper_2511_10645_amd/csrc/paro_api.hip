@@ -99,7 +99,9 @@ struct WsLayout {
     size_t total;
 };
 
-WsLayout ws_layout(const paro_rotation *rot, const paro_w4_weight *w, int T, bool always_fuse = false)
+// `lean`: without the pieces that only make a call faster (partial tiles of linear_tile.hip and linear_rows.hip).
+// A buffer of that size is accepted too and the call takes the routes that fit it.
+WsLayout ws_layout(const paro_rotation *rot, const paro_w4_weight *w, int T, bool always_fuse = false, bool lean = false)
 {
     WsLayout L{0, 0, 0, 0, 0};
     const bool fused = fused_decode(rot, w, T, always_fuse);
@@ -110,9 +112,12 @@ WsLayout ws_layout(const paro_rotation *rot, const paro_w4_weight *w, int T, boo
                                                             : decode_wide_partial_bytes(w->c_in, w->c_out, T);
         // the bare linear without partial sums to exchange needs no workspace at all
         L.exchange_bytes = (rot || part) ? kWsPartialOff + round_up(part, 256) : 0;
-        if (T > kDecodeMaxTokens)
-            L.gemm_bytes = round_up(std::max(gemm_scratch_bytes(*w, T), T > kStreamPassTokens && T <= 1024 ? linear_tile_scratch_bytes(*w, T) : 0), 256);
-    } else if (rot) {
+        if (T > kDecodeMaxTokens) {
+            size_t scratch = gemm_scratch_bytes(*w, T);
+            if (!lean && T > kStreamPassTokens && T <= 1024) scratch = std::max(scratch, linear_tile_scratch_bytes(*w, T));
+            L.gemm_bytes = round_up(scratch, 256);
+        }
+    } else if (rot && !lean) {
         // weights in the interchange layout; the bare call needs no workspace and runs without the split
         L.gemm_bytes = round_up(T <= kStreamPassTokens ? linear_rows_scratch_bytes(*w, T) : linear_tile_scratch_bytes(*w, T), 256);
     }
@@ -120,6 +125,14 @@ WsLayout ws_layout(const paro_rotation *rot, const paro_w4_weight *w, int T, boo
     L.scratch_bytes = L.xr_bytes + L.gemm_bytes;
     L.total = L.exchange_bytes + L.scratch_bytes;
     return L;
+}
+
+// the layout that the caller's buffer has room for
+WsLayout ws_layout_fit(const paro_rotation *rot, const paro_w4_weight *w, int T, const void *ws, size_t ws_bytes,
+                       bool always_fuse = false)
+{
+    const WsLayout L = ws_layout(rot, w, T, always_fuse);
+    return ws && aligned(ws, 256) && ws_bytes >= L.total ? L : ws_layout(rot, w, T, always_fuse, true);
 }
 
 inline char *ws_scratch(void *ws, size_t ws_bytes, const WsLayout &L)
@@ -150,6 +163,36 @@ paro_status static_scratch(void **out)
     return PARO_OK;
 }
 
+// The kernel that a bare linear on a repacked weight takes, and about how long it runs (0: not estimated).
+struct LinearRoute { enum Kernel { kStream, kGemm, kTile } kernel; double us; };
+LinearRoute linear_route(const paro_w4_weight &w, int64_t ldx, int64_t ldy, int T, size_t scratch_bytes)
+{
+    if (T <= kDecodeMaxTokens || !gemm_supported(w, ldx, ldy, T)) return {LinearRoute::kStream, 0.0};
+    // Moderate token counts leave most of the chip idle in the GEMM (few token tiles), while the
+    // streaming kernel re-reads the weights once per 32 tokens: take the cheaper.  Measured per pass:
+    // 17..32 tokens ~5 us plus the tile bytes at ~3.75 TB/s, up to 16 tokens ~3.5 us plus the bytes at
+    // ~5.2 TB/s, and ~2.5 us (4 us at 17..32 tokens) more where the K-slices of a row are spread over several blocks.
+    const double mb = (double)packed_tiles_bytes(w.c_in, w.c_out) / 1.0e6;
+    const int rem = T % kStreamPassTokens;
+    const double ex32 = decode_wide_partial_bytes(w.c_in, w.c_out, kStreamPassTokens) ? 4.0 : 0.0;
+    const double ex16 = decode_wide_partial_bytes(w.c_in, w.c_out, 16) ? 2.5 : 0.0;
+    const double pass32 = 5.0 + mb / 3.75 + ex32;
+    const double stream_us = (double)(T / kStreamPassTokens) * pass32 +
+                             (rem == 0 ? 0.0 : rem <= 16 ? 3.5 + mb / 5.2 + ex16 : pass32);
+    const bool gemm = T >= 512 || gemm_estimate_us(w, T) <= stream_us;
+    const double us = gemm ? gemm_fitted_us(w, T) : stream_us;
+    // The kernel between the two (linear_tile.hip) neither walks whole GEMM tiles nor re-reads the weights, but costs
+    // most per product.  Its model and the GEMM's fitted one are 6 to 14 % off, hence 0.9: over 918 measured
+    // (shape, tokens) pairs the choice loses more than 3 % on two and takes 1.28x less time in the mean than without
+    // the kernel, 1.29x being the best possible.  Above 1024 tokens it has no shape to itself.  Without room for its partial
+    // tiles it would run unsplit and as slow as the others.
+    if (T > kStreamPassTokens && T <= 1024 && linear_tile_supported(w, false) && linear_tile_scratch_bytes(w, T) <= scratch_bytes) {
+        const double tile_us = linear_tile_estimate_us(w, T);
+        if (tile_us < 0.9 * us) return {LinearRoute::kTile, tile_us};
+    }
+    return {gemm ? LinearRoute::kGemm : LinearRoute::kStream, us};
+}
+
 // bare linear on (already transformed) activations, any T
 paro_status run_linear(const paro_w4_weight *w, const paro_half_t *X, int64_t ldx, paro_half_t *Y, int64_t ldy, int T,
                        void *ws, void *gemm_scratch, size_t gemm_bytes, hipStream_t s)
@@ -173,27 +216,10 @@ paro_status run_linear(const paro_w4_weight *w, const paro_half_t *X, int64_t ld
         }
         return PARO_OK;
     }
-    if (T > kDecodeMaxTokens && gemm_supported(*w, ldx, ldy, T)) {
-        // Moderate token counts leave most of the chip idle in the GEMM (few token tiles), while the
-        // streaming kernel re-reads the weights once per 32 tokens: take the cheaper.  Measured per pass:
-        // 17..32 tokens ~5 us plus the tile bytes at ~3.75 TB/s, up to 16 tokens ~3.5 us plus the bytes at
-        // ~5.2 TB/s, and ~2.5 us (4 us at 17..32 tokens) more where the K-slices of a row are spread over several blocks.
-        const double mb = (double)packed_tiles_bytes(w->c_in, w->c_out) / 1.0e6;
-        const int rem = T % kStreamPassTokens;
-        const double ex32 = decode_wide_partial_bytes(w->c_in, w->c_out, kStreamPassTokens) ? 4.0 : 0.0;
-        const double ex16 = decode_wide_partial_bytes(w->c_in, w->c_out, 16) ? 2.5 : 0.0;
-        const double pass32 = 5.0 + mb / 3.75 + ex32;
-        const double stream_us = (double)(T / kStreamPassTokens) * pass32 +
-                                 (rem == 0 ? 0.0 : rem <= 16 ? 3.5 + mb / 5.2 + ex16 : pass32);
-        const bool gemm = T >= 512 || gemm_estimate_us(*w, T) <= stream_us;
-        // The kernel between the two (linear_tile.hip) neither walks whole GEMM tiles nor re-reads the weights, but costs
-        // most per product.  Its model and the GEMM's fitted one are 6 to 14 % off, hence 0.9: over 918 measured
-        // (shape, tokens) pairs the choice loses more than 3 % on two and takes 1.28x less time in the mean than without
-        // the kernel, 1.29x being the best possible.  Above 1024 tokens it has no shape to itself.
-        if (T > kStreamPassTokens && T <= 1024 && linear_tile_supported(*w, false) &&
-            linear_tile_estimate_us(*w, T) < 0.9 * (gemm ? gemm_fitted_us(*w, T) : stream_us))
-            return from_hip(launch_linear_tile(*w, false, X, ldx, Y, ldy, T, gemm_scratch, gemm_bytes, s));
-        if (gemm) return from_hip(launch_gemm(*w, X, ldx, Y, ldy, T, gemm_scratch, gemm_bytes, s));
+    switch (linear_route(*w, ldx, ldy, T, gemm_bytes).kernel) {
+    case LinearRoute::kTile: return from_hip(launch_linear_tile(*w, false, X, ldx, Y, ldy, T, gemm_scratch, gemm_bytes, s));
+    case LinearRoute::kGemm: return from_hip(launch_gemm(*w, X, ldx, Y, ldy, T, gemm_scratch, gemm_bytes, s));
+    case LinearRoute::kStream: break;
     }
     for (int t0 = 0; t0 < T; t0 += kStreamPassTokens) {
         int tc = T - t0 < kStreamPassTokens ? T - t0 : kStreamPassTokens;
@@ -354,7 +380,7 @@ paro_status paro_w4a16_linear(const paro_w4_weight *w, const paro_half_t *X, int
     if (st != PARO_OK) return st;
     st = check_io(X, ldx, w->c_in, Y, ldy, w->c_out, T, 8);
     if (st != PARO_OK) return st;
-    WsLayout L = ws_layout(nullptr, w, T);
+    WsLayout L = ws_layout_fit(nullptr, w, T, ws, ws_bytes);
     if (L.total && (!ws || ws_bytes < L.total)) return PARO_ERR_WORKSPACE;
     if (L.total && !aligned(ws, 256)) return PARO_ERR_ALIGN;
     return run_linear(w, X, ldx, Y, ldy, T, ws, L.gemm_bytes ? ws_scratch(ws, ws_bytes, L) + L.xr_bytes : nullptr,
@@ -372,7 +398,7 @@ static paro_status rotated_linear(const paro_rotation *rot, const paro_w4_weight
     if (rot->c_in != w->c_in) return PARO_ERR_SHAPE;
     st = check_io(X, ldx, w->c_in, Y, ldy, w->c_out, T, 8);
     if (st != PARO_OK) return st;
-    WsLayout L = ws_layout(rot, w, T, always_fuse);
+    WsLayout L = ws_layout_fit(rot, w, T, ws, ws_bytes, always_fuse);
     if (L.total && (!ws || ws_bytes < L.total)) return PARO_ERR_WORKSPACE;
     if (L.total && !aligned(ws, 256)) return PARO_ERR_ALIGN;
     hipStream_t s = (hipStream_t)stream;
@@ -382,11 +408,11 @@ static paro_status rotated_linear(const paro_rotation *rot, const paro_w4_weight
 
     // two passes: transform into the workspace, then the bare linear
     paro_half_t *xr = (paro_half_t *)ws_scratch(ws, ws_bytes, L);
+    char *scratch2 = L.gemm_bytes ? (char *)xr + L.xr_bytes : nullptr;
     hipError_t e = rot->plan ? launch_rotate_planned(*rot, X, ldx, xr, w->c_in, T, s)
                              : launch_rotate_generic(*rot, X, ldx, xr, w->c_in, T, s);
     if (e != hipSuccess) return PARO_ERR_HIP;
-    return run_linear(w, xr, w->c_in, Y, ldy, T, ws, L.gemm_bytes ? ws_scratch(ws, ws_bytes, L) + L.xr_bytes : nullptr,
-                      L.gemm_bytes, s);
+    return run_linear(w, xr, w->c_in, Y, ldy, T, ws, scratch2, L.gemm_bytes, s);
 }
 
 paro_status paro_rotated_linear(const paro_rotation *rot, const paro_w4_weight *w, const paro_half_t *X, int64_t ldx,
@@ -468,11 +494,11 @@ static paro_status check_multi(int32_t n, const paro_rotation *const *rots, cons
 }
 
 static WsLayout ws_layout_multi(int32_t n_parts, const paro_rotation *const *rots, const paro_w4_weight *const *weights,
-                                int32_t T)
+                                int32_t T, bool lean = false)
 {
     WsLayout M{0, 0, 0};
     for (int p = 0; p < n_parts; ++p) {
-        WsLayout one = ws_layout(rots[p], weights[p], T);
+        WsLayout one = ws_layout(rots[p], weights[p], T, false, lean);
         if (one.exchange_bytes > M.exchange_bytes) M.exchange_bytes = one.exchange_bytes;
         if (one.scratch_bytes > M.scratch_bytes) M.scratch_bytes = one.scratch_bytes;
     }
@@ -511,7 +537,7 @@ paro_status paro_rotated_linear_multi(int32_t n_parts, const paro_rotation *cons
         st = check_io(X, ldx, weights[p]->c_in, Y[p], ldy[p], weights[p]->c_out, T, 8);
         if (st != PARO_OK) return st;
     }
-    const size_t need = paro_workspace_bytes_multi(n_parts, rots, weights, T);
+    const size_t need = ws_layout_multi(n_parts, rots, weights, T, true).total;
     if (need && (!ws || ws_bytes < need)) return PARO_ERR_WORKSPACE;
     if (need && !aligned(ws, 256)) return PARO_ERR_ALIGN;
     if (multi_one_launch(n_parts, rots, weights, T))

@@ -52,6 +52,19 @@ CASES = [
 @pytest.mark.parametrize("T,c_in,c_out,form", CASES)
 @pytest.mark.parametrize("rotated", [False, True])
 def test_linear_against_oracle(P, T, c_in, c_out, form, rotated):
+    _check_linear(P, T, c_in, c_out, form, rotated)
+
+
+# The least that calls have always needed: nothing for a bare linear whose GEMM does not split, the transformed activations
+# (exchange header in front for repacked weights) otherwise.  Partial tiles that only save time are not insisted on.
+@pytest.mark.parametrize("T,c_in,c_out,form,rotated,least", [
+    (600, 2048, 528, "packed", False, 0), (24, 11008, 272, "plain", True, 24 * 11008 * 2), (600, 2048, 528, "packed", True, 256 + 600 * 2048 * 2),
+])
+def test_least_workspace(P, T, c_in, c_out, form, rotated, least):
+    _check_linear(P, T, c_in, c_out, form, rotated, least)
+
+
+def _check_linear(P, T, c_in, c_out, form, rotated, least=None):
     import torch
     print(f"linear T={T} {c_in}->{c_out} {form} rotated={rotated}", flush=True)
     li = pin.make_custom(4000 + T + c_in, T, c_in, c_out, n_outlier=2)
@@ -61,7 +74,9 @@ def test_linear_against_oracle(P, T, c_in, c_out, form, rotated):
     if rotated:
         rot = P.Rotation(li.pairs, li.theta, li.ch_scale)
         P.paro_rotation_plan_build(rot)
-    ws = P.Workspace(P.paro_workspace_bytes(rot, w, T))
+    want = P.paro_workspace_bytes(rot, w, T)
+    assert least is None or least < want
+    ws = P.Workspace(want if least is None else least)
     x = torch.as_tensor(li.x).cuda()
     ybuf = torch.full((T, c_out + 24), 7.0, dtype=torch.float16, device="cuda")
     if rotated:
