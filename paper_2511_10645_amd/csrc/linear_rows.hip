@@ -1,20 +1,28 @@
-// W4A16 linear on weights in the interchange layout, up to 32 tokens (Eq. 2): what a call runs on when the weight was not
-// repacked, or has no repacked form because its input width is no multiple of 512 channels.  More tokens take
-// linear_tile.hip.
+// W4A16 linear in which every wave is on its own until its sums are complete (Eq. 2), in two forms:
+//   - weights in the interchange layout, up to 32 tokens: what a call runs on when the weight was not repacked, or has no
+//     repacked form because its input width is no multiple of 512 channels (more tokens: linear_tile.hip);
+//   - repacked weights with activations in operand order, 33 to 256 tokens, where the outputs are few: a rotation pass can
+//     write its result in any order, and writes it in this one (rotate.hip) where this kernel follows.
 //
-// A wave is independent of every other wave until its sums are complete.  A block is 4 waves and owns all tokens of 64
-// outputs; its waves take the channel groups in turn (wave w: groups w, w + 4, ...), so that every weight and every
-// activation enters the compute unit once and the loop has no LDS, no barrier and no hand-over:
+// A block is 4 waves and owns (16 TB tokens) x (16 NT outputs); its waves take the channel groups in turn (wave w: groups
+// w, w + 4, ...), so that every weight and every activation enters the compute unit once and the loop has no LDS, no
+// barrier and no hand-over:
 //   - weights: a lane's 16 bytes of a row's group are 32 channels of that row, which is the B operand of four
 //     v_mfma_f32_16x16x32_f16 once the codes stand in fp16 registers as q - z (exact; 14 vector instructions per 8
 //     weights in the natural code order, 9 in the repacked one); the group's scale multiplies the fp32 sums;
+//   - activations straight into fragment registers: in operand order a fragment is one contiguous kilobyte, of row-major
+//     rows it is 16-byte pieces of 32 cache lines (4096 -> 6144 at 64 tokens 10.6 against 14.6 us), which matters less
+//     the fewer the tokens are;
 //   - registers are a ring of two groups: a register is refilled for the group after next right after its last use.
 // The loop is written as slots, one MFMA each, with a piece of the next tile's dequantisation, a piece of the previous
 // tile's scaling and at most two loads in its shadow, pinned by scheduling barriers.  The 4 waves' sums meet in LDS once;
 // K is also split between blocks where the outputs alone are too few of them and the call has a scratch part.
 //
-// Bound by the weight stream and, at few groups per wave, by the chain load -> dequantise -> multiply -> sum.  The
-// kernel before it read the activations in 2-byte pieces for every output row: 11008 -> 4096 at 24 tokens 939 us.
+// Bound by the weight stream and, at few groups per wave, by the chain load -> dequantise -> multiply -> sum; at more
+// tokens by what a compute unit takes in (every block reads all activations: 512 KB at 64 tokens of 4096 channels), hence
+// only where the outputs are few.  Before, interchange layout, 11008 -> 4096 at 24 tokens: 939 us, now 17.  Before, repacked
+// (linear_tile.hip, mostly with split K and its summing launch), 64 tokens: 4096 -> 4096 13.3 us, now 6.9; 4096 -> 6144 14.7,
+// now 9.5; 14336 -> 4096 20.6, now 19.1; 128 tokens: 16.5, now 9.8; 18.3, now 14.6; 27.8, now 27.0.
 #include "paro_internal.h"
 #include <type_traits>
 
@@ -25,7 +33,7 @@ typedef _Float16 half2v __attribute__((ext_vector_type(2)));
 typedef float float4v __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
-constexpr int kRowsWaves = 4, kRowsTiles = 4;       // waves per block (K in turn); 16-output tiles per block
+constexpr int kRowsWaves = 4, kRowsTiles = 4;       // waves per block (K in turn); 16-output tiles per block (interchange layout)
 constexpr uint32_t kOobR = 0x80000000u;             // beyond every buffer: reads as zero
 
 __device__ inline __amdgpu_buffer_rsrc_t rows_rsrc(const void *p, size_t bytes)
@@ -46,47 +54,73 @@ __device__ __forceinline__ void rows_for(F &&f)
 }
 
 struct RowsArgs {
-    const char *qweight;
-    const _Float16 *scales;
+    const char *w;                                   // qweight, or the repacked blob
+    uint32_t scales_off, zeros_off;                  // of the blob
+    const _Float16 *scales;                          // interchange layout
     const uint32_t *qzeros;
-    const _Float16 *X; int64_t ldx;
+    const _Float16 *X; int64_t ldx;                  // row-major, or (OPERAND) blocks of 16 tokens x 128 channels of 4 KB
     _Float16 *Y; int64_t ldy;
     const _Float16 *bias;
     float *partial;                                  // [k slices][T][N] where K is split between blocks, else NULL
-    int T, C, N, G, groups_per_split;
-    uint32_t m_lo, k_lo;                             // 0x000F000F, 0x64006400: arguments, so that (u & m) | k is one instruction
-};
+    int T, C, N, G, m_tiles, n_tiles, k_split, groups_per_split;
+    uint32_t m_lo, m_hi, k_lo, k_hi;                 // 0x000F000F, 0x00F000F0, 0x64006400, 0x54005400: arguments, so that
+};                                                   // (u & m) | k is one instruction
 
-// TB: blocks of 16 tokens, 1 or 2
-template <int TB>
+// TB: blocks of 16 tokens per block; NT: tiles of 16 outputs; OPERAND: the second form above.  Activations in operand order:
+// a block of 16 tokens x one group is [4 fragments j][64 lanes][16 B], lane = 16 kb + token, channels 32 kb + 8 j .. + 7.
+template <int TB, int NT, bool OPERAND>
 __global__ __launch_bounds__(kRowsWaves * 64, 2) void linear_rows_kernel(RowsArgs a)
 {
-    constexpr int NT = kRowsTiles, R = 2;            // tiles of 16 outputs; ring of groups
+    constexpr int R = 2;                             // ring of groups
     constexpr int S = 4 * TB;                        // slots (MFMAs) per tile
     constexpr int P = 16 / S;                        // dequantisation pieces per slot
     static_assert(NT % 2 == 0 && (TB == 1 || TB == 2), "");
     __shared__ __attribute__((aligned(16))) float s_sum[kRowsWaves * TB * NT * 256];
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int n0 = blockIdx.x * 16 * NT;
+    // OPERAND: an XCD's blocks are a run of (K-slice, output tile, token tile), the last running fastest: its L2 serves a
+    // weight tile to the further token tiles, and every XCD gets the same number of blocks
+    const int tiles = a.m_tiles * a.n_tiles, all = tiles * a.k_split, per_xcd = (all + 7) / 8;
+    const int idx = OPERAND ? (int)(blockIdx.x & 7) * per_xcd + (int)(blockIdx.x >> 3) : 0;
+    if (OPERAND && idx >= all) return;
+    const int kslice = OPERAND ? idx / tiles : (int)blockIdx.y;
+    const int mt = OPERAND ? idx % tiles % a.m_tiles : 0, ntile = OPERAND ? idx % tiles / a.m_tiles : (int)blockIdx.x;
+    const int m0 = (int)rows_uniform(mt * 16 * TB), n0 = (int)rows_uniform(ntile * 16 * NT);
+    const int m_rows = min(a.T - m0, 16 * TB);
     const int n_rows = min(a.N - n0, 16 * NT);       // multiple of 16
-    const int g_end = min(a.G, (int)(blockIdx.y + 1) * a.groups_per_split);
-    const int g_first = blockIdx.y * a.groups_per_split + wave;
+    const int g_end = min(a.G, (int)rows_uniform((kslice + 1) * a.groups_per_split));
+    const int g_first = (int)rows_uniform(kslice * a.groups_per_split) + wave;
     const int n_grp = g_first < g_end ? (g_end - g_first + kRowsWaves - 1) / kRowsWaves : 0;   // of this wave
     const int ft = lane & 15, fkb = lane >> 4;
 
     // ---- addresses: a per-lane offset that is fixed (or out of range) plus a wave-uniform one -----------------------
-    const __amdgpu_buffer_rsrc_t xr = rows_rsrc(a.X, ((size_t)(a.T - 1) * a.ldx + a.C) * 2);
-    const __amdgpu_buffer_rsrc_t wr = rows_rsrc(a.qweight + (size_t)n0 * (a.C / 2), (size_t)n_rows * (a.C / 2));
-    const __amdgpu_buffer_rsrc_t sr = rows_rsrc(a.scales, (size_t)a.G * a.N * 2);
-    const __amdgpu_buffer_rsrc_t zr = rows_rsrc(a.qzeros, (size_t)a.G * a.N / 2);
-    uint32_t xv[TB];
-    rows_for<TB>([&](auto B) { xv[B] = B * 16 + ft < a.T ? (uint32_t)(((size_t)(B * 16 + ft) * a.ldx + fkb * 32) * 2) : kOobR; });
-    const uint32_t wv = (uint32_t)ft * (uint32_t)(a.C / 2) + fkb * 16;
-    // whole dwords, shifted where they are used: a 16-bit load's extension would be waited for where it is loaded
-    const uint32_t sv = (ft & 14) * 2u, zv = (ft >> 3) * 4u;
-    uint32_t n_tile[NT];                             // tiles beyond N read the last one again: their sums are not stored
-    rows_for<NT>([&](auto N_) { n_tile[N_] = rows_uniform(min((int)N_, n_rows / kTileN - 1) * kTileN); });
+    const int n_tb = (m_rows + 15) / 16;
+    const __amdgpu_buffer_rsrc_t xr = OPERAND ? rows_rsrc((const char *)a.X + (size_t)m0 * a.C * 2, (size_t)n_tb * 32 * a.C)
+                                              : rows_rsrc(a.X, ((size_t)(a.T - 1) * a.ldx + a.C) * 2);
+    const __amdgpu_buffer_rsrc_t wr = OPERAND ? rows_rsrc(a.w, a.zeros_off + packed_zeros_bytes(a.C, a.N))
+                                              : rows_rsrc(a.w + (size_t)n0 * (a.C / 2), (size_t)n_rows * (a.C / 2));
+    const __amdgpu_buffer_rsrc_t sr = rows_rsrc(a.scales, OPERAND ? 0 : (size_t)a.G * a.N * 2);
+    const __amdgpu_buffer_rsrc_t zr = rows_rsrc(a.qzeros, OPERAND ? 0 : (size_t)a.G * a.N / 2);
+    uint32_t xv[TB], x_base[TB];                     // per lane, and per block of 16 tokens (surplus blocks repeat the first)
+    rows_for<TB>([&](auto B) {
+        xv[B] = OPERAND ? lane * 16u : B * 16 + ft < a.T ? (uint32_t)(((size_t)(B * 16 + ft) * a.ldx + fkb * 32) * 2) : kOobR;
+        x_base[B] = OPERAND ? rows_uniform(B < n_tb ? B * 32u * (uint32_t)a.C : 0u) : 0u;
+    });
+    constexpr uint32_t kXGroup = OPERAND ? 4096 : kGroup * 2, kXFrag = OPERAND ? 1024 : 16;
+    const uint32_t wv = OPERAND ? lane * 16u : (uint32_t)ft * (uint32_t)(a.C / 2) + fkb * 16;
+    // Whole dwords, shifted where they are used: a 16-bit load's extension would be waited for where it is loaded.  (The
+    // wave's groups share g % 4 in the blob: they are kRowsWaves = 4 apart, and a split begins at a multiple of 4.)
+    static_assert(kRowsWaves == kSliceGroups, "");
+    const int g4 = g_first & 3;
+    const uint32_t sv = OPERAND ? ft * 8u + (g4 & 2) * 2 : (ft & 14) * 2u, zv = OPERAND ? (ft & 14) * 2u : (ft >> 3) * 4u;
+    const uint32_t s_shift = OPERAND ? 16 * (g4 & 1) : 16 * (ft & 1), z_shift = OPERAND ? 16 * (ft & 1) + 4 * g4 : 4 * (ft & 7);
+    // tiles beyond N read the last one again: their sums are not stored
+    uint32_t w_tile[NT], s_tile[NT];
+    rows_for<NT>([&](auto N_) {
+        const int n = min((int)N_, n_rows / kTileN - 1), tile = n0 / kTileN + n;
+        w_tile[N_] = rows_uniform(OPERAND ? (uint32_t)tile * (uint32_t)a.G * 1024u : (uint32_t)n * 16u * (uint32_t)(a.C / 2));
+        s_tile[N_] = rows_uniform(OPERAND ? (uint32_t)tile * (uint32_t)(a.G / kSliceGroups) : (uint32_t)(n0 + n * kTileN));
+    });
 
     half8 xa[R][TB][4];
     u32x4 wq[R][NT];
@@ -101,23 +135,30 @@ __global__ __launch_bounds__(kRowsWaves * 64, 2) void linear_rows_kernel(RowsArg
     };
     auto load_x = [&](int ring, int tb, int j) {
         union { u32x4 u; half8 h; } v;
-        v.u = __builtin_amdgcn_raw_buffer_load_b128(xr, (int)(l_xv[tb] + j * 16), (int)(l_g * kGroup * 2), 0);
+        v.u = __builtin_amdgcn_raw_buffer_load_b128(xr, (int)(l_xv[tb] + j * kXFrag), (int)(x_base[tb] + l_g * kXGroup), 0);
         xa[ring][tb][j] = v.h;
     };
     auto load_w = [&](int ring, int n) {
-        const uint32_t first = l_g * (uint32_t)a.N + n0 + n_tile[n];
-        wq[ring][n] = __builtin_amdgcn_raw_buffer_load_b128(wr, (int)l_wv, (int)(n_tile[n] * (uint32_t)(a.C / 2) + l_g * 64), 2);
-        wsc[ring][n] = (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(sr, (int)l_sv, (int)(first * 2u), 0);
-        wz[ring][n] = (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(zr, (int)l_zv, (int)(first / 2u), 0);
+        if constexpr (OPERAND) {
+            const uint32_t sl = s_tile[n] + (l_g >> 2);
+            wq[ring][n] = __builtin_amdgcn_raw_buffer_load_b128(wr, (int)l_wv, (int)(w_tile[n] + l_g * 1024u), 0);
+            wsc[ring][n] = (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(wr, (int)l_sv, (int)(a.scales_off + sl * 128u), 0);
+            wz[ring][n] = (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(wr, (int)l_zv, (int)(a.zeros_off + sl * 32u), 0);
+        } else {
+            const uint32_t first = l_g * (uint32_t)a.N + s_tile[n];
+            wq[ring][n] = __builtin_amdgcn_raw_buffer_load_b128(wr, (int)l_wv, (int)(w_tile[n] + l_g * 64u), 2);
+            wsc[ring][n] = (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(sr, (int)l_sv, (int)(first * 2u), 0);
+            wz[ring][n] = (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(zr, (int)l_zv, (int)(first / 2u), 0);
+        }
     };
 
     auto to_vgpr = [&](uint32_t v) { return (uint32_t)__builtin_amdgcn_ds_bpermute(lane << 2, (int)v); };
-    const uint32_t c_mlo = to_vgpr(a.m_lo), c_klo = to_vgpr(a.k_lo);
+    const uint32_t c_mlo = to_vgpr(a.m_lo), c_mhi = to_vgpr(a.m_hi), c_klo = to_vgpr(a.k_lo), c_khi = to_vgpr(a.k_hi);
 
     float4v tot[TB][NT], gacc[2][TB];
     union BFrag { u32x4 u; half8 h; } bf[2][4];
     float sc[2] = {0.f, 0.f};
-    half2v nz = rows_h2(0);
+    half2v nlo = rows_h2(0), nhi = rows_h2(0);
     uint32_t sp = 0;                                 // codes 0, 2 (then 1, 3 eight bits higher) of a half word, spread
     rows_for<TB>([&](auto B) {
         rows_for<NT>([&](auto N_) { tot[B][N_] = float4v{0.f, 0.f, 0.f, 0.f}; });
@@ -127,14 +168,24 @@ __global__ __launch_bounds__(kRowsWaves * 64, 2) void linear_rows_kernel(RowsArg
     // scale and refills the tile's registers (tile 0's are refilled in the next group's second slot)
     auto deq_piece = [&](auto PC, auto RING, auto N_, auto PAR) {
         constexpr int p = PC, w4 = p / 4, part = p % 4, ring = RING, n = N_, par = PAR;
-        if constexpr (p == 0) nz = rows_h2((0xE400u + ((wz[ring][n] >> (4 * (ft & 7))) & 15u)) * 0x00010001u);   // -(1024 + z), twice
+        if constexpr (p == 0) {
+            const uint32_t z = (wz[ring][n] >> z_shift) & 15u;
+            nlo = rows_h2((0xE400u + z) * 0x00010001u);                      // -(1024 + z), twice
+            if constexpr (OPERAND) nhi = rows_h2((0xD400u + (z << 4)) * 0x00010001u);    // -(64 + z), twice
+        }
         const uint32_t u = wq[ring][n][w4];
-        // codes 2 part and 2 part + 1 into the low nibbles of the two halves
-        if constexpr (part == 0) { const uint32_t x = u & 0xffffu; sp = x | (x << 12); }
-        if constexpr (part == 2) { const uint32_t x = u >> 16; sp = x | (x << 12); }
-        bf[par][w4].u[part] = rows_u32(rows_h2(((part & 1 ? sp >> 8 : sp) & c_mlo) | c_klo) + nz);
+        if constexpr (OPERAND) {
+            const uint32_t v = part < 2 ? u : u >> 8;
+            if constexpr (part & 1) bf[par][w4].u[part] = rows_u32(rows_h2((v & c_mhi) | c_khi) + nhi);
+            else bf[par][w4].u[part] = rows_u32(rows_h2((v & c_mlo) | c_klo) + nlo);
+        } else {
+            // codes 2 part and 2 part + 1 into the low nibbles of the two halves
+            if constexpr (part == 0) { const uint32_t x = u & 0xffffu; sp = x | (x << 12); }
+            if constexpr (part == 2) { const uint32_t x = u >> 16; sp = x | (x << 12); }
+            bf[par][w4].u[part] = rows_u32(rows_h2(((part & 1 ? sp >> 8 : sp) & c_mlo) | c_klo) + nlo);
+        }
         if constexpr (p == 15) {
-            union { uint16_t u; _Float16 h; } c; c.u = (uint16_t)(wsc[ring][n] >> (16 * (ft & 1)));
+            union { uint16_t u; _Float16 h; } c; c.u = (uint16_t)(wsc[ring][n] >> s_shift);
             sc[par] = (float)c.h;
             if constexpr (n > 0) load_w(ring, n);
         }
@@ -192,16 +243,16 @@ __global__ __launch_bounds__(kRowsWaves * 64, 2) void linear_rows_kernel(RowsArg
         for (int w = 1; w < kRowsWaves; ++w) sum += *(const float4v *)(s_sum + w * TB * NT * 256 + u * 4);
         const int col = n0 + n * 16 + (l & 15);
         if (a.partial) {
-            float *dst = a.partial + ((size_t)blockIdx.y * a.T + t0) * a.N + col;
+            float *dst = a.partial + ((size_t)kslice * a.T + m0 + t0) * a.N + col;
 #pragma unroll
             for (int r = 0; r < 4; ++r)
-                if (t0 + r < a.T) dst[(size_t)r * a.N] = sum[r];
+                if (t0 + r < m_rows) dst[(size_t)r * a.N] = sum[r];
         } else {
             const float bv = a.bias ? (float)a.bias[col] : 0.f;
-            _Float16 *dst = a.Y + (size_t)t0 * a.ldy + col;
+            _Float16 *dst = a.Y + (size_t)(m0 + t0) * a.ldy + col;
 #pragma unroll
             for (int r = 0; r < 4; ++r)
-                if (t0 + r < a.T) dst[(size_t)r * a.ldy] = (_Float16)(sum[r] + bv);
+                if (t0 + r < m_rows) dst[(size_t)r * a.ldy] = (_Float16)(sum[r] + bv);
         }
     }
 }
@@ -237,21 +288,95 @@ hipError_t launch_linear_rows(const paro_w4_weight &w, const paro_half_t *X, int
                               void *scratch, size_t scratch_bytes, hipStream_t s)
 {
     RowsArgs a;
-    a.qweight = (const char *)w.qweight; a.scales = (const _Float16 *)w.scales; a.qzeros = w.qzeros;
+    a.w = (const char *)w.qweight; a.scales_off = a.zeros_off = 0; a.m_tiles = a.n_tiles = a.k_split = 0; a.scales = (const _Float16 *)w.scales; a.qzeros = w.qzeros;
     a.X = (const _Float16 *)X; a.ldx = ldx; a.Y = (_Float16 *)Y; a.ldy = ldy; a.bias = (const _Float16 *)w.bias;
     a.T = T; a.C = w.c_in; a.N = w.c_out; a.G = w.c_in / kGroup;
-    a.m_lo = 0x000F000Fu; a.k_lo = 0x64006400u;
+    a.m_lo = 0x000F000Fu; a.m_hi = 0x00F000F0u; a.k_lo = 0x64006400u; a.k_hi = 0x54005400u;
     int ks;
     rows_split(w.c_in, w.c_out, ks, a.groups_per_split);
     const bool split = ks > 1 && scratch && scratch_bytes >= (size_t)ks * T * w.c_out * sizeof(float) && ((uintptr_t)scratch % 16) == 0;
     if (!split) { ks = 1; a.groups_per_split = a.G; }
     a.partial = split ? (float *)scratch : nullptr;
     const dim3 grid((w.c_out + 16 * kRowsTiles - 1) / (16 * kRowsTiles), ks), block(kRowsWaves * 64);
-    if (T <= 16) hipLaunchKernelGGL(linear_rows_kernel<1>, grid, block, 0, s, a);
-    else         hipLaunchKernelGGL(linear_rows_kernel<2>, grid, block, 0, s, a);
+    if (T <= 16) hipLaunchKernelGGL((linear_rows_kernel<1, kRowsTiles, false>), grid, block, 0, s, a);
+    else         hipLaunchKernelGGL((linear_rows_kernel<2, kRowsTiles, false>), grid, block, 0, s, a);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || !split) return e;
     return launch_splitk_reduce(a.partial, ks, T, 0, w.c_out, w.bias, Y, ldy, s);
+}
+
+// ---- repacked weights, activations in operand order ---------------------------------------------------------------------
+// Outputs per block and K split from a cost model fitted to 4226 timings (140 shapes, 33 to 256 tokens, activations already in
+// operand order), 4 to 6 % off: per round of blocks over the chip a chain of steps (a group per wave each), the weight
+// stream, what further blocks of the same compute unit add, and for split K the summing launch and the partial tiles.
+// 32 outputs per block where they then fit one round (4096 -> 4096 at 64 tokens: 6.9 us, 64 outputs 9.4); 64 beyond it, for
+// every block reads all of its activations (4096 -> 28672: 33.4 against 40.3 us).
+struct OperandPlan { int nt, k_split, groups_per_split; double est_us; };
+static OperandPlan plan_operand(int c_in, int c_out, int T)
+{
+    OperandPlan best{4, 1, 0, 1e30};
+    const int G = c_in / kGroup, m_tiles = (T + 31) / 32;
+    const double mb = (double)c_in * c_out / 2.0e6;
+    for (int nt = 2; nt <= 4; nt += 2) {
+        const int n_tiles = (c_out + 16 * nt - 1) / (16 * nt);
+        for (int ks = 1; ks <= 4 && (ks == 1 || (G >= ks * 8 && (long)m_tiles * n_tiles * ks <= 512)); ++ks) {
+            const int gps = ((G + ks - 1) / ks + kRowsWaves - 1) / kRowsWaves * kRowsWaves;
+            if ((G + gps - 1) / gps != ks) continue;
+            const long blocks = (long)m_tiles * n_tiles * ks;
+            const double rounds = (double)((blocks + 255) / 256), steps = (gps / kRowsWaves + 1) / 2 * 2;
+            const double more = blocks > 256 ? (double)blocks / 256.0 - 1.0 : 0.0, part_mb = (double)ks * T * c_out * 8.0 / 1.0e6;
+            double us = nt == 2 ? 2.74 + rounds * (0.21 + 0.40 * steps) + more * (0.28 + 0.057 * steps) + 0.108 * mb
+                                : 3.82 + rounds * 0.637 * steps + more * (1.03 + 0.019 * steps) + 0.085 * mb;
+            if (ks > 1) us += 2.0 + (nt == 2 ? 0.227 : 0.175) * part_mb;
+            if (us < best.est_us) best = OperandPlan{nt, ks, gps, us};
+        }
+    }
+    return best;
+}
+
+// 33 to 256 tokens (measured range; below, the streaming kernel hosts or follows the rotation), 31-bit byte offsets
+bool linear_operand_supported(const paro_w4_weight &w, int T)
+{
+    return T > 32 && T <= 256 && linear_tile_supported(w, false) && (size_t)(T + 15) * w.c_in * 2 < (1ull << 31);
+}
+
+double linear_operand_estimate_us(const paro_w4_weight &w, int T) { return plan_operand(w.c_in, w.c_out, T).est_us; }
+
+size_t linear_operand_scratch_bytes(const paro_w4_weight &w, int T)
+{
+    const OperandPlan p = plan_operand(w.c_in, w.c_out, T);
+    return p.k_split > 1 ? (size_t)p.k_split * T * w.c_out * sizeof(float) : 0;
+}
+
+template <int NT>
+static hipError_t launch_operand_nt(RowsArgs &a, hipStream_t s)
+{
+    a.m_tiles = (a.T + 31) / 32; a.n_tiles = (a.N + 16 * NT - 1) / (16 * NT);
+    hipLaunchKernelGGL((linear_rows_kernel<2, NT, true>), dim3((unsigned)(a.m_tiles * a.n_tiles * a.k_split + 7) / 8 * 8),
+                       dim3(kRowsWaves * 64), 0, s, a);
+    return hipGetLastError();
+}
+
+hipError_t launch_linear_operand(const paro_w4_weight &w, const paro_half_t *Xop, paro_half_t *Y, int64_t ldy, int T, void *scratch,
+                                 size_t scratch_bytes, hipStream_t s)
+{
+    OperandPlan p = plan_operand(w.c_in, w.c_out, T);
+    RowsArgs a;
+    a.w = (const char *)w.packed;
+    a.scales_off = (uint32_t)packed_tiles_bytes(w.c_in, w.c_out);
+    a.zeros_off = a.scales_off + (uint32_t)packed_scales_bytes(w.c_in, w.c_out);
+    a.scales = nullptr; a.qzeros = nullptr;
+    a.X = (const _Float16 *)Xop; a.ldx = 0; a.Y = (_Float16 *)Y; a.ldy = ldy; a.bias = (const _Float16 *)w.bias;
+    a.T = T; a.C = w.c_in; a.N = w.c_out; a.G = w.c_in / kGroup;
+    a.m_lo = 0x000F000Fu; a.m_hi = 0x00F000F0u; a.k_lo = 0x64006400u; a.k_hi = 0x54005400u;
+    if (p.k_split > 1 && !(scratch && scratch_bytes >= (size_t)p.k_split * T * w.c_out * sizeof(float) && ((uintptr_t)scratch % 16) == 0)) {
+        p.k_split = 1; p.groups_per_split = a.G;
+    }
+    a.k_split = p.k_split; a.groups_per_split = p.groups_per_split;
+    a.partial = p.k_split > 1 ? (float *)scratch : nullptr;
+    const hipError_t e = p.nt == 2 ? launch_operand_nt<2>(a, s) : launch_operand_nt<4>(a, s);
+    if (e != hipSuccess || p.k_split == 1) return e;
+    return launch_splitk_reduce(a.partial, p.k_split, T, 0, w.c_out, w.bias, Y, ldy, s);
 }
 
 }  // namespace paro

@@ -124,6 +124,8 @@ inline void once_done(std::atomic<uint64_t> &done, int dev)
 hipError_t launch_plan_build(const paro_rotation &rot, void *plan_out, hipStream_t s);
 hipError_t launch_rotate_planned(const paro_rotation &rot, const paro_half_t *X, int64_t ldx,
                                  paro_half_t *Xr, int64_t ldxr, int T, hipStream_t s);
+// The same into whole blocks of 16 tokens in operand order (linear_rows.hip): room for ceil(T / 16) * 16 rows.
+hipError_t launch_rotate_operand(const paro_rotation &rot, const paro_half_t *X, int64_t ldx, paro_half_t *Xop, int T, hipStream_t s);
 hipError_t launch_rotate_generic(const paro_rotation &rot, const paro_half_t *X, int64_t ldx,
                                  paro_half_t *Xr, int64_t ldxr, int T, hipStream_t s);
 
@@ -189,6 +191,13 @@ bool linear_rows_supported(const paro_w4_weight &w, int64_t ldx, int T);
 size_t linear_rows_scratch_bytes(const paro_w4_weight &w, int T);
 hipError_t launch_linear_rows(const paro_w4_weight &w, const paro_half_t *X, int64_t ldx, paro_half_t *Y, int64_t ldy,
                               int T, void *scratch, size_t scratch_bytes, hipStream_t s);
+
+// Repacked weights on activations in operand order (linear_rows.hip); scratch as above.
+bool linear_operand_supported(const paro_w4_weight &w, int T);
+double linear_operand_estimate_us(const paro_w4_weight &w, int T);
+size_t linear_operand_scratch_bytes(const paro_w4_weight &w, int T);
+hipError_t launch_linear_operand(const paro_w4_weight &w, const paro_half_t *Xop, paro_half_t *Y, int64_t ldy, int T, void *scratch,
+                                 size_t scratch_bytes, hipStream_t s);
 
 // Tiled linear with the weights in registers (linear_tile.hip), repacked or interchange layout; scratch as above.
 bool linear_tile_supported(const paro_w4_weight &w, bool interchange);

@@ -219,7 +219,10 @@ __device__ __forceinline__ void static_while_rot(F &&f)
 // barrier: LDS operations of one wave execute in issue order).  The loads of the next batch of
 // tokens are issued before the current batch is rotated.  Rows are read completely before any of
 // them is written, so X and Xr may be the same buffer.
-template <int K>
+// OPERAND: the result leaves in the operand order of linear_rows.hip, whole blocks of 16 tokens x 128 channels of 4 KB
+// [4 fragments][64 lanes][16 B], lane = 16 (channel / 32) + token: 4 lanes exchange their 4 tokens, and a batch leaves as one
+// store of 16 pieces of 64 bytes.  Rows beyond T up to the next multiple of 4 are written too (the blocks have room).
+template <int K, bool OPERAND = false>
 __global__ __launch_bounds__(kRotWaves * 64) void rotate_planned_kernel(const uint32_t *__restrict__ plan,
                                                                          const _Float16 *X, int64_t ldx,
                                                                          _Float16 *Xr, int64_t ldxr, int T,
@@ -240,10 +243,15 @@ __global__ __launch_bounds__(kRotWaves * 64) void rotate_planned_kernel(const ui
     const __amdgpu_buffer_rsrc_t xr = __builtin_amdgcn_make_buffer_rsrc(
         const_cast<_Float16 *>(X + (size_t)t0 * ldx + (size_t)g * kGroup), 0, (int)((size_t)(n_tok - 1) * ldx * 2 + kGroup * 2),
         0x00020000);
-    const __amdgpu_buffer_rsrc_t yr = __builtin_amdgcn_make_buffer_rsrc(
-        Xr + (size_t)t0 * ldxr + (size_t)g * kGroup, 0, (int)((size_t)(n_tok - 1) * ldxr * 2 + kGroup * 2), 0x00020000);
+    const size_t block = (size_t)gridDim.x * 4096;                     // OPERAND: bytes per 16 tokens
+    const __amdgpu_buffer_rsrc_t yr =
+        OPERAND ? __builtin_amdgcn_make_buffer_rsrc((char *)Xr + t0 / 16 * block + (size_t)g * 4096, 0,
+                                                    (int)((size_t)((t0 + n_tok + 15) / 16 - t0 / 16 - 1) * block + 4096), 0x00020000)
+                : __builtin_amdgcn_make_buffer_rsrc(Xr + (size_t)t0 * ldxr + (size_t)g * kGroup, 0,
+                                                    (int)((size_t)(n_tok - 1) * ldxr * 2 + kGroup * 2), 0x00020000);
     const int row_x = (int)(ldx * 2), row_y = (int)(ldxr * 2);         // bytes per token row
     const int v4 = lane * 4;
+    const int vop = ((lane >> 2) & 3) * 1024 + (lane >> 4) * 256 + (lane & 3) * 16;  // OPERAND: fragment, quarter of the channels, token
     uint32_t cur[kRotTU], nxt[kRotTU];
 #pragma unroll
     for (int u = 0; u < kRotTU; ++u) cur[u] = __builtin_amdgcn_raw_buffer_load_b32(xr, v4 + u * row_x, 0, 0);
@@ -295,8 +303,23 @@ __global__ __launch_bounds__(kRotWaves * 64) void rotate_planned_kernel(const ui
         __builtin_amdgcn_wave_barrier();
         const u32x4v out = *(const u32x4v *)(sp + lane * 16);
         const uint32_t o[kRotTU] = {lo_pair(out[0], out[2]), hi_pair(out[0], out[2]), lo_pair(out[1], out[3]), hi_pair(out[1], out[3])};
+        if constexpr (OPERAND) {
+            // 4 x 4 transpose between the 4 lanes of 8 channels: lane i has their 16 bytes of token i
+            auto exchange = [&](uint32_t &x, uint32_t &y, bool upper, auto perm) {
+                const uint32_t r = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(upper ? x : y), decltype(perm)::value, 0xF, 0xF, true);
+                if (upper) x = r; else y = r;
+            };
+            uint32_t v0 = o[0], v1 = o[1], v2 = o[2], v3 = o[3];
+            const std::integral_constant<int, 0xB1> xor1; const std::integral_constant<int, 0x4E> xor2;
+            exchange(v0, v1, lane & 1, xor1); exchange(v2, v3, lane & 1, xor1);
+            exchange(v0, v2, lane & 2, xor2); exchange(v1, v3, lane & 2, xor2);
+            const u32x4v v = {v0, v1, v2, v3};
+            const int tau = (t0 & 15) + t;
+            __builtin_amdgcn_raw_buffer_store_b128(v, yr, vop + (tau & 15) * 16 + (tau >> 4) * (int)block, 0, 0);
+        } else {
 #pragma unroll
-        for (int u = 0; u < kRotTU; ++u) __builtin_amdgcn_raw_buffer_store_b32(o[u], yr, v4 + (t + u) * row_y, 0, 0);
+            for (int u = 0; u < kRotTU; ++u) __builtin_amdgcn_raw_buffer_store_b32(o[u], yr, v4 + (t + u) * row_y, 0, 0);
+        }
         __builtin_amdgcn_wave_barrier();
 #pragma unroll
         for (int u = 0; u < kRotTU; ++u) cur[u] = nxt[u];
@@ -304,7 +327,7 @@ __global__ __launch_bounds__(kRotWaves * 64) void rotate_planned_kernel(const ui
     });
 }
 
-template <int K>
+template <int K, bool OPERAND>
 static hipError_t launch_rotate_k(const paro_rotation &rot, const paro_half_t *X, int64_t ldx, paro_half_t *Xr,
                                   int64_t ldxr, int T, hipStream_t s)
 {
@@ -315,25 +338,37 @@ static hipError_t launch_rotate_k(const paro_rotation &rot, const paro_half_t *X
     while (tpw > kRotTU && (int64_t)G * ((T + tpw - 1) / tpw) < 4096) tpw >>= 1;
     int waves_t = (T + tpw - 1) / tpw;
     dim3 grid(G, (waves_t + kRotWaves - 1) / kRotWaves);
-    hipLaunchKernelGGL(rotate_planned_kernel<K>, grid, dim3(kRotWaves * 64), 0, s, (const uint32_t *)rot.plan,
+    hipLaunchKernelGGL((rotate_planned_kernel<K, OPERAND>), grid, dim3(kRotWaves * 64), 0, s, (const uint32_t *)rot.plan,
                        (const _Float16 *)X, ldx, (_Float16 *)Xr, ldxr, T, tpw);
     return hipGetLastError();
+}
+
+template <bool OPERAND>
+static hipError_t launch_rotate(const paro_rotation &rot, const paro_half_t *X, int64_t ldx, paro_half_t *Xr, int64_t ldxr, int T,
+                                hipStream_t s)
+{
+    switch (rot.n_layers) {
+    case 0: return launch_rotate_k<0, OPERAND>(rot, X, ldx, Xr, ldxr, T, s);
+    case 1: return launch_rotate_k<1, OPERAND>(rot, X, ldx, Xr, ldxr, T, s);
+    case 2: return launch_rotate_k<2, OPERAND>(rot, X, ldx, Xr, ldxr, T, s);
+    case 3: return launch_rotate_k<3, OPERAND>(rot, X, ldx, Xr, ldxr, T, s);
+    case 4: return launch_rotate_k<4, OPERAND>(rot, X, ldx, Xr, ldxr, T, s);
+    case 5: return launch_rotate_k<5, OPERAND>(rot, X, ldx, Xr, ldxr, T, s);
+    case 6: return launch_rotate_k<6, OPERAND>(rot, X, ldx, Xr, ldxr, T, s);
+    case 7: return launch_rotate_k<7, OPERAND>(rot, X, ldx, Xr, ldxr, T, s);
+    default: return launch_rotate_k<8, OPERAND>(rot, X, ldx, Xr, ldxr, T, s);
+    }
 }
 
 hipError_t launch_rotate_planned(const paro_rotation &rot, const paro_half_t *X, int64_t ldx, paro_half_t *Xr,
                                  int64_t ldxr, int T, hipStream_t s)
 {
-    switch (rot.n_layers) {
-    case 0: return launch_rotate_k<0>(rot, X, ldx, Xr, ldxr, T, s);
-    case 1: return launch_rotate_k<1>(rot, X, ldx, Xr, ldxr, T, s);
-    case 2: return launch_rotate_k<2>(rot, X, ldx, Xr, ldxr, T, s);
-    case 3: return launch_rotate_k<3>(rot, X, ldx, Xr, ldxr, T, s);
-    case 4: return launch_rotate_k<4>(rot, X, ldx, Xr, ldxr, T, s);
-    case 5: return launch_rotate_k<5>(rot, X, ldx, Xr, ldxr, T, s);
-    case 6: return launch_rotate_k<6>(rot, X, ldx, Xr, ldxr, T, s);
-    case 7: return launch_rotate_k<7>(rot, X, ldx, Xr, ldxr, T, s);
-    default: return launch_rotate_k<8>(rot, X, ldx, Xr, ldxr, T, s);
-    }
+    return launch_rotate<false>(rot, X, ldx, Xr, ldxr, T, s);
+}
+
+hipError_t launch_rotate_operand(const paro_rotation &rot, const paro_half_t *X, int64_t ldx, paro_half_t *Xop, int T, hipStream_t s)
+{
+    return launch_rotate<true>(rot, X, ldx, Xop, 0, T, s);
 }
 
 // ------------------------------------------------------------------------------------------
