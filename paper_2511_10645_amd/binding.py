@@ -126,7 +126,8 @@ def _check(st: int, where: str):
 
 
 def _stream() -> int:
-    return torch.cuda.current_stream().cuda_stream
+    # the current stream's handle without a Stream object around it: 0.3 us of host time a call instead of 2.7
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
 
 
 def _ptr(t):
@@ -345,8 +346,9 @@ def paro_rotate_scale(rot: Rotation, X: torch.Tensor, Xr: torch.Tensor | None = 
 def paro_w4a16_linear(w: W4Weight, X: torch.Tensor, ws: Workspace | None = None, Y: torch.Tensor | None = None):
     T, ldx = _rows(X)
     if Y is None:
-        Y = torch.empty((T, w.c_out), dtype=torch.float16, device=X.device)
-    _, ldy = _rows(Y)
+        Y, ldy = torch.empty((T, w.c_out), dtype=torch.float16, device=X.device), w.c_out
+    else:
+        _, ldy = _rows(Y)
     _check(lib().paro_w4a16_linear(w.ref(), X.data_ptr(), ldx, Y.data_ptr(), ldy, T,
                                    ws.buf.data_ptr() if ws else None, ws.nbytes if ws else 0, _stream()),
            "paro_w4a16_linear")
@@ -356,8 +358,9 @@ def paro_w4a16_linear(w: W4Weight, X: torch.Tensor, ws: Workspace | None = None,
 def paro_rotated_linear(rot: Rotation, w: W4Weight, X: torch.Tensor, ws: Workspace, Y: torch.Tensor | None = None):
     T, ldx = _rows(X)
     if Y is None:
-        Y = torch.empty((T, w.c_out), dtype=torch.float16, device=X.device)
-    _, ldy = _rows(Y)
+        Y, ldy = torch.empty((T, w.c_out), dtype=torch.float16, device=X.device), w.c_out
+    else:
+        _, ldy = _rows(Y)
     _check(lib().paro_rotated_linear(rot.ref(), w.ref(), X.data_ptr(), ldx, Y.data_ptr(), ldy, T,
                                      ws.buf.data_ptr(), ws.nbytes, _stream()), "paro_rotated_linear")
     return Y
@@ -519,8 +522,9 @@ def paro_rotated_linear_mxfp4(rot: Rotation, w: Mxfp4Weight, X: torch.Tensor, ws
     """Transform + MXFP4-quantise the activations into `ws` (uint8 tensor), then the MXFP4 x MXFP4 linear."""
     T, ldx = _rows(X)
     if Y is None:
-        Y = torch.empty((T, w.c_out), dtype=torch.float16, device=X.device)
-    _, ldy = _rows(Y)
+        Y, ldy = torch.empty((T, w.c_out), dtype=torch.float16, device=X.device), w.c_out
+    else:
+        _, ldy = _rows(Y)
     _check(lib().paro_rotated_linear_mxfp4(rot.ref(), w.ref(), X.data_ptr(), ldx, Y.data_ptr(), ldy, T, ws.data_ptr(),
                                            ws.numel(), _stream()), "paro_rotated_linear_mxfp4")
     return Y
