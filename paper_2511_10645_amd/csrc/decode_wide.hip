@@ -58,10 +58,28 @@ __device__ __forceinline__ void static_while(F &&f)
 // of one wave execute in issue order.
 constexpr int kXsRowBytes = kGroup * 2 + 16;
 constexpr int kXsWords = 16 * kXsRowBytes / 4;      // 1088 floats per wave
-template <int TB>
+// XOP: X is in operand order (a rotation pass can write it: rotate.hip), blocks of 16 tokens x 128 channels of 4 KB whose
+// fragments are one contiguous kilobyte each: no detour through LDS.  Rotated linears at 16
+// tokens, four layers of 4096 -> 6144, 4096 -> 4096, 4096 -> 28672 and 14336 -> 4096: 210 -> 204 us.
+template <int TB, bool XOP>
 __device__ __forceinline__ void load_x_fragments(const DecodeArgs &a, int ks, bool slice_ok, int lane, char *xs,
                                                  half8 (&xf)[TB][kSliceGroups][4])
 {
+    if constexpr (XOP) {
+        const __amdgpu_buffer_rsrc_t xr = make_rsrc(a.X, (uint32_t)TB * 32u * (uint32_t)a.C);
+        const uint32_t off = slice_ok ? (uint32_t)ks * (kSliceGroups * 4096u) + lane * 16u : kOob;
+#pragma unroll
+        for (int g2 = 0; g2 < kSliceGroups; ++g2)
+#pragma unroll
+            for (int tb = 0; tb < TB; ++tb)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    union { u32x4 u; half8 h; } v;
+                    v.u = __builtin_amdgcn_raw_buffer_load_b128(xr, (int)(off + g2 * 4096 + j * 1024), tb * 32 * a.C, 0);
+                    xf[tb][g2][j] = v.h;
+                }
+        return;
+    }
     const __amdgpu_buffer_rsrc_t xr = make_rsrc(a.X, (uint32_t)(((size_t)(a.T - 1) * a.ldx + a.C) * 2));
     const int lr = lane >> 4, lc = lane & 15;
     u32x4 raw[TB][kSliceGroups][4];
@@ -103,7 +121,7 @@ __device__ __forceinline__ void load_x_fragments(const DecodeArgs &a, int ks, bo
 // MAXW: most waves per block (8: two waves per SIMD and 256 registers; otherwise kWideWaves).
 constexpr int kRotStageWords = kSliceCh / 2;     // the slice's 512 fp16 activations of one token, in floats
 
-template <bool SPLIT, bool T1, int ROTK = 0, int MAXW = kWideWaves>
+template <bool SPLIT, bool T1, int ROTK = 0, int MAXW = kWideWaves, bool XOP = false>
 __global__ __launch_bounds__(MAXW * 64) void decode_wide_kernel(DecodeArgs a)
 {
     static_assert(ROTK == 0 || T1, "the hosted transform is for one token");
@@ -195,7 +213,7 @@ __global__ __launch_bounds__(MAXW * 64) void decode_wide_kernel(DecodeArgs a)
         __builtin_amdgcn_wave_barrier();                                      // the area holds partial sums from here on
     } else if constexpr (!T1) {
         half8 xt[1][kSliceGroups][4];
-        load_x_fragments<1>(a, ks, slice_ok, lane, (char *)s_mine, xt);
+        load_x_fragments<1, XOP>(a, ks, slice_ok, lane, (char *)s_mine, xt);
 #pragma unroll
         for (int g2 = 0; g2 < kSliceGroups; ++g2)
 #pragma unroll
@@ -290,7 +308,7 @@ __global__ __launch_bounds__(MAXW * 64) void decode_wide_kernel(DecodeArgs a)
 constexpr int kWide2MaxTiles = 9;
 constexpr int kWide2Waves = 8;                   // 2 waves per SIMD: the two sets of activation fragments need 256 registers
 
-template <bool SPLIT>
+template <bool SPLIT, bool XOP>
 __global__ __launch_bounds__(kWide2Waves * 64) void decode_wide2_kernel(DecodeArgs a)
 {
     constexpr int NS = kWideStages;
@@ -312,7 +330,7 @@ __global__ __launch_bounds__(kWide2Waves * 64) void decode_wide2_kernel(DecodeAr
 
     Stage st[NS];
     half8 xf[2][kSliceGroups][4];
-    load_x_fragments<2>(a, ks, slice_ok, lane, (char *)s_mine, xf);
+    load_x_fragments<2, XOP>(a, ks, slice_ok, lane, (char *)s_mine, xf);
 #pragma unroll
     for (int s = 0; s + 1 < NS; ++s) load_stage(blob, a, tile_of(s), ks, lane, st[s]);
     auto to_vgpr = [&](uint32_t v) { return (uint32_t)__builtin_amdgcn_ds_bpermute(lane << 2, (int)v); };
@@ -430,9 +448,11 @@ bool decode_wide_hosting_pays(int c_in, int c_out)
 
 // ws: the exchange part of the workspace (may be NULL where no partial sums are exchanged).
 // rot: NULL for the bare linear; otherwise a transform decode_wide_hosts() accepts, applied to X by the kernel itself.
+// x_operand: X holds ceil(T / 16) blocks in operand order (2..32 tokens).
 hipError_t launch_decode_wide(const paro_w4_weight &w, const paro_half_t *X, int64_t ldx, paro_half_t *Y, int64_t ldy,
-                              int T, void *ws, hipStream_t s, const paro_rotation *rot)
+                              int T, void *ws, hipStream_t s, const paro_rotation *rot, bool x_operand)
 {
+    if (x_operand && (rot || T < 2 || T > kWideMaxTokens)) return hipErrorInvalidValue;
     if (packed_blob_bytes(w.c_in, w.c_out) >= (1ull << 31)) return hipErrorInvalidValue;   // 32-bit buffer offsets (checked by the caller)
     if (rot && (!decode_wide_hosts(*rot, T) || rot->c_in != w.c_in)) return hipErrorInvalidValue;
     const WideGeometry g = wide_geometry(w.c_in, w.c_out, T, rot != nullptr);
@@ -455,7 +475,10 @@ hipError_t launch_decode_wide(const paro_w4_weight &w, const paro_half_t *X, int
     if (const int dev = once_pending(attr_done); dev >= 0) {
         const void *fns[] = {(const void *)decode_wide_kernel<false, false>, (const void *)decode_wide_kernel<false, true>,
                              (const void *)decode_wide_kernel<true, false>, (const void *)decode_wide_kernel<true, true>,
-                             (const void *)decode_wide2_kernel<false>, (const void *)decode_wide2_kernel<true>,
+                             (const void *)decode_wide2_kernel<false, false>, (const void *)decode_wide2_kernel<true, false>,
+                             (const void *)decode_wide2_kernel<false, true>, (const void *)decode_wide2_kernel<true, true>,
+                             (const void *)decode_wide_kernel<false, false, 0, kWideWaves, true>,
+                             (const void *)decode_wide_kernel<true, false, 0, kWideWaves, true>,
                              (const void *)decode_wide_kernel<false, true, 8, 8>, (const void *)decode_wide_kernel<true, true, 8, 8>,
                              (const void *)decode_wide_kernel<false, true, 8>};
         for (const void *f : fns) {
@@ -471,9 +494,14 @@ hipError_t launch_decode_wide(const paro_w4_weight &w, const paro_half_t *X, int
         if (g.kb > 1)          hipLaunchKernelGGL((decode_wide_kernel<true, true, 8, 8>), grid, block, g.lds, s, a);
         else if (g.waves <= 8) hipLaunchKernelGGL((decode_wide_kernel<false, true, 8, 8>), grid, block, g.lds, s, a);
         else                   hipLaunchKernelGGL((decode_wide_kernel<false, true, 8>), grid, block, g.lds, s, a);
+    } else if (x_operand) {
+        if (T > 16 && g.kb > 1) hipLaunchKernelGGL((decode_wide2_kernel<true, true>), grid, block, g.lds, s, a);
+        else if (T > 16)        hipLaunchKernelGGL((decode_wide2_kernel<false, true>), grid, block, g.lds, s, a);
+        else if (g.kb > 1)      hipLaunchKernelGGL((decode_wide_kernel<true, false, 0, kWideWaves, true>), grid, block, g.lds, s, a);
+        else                    hipLaunchKernelGGL((decode_wide_kernel<false, false, 0, kWideWaves, true>), grid, block, g.lds, s, a);
     } else if (T > 16) {
-        if (g.kb > 1) hipLaunchKernelGGL((decode_wide2_kernel<true>), grid, block, g.lds, s, a);
-        else          hipLaunchKernelGGL((decode_wide2_kernel<false>), grid, block, g.lds, s, a);
+        if (g.kb > 1) hipLaunchKernelGGL((decode_wide2_kernel<true, false>), grid, block, g.lds, s, a);
+        else          hipLaunchKernelGGL((decode_wide2_kernel<false, false>), grid, block, g.lds, s, a);
     } else if (T == 1) {
         if (g.kb > 1) hipLaunchKernelGGL((decode_wide_kernel<true, true>), grid, block, g.lds, s, a);
         else          hipLaunchKernelGGL((decode_wide_kernel<false, true>), grid, block, g.lds, s, a);

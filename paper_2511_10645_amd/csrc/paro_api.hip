@@ -11,6 +11,7 @@ namespace {
 constexpr int kFuseMaxTokens = 4;            // the K-major decode kernel hosts the rotation up to this many tokens
 constexpr int64_t kMaxRowStride = 1 << 22;   // elements; the kernels address a run of up to 256 rows with 31-bit byte offsets
 constexpr int kDecodeMaxTokens = 16;         // above this the MFMA GEMM competes with passes of the streaming decode kernel
+constexpr int kOperandMinTokens = 9;         // rotation pass in operand order (whole blocks of 16 rows) from here on
 constexpr int kStreamPassTokens = 32;        // tokens of one pass of the streaming kernel (two blocks of 16)
 
 inline bool aligned(const void *p, size_t a) { return ((uintptr_t)p % a) == 0; }
@@ -122,6 +123,7 @@ WsLayout ws_layout(const paro_rotation *rot, const paro_w4_weight *w, int T, boo
             }
             L.gemm_bytes = round_up(scratch, 256);
         }
+        if (!lean && rot && rot->plan && T >= kOperandMinTokens && T <= kStreamPassTokens) xr_rows = (T + 15) / 16 * 16;
     } else if (rot && !lean) {
         // weights in the interchange layout; the bare call needs no workspace and runs without the split
         L.gemm_bytes = round_up(T <= kStreamPassTokens ? linear_rows_scratch_bytes(*w, T) : linear_tile_scratch_bytes(*w, T), 256);
@@ -428,6 +430,11 @@ static paro_status rotated_linear(const paro_rotation *rot, const paro_w4_weight
     if (operand_route(rot, w, ldy, T, L)) {
         if (launch_rotate_operand(*rot, X, ldx, xr, T, s) != hipSuccess) return PARO_ERR_HIP;
         return from_hip(launch_linear_operand(*w, xr, Y, ldy, T, scratch2, L.gemm_bytes, s));
+    }
+    if (rot->plan && fast_weight(w) && T >= kOperandMinTokens && T <= kStreamPassTokens &&
+        L.xr_bytes >= (size_t)(T + 15) / 16 * 16 * w->c_in * 2 && linear_route(*w, w->c_in, ldy, T, L.gemm_bytes).kernel == LinearRoute::kStream) {
+        if (launch_rotate_operand(*rot, X, ldx, xr, T, s) != hipSuccess) return PARO_ERR_HIP;
+        return from_hip(launch_decode_wide(*w, xr, w->c_in, Y, ldy, T, ws, s, nullptr, true));
     }
     hipError_t e = rot->plan ? launch_rotate_planned(*rot, X, ldx, xr, w->c_in, T, s)
                              : launch_rotate_generic(*rot, X, ldx, xr, w->c_in, T, s);
