@@ -83,7 +83,9 @@ def _check_linear(P, T, c_in, c_out, form, rotated, least=None):
     want = P.paro_workspace_bytes(rot, w, T)
     assert least is None or least < want
     ws = P.Workspace(want if least is None else least)
-    x = torch.as_tensor(li.x).cuda()
+    xbuf = torch.full((T, c_in + 24), 3.0, dtype=torch.float16, device="cuda")
+    x = xbuf[:, 8:8 + c_in]                            # rows with a stride of their own
+    x.copy_(torch.as_tensor(li.x))
     ybuf = torch.full((T, c_out + 24), 7.0, dtype=torch.float16, device="cuda")
     if rotated:
         P.paro_rotated_linear(rot, w, x, ws, Y=ybuf[:, 8:8 + c_out])
