@@ -158,10 +158,15 @@ paro_status paro_w4_repack(const paro_w4_weight *w, void *packed_out, void *stre
  * paro_workspace_bytes() is the sum: enough for a buffer that only serves calls of that one shape.
  * A buffer shared by calls of several shapes must hold the largest exchange part plus the largest
  * scratch part of all of them, so that no call's scratch reaches into another's exchange part;
- * pass its full size as ws_bytes.  Calls that share a workspace must not overlap in time.
+ * pass its full size as ws_bytes, and count every T that the buffer will serve: neither part grows
+ * steadily with T.  Calls that share a workspace must not overlap in time.
  * The bare linear needs no workspace (0 bytes, ws may be NULL) where it neither splits K between
- * blocks nor runs the GEMM's split.  A call whose buffer lacks only room for what makes it faster (the partial
- * tiles of the kernels between streaming and GEMM) is not refused: it takes the routes that fit. */
+ * blocks nor runs the GEMM's split.
+ * A call whose buffer lacks only room for what makes it faster (the partial tiles of the kernels
+ * between streaming and GEMM) is not refused: it takes the routes that fit.  The largest exchange
+ * part plus the largest scratch part without that room (transformed activations and the GEMM's
+ * partial tiles) is enough for sharing as well: what a call writes below its own such part is zero
+ * again after the call. */
 size_t paro_workspace_error_offset(void);
 size_t paro_workspace_partials_offset(void);
 size_t paro_workspace_bytes(const paro_rotation *rot, const paro_w4_weight *w, int32_t T);

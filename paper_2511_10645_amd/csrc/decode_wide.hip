@@ -58,16 +58,19 @@ __device__ __forceinline__ void static_while(F &&f)
 // of one wave execute in issue order.
 constexpr int kXsRowBytes = kGroup * 2 + 16;
 constexpr int kXsWords = 16 * kXsRowBytes / 4;      // 1088 floats per wave
-// XOP: X is in operand order (a rotation pass can write it: rotate.hip), blocks of 16 tokens x 128 channels of 4 KB whose
-// fragments are one contiguous kilobyte each: no detour through LDS.  Rotated linears at 16
+// XOP: X is in operand order (a rotation pass can write it: rotate.hip), blocks of 16 tokens x 128 channels whose
+// fragments are contiguous (a kilobyte each; the last block holds only its own rows): no detour through LDS.  Rotated linears at 16
 // tokens, four layers of 4096 -> 6144, 4096 -> 4096, 4096 -> 28672 and 14336 -> 4096: 210 -> 204 us.
 template <int TB, bool XOP>
 __device__ __forceinline__ void load_x_fragments(const DecodeArgs &a, int ks, bool slice_ok, int lane, char *xs,
                                                  half8 (&xf)[TB][kSliceGroups][4])
 {
     if constexpr (XOP) {
-        const __amdgpu_buffer_rsrc_t xr = make_rsrc(a.X, (uint32_t)TB * 32u * (uint32_t)a.C);
+        const __amdgpu_buffer_rsrc_t xr = make_rsrc(a.X, (uint32_t)a.T * 2u * (uint32_t)a.C);
+        const int ft = lane & 15, fkb = lane >> 4;
         const uint32_t off = slice_ok ? (uint32_t)ks * (kSliceGroups * 4096u) + lane * 16u : kOob;
+        const int rows = a.T - (TB - 1) * 16;                                 // of the last block
+        const uint32_t off_r = slice_ok && ft < rows ? (uint32_t)(__mul24(fkb * 16, rows) + ft * 16) : kOob;
 #pragma unroll
         for (int g2 = 0; g2 < kSliceGroups; ++g2)
 #pragma unroll
@@ -75,7 +78,8 @@ __device__ __forceinline__ void load_x_fragments(const DecodeArgs &a, int ks, bo
 #pragma unroll
                 for (int j = 0; j < 4; ++j) {
                     union { u32x4 u; half8 h; } v;
-                    v.u = __builtin_amdgcn_raw_buffer_load_b128(xr, (int)(off + g2 * 4096 + j * 1024), tb * 32 * a.C, 0);
+                    if (tb + 1 < TB) v.u = __builtin_amdgcn_raw_buffer_load_b128(xr, (int)(off + g2 * 4096 + j * 1024), tb * 32 * a.C, 0);
+                    else v.u = __builtin_amdgcn_raw_buffer_load_b128(xr, (int)off_r, tb * 32 * a.C + ((ks * kSliceGroups + g2) * 256 + j * 64) * rows, 0);
                     xf[tb][g2][j] = v.h;
                 }
         return;
@@ -448,7 +452,7 @@ bool decode_wide_hosting_pays(int c_in, int c_out)
 
 // ws: the exchange part of the workspace (may be NULL where no partial sums are exchanged).
 // rot: NULL for the bare linear; otherwise a transform decode_wide_hosts() accepts, applied to X by the kernel itself.
-// x_operand: X holds ceil(T / 16) blocks in operand order (2..32 tokens).
+// x_operand: X is in operand order (2..32 tokens).
 hipError_t launch_decode_wide(const paro_w4_weight &w, const paro_half_t *X, int64_t ldx, paro_half_t *Y, int64_t ldy,
                               int T, void *ws, hipStream_t s, const paro_rotation *rot, bool x_operand)
 {

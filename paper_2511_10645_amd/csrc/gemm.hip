@@ -341,20 +341,26 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_w4a16_kernel(GemmArgs a)
 }
 
 // Split K, second step: Y[t][n0 + n] = fp16( sum_k partial[k][t][n] + bias[n0 + n] ) for n < width,
-// slices added in index order (deterministic).  One thread per 4 consecutive outputs of a token.
-__global__ __launch_bounds__(256) void gemm_splitk_reduce_kernel(const float *__restrict__ partial, int k_split, int T,
+// slices added in index order (deterministic).  One thread per 4 consecutive outputs of a token.  Partial sums below
+// `least` (256-byte aligned, may be NULL) are returned to zero: see launch_splitk_reduce.
+__global__ __launch_bounds__(256) void gemm_splitk_reduce_kernel(float *__restrict__ partial, int k_split, int T,
                                                                  int n0, int width, const _Float16 *__restrict__ bias,
-                                                                 _Float16 *__restrict__ Y, int64_t ldy)
+                                                                 _Float16 *__restrict__ Y, int64_t ldy, const char *least)
 {
     const int n4 = width / 4;
     const long idx = (long)blockIdx.x * 256 + threadIdx.x;
     if (idx >= (long)T * n4) return;
     const int t = (int)(idx / n4), n = (int)(idx % n4) * 4;
     const size_t slice = (size_t)T * width;
-    const float *p = partial + (size_t)t * width + n;
-    float4 sum = *(const float4 *)p;
+    float *p = partial + (size_t)t * width + n;
+    auto take = [&](float *q) {
+        const float4 v = *(const float4 *)q;
+        if ((const char *)q < least) *(float4 *)q = make_float4(0.f, 0.f, 0.f, 0.f);
+        return v;
+    };
+    float4 sum = take(p);
     for (int k = 1; k < k_split; ++k) {
-        const float4 v = *(const float4 *)(p + k * slice);
+        const float4 v = take(p + k * slice);
         sum.x += v.x; sum.y += v.y; sum.z += v.z; sum.w += v.w;
     }
     if (bias) {
@@ -366,12 +372,12 @@ __global__ __launch_bounds__(256) void gemm_splitk_reduce_kernel(const float *__
     *(uint2 *)(Y + (size_t)t * ldy + n0 + n) = o.u;
 }
 
-hipError_t launch_splitk_reduce(const float *partial, int k_split, int T, int n0, int width, const paro_half_t *bias,
-                                paro_half_t *Y, int64_t ldy, hipStream_t s)
+hipError_t launch_splitk_reduce(float *partial, int k_split, int T, int n0, int width, const paro_half_t *bias,
+                                paro_half_t *Y, int64_t ldy, const void *least, hipStream_t s)
 {
     const long quads = (long)T * (width / 4);
     hipLaunchKernelGGL(gemm_splitk_reduce_kernel, dim3((unsigned)((quads + 255) / 256)), dim3(256), 0, s, partial, k_split, T, n0,
-                       width, (const _Float16 *)bias, (_Float16 *)Y, ldy);
+                       width, (const _Float16 *)bias, (_Float16 *)Y, ldy, (const char *)least);
     return hipGetLastError();
 }
 
@@ -560,7 +566,7 @@ hipError_t launch_gemm(const paro_w4_weight &w, const paro_half_t *X, int64_t ld
     const GemmPlan p = plan_gemm(w, T);
     if (p.n_192 > 0) return launch_gemm_cfg<2, 3, 4, 2>(a, 0, p.n_192, s);
     auto reduce = [&](int k_split) {
-        return launch_splitk_reduce((const float *)scratch, k_split, T, a.part_n0, a.part_w, w.bias, Y, ldy, s);
+        return launch_splitk_reduce((float *)scratch, k_split, T, a.part_n0, a.part_w, w.bias, Y, ldy, nullptr, s);
     };
     const bool have_scratch = scratch && scratch_bytes >= p.scratch && ((uintptr_t)scratch % 16) == 0;
     if (p.big_split > 1) {

@@ -58,7 +58,7 @@ struct RowsArgs {
     uint32_t scales_off, zeros_off;                  // of the blob
     const _Float16 *scales;                          // interchange layout
     const uint32_t *qzeros;
-    const _Float16 *X; int64_t ldx;                  // row-major, or (OPERAND) blocks of 16 tokens x 128 channels of 4 KB
+    const _Float16 *X; int64_t ldx;                  // row-major, or (OPERAND) blocks of 16 tokens x 128 channels
     _Float16 *Y; int64_t ldy;
     const _Float16 *bias;
     float *partial;                                  // [k slices][T][N] where K is split between blocks, else NULL
@@ -67,24 +67,19 @@ struct RowsArgs {
 };                                                   // (u & m) | k is one instruction
 
 // TB: blocks of 16 tokens per block; NT: tiles of 16 outputs; OPERAND: the second form above.  Activations in operand order:
-// a block of 16 tokens x one group is [4 fragments j][64 lanes][16 B], lane = 16 kb + token, channels 32 kb + 8 j .. + 7.
-template <int TB, int NT, bool OPERAND>
-__global__ __launch_bounds__(kRowsWaves * 64, 2) void linear_rows_kernel(RowsArgs a)
+// a block of r = 16 tokens (the last one: of those that are left) x one group is [4 fragments j][4 kb][r tokens][16 B],
+// channels 32 kb + 8 j .. + 7.
+// WHOLE: every block of 16 tokens of this tile is whole, so that its strides are constants (with strides in registers, as a
+// ragged last tile has them, 4096 -> 4096 at 64 tokens takes 0.1 to 0.2 us more).
+template <int TB, int NT, bool OPERAND, bool WHOLE>
+__device__ __forceinline__ void linear_rows_tile(const RowsArgs &a, float *s_sum, int kslice, int mt, int ntile)
 {
     constexpr int R = 2;                             // ring of groups
     constexpr int S = 4 * TB;                        // slots (MFMAs) per tile
     constexpr int P = 16 / S;                        // dequantisation pieces per slot
     static_assert(NT % 2 == 0 && (TB == 1 || TB == 2), "");
-    __shared__ __attribute__((aligned(16))) float s_sum[kRowsWaves * TB * NT * 256];
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    // OPERAND: an XCD's blocks are a run of (K-slice, output tile, token tile), the last running fastest: its L2 serves a
-    // weight tile to the further token tiles, and every XCD gets the same number of blocks
-    const int tiles = a.m_tiles * a.n_tiles, all = tiles * a.k_split, per_xcd = (all + 7) / 8;
-    const int idx = OPERAND ? (int)(blockIdx.x & 7) * per_xcd + (int)(blockIdx.x >> 3) : 0;
-    if (OPERAND && idx >= all) return;
-    const int kslice = OPERAND ? idx / tiles : (int)blockIdx.y;
-    const int mt = OPERAND ? idx % tiles % a.m_tiles : 0, ntile = OPERAND ? idx % tiles / a.m_tiles : (int)blockIdx.x;
     const int m0 = (int)rows_uniform(mt * 16 * TB), n0 = (int)rows_uniform(ntile * 16 * NT);
     const int m_rows = min(a.T - m0, 16 * TB);
     const int n_rows = min(a.N - n0, 16 * NT);       // multiple of 16
@@ -95,18 +90,21 @@ __global__ __launch_bounds__(kRowsWaves * 64, 2) void linear_rows_kernel(RowsArg
 
     // ---- addresses: a per-lane offset that is fixed (or out of range) plus a wave-uniform one -----------------------
     const int n_tb = (m_rows + 15) / 16;
-    const __amdgpu_buffer_rsrc_t xr = OPERAND ? rows_rsrc((const char *)a.X + (size_t)m0 * a.C * 2, (size_t)n_tb * 32 * a.C)
+    const __amdgpu_buffer_rsrc_t xr = OPERAND ? rows_rsrc((const char *)a.X + (size_t)m0 * a.C * 2, (size_t)m_rows * 2 * a.C)
                                               : rows_rsrc(a.X, ((size_t)(a.T - 1) * a.ldx + a.C) * 2);
     const __amdgpu_buffer_rsrc_t wr = OPERAND ? rows_rsrc(a.w, a.zeros_off + packed_zeros_bytes(a.C, a.N))
                                               : rows_rsrc(a.w + (size_t)n0 * (a.C / 2), (size_t)n_rows * (a.C / 2));
     const __amdgpu_buffer_rsrc_t sr = rows_rsrc(a.scales, OPERAND ? 0 : (size_t)a.G * a.N * 2);
     const __amdgpu_buffer_rsrc_t zr = rows_rsrc(a.qzeros, OPERAND ? 0 : (size_t)a.G * a.N / 2);
-    uint32_t xv[TB], x_base[TB];                     // per lane, and per block of 16 tokens (surplus blocks repeat the first)
+    uint32_t xv[TB], x_base[TB], x_rows[TB];         // per lane, and per block of 16 tokens (surplus blocks repeat the first)
     rows_for<TB>([&](auto B) {
-        xv[B] = OPERAND ? lane * 16u : B * 16 + ft < a.T ? (uint32_t)(((size_t)(B * 16 + ft) * a.ldx + fkb * 32) * 2) : kOobR;
         x_base[B] = OPERAND ? rows_uniform(B < n_tb ? B * 32u * (uint32_t)a.C : 0u) : 0u;
+        x_rows[B] = !OPERAND ? 1u : WHOLE ? 16u : rows_uniform((uint32_t)min(16, B < n_tb ? m_rows - B * 16 : m_rows));
+        if constexpr (!OPERAND) xv[B] = B * 16 + ft < a.T ? (uint32_t)(((size_t)(B * 16 + ft) * a.ldx + fkb * 32) * 2) : kOobR;
+        else if constexpr (WHOLE) xv[B] = lane * 16u;
+        else xv[B] = (uint32_t)ft < x_rows[B] ? __umul24(fkb * 16u, x_rows[B]) + ft * 16u : kOobR;
     });
-    constexpr uint32_t kXGroup = OPERAND ? 4096 : kGroup * 2, kXFrag = OPERAND ? 1024 : 16;
+    constexpr uint32_t kXGroup = kGroup * 2, kXFrag = OPERAND ? 64 : 16;             // per row of the block, or of the input
     const uint32_t wv = OPERAND ? lane * 16u : (uint32_t)ft * (uint32_t)(a.C / 2) + fkb * 16;
     // Whole dwords, shifted where they are used: a 16-bit load's extension would be waited for where it is loaded.  (The
     // wave's groups share g % 4 in the blob: they are kRowsWaves = 4 apart, and a split begins at a multiple of 4.)
@@ -135,7 +133,9 @@ __global__ __launch_bounds__(kRowsWaves * 64, 2) void linear_rows_kernel(RowsArg
     };
     auto load_x = [&](int ring, int tb, int j) {
         union { u32x4 u; half8 h; } v;
-        v.u = __builtin_amdgcn_raw_buffer_load_b128(xr, (int)(l_xv[tb] + j * kXFrag), (int)(x_base[tb] + l_g * kXGroup), 0);
+        const uint32_t group = x_base[tb] + l_g * kXGroup * x_rows[tb], frag = j * kXFrag * x_rows[tb];
+        if constexpr (OPERAND && !WHOLE) v.u = __builtin_amdgcn_raw_buffer_load_b128(xr, (int)l_xv[tb], (int)(group + frag), 0);
+        else v.u = __builtin_amdgcn_raw_buffer_load_b128(xr, (int)(l_xv[tb] + frag), (int)group, 0);
         xa[ring][tb][j] = v.h;
     };
     auto load_w = [&](int ring, int n) {
@@ -257,6 +257,24 @@ __global__ __launch_bounds__(kRowsWaves * 64, 2) void linear_rows_kernel(RowsArg
     }
 }
 
+template <int TB, int NT, bool OPERAND>
+__global__ __launch_bounds__(kRowsWaves * 64, 2) void linear_rows_kernel(RowsArgs a)
+{
+    __shared__ __attribute__((aligned(16))) float s_sum[kRowsWaves * TB * NT * 256];
+    if constexpr (OPERAND) {
+        // an XCD's blocks are a run of (K-slice, output tile, token tile), the last running fastest: its L2 serves a
+        // weight tile to the further token tiles, and every XCD gets the same number of blocks
+        const int tiles = a.m_tiles * a.n_tiles, all = tiles * a.k_split, per_xcd = (all + 7) / 8;
+        const int idx = (int)(blockIdx.x & 7) * per_xcd + (int)(blockIdx.x >> 3);
+        if (idx >= all) return;
+        const int mt = idx % tiles % a.m_tiles, ntile = idx % tiles / a.m_tiles;
+        if (a.T % 16 == 0 || mt + 1 < a.m_tiles) linear_rows_tile<TB, NT, true, true>(a, s_sum, idx / tiles, mt, ntile);
+        else linear_rows_tile<TB, NT, true, false>(a, s_sum, idx / tiles, mt, ntile);
+    } else {
+        linear_rows_tile<TB, NT, false, false>(a, s_sum, (int)blockIdx.y, 0, (int)blockIdx.x);
+    }
+}
+
 // Slices of K so that there is about one block per compute unit, each of whole rounds of the block's 4 waves and of at
 // least two groups per wave.  (11008 -> 4096, 64 blocks per slice, at 24 tokens: 1 / 2 / 4 / 8 slices 30 / 18 / 13 / 15 us
 // before the summing launch of about 2 us.)
@@ -285,7 +303,7 @@ bool linear_rows_supported(const paro_w4_weight &w, int64_t ldx, int T)
 }
 
 hipError_t launch_linear_rows(const paro_w4_weight &w, const paro_half_t *X, int64_t ldx, paro_half_t *Y, int64_t ldy, int T,
-                              void *scratch, size_t scratch_bytes, hipStream_t s)
+                              void *scratch, size_t scratch_bytes, const void *least, hipStream_t s)
 {
     RowsArgs a;
     a.w = (const char *)w.qweight; a.scales_off = a.zeros_off = 0; a.m_tiles = a.n_tiles = a.k_split = 0; a.scales = (const _Float16 *)w.scales; a.qzeros = w.qzeros;
@@ -302,7 +320,7 @@ hipError_t launch_linear_rows(const paro_w4_weight &w, const paro_half_t *X, int
     else         hipLaunchKernelGGL((linear_rows_kernel<2, kRowsTiles, false>), grid, block, 0, s, a);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || !split) return e;
-    return launch_splitk_reduce(a.partial, ks, T, 0, w.c_out, w.bias, Y, ldy, s);
+    return launch_splitk_reduce(a.partial, ks, T, 0, w.c_out, w.bias, Y, ldy, least, s);
 }
 
 // ---- repacked weights, activations in operand order ---------------------------------------------------------------------
@@ -337,7 +355,7 @@ static OperandPlan plan_operand(int c_in, int c_out, int T)
 // 33 to 256 tokens (measured range; below, the streaming kernel hosts or follows the rotation), 31-bit byte offsets
 bool linear_operand_supported(const paro_w4_weight &w, int T)
 {
-    return T > 32 && T <= 256 && linear_tile_supported(w, false) && (size_t)(T + 15) * w.c_in * 2 < (1ull << 31);
+    return T > 32 && T <= 256 && linear_tile_supported(w, false) && (size_t)T * w.c_in * 2 < (1ull << 31);
 }
 
 double linear_operand_estimate_us(const paro_w4_weight &w, int T) { return plan_operand(w.c_in, w.c_out, T).est_us; }
@@ -358,7 +376,7 @@ static hipError_t launch_operand_nt(RowsArgs &a, hipStream_t s)
 }
 
 hipError_t launch_linear_operand(const paro_w4_weight &w, const paro_half_t *Xop, paro_half_t *Y, int64_t ldy, int T, void *scratch,
-                                 size_t scratch_bytes, hipStream_t s)
+                                 size_t scratch_bytes, const void *least, hipStream_t s)
 {
     OperandPlan p = plan_operand(w.c_in, w.c_out, T);
     RowsArgs a;
@@ -376,7 +394,7 @@ hipError_t launch_linear_operand(const paro_w4_weight &w, const paro_half_t *Xop
     a.partial = p.k_split > 1 ? (float *)scratch : nullptr;
     const hipError_t e = p.nt == 2 ? launch_operand_nt<2>(a, s) : launch_operand_nt<4>(a, s);
     if (e != hipSuccess || p.k_split == 1) return e;
-    return launch_splitk_reduce(a.partial, p.k_split, T, 0, w.c_out, w.bias, Y, ldy, s);
+    return launch_splitk_reduce(a.partial, p.k_split, T, 0, w.c_out, w.bias, Y, ldy, least, s);
 }
 
 }  // namespace paro

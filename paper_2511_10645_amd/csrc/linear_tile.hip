@@ -321,7 +321,7 @@ bool linear_tile_supported(const paro_w4_weight &w, bool interchange)
 }
 
 hipError_t launch_linear_tile(const paro_w4_weight &w, bool interchange, const paro_half_t *X, int64_t ldx, paro_half_t *Y,
-                              int64_t ldy, int T, void *scratch, size_t scratch_bytes, hipStream_t s)
+                              int64_t ldy, int T, void *scratch, size_t scratch_bytes, const void *least, hipStream_t s)
 {
     TilePlan p = plan_tile(w.c_in, w.c_out, T);
     TileArgs a;
@@ -340,7 +340,7 @@ hipError_t launch_linear_tile(const paro_w4_weight &w, bool interchange, const p
     hipError_t e = interchange ? (p.two_m ? launch_tile_cfg<2, 4, 1, true>(a, s) : launch_tile_cfg<1, 4, 2, true>(a, s))
                                : (p.two_m ? launch_tile_cfg<2, 4, 1, false>(a, s) : launch_tile_cfg<1, 4, 2, false>(a, s));
     if (e != hipSuccess || p.k_split == 1) return e;
-    return launch_splitk_reduce(a.partial, p.k_split, T, 0, w.c_out, w.bias, Y, ldy, s);
+    return launch_splitk_reduce(a.partial, p.k_split, T, 0, w.c_out, w.bias, Y, ldy, least, s);
 }
 
 }  // namespace paro

@@ -11,7 +11,7 @@ namespace {
 constexpr int kFuseMaxTokens = 4;            // the K-major decode kernel hosts the rotation up to this many tokens
 constexpr int64_t kMaxRowStride = 1 << 22;   // elements; the kernels address a run of up to 256 rows with 31-bit byte offsets
 constexpr int kDecodeMaxTokens = 16;         // above this the MFMA GEMM competes with passes of the streaming decode kernel
-constexpr int kOperandMinTokens = 9;         // rotation pass in operand order (whole blocks of 16 rows) from here on
+constexpr int kOperandMinTokens = 9;         // rotation pass in operand order from here on
 constexpr int kStreamPassTokens = 32;        // tokens of one pass of the streaming kernel (two blocks of 16)
 
 inline bool aligned(const void *p, size_t a) { return ((uintptr_t)p % a) == 0; }
@@ -94,18 +94,20 @@ paro_status check_io(const void *X, int64_t ldx, int width_x, const void *Y, int
 // every call's scratch out of every other call's exchange part.
 struct WsLayout {
     size_t exchange_bytes;
-    size_t xr_bytes;        // scratch, first piece: rotated activations of a separate rotation pass
-    size_t gemm_bytes;      // scratch, second piece: split-K partial tiles at moderate token counts
+    size_t extra_bytes;     // scratch, first piece: room for more partial tiles, which only makes the call faster
+    size_t gemm_bytes;      // scratch: split-K partial tiles at moderate token counts
+    size_t xr_bytes;        // scratch: rotated activations of a separate rotation pass
     size_t scratch_bytes;
     size_t total;
 };
 
-// `lean`: without the pieces that only make a call faster (partial tiles of linear_tile.hip and linear_rows.hip, whole blocks
-// of 16 rows for operand order).  A buffer of that size is accepted too and the call takes the routes that fit it.
+// `lean`: without the first piece.  A buffer of that size is accepted too and the call takes the routes that fit it.  Such a
+// buffer may serve other calls whose exchange part is larger than this one's, and the first piece, where it fits at all,
+// may then lie inside theirs: whatever a call writes into it is returned to zero by the launch that sums the partial tiles.
 WsLayout ws_layout(const paro_rotation *rot, const paro_w4_weight *w, int T, bool always_fuse = false, bool lean = false)
 {
-    int xr_rows = T;
-    WsLayout L{0, 0, 0, 0, 0};
+    WsLayout L{0, 0, 0, 0, 0, 0};
+    size_t faster = 0;
     const bool fused = fused_decode(rot, w, T, always_fuse);
     if (fast_weight(w)) {
         // partial sums of the kernel this call launches: the K-major one (one part per K-slice) or the bare one
@@ -115,21 +117,18 @@ WsLayout ws_layout(const paro_rotation *rot, const paro_w4_weight *w, int T, boo
         // the bare linear without partial sums to exchange needs no workspace at all
         L.exchange_bytes = (rot || part) ? kWsPartialOff + round_up(part, 256) : 0;
         if (T > kDecodeMaxTokens) {
-            size_t scratch = gemm_scratch_bytes(*w, T);
-            if (!lean && T > kStreamPassTokens && T <= 1024) scratch = std::max(scratch, linear_tile_scratch_bytes(*w, T));
-            if (!lean && rot && rot->plan && linear_operand_supported(*w, T)) {
-                scratch = std::max(scratch, linear_operand_scratch_bytes(*w, T));
-                xr_rows = (T + 15) / 16 * 16;
-            }
-            L.gemm_bytes = round_up(scratch, 256);
+            L.gemm_bytes = round_up(gemm_scratch_bytes(*w, T), 256);
+            if (T > kStreamPassTokens && T <= 1024) faster = linear_tile_scratch_bytes(*w, T);
+            if (rot && rot->plan && linear_operand_supported(*w, T)) faster = std::max(faster, linear_operand_scratch_bytes(*w, T));
         }
-        if (!lean && rot && rot->plan && T >= kOperandMinTokens && T <= kStreamPassTokens) xr_rows = (T + 15) / 16 * 16;
-    } else if (rot && !lean) {
+    } else if (rot) {
         // weights in the interchange layout; the bare call needs no workspace and runs without the split
-        L.gemm_bytes = round_up(T <= kStreamPassTokens ? linear_rows_scratch_bytes(*w, T) : linear_tile_scratch_bytes(*w, T), 256);
+        faster = T <= kStreamPassTokens ? linear_rows_scratch_bytes(*w, T) : linear_tile_scratch_bytes(*w, T);
     }
-    L.xr_bytes = (rot && !fused) ? round_up((size_t)xr_rows * w->c_in * 2, 256) : 0;
-    L.scratch_bytes = L.xr_bytes + L.gemm_bytes;
+    faster = round_up(faster, 256);
+    if (!lean && faster > L.gemm_bytes) L.extra_bytes = faster - L.gemm_bytes;
+    L.xr_bytes = (rot && !fused) ? round_up((size_t)T * w->c_in * 2, 256) : 0;
+    L.scratch_bytes = L.extra_bytes + L.gemm_bytes + L.xr_bytes;
     L.total = L.exchange_bytes + L.scratch_bytes;
     return L;
 }
@@ -142,9 +141,23 @@ WsLayout ws_layout_fit(const paro_rotation *rot, const paro_w4_weight *w, int T,
     return ws && aligned(ws, 256) && ws_bytes >= L.total ? L : ws_layout(rot, w, T, always_fuse, true);
 }
 
-inline char *ws_scratch(void *ws, size_t ws_bytes, const WsLayout &L)
+// The scratch part of a call.  Without a first piece the activations come first, so that calls of different sizes on one
+// buffer do not rotate into the same lines (four layers at 64 tokens 326 us, with the activations last 332); with one the
+// partial tiles have to be contiguous.
+struct Scratch {
+    char *xr;               // rotated activations
+    char *end;              // of the partial tiles
+    size_t bytes;           // room for partial tiles
+    char *least;            // start of the two pieces that the call cannot do without
+    void *partials(size_t need) const { return need && need <= bytes ? end - round_up(need, 256) : nullptr; }
+};
+
+inline Scratch ws_scratch(void *ws, size_t ws_bytes, const WsLayout &L)
 {
-    return (char *)ws + (ws_bytes - L.scratch_bytes) / 256 * 256;
+    if (!L.scratch_bytes) return {nullptr, nullptr, 0, nullptr};
+    char *start = (char *)ws + (ws_bytes - L.scratch_bytes) / 256 * 256, *end = start + L.scratch_bytes;
+    if (!L.extra_bytes) return {start, end, L.gemm_bytes, start};
+    return {end - L.xr_bytes, end - L.xr_bytes, L.extra_bytes + L.gemm_bytes, start + L.extra_bytes};
 }
 
 paro_status from_hip(hipError_t e) { return e == hipSuccess ? PARO_OK : PARO_ERR_HIP; }
@@ -202,13 +215,19 @@ LinearRoute linear_route(const paro_w4_weight &w, int64_t ldx, int64_t ldy, int 
 
 // bare linear on (already transformed) activations, any T
 paro_status run_linear(const paro_w4_weight *w, const paro_half_t *X, int64_t ldx, paro_half_t *Y, int64_t ldy, int T,
-                       void *ws, void *gemm_scratch, size_t gemm_bytes, hipStream_t s)
+                       void *ws, const Scratch &scratch, hipStream_t s)
 {
+    auto tile = [&](bool interchange) {
+        const size_t need = linear_tile_scratch_bytes(*w, T);
+        return from_hip(launch_linear_tile(*w, interchange, X, ldx, Y, ldy, T, scratch.partials(need), need, scratch.least, s));
+    };
     if (!fast_weight(w)) {
         if (!(w->qweight && w->scales && w->qzeros)) return PARO_ERR_UNSUPPORTED;
-        if (linear_rows_supported(*w, ldx, T)) return from_hip(launch_linear_rows(*w, X, ldx, Y, ldy, T, gemm_scratch, gemm_bytes, s));
-        if (T > kStreamPassTokens && linear_tile_supported(*w, true))
-            return from_hip(launch_linear_tile(*w, true, X, ldx, Y, ldy, T, gemm_scratch, gemm_bytes, s));
+        if (linear_rows_supported(*w, ldx, T)) {
+            const size_t need = linear_rows_scratch_bytes(*w, T);
+            return from_hip(launch_linear_rows(*w, X, ldx, Y, ldy, T, scratch.partials(need), need, scratch.least, s));
+        }
+        if (T > kStreamPassTokens && linear_tile_supported(*w, true)) return tile(true);
         return from_hip(launch_linear_generic(*w, X, ldx, Y, ldy, T, s));
     }
     if (T >= 512 && !gemm_supported(*w, ldx, ldy, T) && gemm_supported(*w, ldx, ldy, 256)) {
@@ -218,14 +237,17 @@ paro_status run_linear(const paro_w4_weight *w, const paro_half_t *X, int64_t ld
         const int64_t chunk = (((int64_t)1 << 30) - 1) / ld / 256 * 256;
         for (int64_t t0 = 0; t0 < T; t0 += chunk) {
             const int tc = (int)(T - t0 < chunk ? T - t0 : chunk);
-            paro_status st = run_linear(w, X + t0 * ldx, ldx, Y + t0 * ldy, ldy, tc, ws, gemm_scratch, gemm_bytes, s);
+            paro_status st = run_linear(w, X + t0 * ldx, ldx, Y + t0 * ldy, ldy, tc, ws, scratch, s);
             if (st != PARO_OK) return st;
         }
         return PARO_OK;
     }
-    switch (linear_route(*w, ldx, ldy, T, gemm_bytes).kernel) {
-    case LinearRoute::kTile: return from_hip(launch_linear_tile(*w, false, X, ldx, Y, ldy, T, gemm_scratch, gemm_bytes, s));
-    case LinearRoute::kGemm: return from_hip(launch_gemm(*w, X, ldx, Y, ldy, T, gemm_scratch, gemm_bytes, s));
+    switch (linear_route(*w, ldx, ldy, T, scratch.bytes).kernel) {
+    case LinearRoute::kTile: return tile(false);
+    case LinearRoute::kGemm: {
+        const size_t need = gemm_scratch_bytes(*w, T);
+        return from_hip(launch_gemm(*w, X, ldx, Y, ldy, T, scratch.partials(need), need, s));
+    }
     case LinearRoute::kStream: break;
     }
     for (int t0 = 0; t0 < T; t0 += kStreamPassTokens) {
@@ -390,18 +412,17 @@ paro_status paro_w4a16_linear(const paro_w4_weight *w, const paro_half_t *X, int
     WsLayout L = ws_layout_fit(nullptr, w, T, ws, ws_bytes);
     if (L.total && (!ws || ws_bytes < L.total)) return PARO_ERR_WORKSPACE;
     if (L.total && !aligned(ws, 256)) return PARO_ERR_ALIGN;
-    return run_linear(w, X, ldx, Y, ldy, T, ws, L.gemm_bytes ? ws_scratch(ws, ws_bytes, L) + L.xr_bytes : nullptr,
-                      L.gemm_bytes, (hipStream_t)stream);
+    return run_linear(w, X, ldx, Y, ldy, T, ws, ws_scratch(ws, ws_bytes, L), (hipStream_t)stream);
 }
 
 // Whether the rotation pass writes operand order and the kernel that reads it follows (linear_rows.hip): where its model says
 // so, which is 5 % off, by the margin of linear_route.  Over 1207 measured (shape, tokens) pairs the choice loses more
 // than 3 % on three (5 to 8 % there) and takes 1.28x less time in the mean than linear_route's kernel, 1.29x being the best possible.
-static bool operand_route(const paro_rotation *rot, const paro_w4_weight *w, int64_t ldy, int T, const WsLayout &L)
+static bool operand_route(const paro_rotation *rot, const paro_w4_weight *w, int64_t ldy, int T, size_t scratch_bytes)
 {
     if (!rot->plan || !fast_weight(w) || !linear_operand_supported(*w, T)) return false;
-    if (L.xr_bytes < (size_t)(T + 15) / 16 * 16 * w->c_in * 2 || L.gemm_bytes < linear_operand_scratch_bytes(*w, T)) return false;
-    const LinearRoute r = linear_route(*w, w->c_in, ldy, T, L.gemm_bytes);
+    if (scratch_bytes < linear_operand_scratch_bytes(*w, T)) return false;
+    const LinearRoute r = linear_route(*w, w->c_in, ldy, T, scratch_bytes);
     return r.us > 0.0 && linear_operand_estimate_us(*w, T) < 0.9 * r.us;
 }
 
@@ -425,21 +446,22 @@ static paro_status rotated_linear(const paro_rotation *rot, const paro_w4_weight
     if (fused_decode(rot, w, T, always_fuse)) return from_hip(launch_decode(rot, *w, X, ldx, Y, ldy, T, ws, s));
 
     // two passes: transform into the workspace, then the bare linear
-    paro_half_t *xr = (paro_half_t *)ws_scratch(ws, ws_bytes, L);
-    char *scratch2 = L.gemm_bytes ? (char *)xr + L.xr_bytes : nullptr;
-    if (operand_route(rot, w, ldy, T, L)) {
+    const Scratch scratch = ws_scratch(ws, ws_bytes, L);
+    paro_half_t *xr = (paro_half_t *)scratch.xr;
+    if (operand_route(rot, w, ldy, T, scratch.bytes)) {
         if (launch_rotate_operand(*rot, X, ldx, xr, T, s) != hipSuccess) return PARO_ERR_HIP;
-        return from_hip(launch_linear_operand(*w, xr, Y, ldy, T, scratch2, L.gemm_bytes, s));
+        const size_t need = linear_operand_scratch_bytes(*w, T);
+        return from_hip(launch_linear_operand(*w, xr, Y, ldy, T, scratch.partials(need), need, scratch.least, s));
     }
     if (rot->plan && fast_weight(w) && T >= kOperandMinTokens && T <= kStreamPassTokens &&
-        L.xr_bytes >= (size_t)(T + 15) / 16 * 16 * w->c_in * 2 && linear_route(*w, w->c_in, ldy, T, L.gemm_bytes).kernel == LinearRoute::kStream) {
+        linear_route(*w, w->c_in, ldy, T, scratch.bytes).kernel == LinearRoute::kStream) {
         if (launch_rotate_operand(*rot, X, ldx, xr, T, s) != hipSuccess) return PARO_ERR_HIP;
         return from_hip(launch_decode_wide(*w, xr, w->c_in, Y, ldy, T, ws, s, nullptr, true));
     }
     hipError_t e = rot->plan ? launch_rotate_planned(*rot, X, ldx, xr, w->c_in, T, s)
                              : launch_rotate_generic(*rot, X, ldx, xr, w->c_in, T, s);
     if (e != hipSuccess) return PARO_ERR_HIP;
-    return run_linear(w, xr, w->c_in, Y, ldy, T, ws, scratch2, L.gemm_bytes, s);
+    return run_linear(w, xr, w->c_in, Y, ldy, T, ws, scratch, s);
 }
 
 paro_status paro_rotated_linear(const paro_rotation *rot, const paro_w4_weight *w, const paro_half_t *X, int64_t ldx,
@@ -523,7 +545,7 @@ static paro_status check_multi(int32_t n, const paro_rotation *const *rots, cons
 static WsLayout ws_layout_multi(int32_t n_parts, const paro_rotation *const *rots, const paro_w4_weight *const *weights,
                                 int32_t T, bool lean = false)
 {
-    WsLayout M{0, 0, 0};
+    WsLayout M{0, 0, 0, 0, 0, 0};
     for (int p = 0; p < n_parts; ++p) {
         WsLayout one = ws_layout(rots[p], weights[p], T, false, lean);
         if (one.exchange_bytes > M.exchange_bytes) M.exchange_bytes = one.exchange_bytes;
@@ -564,7 +586,7 @@ paro_status paro_rotated_linear_multi(int32_t n_parts, const paro_rotation *cons
         st = check_io(X, ldx, weights[p]->c_in, Y[p], ldy[p], weights[p]->c_out, T, 8);
         if (st != PARO_OK) return st;
     }
-    const size_t need = ws_layout_multi(n_parts, rots, weights, T, true).total;
+    const size_t need = ws_layout_multi(n_parts, rots, weights, T, true).total;      // each part then takes what fits it
     if (need && (!ws || ws_bytes < need)) return PARO_ERR_WORKSPACE;
     if (need && !aligned(ws, 256)) return PARO_ERR_ALIGN;
     if (multi_one_launch(n_parts, rots, weights, T))

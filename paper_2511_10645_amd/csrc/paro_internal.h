@@ -124,7 +124,7 @@ inline void once_done(std::atomic<uint64_t> &done, int dev)
 hipError_t launch_plan_build(const paro_rotation &rot, void *plan_out, hipStream_t s);
 hipError_t launch_rotate_planned(const paro_rotation &rot, const paro_half_t *X, int64_t ldx,
                                  paro_half_t *Xr, int64_t ldxr, int T, hipStream_t s);
-// The same into whole blocks of 16 tokens in operand order (linear_rows.hip): room for ceil(T / 16) * 16 rows.
+// The same in operand order (linear_rows.hip).
 hipError_t launch_rotate_operand(const paro_rotation &rot, const paro_half_t *X, int64_t ldx, paro_half_t *Xop, int T, hipStream_t s);
 hipError_t launch_rotate_generic(const paro_rotation &rot, const paro_half_t *X, int64_t ldx,
                                  paro_half_t *Xr, int64_t ldxr, int T, hipStream_t s);
@@ -186,29 +186,32 @@ hipError_t launch_quantize_act_mxfp4(const paro_rotation &rot, const paro_half_t
                                      uint8_t *scales, hipStream_t s);
 
 // Weights in the interchange layout, up to 32 tokens (linear_rows.hip).  scratch: room for the partial sums of K split
-// between blocks (any contents before and after); without it the call runs unsplit.
+// between blocks (any contents before; after, those below `least` are zero: launch_splitk_reduce); without it the call
+// runs unsplit.
 bool linear_rows_supported(const paro_w4_weight &w, int64_t ldx, int T);
 size_t linear_rows_scratch_bytes(const paro_w4_weight &w, int T);
 hipError_t launch_linear_rows(const paro_w4_weight &w, const paro_half_t *X, int64_t ldx, paro_half_t *Y, int64_t ldy,
-                              int T, void *scratch, size_t scratch_bytes, hipStream_t s);
+                              int T, void *scratch, size_t scratch_bytes, const void *least, hipStream_t s);
 
 // Repacked weights on activations in operand order (linear_rows.hip); scratch as above.
 bool linear_operand_supported(const paro_w4_weight &w, int T);
 double linear_operand_estimate_us(const paro_w4_weight &w, int T);
 size_t linear_operand_scratch_bytes(const paro_w4_weight &w, int T);
 hipError_t launch_linear_operand(const paro_w4_weight &w, const paro_half_t *Xop, paro_half_t *Y, int64_t ldy, int T, void *scratch,
-                                 size_t scratch_bytes, hipStream_t s);
+                                 size_t scratch_bytes, const void *least, hipStream_t s);
 
 // Tiled linear with the weights in registers (linear_tile.hip), repacked or interchange layout; scratch as above.
 bool linear_tile_supported(const paro_w4_weight &w, bool interchange);
 double linear_tile_estimate_us(const paro_w4_weight &w, int T);
 size_t linear_tile_scratch_bytes(const paro_w4_weight &w, int T);
 hipError_t launch_linear_tile(const paro_w4_weight &w, bool interchange, const paro_half_t *X, int64_t ldx, paro_half_t *Y,
-                              int64_t ldy, int T, void *scratch, size_t scratch_bytes, hipStream_t s);
+                              int64_t ldy, int T, void *scratch, size_t scratch_bytes, const void *least, hipStream_t s);
 
-// Y[t][n0 + n] = fp16(sum over k_split of partial[k][t][n] + bias[n0 + n]), slices in index order (gemm.hip)
-hipError_t launch_splitk_reduce(const float *partial, int k_split, int T, int n0, int width, const paro_half_t *bias,
-                                paro_half_t *Y, int64_t ldy, hipStream_t s);
+// Y[t][n0 + n] = fp16(sum over k_split of partial[k][t][n] + bias[n0 + n]), slices in index order (gemm.hip).
+// Partial sums at addresses below `least` are zero afterwards: there the scratch reaches below what a call cannot do
+// without, where a caller's other calls may keep their exchange part (all zero between calls).
+hipError_t launch_splitk_reduce(float *partial, int k_split, int T, int n0, int width, const paro_half_t *bias,
+                                paro_half_t *Y, int64_t ldy, const void *least, hipStream_t s);
 
 // Prefill-side linear (MFMA GEMM on the repacked weight), any T.
 bool gemm_supported(const paro_w4_weight &w, int64_t ldx, int64_t ldy, int T);

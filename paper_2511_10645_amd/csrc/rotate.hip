@@ -219,9 +219,9 @@ __device__ __forceinline__ void static_while_rot(F &&f)
 // barrier: LDS operations of one wave execute in issue order).  The loads of the next batch of
 // tokens are issued before the current batch is rotated.  Rows are read completely before any of
 // them is written, so X and Xr may be the same buffer.
-// OPERAND: the result leaves in the operand order of linear_rows.hip, whole blocks of 16 tokens x 128 channels of 4 KB
-// [4 fragments][64 lanes][16 B], lane = 16 (channel / 32) + token: 4 lanes exchange their 4 tokens, and a batch leaves as one
-// store of 16 pieces of 64 bytes.  Rows beyond T up to the next multiple of 4 are written too (the blocks have room).
+// OPERAND: the result leaves in the operand order of linear_rows.hip, blocks of r = 16 tokens (the last one: of those that
+// are left) x 128 channels, [4 fragments][4 quarters of the channels][r tokens][16 B]: 4 lanes exchange their 4 tokens, and
+// a batch leaves as one store of 16 pieces of 64 bytes.  T rows take T rows' room, nothing is written beyond them.
 template <int K, bool OPERAND = false>
 __global__ __launch_bounds__(kRotWaves * 64) void rotate_planned_kernel(const uint32_t *__restrict__ plan,
                                                                          const _Float16 *X, int64_t ldx,
@@ -244,14 +244,14 @@ __global__ __launch_bounds__(kRotWaves * 64) void rotate_planned_kernel(const ui
         const_cast<_Float16 *>(X + (size_t)t0 * ldx + (size_t)g * kGroup), 0, (int)((size_t)(n_tok - 1) * ldx * 2 + kGroup * 2),
         0x00020000);
     const size_t block = (size_t)gridDim.x * 4096;                     // OPERAND: bytes per 16 tokens
+    const int rows_y = min(T, (t0 + n_tok + 15) / 16 * 16) - t0 / 16 * 16;           // of the blocks that the run touches
     const __amdgpu_buffer_rsrc_t yr =
-        OPERAND ? __builtin_amdgcn_make_buffer_rsrc((char *)Xr + t0 / 16 * block + (size_t)g * 4096, 0,
-                                                    (int)((size_t)((t0 + n_tok + 15) / 16 - t0 / 16 - 1) * block + 4096), 0x00020000)
+        OPERAND ? __builtin_amdgcn_make_buffer_rsrc((char *)Xr + t0 / 16 * block, 0, (int)((size_t)rows_y * (block / 16)), 0x00020000)
                 : __builtin_amdgcn_make_buffer_rsrc(Xr + (size_t)t0 * ldxr + (size_t)g * kGroup, 0,
                                                     (int)((size_t)(n_tok - 1) * ldxr * 2 + kGroup * 2), 0x00020000);
     const int row_x = (int)(ldx * 2), row_y = (int)(ldxr * 2);         // bytes per token row
     const int v4 = lane * 4;
-    const int vop = ((lane >> 2) & 3) * 1024 + (lane >> 4) * 256 + (lane & 3) * 16;  // OPERAND: fragment, quarter of the channels, token
+    const int vop = ((lane >> 2) & 3) * 64 + (lane >> 4) * 16;         // OPERAND: fragment and quarter of the channels, per row of a block
     uint32_t cur[kRotTU], nxt[kRotTU];
 #pragma unroll
     for (int u = 0; u < kRotTU; ++u) cur[u] = __builtin_amdgcn_raw_buffer_load_b32(xr, v4 + u * row_x, 0, 0);
@@ -314,8 +314,9 @@ __global__ __launch_bounds__(kRotWaves * 64) void rotate_planned_kernel(const ui
             exchange(v0, v1, lane & 1, xor1); exchange(v2, v3, lane & 1, xor1);
             exchange(v0, v2, lane & 2, xor2); exchange(v1, v3, lane & 2, xor2);
             const u32x4v v = {v0, v1, v2, v3};
-            const int tau = (t0 & 15) + t;
-            __builtin_amdgcn_raw_buffer_store_b128(v, yr, vop + (tau & 15) * 16 + (tau >> 4) * (int)block, 0, 0);
+            const int tau = (t0 & 15) + t, r = min(16, rows_y - (tau & ~15));
+            const int off = (tau >> 4) * (int)block + g * 256 * r + __mul24(vop, r) + ((tau & 15) + (lane & 3)) * 16;
+            __builtin_amdgcn_raw_buffer_store_b128(v, yr, t + (lane & 3) < n_tok ? off : (int)0x80000000u, 0, 0);
         } else {
 #pragma unroll
             for (int u = 0; u < kRotTU; ++u) __builtin_amdgcn_raw_buffer_store_b32(o[u], yr, v4 + (t + u) * row_y, 0, 0);
