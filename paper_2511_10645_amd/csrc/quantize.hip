@@ -11,7 +11,8 @@
 //                floor 2^-14, zero point clamped to 0..15.  The paper names no activation quantiser of its own: the
 //                same decisions per token and group.
 //   MXFP4        32 consecutive channels share 2^e, e = floor(log2(max |v|)) - 2 (>= -127), stored as e + 127; every value
-//                becomes the E2M1 code of v / 2^e, to nearest, ties to the even code, saturated at 6.
+//                becomes the E2M1 code of v / 2^e, to nearest, ties to the even code, saturated at 6.  A block that is
+//                NaN throughout has e = 126 and codes +-6: what is multiplied with it overflows.
 // so that  sum_c (q - z) s . x'_c  ~  w_n . x  for the activations x' that paro_rotate_scale produces (Eq. 2).
 //
 // One wavefront owns a channel group and a run of rows, four rows at a time, with the lane plan and layer loop of the
@@ -231,9 +232,9 @@ __global__ __launch_bounds__(kQuantWaves * 64) void quantize_kernel(QuantArgs a)
 #pragma unroll
                 for (int k = 0; k < 8; ++k) v[k] = (float)c.h[k];
             }
-            float amax = 0.f;
+            float amax = fabsf(v[0]);                    // NaN where all 32 are
 #pragma unroll
-            for (int k = 0; k < 8; ++k) amax = fmaxf(amax, fabsf(v[k]));
+            for (int k = 1; k < 8; ++k) amax = fmaxf(amax, fabsf(v[k]));
             amax = fmaxf(amax, dpp<kQuadXor1>(amax));
             amax = fmaxf(amax, dpp<kQuadXor2>(amax));
             int e = (int)(__float_as_uint(amax) >> 23) - 127 - 2;
