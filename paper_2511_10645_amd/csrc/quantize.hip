@@ -22,7 +22,9 @@
 // made small against that -
 //   - INT4: minimum and maximum of the four rows are reduced together, each swap of half waves merging two rows, so that
 //     every 16 lanes end up with one row's and the scale, its reciprocal and the zero point are computed once for all
-//     four; v / s is the correctly rounded quotient from the correctly rounded reciprocal and one residual;
+//     four; v / s is the correctly rounded quotient from the correctly rounded reciprocal and one residual (Markstein's
+//     theorem), which holds for finite v and s: rows with an infinite scale, and rows of infinities (whose range is NaN
+//     and whose scale is the floor), divide;
 //   - MXFP4: the rotated values are read back in channel order, 8 per lane, so that a block's maximum is two steps within
 //     four lanes and the codes are four instructions of the FP4 converter (equal to the thresholds of the format on
 //     every tie and its neighbours over the whole range of exponents).
@@ -174,10 +176,11 @@ __global__ __launch_bounds__(kQuantWaves * 64) void quantize_kernel(QuantArgs a)
 #pragma unroll
             for (int u = 0; u < 4; ++u) { mx[u] = fmaxf(va[u], vb[u]); nmn[u] = fmaxf(-va[u], -vb[u]); }
             const float mxv = wave_max4(mx), mnv = -wave_max4(nmn);
-            float s32 = (mxv - mnv) / 15.0f;
+            const float range = mxv - mnv;
+            float s32 = range / 15.0f;
             if (!(s32 >= 6.103515625e-05f)) s32 = 6.103515625e-05f;
             const _Float16 s16 = (_Float16)s32;
-            const float s = (float)s16, rs = 1.0f / s;
+            const float s = (float)s16, rs = range == range ? 1.0f / s : 0.f;    // 0: infinite scale, or a group of infinities
             float zf = -rintf(mnv / s);
             zf = fminf(fmaxf(zf, 0.0f), 15.0f);
             uint32_t ca = 0, cb = 0;
@@ -185,7 +188,7 @@ __global__ __launch_bounds__(kQuantWaves * 64) void quantize_kernel(QuantArgs a)
             for (int u = 0; u < 4; ++u) {
                 const float su = from_lane(s, kRowLane[u]), ru = from_lane(rs, kRowLane[u]), zu = from_lane(zf, kRowLane[u]);
                 float qa, qb;
-                if (su < __builtin_inff()) {             // (uniform)
+                if (ru > 0.f) {                          // (uniform)
                     const float a0 = va[u] * ru, b0 = vb[u] * ru;
                     qa = fmaf(fmaf(-su, a0, va[u]), ru, a0);
                     qb = fmaf(fmaf(-su, b0, vb[u]), ru, b0);

@@ -7,6 +7,7 @@ NaN, or any group whose pair table breaks Def. 1 - must not turn into plausible 
 import numpy as np
 import pytest
 
+import oracle
 import paro_inputs as pin
 
 pytestmark = pytest.mark.gpu
@@ -35,6 +36,21 @@ def mxfp4_definition(v):
     for k, top in ((6, a <= 5.0), (5, a < 3.5), (4, a <= 2.5), (3, a < 1.75), (2, a <= 1.25), (1, a < 0.75), (0, a <= 0.25)):
         code[top] = k
     return code | (np.signbit(v).astype(np.uint8) << 3), (e + 127).astype(np.uint8)
+
+
+def int4_definition(v):
+    """fp32 rows -> codes [R][C], scales fp16 [R][G], zero points [R][G] (Eq. 1)."""
+    v = v.astype(f32)
+    rows, c = v.shape
+    g = v.reshape(rows, c // 128, 128)
+    with np.errstate(all="ignore"):
+        mn, mx = np.fmin.reduce(g, axis=2), np.fmax.reduce(g, axis=2)
+        s = ((mx - mn) / f32(15)).astype(f32)
+        s16 = np.where(s >= f32(2.0 ** -14), s, f32(2.0 ** -14)).astype(np.float16)
+        s = s16.astype(f32)
+        z = np.fmin(np.fmax(-np.rint((mn / s).astype(f32)), f32(0)), f32(15))
+        q = np.fmin(np.fmax(np.rint((g / s[:, :, None]).astype(f32)) + z[:, :, None], f32(0)), f32(15))
+    return q.reshape(rows, c).astype(np.uint8), s16, z.astype(np.uint8)
 
 
 def _nibbles(words):
@@ -134,3 +150,28 @@ def test_nan_stays_visible_behind_the_mxfp4_linear(P, T, bad):
     hit = np.ones(T, dtype=bool) if bad == "pairs" else np.arange(T) == 1
     lost, spread = int(np.isfinite(y[hit]).sum()), int((~np.isfinite(y[~hit])).sum())
     assert lost == 0 and spread == 0
+
+
+def test_int4_weights_without_transform(P):
+    import torch
+    print("special values, INT4 weight side", flush=True)
+    x = special_rows()
+    codes, scales, zeros = int4_definition(x)
+    q = P.paro_w4_quantize(None, torch.as_tensor(x).cuda())
+    assert np.array_equal(q.scales.cpu().numpy().view(np.uint16), scales.T.view(np.uint16))
+    assert np.array_equal(oracle.unpack_zeros(q.qzeros.cpu().numpy().view(np.uint32)), zeros.T)
+    _same(_nibbles(q.qweight), codes, x)
+
+
+@pytest.mark.parametrize("n_layers", [0, 1, 8])
+@pytest.mark.parametrize("exponent", [-14, 0, 15])
+def test_int4_activations(P, n_layers, exponent):
+    """At 2^15 there are ranges above 15 * 65504, whose stored scale is infinite."""
+    import torch
+    print(f"special values, INT4 activations, layers={n_layers} scale=2^{exponent}", flush=True)
+    rot, v, x = _activations(P, n_layers, exponent)
+    codes, scales, zeros = int4_definition(v)
+    assert exponent < 15 or (np.isinf(scales) & np.isfinite(v).reshape(8, 2, 128).all(axis=2)).any()
+    gc, gs, gz = P.paro_rotate_scale_quantize_int4(rot, torch.as_tensor(x).cuda())
+    assert np.array_equal(gs.cpu().numpy().view(np.uint16), scales.view(np.uint16)) and np.array_equal(gz.cpu().numpy(), zeros)
+    _same(_nibbles(gc), codes, v)
