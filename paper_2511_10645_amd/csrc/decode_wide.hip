@@ -59,8 +59,8 @@ __device__ __forceinline__ void static_while(F &&f)
 constexpr int kXsRowBytes = kGroup * 2 + 16;
 constexpr int kXsWords = 16 * kXsRowBytes / 4;      // 1088 floats per wave
 // XOP: X is in operand order (a rotation pass can write it: rotate.hip), blocks of 16 tokens x 128 channels whose
-// fragments are contiguous (a kilobyte each; the last block holds only its own rows): no detour through LDS.  Rotated linears at 16
-// tokens, four layers of 4096 -> 6144, 4096 -> 4096, 4096 -> 28672 and 14336 -> 4096: 210 -> 204 us.
+// fragments are contiguous (a kilobyte each; the last block holds only its own rows): no detour through LDS
+// (decode_wide_operand_pays).
 template <int TB, bool XOP>
 __device__ __forceinline__ void load_x_fragments(const DecodeArgs &a, int ks, bool slice_ok, int lane, char *xs,
                                                  half8 (&xf)[TB][kSliceGroups][4])
@@ -125,7 +125,7 @@ __device__ __forceinline__ void load_x_fragments(const DecodeArgs &a, int ks, bo
 // MAXW: most waves per block (8: two waves per SIMD and 256 registers; otherwise kWideWaves).
 constexpr int kRotStageWords = kSliceCh / 2;     // the slice's 512 fp16 activations of one token, in floats
 
-template <bool SPLIT, bool T1, int ROTK = 0, int MAXW = kWideWaves, bool XOP = false>
+template <bool SPLIT, bool T1, int ROTK = 0, int MAXW = kWideWaves>
 __global__ __launch_bounds__(MAXW * 64) void decode_wide_kernel(DecodeArgs a)
 {
     static_assert(ROTK == 0 || T1, "the hosted transform is for one token");
@@ -217,7 +217,7 @@ __global__ __launch_bounds__(MAXW * 64) void decode_wide_kernel(DecodeArgs a)
         __builtin_amdgcn_wave_barrier();                                      // the area holds partial sums from here on
     } else if constexpr (!T1) {
         half8 xt[1][kSliceGroups][4];
-        load_x_fragments<1, XOP>(a, ks, slice_ok, lane, (char *)s_mine, xt);
+        load_x_fragments<1, false>(a, ks, slice_ok, lane, (char *)s_mine, xt);
 #pragma unroll
         for (int g2 = 0; g2 < kSliceGroups; ++g2)
 #pragma unroll
@@ -450,13 +450,24 @@ bool decode_wide_hosting_pays(int c_in, int c_out)
     return g.tiles_per_block >= (g.waves <= 8 ? 4 : 6);
 }
 
+// Whether activations in operand order pay behind a rotation pass: two blocks of 16 tokens, and K over at most two blocks of
+// the grid.  Rotated call in a replayed graph, row-major / operand order, us: 4096 -> 4096 at 17 tokens 10.05 / 9.64, at 32
+// 10.82 / 10.06; 4096 -> 28672 22.48 / 22.00 at 24; 2048 -> 2048 8.65 / 7.91, 1024 -> 8192 9.72 / 9.26, 5120 -> 5120
+// 16.49 / 16.18, 8192 -> 8192 20.63 / 20.27 at 32; but 14336 -> 4096 20.53 / 20.59, 27648 -> 5120 37.95 / 39.53.  Up to
+// 16 tokens the rotation's scattered stores cost more than the one detour: 9 tokens 4096 -> 4096 8.14 / 8.22,
+// 5120 -> 5120 9.86 / 10.44, 27648 -> 5120 24.3 / 25.2; 16 tokens 8.46 / 8.42, 10.44 / 10.52, 27.4 / 27.7.
+bool decode_wide_operand_pays(int c_in, int T)
+{
+    return T > 16 && T <= kWideMaxTokens && c_in <= 2 * kWide2Waves * kSliceCh;
+}
+
 // ws: the exchange part of the workspace (may be NULL where no partial sums are exchanged).
 // rot: NULL for the bare linear; otherwise a transform decode_wide_hosts() accepts, applied to X by the kernel itself.
-// x_operand: X is in operand order (2..32 tokens).
+// x_operand: X is in operand order (17..32 tokens).
 hipError_t launch_decode_wide(const paro_w4_weight &w, const paro_half_t *X, int64_t ldx, paro_half_t *Y, int64_t ldy,
                               int T, void *ws, hipStream_t s, const paro_rotation *rot, bool x_operand)
 {
-    if (x_operand && (rot || T < 2 || T > kWideMaxTokens)) return hipErrorInvalidValue;
+    if (x_operand && (rot || T <= 16 || T > kWideMaxTokens)) return hipErrorInvalidValue;
     if (packed_blob_bytes(w.c_in, w.c_out) >= (1ull << 31)) return hipErrorInvalidValue;   // 32-bit buffer offsets (checked by the caller)
     if (rot && (!decode_wide_hosts(*rot, T) || rot->c_in != w.c_in)) return hipErrorInvalidValue;
     const WideGeometry g = wide_geometry(w.c_in, w.c_out, T, rot != nullptr);
@@ -481,8 +492,6 @@ hipError_t launch_decode_wide(const paro_w4_weight &w, const paro_half_t *X, int
                              (const void *)decode_wide_kernel<true, false>, (const void *)decode_wide_kernel<true, true>,
                              (const void *)decode_wide2_kernel<false, false>, (const void *)decode_wide2_kernel<true, false>,
                              (const void *)decode_wide2_kernel<false, true>, (const void *)decode_wide2_kernel<true, true>,
-                             (const void *)decode_wide_kernel<false, false, 0, kWideWaves, true>,
-                             (const void *)decode_wide_kernel<true, false, 0, kWideWaves, true>,
                              (const void *)decode_wide_kernel<false, true, 8, 8>, (const void *)decode_wide_kernel<true, true, 8, 8>,
                              (const void *)decode_wide_kernel<false, true, 8>};
         for (const void *f : fns) {
@@ -499,10 +508,8 @@ hipError_t launch_decode_wide(const paro_w4_weight &w, const paro_half_t *X, int
         else if (g.waves <= 8) hipLaunchKernelGGL((decode_wide_kernel<false, true, 8, 8>), grid, block, g.lds, s, a);
         else                   hipLaunchKernelGGL((decode_wide_kernel<false, true, 8>), grid, block, g.lds, s, a);
     } else if (x_operand) {
-        if (T > 16 && g.kb > 1) hipLaunchKernelGGL((decode_wide2_kernel<true, true>), grid, block, g.lds, s, a);
-        else if (T > 16)        hipLaunchKernelGGL((decode_wide2_kernel<false, true>), grid, block, g.lds, s, a);
-        else if (g.kb > 1)      hipLaunchKernelGGL((decode_wide_kernel<true, false, 0, kWideWaves, true>), grid, block, g.lds, s, a);
-        else                    hipLaunchKernelGGL((decode_wide_kernel<false, false, 0, kWideWaves, true>), grid, block, g.lds, s, a);
+        if (g.kb > 1) hipLaunchKernelGGL((decode_wide2_kernel<true, true>), grid, block, g.lds, s, a);
+        else          hipLaunchKernelGGL((decode_wide2_kernel<false, true>), grid, block, g.lds, s, a);
     } else if (T > 16) {
         if (g.kb > 1) hipLaunchKernelGGL((decode_wide2_kernel<true, false>), grid, block, g.lds, s, a);
         else          hipLaunchKernelGGL((decode_wide2_kernel<false, false>), grid, block, g.lds, s, a);

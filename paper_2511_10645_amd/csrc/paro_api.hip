@@ -11,7 +11,6 @@ namespace {
 constexpr int kFuseMaxTokens = 4;            // the K-major decode kernel hosts the rotation up to this many tokens
 constexpr int64_t kMaxRowStride = 1 << 22;   // elements; the kernels address a run of up to 256 rows with 31-bit byte offsets
 constexpr int kDecodeMaxTokens = 16;         // above this the MFMA GEMM competes with passes of the streaming decode kernel
-constexpr int kOperandMinTokens = 9;         // rotation pass in operand order from here on
 constexpr int kStreamPassTokens = 32;        // tokens of one pass of the streaming kernel (two blocks of 16)
 
 inline bool aligned(const void *p, size_t a) { return ((uintptr_t)p % a) == 0; }
@@ -453,7 +452,7 @@ static paro_status rotated_linear(const paro_rotation *rot, const paro_w4_weight
         const size_t need = linear_operand_scratch_bytes(*w, T);
         return from_hip(launch_linear_operand(*w, xr, Y, ldy, T, scratch.partials(need), need, scratch.least, s));
     }
-    if (rot->plan && fast_weight(w) && T >= kOperandMinTokens && T <= kStreamPassTokens &&
+    if (rot->plan && fast_weight(w) && decode_wide_operand_pays(w->c_in, T) &&
         linear_route(*w, w->c_in, ldy, T, scratch.bytes).kernel == LinearRoute::kStream) {
         if (launch_rotate_operand(*rot, X, ldx, xr, T, s) != hipSuccess) return PARO_ERR_HIP;
         return from_hip(launch_decode_wide(*w, xr, w->c_in, Y, ldy, T, ws, s, nullptr, true));

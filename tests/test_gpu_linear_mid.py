@@ -46,9 +46,9 @@ CASES = [
     # repacked: 64- and 128-token tiles, K split and not, ragged tokens and outputs
     (33, 4096, 4112, "packed"), (64, 4096, 6144, "packed"), (64, 512, 16400, "packed"), (80, 2048, 2064, "packed"),
     (128, 4096, 2048, "packed"), (129, 1536, 4112, "packed"), (193, 4096, 1552, "packed"), (40, 13824, 1040, "packed"),
-    # streaming kernel behind a rotation (operand order up to 32 tokens): one and two blocks of 16 tokens, K split between blocks
+    # streaming kernel behind a rotation: one and two blocks of 16 tokens, K split between blocks (operand order from 17 tokens on, up to 8192 channels)
     (8, 512, 16, "packed"), (9, 512, 16, "packed"), (12, 13824, 528, "packed"), (16, 4096, 4112, "packed"), (17, 4096, 2064, "packed"), (31, 13824, 1040, "packed"),
-    (32, 2560, 528, "packed"),
+    (32, 2560, 528, "packed"), (19, 6656, 1040, "packed"), (32, 8192, 528, "packed"),
     # few outputs behind a rotation (operand order): one wave without groups, ragged blocks of 32 tokens and 32 / 64 outputs, K split
     (33, 512, 16, "packed"), (47, 512, 4112, "packed"), (64, 4096, 4096, "packed"), (64, 13824, 4096, "packed"), (65, 2560, 2064, "packed"), (97, 1536, 1040, "packed"),
     (176, 1024, 3088, "packed"), (255, 2048, 80, "packed"), (256, 512, 528, "packed"),
