@@ -366,6 +366,12 @@ size_t linear_operand_scratch_bytes(const paro_w4_weight &w, int T)
     return p.k_split > 1 ? (size_t)p.k_split * T * w.c_out * sizeof(float) : 0;
 }
 
+void linear_operand_plan(const paro_w4_weight &w, int T, int &outputs, int &k_slices)
+{
+    const OperandPlan p = plan_operand(w.c_in, w.c_out, T);
+    outputs = 16 * p.nt; k_slices = p.k_split;
+}
+
 template <int NT>
 static hipError_t launch_operand_nt(RowsArgs &a, hipStream_t s)
 {

@@ -313,6 +313,12 @@ size_t linear_tile_scratch_bytes(const paro_w4_weight &w, int T)
     return p.k_split > 1 ? (size_t)p.k_split * T * w.c_out * sizeof(float) : 0;
 }
 
+void linear_tile_plan(const paro_w4_weight &w, int T, int &tokens, int &k_slices)
+{
+    const TilePlan p = plan_tile(w.c_in, w.c_out, T);
+    tokens = p.two_m ? 128 : 64; k_slices = p.k_split;
+}
+
 // the weights are addressed with 31-bit byte offsets, the scales of the interchange layout as dwords
 bool linear_tile_supported(const paro_w4_weight &w, bool interchange)
 {

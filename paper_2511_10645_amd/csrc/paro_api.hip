@@ -463,6 +463,24 @@ static paro_status rotated_linear(const paro_rotation *rot, const paro_w4_weight
     return run_linear(w, xr, w->c_in, Y, ldy, T, ws, scratch, s);
 }
 
+int paro_internal_linear_plan(const paro_rotation *rot, const paro_w4_weight *w, int32_t T, int32_t *tile, int32_t *k_slices)
+{
+    const WsLayout L = ws_layout(rot, w, T);
+    const size_t scratch = L.extra_bytes + L.gemm_bytes;
+    int t = 0, k = 0, kernel = kPlanGeneric;
+    if (rot && fused_decode(rot, w, T)) kernel = kPlanHosted;
+    else if (rot && operand_route(rot, w, w->c_out, T, scratch)) { kernel = kPlanOperand; linear_operand_plan(*w, T, t, k); }
+    else if (fast_weight(w)) {
+        const LinearRoute::Kernel r = linear_route(*w, w->c_in, w->c_out, T, scratch).kernel;
+        kernel = r == LinearRoute::kTile ? kPlanTile : r == LinearRoute::kGemm ? kPlanGemm : kPlanStream;
+        if (kernel == kPlanStream) t = rot && rot->plan && decode_wide_operand_pays(w->c_in, T);
+    } else if (linear_rows_supported(*w, w->c_in, T)) { kernel = kPlanRows; k = scratch ? (int)(linear_rows_scratch_bytes(*w, T) / ((size_t)T * w->c_out * 4)) : 1; }
+    else if (T > kStreamPassTokens && linear_tile_supported(*w, true)) kernel = kPlanTile;
+    if (kernel == kPlanTile) { linear_tile_plan(*w, T, t, k); if (linear_tile_scratch_bytes(*w, T) > scratch) k = 1; }
+    *tile = t; *k_slices = k;
+    return kernel;
+}
+
 paro_status paro_rotated_linear(const paro_rotation *rot, const paro_w4_weight *w, const paro_half_t *X, int64_t ldx,
                                 paro_half_t *Y, int64_t ldy, int32_t T, void *ws, size_t ws_bytes, void *stream)
 {

@@ -197,6 +197,7 @@ hipError_t launch_linear_rows(const paro_w4_weight &w, const paro_half_t *X, int
 // Repacked weights on activations in operand order (linear_rows.hip); scratch as above.
 bool linear_operand_supported(const paro_w4_weight &w, int T);
 double linear_operand_estimate_us(const paro_w4_weight &w, int T);
+void linear_operand_plan(const paro_w4_weight &w, int T, int &outputs, int &k_slices);
 size_t linear_operand_scratch_bytes(const paro_w4_weight &w, int T);
 hipError_t launch_linear_operand(const paro_w4_weight &w, const paro_half_t *Xop, paro_half_t *Y, int64_t ldy, int T, void *scratch,
                                  size_t scratch_bytes, const void *least, hipStream_t s);
@@ -204,6 +205,7 @@ hipError_t launch_linear_operand(const paro_w4_weight &w, const paro_half_t *Xop
 // Tiled linear with the weights in registers (linear_tile.hip), repacked or interchange layout; scratch as above.
 bool linear_tile_supported(const paro_w4_weight &w, bool interchange);
 double linear_tile_estimate_us(const paro_w4_weight &w, int T);
+void linear_tile_plan(const paro_w4_weight &w, int T, int &tokens, int &k_slices);
 size_t linear_tile_scratch_bytes(const paro_w4_weight &w, int T);
 hipError_t launch_linear_tile(const paro_w4_weight &w, bool interchange, const paro_half_t *X, int64_t ldx, paro_half_t *Y,
                               int64_t ldy, int T, void *scratch, size_t scratch_bytes, const void *least, hipStream_t s);
@@ -225,3 +227,10 @@ hipError_t launch_gemm(const paro_w4_weight &w, const paro_half_t *X, int64_t ld
                        int T, void *scratch, size_t scratch_bytes, hipStream_t s);
 
 }  // namespace paro
+
+// The kernel that a linear call (rot NULL: the bare one) with the reported workspace and dense rows runs on; tile: tokens
+// per tile (kPlanTile), outputs per block (kPlanOperand), 1 for activations in operand order (kPlanStream), else 0;
+// k_slices: the split of K of kPlanTile, kPlanOperand and kPlanRows (0 or 1: none).
+// Host only: the tests pin with it that a shape reaches the kernel it is there for.
+enum { kPlanHosted, kPlanStream, kPlanGemm, kPlanTile, kPlanOperand, kPlanRows, kPlanGeneric };
+extern "C" int paro_internal_linear_plan(const paro_rotation *rot, const paro_w4_weight *w, int32_t T, int32_t *tile, int32_t *k_slices);

@@ -43,7 +43,7 @@ CASES = [
     (1, 640, 48, "plain"), (1, 11008, 272, "plain"), (16, 128, 16, "plain"), (17, 1920, 80, "plain"), (32, 640, 528, "plain"),
     (24, 2176, 4112, "plain"), (33, 128, 16, "plain"), (33, 640, 144, "plain"), (64, 1152, 2064, "plain"),
     (65, 1920, 272, "plain"), (129, 4096, 1040, "plain"), (200, 2176, 1296, "plain"), (5, 640, 80, "scales_odd"), (40, 640, 80, "scales_odd"),
-    # repacked: 64- and 128-token tiles, K split and not, ragged tokens and outputs
+    # repacked: 64-token tiles, K split and not, ragged tokens and outputs
     (33, 4096, 4112, "packed"), (64, 4096, 6144, "packed"), (64, 512, 16400, "packed"), (80, 2048, 2064, "packed"),
     (128, 4096, 2048, "packed"), (129, 1536, 4112, "packed"), (193, 4096, 1552, "packed"), (40, 13824, 1040, "packed"),
     # streaming kernel behind a rotation: one and two blocks of 16 tokens, K split between blocks (operand order from 17 tokens on, up to 8192 channels)
@@ -52,6 +52,9 @@ CASES = [
     # few outputs behind a rotation (operand order): one wave without groups, ragged blocks of 32 tokens and 32 / 64 outputs, K split
     (33, 512, 16, "packed"), (47, 512, 4112, "packed"), (64, 4096, 4096, "packed"), (64, 13824, 4096, "packed"), (65, 2560, 2064, "packed"), (97, 1536, 1040, "packed"),
     (176, 1024, 3088, "packed"), (255, 2048, 80, "packed"), (256, 512, 528, "packed"),
+    # 128-token tiles: interchange layout and repacked, unsplit with a bias, and (behind a rotation, bare) with K split;
+    # the last two behind a rotation: operand order with 64 outputs per block and K unsplit, split
+    (65, 640, 16400, "plain"), (66, 2560, 6160, "plain"), (67, 512, 16400, "packed"), (66, 14336, 4112, "packed"), (64, 14336, 2064, "packed"),
 ]
 
 
@@ -70,15 +73,22 @@ def test_least_workspace(P, T, c_in, c_out, form, rotated, least):
     _check_linear(P, T, c_in, c_out, form, rotated, least)
 
 
-def _check_linear(P, T, c_in, c_out, form, rotated, least=None):
+# the rotation that writes operand order: every number of layers, the scale before and after them, whole and ragged blocks
+@pytest.mark.parametrize("n_layers", range(9))
+@pytest.mark.parametrize("T,c_in,c_out,order", [(19, 512, 80, 0), (32, 512, 48, 1), (48, 512, 48, 0), (61, 1024, 80, 1)])
+def test_operand_order_of_every_rotation(P, T, c_in, c_out, order, n_layers):
+    _check_linear(P, T, c_in, c_out, "packed", True, n_layers=n_layers, order=order)
+
+
+def _check_linear(P, T, c_in, c_out, form, rotated, least=None, n_layers=8, order=0):
     import torch
-    print(f"linear T={T} {c_in}->{c_out} {form} rotated={rotated}", flush=True)
-    li = pin.make_custom(4000 + T + c_in, T, c_in, c_out, n_outlier=2)
+    print(f"linear T={T} {c_in}->{c_out} {form} rotated={rotated} layers={n_layers} order={order}", flush=True)
+    li = pin.make_custom(4000 + T + c_in, T, c_in, c_out, n_layers=n_layers, n_outlier=2)
     bias = pin.make_bias(8, 8, c_out) if T % 2 else None
     w = _weight(P, li, bias, form)
     rot = None
     if rotated:
-        rot = P.Rotation(li.pairs, li.theta, li.ch_scale)
+        rot = P.Rotation(li.pairs, li.theta, li.ch_scale, scale_order=order)
         P.paro_rotation_plan_build(rot)
     want = P.paro_workspace_bytes(rot, w, T)
     assert least is None or least < want
