@@ -384,7 +384,7 @@ static hipError_t launch_operand_nt(RowsArgs &a, hipStream_t s)
 hipError_t launch_linear_operand(const paro_w4_weight &w, const paro_half_t *Xop, paro_half_t *Y, int64_t ldy, int T, void *scratch,
                                  size_t scratch_bytes, const void *least, hipStream_t s)
 {
-    OperandPlan p = plan_operand(w.c_in, w.c_out, T);
+    const OperandPlan p = plan_operand(w.c_in, w.c_out, T);
     RowsArgs a;
     a.w = (const char *)w.packed;
     a.scales_off = (uint32_t)packed_tiles_bytes(w.c_in, w.c_out);
@@ -393,9 +393,8 @@ hipError_t launch_linear_operand(const paro_w4_weight &w, const paro_half_t *Xop
     a.X = (const _Float16 *)Xop; a.ldx = 0; a.Y = (_Float16 *)Y; a.ldy = ldy; a.bias = (const _Float16 *)w.bias;
     a.T = T; a.C = w.c_in; a.N = w.c_out; a.G = w.c_in / kGroup;
     a.m_lo = 0x000F000Fu; a.m_hi = 0x00F000F0u; a.k_lo = 0x64006400u; a.k_hi = 0x54005400u;
-    if (p.k_split > 1 && !(scratch && scratch_bytes >= (size_t)p.k_split * T * w.c_out * sizeof(float) && ((uintptr_t)scratch % 16) == 0)) {
-        p.k_split = 1; p.groups_per_split = a.G;
-    }
+    // the caller takes this kernel only where its partial tiles have room
+    if (p.k_split > 1 && !(scratch && scratch_bytes >= (size_t)p.k_split * T * w.c_out * sizeof(float) && ((uintptr_t)scratch % 16) == 0)) return hipErrorInvalidValue;
     a.k_split = p.k_split; a.groups_per_split = p.groups_per_split;
     a.partial = p.k_split > 1 ? (float *)scratch : nullptr;
     const hipError_t e = p.nt == 2 ? launch_operand_nt<2>(a, s) : launch_operand_nt<4>(a, s);

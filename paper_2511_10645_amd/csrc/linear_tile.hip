@@ -339,6 +339,7 @@ hipError_t launch_linear_tile(const paro_w4_weight &w, bool interchange, const p
     a.T = T; a.C = w.c_in; a.N = w.c_out; a.G = w.c_in / kGroup;
     a.m_lo = 0x000F000Fu; a.m_hi = 0x00F000F0u; a.k_lo = 0x64006400u; a.k_hi = 0x54005400u;
     if (p.k_split > 1 && !(scratch && scratch_bytes >= (size_t)p.k_split * T * w.c_out * sizeof(float) && ((uintptr_t)scratch % 16) == 0)) {
+        if (!interchange) return hipErrorInvalidValue;                   // the caller takes another kernel then
         p.k_split = 1; p.groups_per_split = (a.G + 3) / 4 * 4;           // no room for partial tiles
     }
     a.k_split = p.k_split; a.groups_per_split = p.groups_per_split;
