@@ -511,7 +511,9 @@ double gemm_estimate_us(const paro_w4_weight &w, int T) { return plan_gemm(w, T)
 
 // The same for the choice between either and the kernel of linear_tile.hip: fitted to 700 timings (58 shapes, 33 to 2048
 // tokens), 6 % off in the mean for unsplit launches, 8 and 14 % for split ones.  (plan_gemm's model ranks its own
-// choices, but is 24 % off as a time.)
+// choices, but is 24 % off as a time.)  Calls with a tail: 3144 timings (393 shapes, 129 to 1024 tokens), 13 % off; 6 % below
+// that fit on purpose, so that none of them runs more than 3 % slower than the GEMM does (a tail charged 0.6 of a round,
+// whatever its size, made that 229: 6144 -> 16496 at 946 tokens 246 us instead of 198).
 double gemm_fitted_us(const paro_w4_weight &w, int T)
 {
     const GemmPlan p = plan_gemm(w, T);
@@ -524,7 +526,8 @@ double gemm_fitted_us(const paro_w4_weight &w, int T)
         return 2.8 + 0.846 * n_ks * (double)((tiles + 255) / 256) + 0.374 * out_mb;
     }
     const long rounds = ((long)p.m_big * p.n_main + 255) / 256;
-    return 1.2 + 1.678 * n_ks * ((double)rounds + (p.n_small ? 0.6 : 0.0)) + 0.34 * out_mb;
+    if (p.n_small > 0) return 2.5 + 1.66 * n_ks * (double)rounds + 1.21 * p.k_steps + (p.k_split > 1 ? 6.6 : 0.0) + 0.31 * out_mb;
+    return 1.2 + 1.678 * n_ks * (double)rounds + 0.34 * out_mb;
 }
 
 // output tiles [n_tile0, n_tile0 + n_count) x all token tiles

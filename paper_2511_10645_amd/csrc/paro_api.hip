@@ -199,11 +199,16 @@ LinearRoute linear_route(const paro_w4_weight &w, int64_t ldx, int64_t ldy, int 
     const double stream_us = (double)(T / kStreamPassTokens) * pass32 +
                              (rem == 0 ? 0.0 : rem <= 16 ? 3.5 + mb / 5.2 + ex16 : pass32);
     const bool gemm = T >= 512 || gemm_estimate_us(w, T) <= stream_us;
-    const double us = gemm ? gemm_fitted_us(w, T) : stream_us;
+    // As a time that model is 21 % off, mostly too long for short streams; fitted to 1279 timings (649 shapes) it is 15 % off.
+    const double part32 = (double)decode_wide_partial_bytes(w.c_in, w.c_out, kStreamPassTokens) / 1.0e6;
+    const double part16 = (double)decode_wide_partial_bytes(w.c_in, w.c_out, 16) / 1.0e6;
+    const double us = gemm ? gemm_fitted_us(w, T)
+                           : (double)(T / kStreamPassTokens + (rem > 16)) * (4.6 + 0.37 * mb + 1.34 * part32) +
+                                 (rem > 0 && rem <= 16 ? 3.5 + 0.25 * mb + 1.34 * part16 : 0.0);
     // The kernel between the two (linear_tile.hip) neither walks whole GEMM tiles nor re-reads the weights, but costs
-    // most per product.  Its model and the GEMM's fitted one are 6 to 14 % off, hence 0.9: over 918 measured
-    // (shape, tokens) pairs the choice loses more than 3 % on two and takes 1.28x less time in the mean than without
-    // the kernel, 1.29x being the best possible.  Above 1024 tokens it has no shape to itself.  Without room for its partial
+    // most per product.  The models are 6 to 15 % off, hence 0.9: over 5131 measured bare (shape, tokens) pairs (649 shapes,
+    // 33 to 1024 tokens, every route forced) the choice loses more than 3 % on three (4 % there) and takes 1.32x less
+    // time in the mean than the better of the other two, 1.34x being the best possible.  Above 1024 tokens it has no shape to itself.  Without room for its partial
     // tiles it would run unsplit and as slow as the others.
     if (T > kStreamPassTokens && T <= 1024 && linear_tile_supported(w, false) && linear_tile_scratch_bytes(w, T) <= scratch_bytes) {
         const double tile_us = linear_tile_estimate_us(w, T);
@@ -415,8 +420,9 @@ paro_status paro_w4a16_linear(const paro_w4_weight *w, const paro_half_t *X, int
 }
 
 // Whether the rotation pass writes operand order and the kernel that reads it follows (linear_rows.hip): where its model says
-// so, which is 5 % off, by the margin of linear_route.  Over 1207 measured (shape, tokens) pairs the choice loses more
-// than 3 % on three (5 to 8 % there) and takes 1.28x less time in the mean than linear_route's kernel, 1.29x being the best possible.
+// so, which is 5 % off, by the margin of linear_route.  Of 3833 measured rotated (shape, tokens) pairs (649 shapes, 33 to 256
+// tokens, every route forced) it is taken on 2096, where it is 1.32x faster in the mean than the best other route and more
+// than 3 % slower (up to 7 %) on seven.
 static bool operand_route(const paro_rotation *rot, const paro_w4_weight *w, int64_t ldy, int T, size_t scratch_bytes)
 {
     if (!rot->plan || !fast_weight(w) || !linear_operand_supported(*w, T)) return false;

@@ -38,3 +38,10 @@ def test_rotations_of_every_depth_are_read_in_operand_order():
     for T, c_in, c_out in ((19, 512, 80), (32, 512, 48), (48, 512, 48), (61, 1024, 80)):
         kernel, tile, _ = plan(T, c_in, c_out, "packed", True)
         assert kernel == OPERAND or (kernel, tile) == (STREAM, 1), (T, c_in, c_out, kernel)
+
+
+def test_the_tiled_kernel_is_not_taken_where_it_is_slower():
+    """Calls whose last round of GEMM tiles is a small tail, and two short passes of the streaming kernel on few outputs
+    (measured, tiled kernel against the one expected here: 246 / 198, 317 / 275, 453 / 335 and 16.2 / 14.9 us)."""
+    for T, c_in, c_out, want in ((946, 6144, 16496, GEMM), (888, 8704, 17328, GEMM), (910, 11264, 16480, GEMM), (42, 20992, 672, STREAM)):
+        assert plan(T, c_in, c_out, "packed", False)[0] == want, (T, c_in, c_out)
