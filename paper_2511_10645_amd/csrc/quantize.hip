@@ -15,7 +15,7 @@
 //                NaN throughout has e = 126 and codes +-6: what is multiplied with it overflows.
 // so that  sum_c (q - z) s . x'_c  ~  w_n . x  for the activations x' that paro_rotate_scale produces (Eq. 2).
 //
-// One wavefront owns a channel group and a run of rows, four rows at a time, with the lane plan and layer loop of the
+// One wavefront owns a channel group and a run of rows, four rows at a time (few rows: one each, kQuantFewRows), with the lane plan and layer loop of the
 // activation kernel (rotate_lane.h): the plan (7.4 KB at K = 8, 29 times a row's group) is read once per run, the four
 // rows' chains of multiply-adds and permutes are independent, and rows go through a wave-private LDS area as
 // [channel][4 rows].  What bounds it is the vector pipes: 38 instructions per (row, group) of rotation, and the rest was
@@ -28,10 +28,10 @@
 //   - MXFP4: the rotated values are read back in channel order, 8 per lane, so that a block's maximum is two steps within
 //     four lanes and the codes are four instructions of the FP4 converter (equal to the thresholds of the format on
 //     every tie and its neighbours over the whole range of exponents).
-// Measured (before: one row of INT4 weights per wave, plan re-read for each; MXFP4 one row at a time, 14 instructions of
+// Measured in a replayed graph (before: one row of INT4 weights per wave, plan re-read for each; MXFP4 one row at a time, 14 instructions of
 // thresholds per value): INT4 weight 28672 x 4096 395 -> 142 us (448 -> 140 repeated on one weight), MXFP4 activations
-// 2048 x 4096 21.0 -> 12.8, 2048 x 14336 55.8 -> 36.4 us, INT4 activations 25.4 -> 15.1 and 80.3 -> 40.3 us; the same bits
-// throughout.
+// 2048 x 4096 21.0 -> 12.8, 2048 x 14336 55.8 -> 36.4 us, INT4 activations 25.4 -> 15.1 and 80.3 -> 40.3 us; 1 x 4096
+// MXFP4 3.0 -> 2.6, INT4 2.9 -> 2.8; the same bits throughout.
 #include "paro_internal.h"
 #include "rotate_lane.h"
 #include <type_traits>
@@ -42,16 +42,19 @@ constexpr int kQuantWaves = 4;       // waves per block
 constexpr int kQuantRows = 4;        // rows side by side
 constexpr int kQuantBatches = 8;     // most batches of kQuantRows rows per wave (unrolled, see rotate.hip)
 constexpr int kQuantPad = kGroup + 4;
+// (row, group) pairs below which rows go one to a wave.  Replayed graph, one row / four rows side by side, us: MXFP4 activations
+// 1 x 4096 2.62 / 3.0, 112 x 4096 (3584 pairs) 3.63 / 3.5; INT4 activations 1 x 4096 2.80 / 3.47, 78 x 896 3.0 / 3.82.
+constexpr int64_t kQuantFewRows = 3072;
 
 enum QuantKind { kW4Weight, kA4Act, kMxAct, kMxWeight };
 
 struct QuantArgs {
     const uint32_t *plan;
     const _Float16 *X; int64_t ldx;
-    int T, C, rows_per_wave;         // rows; rows_per_wave: a multiple of kQuantRows (of 8 for kW4Weight)
+    int T, C, rows_per_wave;         // rows; rows_per_wave: a multiple of the kernel's U
     uint32_t *codes;                 // [T][C/8]
     _Float16 *scales;                // kW4Weight: [C/128][T], kA4Act: [T][C/128]
-    uint32_t *qzeros;                // kW4Weight: [C/128][T/8]
+    uint16_t *qzeros;                // kW4Weight: [C/128][T/8] words, as halves
     uint8_t *bytes;                  // kA4Act: zero points [T][C/128]; MXFP4: scales [T][C/32]
 };
 
@@ -92,13 +95,13 @@ __device__ __forceinline__ float from_lane(float v, int lane) { return __int_as_
 
 // rotate_layers with the order of the two products of every sum written out (the one that is there first is rounded, the
 // later one joins it in a fused multiply-add): a code on a rounding tie must not depend on how the compiler schedules.
-template <int K>
-__device__ __forceinline__ void quant_rotate(const LanePlan<K> &P, float (&a)[kQuantRows], float (&b)[kQuantRows])
+template <int K, int U>
+__device__ __forceinline__ void quant_rotate(const LanePlan<K> &P, float (&a)[U], float (&b)[U])
 {
 #pragma unroll
     for (int l = 0; l < K; ++l)
 #pragma unroll
-        for (int u = 0; u < kQuantRows; ++u) {
+        for (int u = 0; u < U; ++u) {
             const float na = l == 0 ? fmaf(P.m00[l], a[u], P.m01[l] * b[u]) : fmaf(P.m01[l], b[u], P.m00[l] * a[u]);
             const float nb = l == 0 ? fmaf(P.m10[l], a[u], P.m11[l] * b[u]) : fmaf(P.m11[l], b[u], P.m10[l] * a[u]);
             a[u] = na;
@@ -106,13 +109,15 @@ __device__ __forceinline__ void quant_rotate(const LanePlan<K> &P, float (&a)[kQ
         }
 }
 
-// K < 0: no transform (rows quantised as they are).
-template <int K, int KIND>
+// K < 0: no transform (rows quantised as they are).  U: rows side by side, kQuantRows, or one where the rows do not fill the
+// chip: four rows then only lengthen the chain of one wave.
+template <int K, int KIND, int U>
 __global__ __launch_bounds__(kQuantWaves * 64) void quantize_kernel(QuantArgs a)
 {
     constexpr bool WSIDE = KIND == kW4Weight || KIND == kMxWeight, INT4 = KIND == kW4Weight || KIND == kA4Act;
-    __shared__ __attribute__((aligned(16))) uint32_t s_stage[kQuantWaves][kGroup * 2];                   // [channel][4 rows] fp16
-    __shared__ __attribute__((aligned(16))) uint32_t s_out[kQuantWaves][INT4 ? kGroup : 4 * kQuantPad];  // codes [channel][4 rows], or values [4 rows][channel]
+    static_assert(U == kQuantRows || (U == 1 && KIND != kW4Weight && K >= 0), "");
+    __shared__ __attribute__((aligned(16))) uint32_t s_stage[kQuantWaves][kGroup * U / 2];               // [channel][U rows] fp16
+    __shared__ __attribute__((aligned(16))) uint32_t s_out[kQuantWaves][INT4 ? kGroup : U * kQuantPad];  // codes [channel][4 rows], or values [U rows][channel]
     const int g = blockIdx.x, G = a.C / kGroup;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -124,9 +129,9 @@ __global__ __launch_bounds__(kQuantWaves * 64) void quantize_kernel(QuantArgs a)
     // its last one and are not written
     const _Float16 *x0 = a.X + t0 * a.ldx + (size_t)g * kGroup;
     auto load_row = [&](int r) { return *((const uint32_t *)(x0 + (int64_t)(r < n_rows ? r : n_rows - 1) * a.ldx) + lane); };
-    uint32_t cur[kQuantRows], nxt[kQuantRows];
+    uint32_t cur[U], nxt[U];
 #pragma unroll
-    for (int u = 0; u < kQuantRows; ++u) cur[u] = load_row(u);
+    for (int u = 0; u < U; ++u) cur[u] = load_row(u);
 
     LanePlan<(K > 0 ? K : 0)> P;
     float ia = 1.f, ib = 1.f, oa = 1.f, ob = 1.f;
@@ -144,38 +149,50 @@ __global__ __launch_bounds__(kQuantWaves * 64) void quantize_kernel(QuantArgs a)
     auto lo_pair = [](uint32_t x, uint32_t y) { return (x & 0xffffu) | (y << 16); };
     auto hi_pair = [](uint32_t x, uint32_t y) { return (x >> 16) | (y & 0xffff0000u); };
     const int orow = lane >> 4, oword = lane & 15;       // the row of a batch and its 8 channels this lane writes out
-    uint32_t zword = 0;
 
-    quant_while<kQuantBatches>([&](auto I) {
-        constexpr int t = I * kQuantRows;
+    quant_while<U == 1 ? 1 : kQuantBatches>([&](auto I) {
+        constexpr int t = I * U;
         if (t >= n_rows) return false;
+        if constexpr (U > 1)
 #pragma unroll
-        for (int u = 0; u < kQuantRows; ++u) nxt[u] = load_row(t + kQuantRows + u);
-        float va[kQuantRows], vb[kQuantRows];
-        if constexpr (K >= 0) {
+            for (int u = 0; u < U; ++u) nxt[u] = load_row(t + U + u);
+        float va[U], vb[U];
+        if constexpr (K >= 0 && U == 1) {
+            *(uint32_t *)(sp + lane * 4) = cur[0];
+            __builtin_amdgcn_wave_barrier();
+            va[0] = (float)*(const _Float16 *)(sp + P.in_a * 2) * ia;
+            vb[0] = (float)*(const _Float16 *)(sp + P.in_b * 2) * ib;
+            quant_rotate<K, U>(P, va, vb);
+            va[0] *= oa; vb[0] *= ob;
+        } else if constexpr (K >= 0) {
             const u32x4v in = {lo_pair(cur[0], cur[1]), lo_pair(cur[2], cur[3]), hi_pair(cur[0], cur[1]), hi_pair(cur[2], cur[3])};
             *(u32x4v *)(sp + lane * 16) = in;
             __builtin_amdgcn_wave_barrier();
             const half4v ha = *(const half4v *)(sp + P.in_a * 8), hb = *(const half4v *)(sp + P.in_b * 8);
 #pragma unroll
-            for (int u = 0; u < kQuantRows; ++u) { va[u] = (float)ha[u] * ia; vb[u] = (float)hb[u] * ib; }
-            quant_rotate<K>(P, va, vb);
+            for (int u = 0; u < U; ++u) { va[u] = (float)ha[u] * ia; vb[u] = (float)hb[u] * ib; }
+            quant_rotate<K, U>(P, va, vb);
 #pragma unroll
-            for (int u = 0; u < kQuantRows; ++u) { va[u] *= oa; vb[u] *= ob; }
+            for (int u = 0; u < U; ++u) { va[u] *= oa; vb[u] *= ob; }
         } else {
 #pragma unroll
-            for (int u = 0; u < kQuantRows; ++u) {
+            for (int u = 0; u < U; ++u) {
                 union { uint32_t u; _Float16 h[2]; } c; c.u = cur[u];
                 va[u] = (float)c.h[0]; vb[u] = (float)c.h[1];
             }
         }
         const int64_t row = t0 + t + orow;               // the row this lane writes out
-        const bool live = t + orow < n_rows;
+        const bool live = orow < U && t + orow < n_rows;
         if constexpr (INT4) {
-            float mx[4], nmn[4];
+            float mx[U], nmn[U], mxv, mnv;
 #pragma unroll
-            for (int u = 0; u < 4; ++u) { mx[u] = fmaxf(va[u], vb[u]); nmn[u] = fmaxf(-va[u], -vb[u]); }
-            const float mxv = wave_max4(mx), mnv = -wave_max4(nmn);
+            for (int u = 0; u < U; ++u) { mx[u] = fmaxf(va[u], vb[u]); nmn[u] = fmaxf(-va[u], -vb[u]); }
+            if constexpr (U == 1) {
+                const float m = wave_max4({mx[0], nmn[0], mx[0], nmn[0]});
+                mxv = from_lane(m, kRowLane[0]); mnv = -from_lane(m, kRowLane[1]);
+            } else {
+                mxv = wave_max4(mx); mnv = -wave_max4(nmn);
+            }
             const float range = mxv - mnv;
             float s32 = range / 15.0f;
             if (!(s32 >= 6.103515625e-05f)) s32 = 6.103515625e-05f;
@@ -183,9 +200,9 @@ __global__ __launch_bounds__(kQuantWaves * 64) void quantize_kernel(QuantArgs a)
             const float s = (float)s16, rs = range == range ? 1.0f / s : 0.f;    // 0: infinite scale, or a group of infinities
             float zf = -rintf(mnv / s);
             zf = fminf(fmaxf(zf, 0.0f), 15.0f);
-            uint32_t ca = 0, cb = 0;
+            uint32_t ca = 0, cb = 0, zhalf = 0;
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
+            for (int u = 0; u < U; ++u) {
                 const float su = from_lane(s, kRowLane[u]), ru = from_lane(rs, kRowLane[u]), zu = from_lane(zf, kRowLane[u]);
                 float qa, qb;
                 if (ru > 0.f) {                          // (uniform)
@@ -197,7 +214,7 @@ __global__ __launch_bounds__(kQuantWaves * 64) void quantize_kernel(QuantArgs a)
                 }
                 ca = __builtin_amdgcn_cvt_pk_u8_f32(fminf(fmaxf(rintf(qa) + zu, 0.0f), 15.0f), u, ca);
                 cb = __builtin_amdgcn_cvt_pk_u8_f32(fminf(fmaxf(rintf(qb) + zu, 0.0f), 15.0f), u, cb);
-                if constexpr (KIND == kW4Weight) zword |= (uint32_t)zu << (4 * (t % 8 + u));
+                if constexpr (KIND == kW4Weight) zhalf |= (uint32_t)zu << (4 * u);
             }
             s_out[wave][ch_a] = ca;
             s_out[wave][ch_b] = cb;
@@ -209,27 +226,26 @@ __global__ __launch_bounds__(kQuantWaves * 64) void quantize_kernel(QuantArgs a)
             for (int k = 0; k < 8; ++k) word |= ((d[k] >> (8 * orow)) & 15u) << (4 * k);
             if (live) a.codes[(size_t)row * (a.C / 8) + (size_t)g * (kGroup / 8) + oword] = word;
             const int64_t prow = t0 + t + row_of_lane(lane);         // the row whose scale this lane holds
-            if (oword == 0 && t + row_of_lane(lane) < n_rows) {
+            if (oword == 0 && row_of_lane(lane) < U && t + row_of_lane(lane) < n_rows) {
                 if constexpr (KIND == kW4Weight) a.scales[(size_t)g * a.T + prow] = s16;
                 else { a.scales[(size_t)prow * G + g] = s16; a.bytes[(size_t)prow * G + g] = (uint8_t)zf; }
             }
-            if constexpr (KIND == kW4Weight && t % 8 == 4) {
-                if (lane == 0) a.qzeros[(size_t)g * (a.T / 8) + (t0 + t) / 8] = zword;
-                zword = 0;
-            }
+            if constexpr (KIND == kW4Weight)             // T is a multiple of 8, t0 + t of 4: half a word
+                if (lane == 0) a.qzeros[(size_t)g * (a.T / 4) + (t0 + t) / 4] = (uint16_t)zhalf;
         } else {
             float v[8];
             if constexpr (K >= 0) {
                 float *so = (float *)s_out[wave];
 #pragma unroll
-                for (int u = 0; u < 4; ++u) { so[u * kQuantPad + ch_a] = va[u]; so[u * kQuantPad + ch_b] = vb[u]; }
+                for (int u = 0; u < U; ++u) { so[u * kQuantPad + ch_a] = va[u]; so[u * kQuantPad + ch_b] = vb[u]; }
                 __builtin_amdgcn_wave_barrier();
-                *(float4 *)&v[0] = *(const float4 *)(so + orow * kQuantPad + oword * 8);
-                *(float4 *)&v[4] = *(const float4 *)(so + orow * kQuantPad + oword * 8 + 4);
+                const float *row_v = so + (U == 1 ? 0 : orow) * kQuantPad + oword * 8;
+                *(float4 *)&v[0] = *(const float4 *)row_v;
+                *(float4 *)&v[4] = *(const float4 *)(row_v + 4);
             } else {
                 uint32_t *so = s_out[wave];
 #pragma unroll
-                for (int u = 0; u < 4; ++u) so[u * kQuantPad + lane] = cur[u];
+                for (int u = 0; u < U; ++u) so[u * kQuantPad + lane] = cur[u];
                 __builtin_amdgcn_wave_barrier();
                 union { u32x4v u; _Float16 h[8]; } c; c.u = *(const u32x4v *)(so + orow * kQuantPad + oword * 4);
 #pragma unroll
@@ -254,8 +270,9 @@ __global__ __launch_bounds__(kQuantWaves * 64) void quantize_kernel(QuantArgs a)
             }
         }
         __builtin_amdgcn_wave_barrier();
+        if constexpr (U > 1)
 #pragma unroll
-        for (int u = 0; u < kQuantRows; ++u) cur[u] = nxt[u];
+            for (int u = 0; u < U; ++u) cur[u] = nxt[u];
         return true;
     });
 }
@@ -264,12 +281,20 @@ template <int K, int KIND>
 static hipError_t launch_quant_k(QuantArgs &a, hipStream_t s)
 {
     // runs of up to 32 rows per wave, shorter while that leaves fewer than ~4096 waves
-    const int G = a.C / kGroup, least = KIND == kW4Weight ? 2 * kQuantRows : kQuantRows;
+    const int G = a.C / kGroup;
     int rpw = kQuantBatches * kQuantRows;
-    while (rpw > least && (int64_t)G * ((a.T + rpw - 1) / rpw) < 4096) rpw >>= 1;
+    while (rpw > kQuantRows && (int64_t)G * ((a.T + rpw - 1) / rpw) < 4096) rpw >>= 1;
+    constexpr bool ONE = KIND != kW4Weight && K >= 0;
+    if (ONE && (int64_t)G * a.T < kQuantFewRows) rpw = 1;
     a.rows_per_wave = rpw;
     const int waves_t = (a.T + rpw - 1) / rpw;
-    hipLaunchKernelGGL((quantize_kernel<K, KIND>), dim3(G, (waves_t + kQuantWaves - 1) / kQuantWaves), dim3(kQuantWaves * 64), 0, s, a);
+    const dim3 grid(G, (waves_t + kQuantWaves - 1) / kQuantWaves), block(kQuantWaves * 64);
+    if constexpr (ONE)
+        if (rpw == 1) {
+            hipLaunchKernelGGL((quantize_kernel<K, KIND, 1>), grid, block, 0, s, a);
+            return hipGetLastError();
+        }
+    hipLaunchKernelGGL((quantize_kernel<K, KIND, kQuantRows>), grid, block, 0, s, a);
     return hipGetLastError();
 }
 
@@ -297,7 +322,7 @@ static hipError_t launch_quant(const paro_rotation *rot, QuantArgs &a, hipStream
 hipError_t launch_quantize(const paro_rotation *rot, const paro_half_t *W, int64_t ldw, int N, int C, uint32_t *qweight,
                            paro_half_t *scales, uint32_t *qzeros, hipStream_t s)
 {
-    QuantArgs a{nullptr, (const _Float16 *)W, ldw, N, C, 0, qweight, (_Float16 *)scales, qzeros, nullptr};
+    QuantArgs a{nullptr, (const _Float16 *)W, ldw, N, C, 0, qweight, (_Float16 *)scales, (uint16_t *)qzeros, nullptr};
     return launch_quant<kW4Weight>(rot, a, s);
 }
 

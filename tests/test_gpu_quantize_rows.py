@@ -45,6 +45,25 @@ def test_activation_rows_do_not_depend_on_their_batch(P, T, n_layers):
                 assert torch.equal(a[t], b[0]), (fn.__name__, t)
 
 
+@pytest.mark.parametrize("T", [1023, 1025, 2051, 43693])
+def test_rows_side_by_side_equal_rows_alone(P, T):
+    """Below 3072 (row, group) pairs a wave has one row, above four side by side and runs of 4, .. 32 of them."""
+    import torch
+    print(f"quantise rows side by side T={T}", flush=True)
+    li = pin.make_custom(6150, 8, 384, 16, n_outlier=3)
+    rot = _rot(P, li)
+    x = torch.randn((T, 384), generator=torch.Generator(device="cuda").manual_seed(T), device="cuda").half()
+    for fn in (P.paro_rotate_scale_quantize_int4, P.paro_rotate_scale_quantize_mxfp4):
+        whole = fn(rot, x)
+        for t0 in (0, T // 2, T - 7):                     # seven rows at a time are 21 pairs
+            for a, b in zip(whole, fn(rot, x[t0:t0 + 7])):
+                assert torch.equal(a[t0:t0 + 7], b), (fn.__name__, t0)
+    w = x[:T // 8 * 8]
+    whole = P.paro_mxfp4_quantize_weight(rot, w)
+    part = P.paro_mxfp4_quantize_weight(rot, w[8:64])
+    assert torch.equal(whole.codes[8:64], part.codes) and torch.equal(whole.scales[8:64], part.scales)
+
+
 @pytest.mark.parametrize("N", [8, 24, 32, 40, 264])
 def test_weight_rows(P, N):
     import torch
