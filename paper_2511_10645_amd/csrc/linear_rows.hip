@@ -11,7 +11,7 @@
 //     v_mfma_f32_16x16x32_f16 once the codes stand in fp16 registers as q - z (exact; 14 vector instructions per 8
 //     weights in the natural code order, 9 in the repacked one); the group's scale multiplies the fp32 sums;
 //   - activations straight into fragment registers: in operand order a fragment is one contiguous kilobyte, of row-major
-//     rows it is 16-byte pieces of 32 cache lines (4096 -> 6144 at 64 tokens 10.6 against 14.6 us), which matters less
+//     rows it is 16-byte pieces of 32 cache lines (about a third more time at 64 tokens), which matters less
 //     the fewer the tokens are;
 //   - registers are a ring of two groups: a register is refilled for the group after next right after its last use.
 // The loop is written as slots, one MFMA each, with a piece of the next tile's dequantisation, a piece of the previous
@@ -19,10 +19,12 @@
 // K is also split between blocks where the outputs alone are too few of them and the call has a scratch part.
 //
 // Bound by the weight stream and, at few groups per wave, by the chain load -> dequantise -> multiply -> sum; at more
-// tokens by what a compute unit takes in (every block reads all activations: 512 KB at 64 tokens of 4096 channels), hence
-// only where the outputs are few.  Before, interchange layout, 11008 -> 4096 at 24 tokens: 939 us, now 17.  Before, repacked
-// (linear_tile.hip, mostly with split K and its summing launch), 64 tokens: 4096 -> 4096 13.3 us, now 6.9; 4096 -> 6144 14.7,
-// now 9.5; 14336 -> 4096 20.6, now 19.1; 128 tokens: 16.5, now 9.8; 18.3, now 14.6; 27.8, now 27.0.
+// tokens by what a compute unit takes in (a block reads all channels of its 32 tokens, 256 KB at 4096), hence
+// only where the outputs are few and K is not long (14336 -> 4096 at 64 tokens: 27.0 against 24.5 us in linear_tile.hip).
+// Whole calls in a replayed graph over 350 MB of weights, us.  Interchange layout, 11008 -> 4096 at 24 tokens: rotated 943
+// before, now 20.6 (K over 4 blocks); bare, which has no workspace and is not split, 941, now 36.9.  Repacked, rotated
+// (before: row-major activations into linear_tile.hip, mostly with split K and its summing launch), 64 tokens: 4096 -> 4096
+// 16.8, now 10.7; 4096 -> 6144 18.6, now 14.1; 128 tokens: 19.7, now 14.9; 23.3, now 20.5.
 #include "paro_internal.h"
 #include <type_traits>
 
@@ -276,8 +278,8 @@ __global__ __launch_bounds__(kRowsWaves * 64, 2) void linear_rows_kernel(RowsArg
 }
 
 // Slices of K so that there is about one block per compute unit, each of whole rounds of the block's 4 waves and of at
-// least two groups per wave.  (11008 -> 4096, 64 blocks per slice, at 24 tokens: 1 / 2 / 4 / 8 slices 30 / 18 / 13 / 15 us
-// before the summing launch of about 2 us.)
+// least two groups per wave.  (11008 -> 4096, 64 blocks per slice, at 24 tokens, begin to end in a kernel trace: one slice
+// 36.3 us; the 4 taken 14.6 us, and 4.7 for the summing launch.)
 static void rows_split(int c_in, int c_out, int &k_split, int &groups_per_split)
 {
     const int G = c_in / kGroup, blocks = (c_out + 16 * kRowsTiles - 1) / (16 * kRowsTiles);
@@ -331,7 +333,7 @@ hipError_t launch_linear_rows(const paro_w4_weight &w, const paro_half_t *X, int
 // Outputs per block and K split from a cost model fitted to 4226 timings (140 shapes, 33 to 256 tokens, activations already in
 // operand order), 4 to 6 % off: per round of blocks over the chip a chain of steps (a group per wave each), the weight
 // stream, what further blocks of the same compute unit add, and for split K the summing launch and the partial tiles.
-// 32 outputs per block where they then fit one round (4096 -> 4096 at 64 tokens: 6.9 us, 64 outputs 9.4); 64 beyond it, for
+// 32 outputs per block where they then fit one round (4096 -> 4096 at 64 tokens, linear alone: 6.9 us, 64 outputs 9.4); 64 beyond it, for
 // every block reads all of its activations (4096 -> 28672: 33.4 against 40.3 us).
 struct OperandPlan { int nt, k_split, groups_per_split; double est_us; };
 static OperandPlan plan_operand(int c_in, int c_out, int T)
@@ -362,7 +364,18 @@ bool linear_operand_supported(const paro_w4_weight &w, int T)
     return T > 32 && T <= 256 && linear_tile_supported(w, false) && (size_t)T * w.c_in * 2 < (1ull << 31);
 }
 
-double linear_operand_estimate_us(const paro_w4_weight &w, int T) { return plan_operand(w.c_in, w.c_out, T).est_us; }
+// The time behind a rotation pass, where activations come from another compute unit's stores: the same model fitted to 3833
+// rotated calls (649 shapes), 5 % off.  (plan_operand's ranks its own choices, but is 4 to 9 % low there.)
+double linear_operand_estimate_us(const paro_w4_weight &w, int T)
+{
+    const OperandPlan p = plan_operand(w.c_in, w.c_out, T);
+    const long blocks = (long)((T + 31) / 32) * ((w.c_out + 16 * p.nt - 1) / (16 * p.nt)) * p.k_split;
+    const double rounds = (double)((blocks + 255) / 256), steps = (p.groups_per_split / kRowsWaves + 1) / 2 * 2;
+    const double more = blocks > 256 ? (double)blocks / 256.0 - 1.0 : 0.0, mb = (double)w.c_in * w.c_out / 2.0e6;
+    const double part_mb = p.k_split > 1 ? (double)p.k_split * T * w.c_out * 8.0 / 1.0e6 : 0.0;
+    if (p.nt == 2) return 2.76 + rounds * (0.297 + 0.454 * steps) + 0.463 * more + 0.07 * mb + (p.k_split > 1 ? 2.34 + 0.345 * part_mb : 0.0);
+    return 4.35 + 0.639 * rounds * steps + 1.09 * more + 0.076 * mb + (p.k_split > 1 ? 2.88 + 0.152 * part_mb : 0.0);
+}
 
 size_t linear_operand_scratch_bytes(const paro_w4_weight &w, int T)
 {

@@ -18,10 +18,11 @@
 // What bounds it: no single unit.  Taking out a part of the step (timing only, 1024 tokens, 1.38 us per step) gives
 // 1.01 without dequantisation, 1.15 without the scaling, 1.16 without LDS reads, 1.04 without staging: the parts add up, as
 // in the GEMM, because the chip's clock pays for every instruction.  That is 0.35 us per 64 x 64 x 128 of work against
-// the GEMM's 0.24 on full tiles, hence the line between the two (linear_tile_estimate_us).  Bare linear, us, before (the
-// cheaper of the other two) -> now: 64 tokens 4096 -> 28672 38.6 -> 28.2, 14336 -> 4096 27.7 -> 20.7; 128 tokens 4096 -> 6144
-// 23.1 -> 19.2, 4096 -> 4096 22.5 -> 17.1, 4096 -> 28672 50.4 -> 42.9; 201 tokens 4096 -> 6144 26.8 -> 21.1, 4096 -> 4096
-// 22.9 -> 18.6; interchange layout, 11008 -> 4096, 48 tokens 16 us.
+// the GEMM's 0.24 on full tiles, hence the line between the two (linear_tile_estimate_us).  Bare calls in a replayed graph
+// over 350 MB of weights, summing launch included, us, before (the cheaper of the other two) -> now: 64 tokens 4096 -> 28672
+// 37.8 -> 25.7, 14336 -> 4096 28.1 -> 20.9; 128 tokens 4096 -> 6144 22.9 -> 19.3, 4096 -> 4096 23.6 -> 16.9, 4096 -> 28672
+// 49.3 -> 43.6; 201 tokens 4096 -> 6144 27.5 -> 22.4, 4096 -> 4096 22.9 -> 18.1.  Interchange layout, 11008 -> 4096 at 48
+// tokens: rotated call 1874 -> 23.5 (K over 8 blocks); the bare call, which has no workspace and is not split, 1872 -> 52.3.
 #include "paro_internal.h"
 #include <type_traits>
 
@@ -66,8 +67,8 @@ constexpr int kTileThreads = 512, kTileBuf = 32768;
 
 // What the 16-byte chunk index of a row is XOR-ed with: the row, bit 3 flipped by bit 2.  A 16-byte LDS read serves lanes
 // 0-3, 12-15 and 20-27 together (then 4-11, 16-19 and 28-31): rows 0-3 and 12-15 of one quarter of the channels and rows
-// 4-11 of the next.  With the row itself the two sets of chunks coincide: 57 k conflict cycles per compute unit of 287 k at
-// 1024 x 14336 -> 4096, now 0.5 k; 1 to 3 % faster (LDS is not what bounds the kernel).
+// 4-11 of the next.  With the row itself the two sets of chunks coincide: 2.01 M conflict cycles over the chip at 64 tokens
+// 4096 -> 28672 (of 1.25 M instruction cycles of LDS), now 57 k; 1 to 4 % faster (LDS is not what bounds the kernel).
 __device__ inline int chunk_xor(int row) { return (row & 15) ^ ((row & 4) << 1); }
 
 template <int MW, int NW, int KW, bool IC>
@@ -284,7 +285,7 @@ static hipError_t launch_tile_cfg(TileArgs &a, hipStream_t s)
 // Which tile, and how many slices of K: the least of a cost model fitted to 4700 timings (58 shapes from 512 to 27648
 // channels and 512 to 55296 outputs, 33 to 2048 tokens; 7 % off in the mean): 1.6 us, per round of 256 blocks 3.5 us (first
 // requests, stores) and 0.96 us per step, 1.09 us where the blocks fill the chip, and for split K 1.7 us (the summing
-// launch), 0.23 us per slice and the partial tiles at 6.9 TB/s.
+// launch's share of a graph; begin to end in a trace it is 4), 0.23 us per slice and the partial tiles at 6.9 TB/s.
 struct TilePlan { bool two_m; int k_split, groups_per_split; double est_us; };
 static TilePlan plan_tile(int c_in, int c_out, int T)
 {

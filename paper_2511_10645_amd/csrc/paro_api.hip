@@ -208,7 +208,8 @@ LinearRoute linear_route(const paro_w4_weight &w, int64_t ldx, int64_t ldy, int 
     // The kernel between the two (linear_tile.hip) neither walks whole GEMM tiles nor re-reads the weights, but costs
     // most per product.  The models are 6 to 15 % off, hence 0.9: over 5131 measured bare (shape, tokens) pairs (649 shapes,
     // 33 to 1024 tokens, every route forced) the choice loses more than 3 % on three (4 % there) and takes 1.32x less
-    // time in the mean than the better of the other two, 1.34x being the best possible.  Above 1024 tokens it has no shape to itself.  Without room for its partial
+    // time in the mean than the better of the other two, 1.34x being the best possible (8192 -> 16384 at 640 tokens, not
+    // among them, loses 6 %: 201 us against the GEMM's 189).  Above 1024 tokens it has no shape to itself.  Without room for its partial
     // tiles it would run unsplit and as slow as the others.
     if (T > kStreamPassTokens && T <= 1024 && linear_tile_supported(w, false) && linear_tile_scratch_bytes(w, T) <= scratch_bytes) {
         const double tile_us = linear_tile_estimate_us(w, T);
@@ -420,15 +421,15 @@ paro_status paro_w4a16_linear(const paro_w4_weight *w, const paro_half_t *X, int
 }
 
 // Whether the rotation pass writes operand order and the kernel that reads it follows (linear_rows.hip): where its model says
-// so, which is 5 % off, by the margin of linear_route.  Of 3833 measured rotated (shape, tokens) pairs (649 shapes, 33 to 256
-// tokens, every route forced) it is taken on 2096, where it is 1.32x faster in the mean than the best other route and more
-// than 3 % slower (up to 7 %) on seven.
+// so, which is 5 % off.  Of 3833 measured rotated (shape, tokens) pairs (649 shapes, 33 to 256 tokens, every route forced) it
+// is taken on 2037, where it is 1.32x faster in the mean than the best other route and more than 3 % slower (up to 5.5 %)
+// on two; a margin of 0.95 would gain 0.3 % more and take long rows at 64 tokens (14336 -> 4096) that are 10 % slower.
 static bool operand_route(const paro_rotation *rot, const paro_w4_weight *w, int64_t ldy, int T, size_t scratch_bytes)
 {
     if (!rot->plan || !fast_weight(w) || !linear_operand_supported(*w, T)) return false;
     if (scratch_bytes < linear_operand_scratch_bytes(*w, T)) return false;
     const LinearRoute r = linear_route(*w, w->c_in, ldy, T, scratch_bytes);
-    return r.us > 0.0 && linear_operand_estimate_us(*w, T) < 0.9 * r.us;
+    return r.us > 0.0 && linear_operand_estimate_us(*w, T) < 0.92 * r.us;
 }
 
 static paro_status rotated_linear(const paro_rotation *rot, const paro_w4_weight *w, const paro_half_t *X, int64_t ldx,

@@ -28,7 +28,7 @@
 //   - MXFP4: the rotated values are read back in channel order, 8 per lane, so that a block's maximum is two steps within
 //     four lanes and the codes are four instructions of the FP4 converter (equal to the thresholds of the format on
 //     every tie and its neighbours over the whole range of exponents).
-// Measured in a replayed graph (before: one row of INT4 weights per wave, plan re-read for each; MXFP4 one row at a time, 14 instructions of
+// Measured over back-to-back calls (before: one row of INT4 weights per wave, plan re-read for each; MXFP4 one row at a time, 14 instructions of
 // thresholds per value): INT4 weight 28672 x 4096 395 -> 142 us (448 -> 140 repeated on one weight), MXFP4 activations
 // 2048 x 4096 21.0 -> 12.8, 2048 x 14336 55.8 -> 36.4 us, INT4 activations 25.4 -> 15.1 and 80.3 -> 40.3 us; 1 x 4096
 // MXFP4 3.0 -> 2.6, INT4 2.9 -> 2.8; the same bits throughout.

@@ -54,8 +54,9 @@ CASES = [
     (33, 512, 16, "packed"), (47, 512, 4112, "packed"), (64, 4096, 4096, "packed"), (64, 13824, 4096, "packed"), (65, 2560, 2064, "packed"), (97, 1536, 1040, "packed"),
     (176, 1024, 3088, "packed"), (255, 2048, 80, "packed"), (256, 512, 528, "packed"),
     # 128-token tiles: interchange layout and repacked, unsplit with a bias, and (behind a rotation, bare) with K split;
-    # the last two behind a rotation: operand order with 64 outputs per block and K unsplit, split
+    # the last behind a rotation: operand order with 64 outputs per block and K split
     (65, 640, 16400, "plain"), (66, 2560, 6160, "plain"), (67, 512, 16400, "packed"), (66, 14336, 4112, "packed"), (64, 14336, 2064, "packed"),
+    (127, 8704, 1040, "packed"),
 ]
 
 
