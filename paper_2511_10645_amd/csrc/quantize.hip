@@ -15,23 +15,24 @@
 //                NaN throughout has e = 126 and codes +-6: what is multiplied with it overflows.
 // so that  sum_c (q - z) s . x'_c  ~  w_n . x  for the activations x' that paro_rotate_scale produces (Eq. 2).
 //
-// One wavefront owns a channel group and a run of rows, four rows at a time (few rows: one each, kQuantFewRows), with the lane plan and layer loop of the
-// activation kernel (rotate_lane.h): the plan (7.4 KB at K = 8, 29 times a row's group) is read once per run, the four
-// rows' chains of multiply-adds and permutes are independent, and rows go through a wave-private LDS area as
-// [channel][4 rows].  What bounds it is the vector pipes: 38 instructions per (row, group) of rotation, and the rest was
-// made small against that -
+// One wavefront owns a channel group and a run of rows, four rows at a time (few rows: one each, kQuantFewRows), with the
+// lane plan and layer loop of the activation kernel (rotate_lane.h): the plan (7.4 KB at K = 8, 29 times a row's group) is
+// read once per run, the four rows' chains of multiply-adds and permutes are independent, and rows go through a
+// wave-private LDS area as [channel][4 rows].  What bounds it is the vector pipes (INT4 weights, counted: 101 instructions
+// per (row, group), at four cycles each the whole launch; LDS with its conflicts under half of it): 38 of rotation, and
+// the rest was made small against that -
 //   - INT4: minimum and maximum of the four rows are reduced together, each swap of half waves merging two rows, so that
 //     every 16 lanes end up with one row's and the scale, its reciprocal and the zero point are computed once for all
 //     four; v / s is the correctly rounded quotient from the correctly rounded reciprocal and one residual (Markstein's
 //     theorem), which holds for finite v and s: rows with an infinite scale, and rows of infinities (whose range is NaN
 //     and whose scale is the floor), divide;
 //   - MXFP4: the rotated values are read back in channel order, 8 per lane, so that a block's maximum is two steps within
-//     four lanes and the codes are four instructions of the FP4 converter (equal to the thresholds of the format on
-//     every tie and its neighbours over the whole range of exponents).
-// Measured over back-to-back calls (before: one row of INT4 weights per wave, plan re-read for each; MXFP4 one row at a time, 14 instructions of
-// thresholds per value): INT4 weight 28672 x 4096 395 -> 142 us (448 -> 140 repeated on one weight), MXFP4 activations
-// 2048 x 4096 21.0 -> 12.8, 2048 x 14336 55.8 -> 36.4 us, INT4 activations 25.4 -> 15.1 and 80.3 -> 40.3 us; 1 x 4096
-// MXFP4 3.0 -> 2.6, INT4 2.9 -> 2.8; the same bits throughout.
+//     four lanes and the codes are four instructions of the FP4 converter (equal to the thresholds of the format on every
+//     tie and its neighbours, probed over all exponents; the tests pin those that fp16 inputs and scales reach).
+// Measured over back-to-back calls (before: one row of INT4 weights per wave, plan re-read for each; MXFP4 one row at a
+// time, 14 instructions of thresholds per value): INT4 weight 28672 x 4096 414 -> 146 us, MXFP4 activations 2048 x 4096
+// 21.0 -> 12.8, 2048 x 14336 55.8 -> 36.4 us, INT4 activations 24.7 -> 14.8 and 78.3 -> 39.6 us; 1 x 4096 MXFP4
+// 3.0 -> 2.6, INT4 2.9 -> 2.8; the same bits throughout.
 #include "paro_internal.h"
 #include "rotate_lane.h"
 #include <type_traits>
@@ -158,7 +159,8 @@ __global__ __launch_bounds__(kQuantWaves * 64) void quantize_kernel(QuantArgs a)
             for (int u = 0; u < U; ++u) nxt[u] = load_row(t + U + u);
         float va[U], vb[U];
         if constexpr (K >= 0 && U == 1) {
-            *(uint32_t *)(sp + lane * 4) = cur[0];
+            typedef uint32_t __attribute__((may_alias)) u32_halves;
+            *(u32_halves *)(sp + lane * 4) = cur[0];
             __builtin_amdgcn_wave_barrier();
             va[0] = (float)*(const _Float16 *)(sp + P.in_a * 2) * ia;
             vb[0] = (float)*(const _Float16 *)(sp + P.in_b * 2) * ib;
