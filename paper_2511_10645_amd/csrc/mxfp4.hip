@@ -15,11 +15,12 @@
 // a tile is one contiguous kilobyte.  Activations stay in the plain row order their quantiser writes:
 // a lane's 32 elements are 16 contiguous bytes of its token's row.
 //
-// Two kernels.  Up to 16 tokens: HBM-bound stream of the weight tiles (0.53 B per weight), one
+// Two kernels.  Up to 64 tokens per pass: HBM-bound stream of the weight tiles (0.53 B per weight), one
 // 512-channel slice per wave and pass, all slices of K inside one block (a wave takes SPW slices when
 // there are more than 12), partial tiles summed through LDS; no exchange between blocks.  More tokens:
-// a tiled GEMM whose operands go through LDS (see below).
+// a tiled GEMM (see below).
 #include "paro_internal.h"
+#include <algorithm>
 #include <type_traits>
 
 namespace paro {
@@ -42,6 +43,16 @@ __device__ __forceinline__ void mx_static_while(F &&f)
         if (f(std::integral_constant<int, I>{})) mx_static_while<N, F, I + 1>(static_cast<F &&>(f));
     }
 }
+template <int N, class F, int I = 0>
+__device__ __forceinline__ void mx_for(F &&f)
+{
+    if constexpr (I < N) {
+        f(std::integral_constant<int, I>{});
+        mx_for<N, F, I + 1>(static_cast<F &&>(f));
+    }
+}
+// until at most N vector-memory requests of this wave are outstanding (LDS and scalar counts unrestricted)
+template <int N> __device__ __forceinline__ void mx_wait_vm() { __builtin_amdgcn_s_waitcnt(0x0f70 | (N & 15) | ((N >> 4) << 14)); }
 
 // ------------------------------------------------------------------------------------------
 // Layout: plain [N][C/8] words + [N][C/32] bytes  <->  blob = tiles | scale dwords
@@ -120,7 +131,7 @@ hipError_t launch_mxfp4_unpack(const paro_mxfp4_weight &w, uint8_t *codes, uint8
 }
 
 // ------------------------------------------------------------------------------------------
-// Up to 16 tokens
+// Up to 64 tokens per pass
 // ------------------------------------------------------------------------------------------
 struct MxArgs {
     const void *blob; uint32_t blob_bytes, scales_off;
@@ -306,19 +317,29 @@ static hipError_t launch_mxfp4_decode(const paro_mxfp4_weight &w, const uint32_t
 }
 
 // ------------------------------------------------------------------------------------------
-// More than 16 tokens: tiled GEMM.  Block tile 256 (or 128, see the launcher) tokens x 256 outputs x 128 channels (one K-step of
-// the matrix instruction: 64 bytes per row of either operand), 8 waves side by side along the outputs:
-// wave tile 256 tokens x 32 outputs = 16 x 2 MFMA tiles of 16 x 16 (128 accumulator registers).
-//   - Weights never touch LDS: the repacked blob IS the operand order, every 16-row tile of a K-step
-//     is needed by exactly one wave, which fetches it straight into registers, 3 K-steps ahead.
-//   - Activations (16 KB of codes + 1 KB of scale bytes per K-step) are shared by all 8 waves: fetched
-//     into registers five K-steps ahead (2 x 16 B + 4 B per thread and stage), written two K-steps ahead
-//     into a ring of three LDS tiles; one barrier per K-step.  LDS rows are 64
-//     bytes; the 16-byte chunk index is XOR-ed with bits 1..2 of the row so that the 16-byte fragment
-//     reads of 8 consecutive rows fall into 8 different bank groups.
-// What bounds the loop is the data in flight per compute unit (measured: with a single K-step in
-// flight a K-step takes 3 us, 7 x the time of its 32 MFMAs per wave), hence the deep register queues.
-// Blocks are numbered in XCD patches as in the fp16 GEMM.
+// More tokens: tiled GEMM on v_mfma_scale_f32_32x32x64_f8f6f4 (lane l of an operand: row l % 32, elements 32 (l / 32) .. + 31 of
+// the 64-wide step, one scale byte; D: lane = column l % 32, rows 8 (r / 4) + 4 (l / 32) + r % 4).  The weight is the A operand
+// and the activations are the B operand, so that a lane's sums are consecutive outputs of one token.
+//
+// A block is 4 waves side by side along the outputs and owns 128 tokens x 128 NTW outputs; two blocks share a compute unit, so
+// that one multiplies while the other waits at a barrier, fills its pipeline or stores its tile.
+//   - Weights never touch LDS: every weight of a tile is needed by exactly one wave, which fetches it from the repacked blob
+//     (contiguous 512-byte runs) into a register ring of three K-steps (128 channels each).
+//   - Activations go from memory to LDS without passing through registers, 256 channels (whole 128-byte lines) of 8 rows per
+//     wave request, into a ring of four such steps: one barrier and one wait per 256 channels, for requests made 768 channels
+//     earlier.  The 16-byte chunk index of a row is XOR-ed with bits 1..3 of the row: a 16-byte read serves lanes 0-3, 12-15 and
+//     20-27 together (then 4-11, 16-19 and 28-31), which are then 16 bank groups, and every four lanes of a request still ask for
+//     64 consecutive bytes (in the order [chunk][row], conflict-free as well, each lane is a request of its own).
+//   - Scale bytes: the weight's as one dword per lane and 512 channels from the blob; the activations' through LDS as
+//     [K-step][row] dwords, two slices of 512 channels deep.
+//   - Outputs leave past the L2 (non-temporal): a round's tiles finish together, and their 33 MB would push the operands out of
+//     the L2s (4096 tokens 5120 -> 55296: 636 us with plain stores, 581).
+// What bounds it (counters, 4096 tokens 5120 -> 55296): the chip's power - 1.6 GHz with the matrix cores busy 55 % of the cycles -
+// and the operand traffic out of L2 (9 GB; with all-zero operands, which cost no switching, 431 us).
+// Measured, us, before (256 x 256 tiles of 8 waves, activations through registers, 16x16x128 instruction, one block per
+// compute unit) -> now: 2048 tokens 4096 -> 6144 42.3 -> 36.0, 4096 -> 4096 26.9 -> 21.1, 4096 -> 28672 168.7 -> 143.1 (3.4
+// PFLOP/s), 14336 -> 4096 74.6 -> 65.9; 4096 tokens 5120 -> 55296 698 -> 579 (4.0); 256 tokens 14336 -> 4096 53.8 -> 27.9; the
+// 152 shapes of the fit below: 0.76 of the time in the geometric mean.
 // ------------------------------------------------------------------------------------------
 struct MxGemmArgs {
     const void *blob; uint32_t blob_bytes, scales_off;
@@ -326,23 +347,24 @@ struct MxGemmArgs {
     _Float16 *Y; int64_t ldy;
     const _Float16 *bias;
     int T, C, N, K128, KS;
-    int m_tiles, n_tiles, n_tile0, patch_m, patch_n;     // the launch covers output tiles [n_tile0, n_tile0 + n_tiles)
+    int m_tiles, n_tiles, patch_m, patch_n;
 };
 
-constexpr int kMxBM = 256, kMxBN = 256;
-constexpr int kMxRowBytes = 64;                          // one K-step of one row
-constexpr int mx_stage_bytes(int bm) { return bm * kMxRowBytes + bm * 4; }   // codes | scale dwords (4 blocks per row)
-constexpr int kMxChunk = 12;                             // K-steps written out in the loop body (24: no faster)
+typedef float float16v __attribute__((ext_vector_type(16)));
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+typedef __attribute__((address_space(3))) void mx_lds;
 
-__device__ __forceinline__ int mx_lds_off(int row, int chunk) { return row * kMxRowBytes + ((chunk ^ ((row >> 1) & 3)) << 4); }
+constexpr int kMxBM = 128;                               // tokens per block
+constexpr int kMxRing = 4, kMxPair = kMxBM * 128;        // activation ring: bytes of 256 channels of all rows
+constexpr int kMxScaleSlice = 4 * kMxBM * 4;             // [K-step][row] scale dwords of 512 channels
+constexpr int kMxGemmLds = kMxRing * kMxPair + 2 * kMxScaleSlice;
+constexpr int kMxChunk = 12;                             // K-steps written out in the loop body: three periods of 4, four of 3
 
-// BM: tokens per block tile, 256, or 128 where 256-token tiles would leave half of the compute units idle
-template <int BM>
-__global__ __launch_bounds__(512) void mxfp4_gemm_kernel(MxGemmArgs a)
+template <int NTW>
+__global__ __launch_bounds__(256, 2) void mxfp4_gemm_kernel(MxGemmArgs a)
 {
-    extern __shared__ __attribute__((aligned(16))) char smem_mx[];          // [3][kStage]
-    constexpr int kStage = mx_stage_bytes(BM);
-    constexpr int MI = BM / 16;                                             // 16-row MFMA tiles of a wave
+    extern __shared__ __attribute__((aligned(16))) char smem_mx[];
+    constexpr int BN = 128 * NTW, MT = kMxBM / 32, XR = 4;   // XR: activation requests of a wave per 256 channels
     const int bid = blockIdx.x;
     const int xcd = bid & 7, j = bid >> 3;
     const int pb = a.patch_m * a.patch_n;
@@ -350,202 +372,232 @@ __global__ __launch_bounds__(512) void mxfp4_gemm_kernel(MxGemmArgs a)
     const int m_patches = (a.m_tiles + a.patch_m - 1) / a.patch_m;
     const int gp = patch * 8 + xcd;
     const int pm = gp % m_patches, pn = gp / m_patches;
-    const int mt = pm * a.patch_m + q % a.patch_m, ntile = pn * a.patch_n + q / a.patch_m;
-    if (mt >= a.m_tiles || ntile >= a.n_tiles) return;
-    const int m0 = mt * BM, n0 = (a.n_tile0 + ntile) * kMxBN;
+    const int mt0 = pm * a.patch_m + q % a.patch_m, ntile = pn * a.patch_n + q / a.patch_m;
+    if (mt0 >= a.m_tiles || ntile >= a.n_tiles) return;
+    const int m0 = mt0 * kMxBM;
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int lr = lane & 31, lh = lane >> 5;
+    const int n0 = ntile * BN + wave * 32 * NTW;             // the wave's outputs
     const __amdgpu_buffer_rsrc_t xr = mx_rsrc(a.xc, (uint32_t)((size_t)a.T * a.C / 2));
     const __amdgpu_buffer_rsrc_t sr = mx_rsrc(a.xs, (uint32_t)((size_t)a.T * a.C / 32));
     const __amdgpu_buffer_rsrc_t br = mx_rsrc(a.blob, a.blob_bytes);
-    const int n_ks = a.K128;
+    const int n_ks = a.K128, n_pairs = n_ks / 2;
 
-    // ---- activations: thread -> chunks (row tid / 4 [+ 128], chunk tid % 4); threads 0..255 also the scale
-    // dword of row tid.  Rows beyond T start beyond the end of their buffers: they read as zero. ----
-    const uint32_t ga = (uint32_t)((size_t)(m0 + (tid >> 2)) * (a.C / 2) + (tid & 3) * 16);
-    const uint32_t ga_step = (uint32_t)(128 * (a.C / 2));
-    const int la0 = mx_lds_off(tid >> 2, tid & 3), la1 = mx_lds_off((tid >> 2) + 128, tid & 3);
-    const uint32_t gs = tid < BM ? (uint32_t)((size_t)(m0 + tid) * (a.C / 32)) : kOobM;
-    const int ls = BM * kMxRowBytes + (tid & (BM - 1)) * 4;
-    struct AStage { u32x4 c0, c1; uint32_t sc; };
-    auto load_a = [&](int ks, AStage &st) {
-        const bool ok = ks < n_ks;
-        st.c0 = __builtin_amdgcn_raw_buffer_load_b128(xr, ok ? (int)ga : (int)kOobM, ks * kMxRowBytes, 0);
-        if constexpr (BM == 256) st.c1 = __builtin_amdgcn_raw_buffer_load_b128(xr, ok ? (int)(ga + ga_step) : (int)kOobM, ks * kMxRowBytes, 0);
-        st.sc = __builtin_amdgcn_raw_buffer_load_b32(sr, ok ? (int)gs : (int)kOobM, ks * 4, 0);
-    };
-    auto store_a = [&](char *buf, const AStage &st) {
-        *(u32x4 *)(buf + la0) = st.c0;
-        if constexpr (BM == 256) *(u32x4 *)(buf + la1) = st.c1;
-        if (tid < BM) *(uint32_t *)(buf + ls) = st.sc;
-    };
-    // ---- weights: the wave's two 16-row tiles, as they lie in the blob ----
-    const int nt16 = n0 / 16 + wave * 2;
-    const bool n_ok0 = nt16 * 16 < a.N, n_ok1 = (nt16 + 1) * 16 < a.N;
-    const uint32_t gb0 = ((uint32_t)nt16 * a.K128 * 64u + lane) * 16u;
-    const uint32_t gb_step = (uint32_t)a.K128 * 1024u;
-    const uint32_t gw0 = a.scales_off + ((uint32_t)nt16 * a.KS * 64u + lane) * 4u;
-    const uint32_t gw_step = (uint32_t)a.KS * 256u;
-    struct BStage { u32x4 t0, t1; };
-    auto load_b = [&](int ks, BStage &st) {
-        const bool ok = ks < n_ks;
-        st.t0 = __builtin_amdgcn_raw_buffer_load_b128(br, ok && n_ok0 ? (int)gb0 : (int)kOobM, ks * 1024, 0);
-        st.t1 = __builtin_amdgcn_raw_buffer_load_b128(br, ok && n_ok1 ? (int)(gb0 + gb_step) : (int)kOobM, ks * 1024, 0);
-    };
-    uint32_t wq0 = 0, wq1 = 0, wq0_n, wq1_n;                 // scale dwords of the current / the next 512-channel slice
-    auto load_wscales = [&](int slice, uint32_t &d0, uint32_t &d1) {
-        const bool ok = slice < a.KS;
-        d0 = __builtin_amdgcn_raw_buffer_load_b32(br, ok && n_ok0 ? (int)gw0 : (int)kOobM, slice * 256, 0);
-        d1 = __builtin_amdgcn_raw_buffer_load_b32(br, ok && n_ok1 ? (int)(gw0 + gw_step) : (int)kOobM, slice * 256, 0);
-    };
-
-    float4v acc[MI][2];
+    // ---- activations: wave w, request i: rows 8 (XR w + i) .. + 7.  Rows beyond T read row T - 1 (their sums are not stored) ----
+    uint32_t gx[XR];
 #pragma unroll
-    for (int i = 0; i < MI; ++i) { acc[i][0] = float4v{0.f, 0.f, 0.f, 0.f}; acc[i][1] = float4v{0.f, 0.f, 0.f, 0.f}; }
+    for (int i = 0; i < XR; ++i) {
+        const int row = min(m0 + (wave * XR + i) * 8 + (lane >> 3), a.T - 1);
+        gx[i] = (uint32_t)((size_t)row * (a.C / 2)) + (((lane & 7) ^ (lane >> 4) ^ (4 * (i & 1))) << 4);
+    }
+    auto load_x = [&](int pair) {
+        const bool ok = pair < n_pairs;                      // beyond the row's end: out of range, nothing is fetched
+        char *dst = smem_mx + (pair & (kMxRing - 1)) * kMxPair + wave * (XR * 1024);
+#pragma unroll
+        for (int i = 0; i < XR; ++i)
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(xr, (mx_lds *)(dst + i * 1024), 16, (int)(ok ? gx[i] : kOobM), pair * 128, 0, 0);
+    };
+    // scale bytes: thread -> row tid / 2, K-steps 2 (tid % 2), + 1 of the slice
+    const uint32_t gs = (uint32_t)((size_t)min(m0 + (tid >> 1), a.T - 1) * (a.C / 32)) + (tid & 1) * 8;
+    char *const scales = smem_mx + kMxRing * kMxPair;
+    u32x2 xs_next;
+    auto load_xs = [&](int slice) { xs_next = __builtin_amdgcn_raw_buffer_load_b64(sr, (int)(slice < a.KS ? gs : kOobM), slice * 16, 0); };
+    auto store_xs = [&](int slice) {
+        char *dst = scales + (slice & 1) * kMxScaleSlice + (tid & 1) * (8 * kMxBM) + (tid >> 1) * 4;
+        *(uint32_t *)dst = xs_next[0];
+        *(uint32_t *)(dst + 4 * kMxBM) = xs_next[1];
+    };
+    // ---- weights: n-tile nt of the wave = two 16-row tiles of the blob; lane: row lr, 32-channel block 2 h + lh ----
+    uint32_t gb[NTW], gw[NTW];
+#pragma unroll
+    for (int nt = 0; nt < NTW; ++nt) {
+        const int n = n0 + nt * 32 + lr;
+        const uint32_t t16 = (uint32_t)(n >> 4), slot = (uint32_t)(lh * 16 + (lr & 15));
+        gb[nt] = n < a.N ? (t16 * (uint32_t)a.K128 * 64u + slot) * 16u : kOobM;
+        gw[nt] = n < a.N ? a.scales_off + (t16 * (uint32_t)a.KS * 64u + slot) * 4u : kOobM;
+    }
+    u32x4 wb[3][NTW][2];
+    auto load_w = [&](int ks, auto R, auto NT, auto H) {
+        wb[R][NT][H] = __builtin_amdgcn_raw_buffer_load_b128(br, (int)(ks < n_ks ? gb[NT] + H * 512 : kOobM), ks * 1024, 0);
+    };
+    uint32_t wsc[3][NTW][2];                                 // scale dwords: ring of three slices (a copy would wait for the load)
+    auto load_ws = [&](int slice, auto R) {
+#pragma unroll
+        for (int nt = 0; nt < NTW; ++nt)
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+                wsc[R][nt][h] = __builtin_amdgcn_raw_buffer_load_b32(br, (int)(slice < a.KS ? gw[nt] + h * 128 : kOobM), slice * 256, 0);
+    };
+
+    float16v acc[NTW][MT];
+#pragma unroll
+    for (int nt = 0; nt < NTW; ++nt)
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[nt][mt][r] = 0.f;
+
+    // fragment of token tile mt, 64-channel step kh = 2 kp + h of a pair: chunk 2 kh + lh of the row
+    int fx[4];
+#pragma unroll
+    for (int kh = 0; kh < 4; ++kh) fx[kh] = lr * 128 + (((2 * kh + lh) ^ ((lr >> 1) & 7)) << 4);
+    constexpr int kAhead = 3, kRegs = kAhead + 1;            // fragments are requested this many token tiles ahead
+    u32x4 xf[kRegs];
+    uint32_t xsd[MT];
+    auto read_x = [&](const char *pair, auto Q) {            // Q: (kp * 2 + h) * MT + mt within the pair
+        constexpr int q = Q, mt = q % MT, kh = q / MT;
+        xf[q % kRegs] = *(const u32x4 *)(pair + mt * 4096 + fx[kh]);
+    };
+    const int fs = lr * 4;
+    const uint32_t s_shift = 8 * lh;
 
     // ---- prologue ----
-    // LDS holds three K-steps of activations: step k is multiplied from buffer k % 3 while step k + 2 is written
-    // into buffer (k + 2) % 3 (last read during step k - 1, i.e. before the previous barrier), so the first
-    // fragments of step k + 1 (written during step k - 1) can be requested BEFORE the barrier that ends step k and
-    // the matrix pipe does not wait for an LDS round trip after every barrier.
-    // Register queues are rings indexed by the K-step (A: 3 deep, holding steps k + 2 .. k + 4; B: 3 deep,
-    // k .. k + 2); a ring must be indexed at compile time and a value still in flight must never be copied (a copy
-    // waits for it), hence the loop body is written out for kMxChunk consecutive K-steps (a multiple of the
-    // rings' periods and of the 4 K-steps of a scale dword) with one early exit.
-    AStage ar[3];
-    BStage bq[3];
-    load_a(0, ar[0]);
-    load_a(1, ar[1]);
-    load_b(0, bq[0]);
-    load_wscales(0, wq0, wq1);
-    load_wscales(1, wq0_n, wq1_n);
-    store_a(smem_mx, ar[0]);
-    store_a(smem_mx + kStage, ar[1]);
-    load_a(2, ar[2]);
-    load_a(3, ar[0]);
-    load_a(4, ar[1]);
-    load_b(1, bq[1]);
-    load_b(2, bq[2]);
-    __syncthreads();
-
-    const int fr = lane & 15, fkb = lane >> 4;
-    const int fa_off = mx_lds_off(fr, fkb);                                          // + 1024 per MFMA tile (16 rows)
-    const int fs_off = BM * kMxRowBytes + fr * 4 + fkb;                           // + 64 per MFMA tile
-    // fragments are requested kFragAhead tiles before their MFMAs (an LDS read takes several times as long as the
-    // two MFMAs of a tile), across the end of a K-step as well
-    constexpr int kFragAhead = 3;
-    u32x4 fa[kFragAhead + 1];
-    uint32_t xsb[kFragAhead + 1];
-#pragma unroll
-    for (int i = 0; i < kFragAhead; ++i) {
-        fa[i] = *(const u32x4 *)(smem_mx + fa_off + i * 1024);
-        xsb[i] = *(const uint8_t *)(smem_mx + fs_off + i * 64);
-    }
+    using I0 = std::integral_constant<int, 0>; using I1 = std::integral_constant<int, 1>; using I2 = std::integral_constant<int, 2>;
+    load_xs(0);
+    load_ws(0, I0{});
+    load_x(0);
+    mx_for<NTW>([&](auto NT) { load_w(0, I0{}, NT, I0{}); load_w(0, I0{}, NT, I1{}); });
+    load_x(1);
+    mx_for<NTW>([&](auto NT) { load_w(1, I1{}, NT, I0{}); load_w(1, I1{}, NT, I1{}); });
+    load_x(2);
+    mx_for<NTW>([&](auto NT) { load_w(2, I2{}, NT, I0{}); load_w(2, I2{}, NT, I1{}); });
+    store_xs(0);
+    load_xs(1);
+    load_ws(1, I1{});
+    // activations of pair 0 are in LDS when at most the requests made after them are outstanding
+    mx_wait_vm<8 * NTW>();
+    __builtin_amdgcn_s_waitcnt(0xc07f);                      // LDS writes done
+    __builtin_amdgcn_s_barrier();
+    mx_for<kAhead>([&](auto Q) { read_x(smem_mx, Q); });
+    mx_for<MT>([&](auto M) { xsd[M] = *(const uint32_t *)(scales + fs + M * 128); });
 
     for (int ks0 = 0; ks0 < n_ks; ks0 += kMxChunk) {
-        mx_static_while<kMxChunk>([&](auto I) {
-            constexpr int u = I;
-            const int ks = ks0 + u;
-            if (ks >= n_ks) return false;
-            const char *cur = smem_mx + (u % 3) * kStage;
-            const char *nxt = smem_mx + ((u + 1) % 3) * kStage;
-            char *fill = smem_mx + ((u + 2) % 3) * kStage;
-            AStage &an = ar[(u + 2) % 3];                                           // holds K-step ks + 2
-            BStage &bc = bq[u % 3];
-            const uint32_t ws0 = wq0 >> (8 * (u & 3)), ws1 = wq1 >> (8 * (u & 3));
-#pragma unroll
-            for (int i = 0; i < MI; ++i) {
-                constexpr int kRing = kFragAhead + 1;
-                const int ip = i + kFragAhead;
-                if (ip < MI) {
-                    fa[ip % kRing] = *(const u32x4 *)(cur + fa_off + ip * 1024);
-                    xsb[ip % kRing] = *(const uint8_t *)(cur + fs_off + ip * 64);
-                } else {
-                    fa[ip % kRing] = *(const u32x4 *)(nxt + fa_off + (ip - MI) * 1024);
-                    xsb[ip % kRing] = *(const uint8_t *)(nxt + fs_off + (ip - MI) * 64);
-                }
-                if (i == MI / 4) {                                                  // requested three K-steps ago
-                    store_a(fill, an);
-                    load_a(ks + 5, an);
-                }
-                const u32x4 fa_cur = fa[i % kRing];
-                const uint32_t xs_cur = xsb[i % kRing];
-                acc[i][0] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(as_operand(fa_cur), as_operand(bc.t0), acc[i][0], 4, 4, 0, (int)xs_cur, 0, (int)ws0);
-                acc[i][1] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(as_operand(fa_cur), as_operand(bc.t1), acc[i][1], 4, 4, 0, (int)xs_cur, 0, (int)ws1);
-                __builtin_amdgcn_sched_barrier(0);                                  // keep the reads this far ahead of their use
-            }
-            load_b(ks + 3, bc);
-            if constexpr ((u & 3) == 3) {
-                wq0 = wq0_n; wq1 = wq1_n;                                          // requested 4 K-steps ago
-                load_wscales((ks >> 2) + 2, wq0_n, wq1_n);
-            }
-            __syncthreads();
+        mx_static_while<kMxChunk / 4>([&](auto S) {
+            const int slice = (ks0 >> 2) + S;
+            if (slice >= a.KS) return false;
+            mx_for<4>([&](auto U) {
+                constexpr int u = U, kp = u & 1, r3 = (S * 4 + u) % 3;
+                const int ks = slice * 4 + u, pair = ks >> 1;
+                const char *cur = smem_mx + (pair & (kMxRing - 1)) * kMxPair;
+                const char *nxt = smem_mx + ((pair + 1) & (kMxRing - 1)) * kMxPair;
+                const char *snx = scales + ((u == 3 ? slice + 1 : slice) & 1) * kMxScaleSlice + ((u + 1) & 3) * 512 + fs;
+                using R3 = std::integral_constant<int, r3>;
+                mx_for<2 * MT>([&](auto Q) {
+                    constexpr int q = Q, h = q / MT, mt = q % MT, qa = kp * 2 * MT + q;   // position within the pair
+                    if constexpr (kp == 1 && q == 2 * MT - kAhead) {
+                        // every wave's part of the next pair has arrived (requested two pairs ago, older than the weights
+                        // of this K-step) and every wave has read the previous pair for the last time
+                        mx_wait_vm<8 * NTW>();
+                        __builtin_amdgcn_s_waitcnt(0xc07f);
+                        __builtin_amdgcn_s_barrier();
+                        load_x(pair + 3);
+                    }
+                    if constexpr (qa + kAhead < 4 * MT) read_x(cur, std::integral_constant<int, qa + kAhead>{});
+                    else read_x(nxt, std::integral_constant<int, qa + kAhead - 4 * MT>{});
+                    if constexpr (h == 0) xsd[mt] >>= s_shift;
+                    mx_for<NTW>([&](auto NT) {
+                        acc[NT][mt] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(as_operand(wb[R3{}][NT][h]), as_operand(xf[qa % kRegs]), acc[NT][mt], 4, 4,
+                                                                                       u, (int)wsc[S][NT][h], 2 * h, (int)xsd[mt]);
+                    });
+                    if constexpr (h == 1) xsd[mt] = *(const uint32_t *)(snx + mt * 128);
+                    if constexpr (h == 1 && mt == 0) mx_for<NTW>([&](auto NT) { load_w(ks + 3, R3{}, NT, I0{}); });
+                    if constexpr (h == 1 && mt == MT - 1) mx_for<NTW>([&](auto NT) { load_w(ks + 3, R3{}, NT, I1{}); });
+                    if constexpr (u == 0 && q == 1) { store_xs(slice + 1); load_xs(slice + 2); load_ws(slice + 2, std::integral_constant<int, (S + 2) % 3>{}); }   // the slice before: last read before the latest barrier
+                    __builtin_amdgcn_sched_barrier(0);
+                });
+            });
             return true;
         });
     }
 
-    // ---- epilogue.  Lane holds column fr, tokens 4 fkb + r of every 16 x 16 tile; a 16 x 32 strip of the wave's
-    // tile goes through a wave-private 1 KB of LDS (the K loop's buffers are free now) and leaves as one 16-byte
-    // store per lane: 64 contiguous bytes per token row instead of 2-byte stores. ----
-    __syncthreads();
-    _Float16 *strip = (_Float16 *)(smem_mx + wave * 1024);                          // [16 tokens][32 outputs]
+    // ---- epilogue.  A wave's 32 tokens x 32 NTW outputs at a time go through a wave-private strip of LDS (the ring is free once
+    // every wave is here and no request is outstanding) and leave as 16 bytes per lane, whole rows of the strip. ----
+    __builtin_amdgcn_s_waitcnt(0x0070);
+    __builtin_amdgcn_s_barrier();
+    constexpr int kStrip = 64 * NTW + 16;                                            // bytes of a strip's row
+    char *strip = smem_mx + wave * 32 * kStrip;
     const __amdgpu_buffer_rsrc_t yr = mx_rsrc(a.Y, (uint32_t)(((size_t)(a.T - 1) * a.ldy + a.N) * 2));
-    const int nw0 = n0 + wave * 32;
-    float bv[2];
+    const bool row_wide = a.ldy % 8 == 0 && ((uintptr_t)a.Y % 16) == 0 && n0 + 32 * NTW <= a.N;
+    if (a.bias) {
+        const __amdgpu_buffer_rsrc_t bias = mx_rsrc(a.bias, (uint32_t)a.N * 2);      // outputs beyond N read as zero
 #pragma unroll
-    for (int jn = 0; jn < 2; ++jn) {
-        const int n = nw0 + jn * 16 + fr;
-        bv[jn] = (a.bias && n < a.N) ? (float)a.bias[n] : 0.f;
+        for (int nt = 0; nt < NTW; ++nt)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                union { uint16_t u; _Float16 h; } b;
+                b.u = (uint16_t)__builtin_amdgcn_raw_buffer_load_b16(bias, (n0 + nt * 32 + (r >> 2) * 8 + lh * 4 + (r & 3)) * 2, 0, 0);
+#pragma unroll
+                for (int mt = 0; mt < MT; ++mt) acc[nt][mt][r] += (float)b.h;
+            }
     }
-    const int orow = lane >> 2, ocol = (lane & 3) * 8;                               // this lane's 8 outputs of the strip
-    const bool row_wide = a.ldy % 8 == 0 && ((uintptr_t)a.Y % 16) == 0 && nw0 + 32 <= a.N;
 #pragma unroll
-    for (int i = 0; i < MI; ++i) {
+    for (int mt = 0; mt < MT; ++mt) {
 #pragma unroll
-        for (int jn = 0; jn < 2; ++jn)
+        for (int nt = 0; nt < NTW; ++nt)
 #pragma unroll
-            for (int r = 0; r < 4; ++r) strip[(fkb * 4 + r) * 32 + jn * 16 + fr] = (_Float16)(acc[i][jn][r] + bv[jn]);
+            for (int g = 0; g < 4; ++g) {
+                const int o = nt * 32 + g * 8 + lh * 4;                              // 4 consecutive outputs
+                union { _Float16 h[4]; u32x2 u; } v;
+#pragma unroll
+                for (int r = 0; r < 4; ++r) v.h[r] = (_Float16)acc[nt][mt][g * 4 + r];
+                *(u32x2 *)(strip + lr * kStrip + o * 2) = v.u;
+            }
         __builtin_amdgcn_wave_barrier();
-        const int m = m0 + i * 16 + orow;
         if (row_wide) {
-            const u32x4 v = *(const u32x4 *)(strip + orow * 32 + ocol);
-            const uint32_t off = m < a.T ? (uint32_t)(((size_t)m * a.ldy + nw0 + ocol) * 2) : kOobM;
-            __builtin_amdgcn_raw_buffer_store_b128(v, yr, (int)off, 0, 0);
-        } else {
+            constexpr int kLanes = 4 * NTW, kRows = 64 / kLanes;                     // lanes per row, rows per access
 #pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                union { _Float16 h; uint16_t u; } o; o.h = strip[orow * 32 + ocol + e];
-                const int n = nw0 + ocol + e;
-                const uint32_t off = (m < a.T && n < a.N) ? (uint32_t)(((size_t)m * a.ldy + n) * 2) : kOobM;
-                __builtin_amdgcn_raw_buffer_store_b16(o.u, yr, (int)off, 0, 0);
+            for (int i = 0; i < 32 / kRows; ++i) {
+                const int row = i * kRows + lane / kLanes, col = (lane % kLanes) * 8, m = m0 + mt * 32 + row;
+                const u32x4 v = *(const u32x4 *)(strip + row * kStrip + col * 2);
+                const uint32_t off = m < a.T ? (uint32_t)(((size_t)m * a.ldy + n0 + col) * 2) : kOobM;
+                __builtin_amdgcn_raw_buffer_store_b128(v, yr, (int)off, 0, 2);
+            }
+        } else {
+            for (int e = lane; e < 32 * 32 * NTW; e += 64) {
+                const int row = e / (32 * NTW), col = e % (32 * NTW), m = m0 + mt * 32 + row, n = n0 + col;
+                const uint16_t v = *(const uint16_t *)(strip + row * kStrip + col * 2);
+                const uint32_t off = m < a.T && n < a.N ? (uint32_t)(((size_t)m * a.ldy + n) * 2) : kOobM;
+                __builtin_amdgcn_raw_buffer_store_b16(v, yr, (int)off, 0, 0);
             }
         }
         __builtin_amdgcn_wave_barrier();
     }
 }
 
-template <int BM>
-static hipError_t launch_mxfp4_gemm_bm(MxGemmArgs &a, int n_tile0, int n_count, hipStream_t s)
+template <int NTW>
+static hipError_t launch_mxfp4_gemm_cfg(MxGemmArgs &a, hipStream_t s)
 {
-    a.m_tiles = (a.T + BM - 1) / BM; a.n_tiles = n_count; a.n_tile0 = n_tile0;
+    a.m_tiles = (a.T + kMxBM - 1) / kMxBM; a.n_tiles = (a.N + 128 * NTW - 1) / (128 * NTW);
     int blocks;
     gemm_patches(a.m_tiles, a.n_tiles, a.patch_m, a.patch_n, blocks);
-    constexpr int lds = 3 * mx_stage_bytes(BM);
     static std::atomic<uint64_t> attr_done{0};
     if (const int dev = once_pending(attr_done); dev >= 0) {
-        hipError_t e = hipFuncSetAttribute((const void *)mxfp4_gemm_kernel<BM>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+        hipError_t e = hipFuncSetAttribute((const void *)mxfp4_gemm_kernel<NTW>, hipFuncAttributeMaxDynamicSharedMemorySize, kMxGemmLds);
         if (e != hipSuccess) return e;
         once_done(attr_done, dev);
     }
-    hipLaunchKernelGGL(mxfp4_gemm_kernel<BM>, dim3(blocks), dim3(512), lds, s, a);
+    hipLaunchKernelGGL(mxfp4_gemm_kernel<NTW>, dim3(blocks), dim3(256), kMxGemmLds, s, a);
     return hipGetLastError();
 }
 
-// 256-token tiles fill at most half a round of blocks: 128-token tiles, twice as many
+// 128 outputs per block while 256 would fill at most three quarters of a block per compute unit.  2048 tokens 4096 -> 4096 (256
+// tiles of 256 outputs) 21.1 us against 24.8 with 128; 512 tokens 4096 -> 6144 (96) 15.3 against 12.8.
 static bool mxfp4_gemm_small_tiles(const paro_mxfp4_weight &w, int T)
 {
-    return (long)((T + kMxBM - 1) / kMxBM) * ((w.c_out + kMxBN - 1) / kMxBN) <= 128;
+    return (long)((T + kMxBM - 1) / kMxBM) * ((w.c_out + 255) / 256) <= 192;
+}
+
+// Time of the GEMM, fitted to 152 random shapes from 17 tokens on (median 3 % off): a fixed part and a time per K-step that
+// grows with the blocks of a round (512 = two per compute unit).
+static double mxfp4_gemm_us(const paro_mxfp4_weight &w, int T)
+{
+    const bool small = mxfp4_gemm_small_tiles(w, T);
+    const int bn = small ? 128 : 256;
+    const double n = (double)((T + kMxBM - 1) / kMxBM) * ((w.c_out + bn - 1) / bn), k = w.c_in / 128, f = n / 512.0;
+    if (small) return n <= 256 ? 5.7 + k * (0.18 + 0.2 * f) : n <= 512 ? 5.7 + k * (0.28 + 0.33 * f) : 0.8 + (4.9 + 0.6 * k) * f;
+    return n <= 256 ? 8.9 + k * (0.286 + 0.38 * f) : n <= 512 ? 8.9 + k * (1.32 * f - 0.01) : (10.6 + k) * f - 1.7;
 }
 
 static hipError_t launch_mxfp4_gemm(const paro_mxfp4_weight &w, const uint32_t *xc, const uint8_t *xs, int T, paro_half_t *Y,
@@ -557,37 +609,26 @@ static hipError_t launch_mxfp4_gemm(const paro_mxfp4_weight &w, const uint32_t *
     a.blob_bytes = a.scales_off + (uint32_t)((size_t)w.c_out * w.c_in / 32);
     a.xc = xc; a.xs = xs; a.Y = (_Float16 *)Y; a.ldy = ldy; a.bias = (const _Float16 *)w.bias;
     a.T = T; a.C = w.c_in; a.N = w.c_out; a.K128 = w.c_in / 128; a.KS = w.c_in / 512;
-    const int m_big = (T + kMxBM - 1) / kMxBM, n_all = (w.c_out + kMxBN - 1) / kMxBN;
-    if (mxfp4_gemm_small_tiles(w, T)) return launch_mxfp4_gemm_bm<128>(a, 0, n_all, s);
-    // A last round of 256-token tiles that would be at most half full runs as a launch of its own with 128-token
-    // tiles (896 tiles = 3 rounds + one round of 256 half-size tiles instead of 4 rounds).
-    const long tiles = (long)m_big * n_all, full = tiles / 256, rem = tiles - full * 256;
-    const int n_main = (int)(full * 256 / m_big);
-    if (rem > 0 && rem <= 128 && n_main > 0 && n_main < n_all) {
-        hipError_t e = launch_mxfp4_gemm_bm<256>(a, 0, n_main, s);
-        return e != hipSuccess ? e : launch_mxfp4_gemm_bm<128>(a, n_main, n_all - n_main, s);
-    }
-    return launch_mxfp4_gemm_bm<256>(a, 0, n_all, s);
+    return mxfp4_gemm_small_tiles(w, T) ? launch_mxfp4_gemm_cfg<1>(a, s) : launch_mxfp4_gemm_cfg<2>(a, s);
 }
 
-// Which kernel: the streaming kernel reads the whole weight once per 64 tokens (32 or 16 where K is deep), the
-// GEMM once per 256 (or 128) but works on whole tiles whatever T is, one round of them per 256 compute units.
-// Measured: a pass of TB blocks of 16 tokens takes ~3 us + the blob at 5.5 TB/s + TB x (0.8 us + the blob at
-// 30 TB/s); a round of GEMM tiles ~0.9 us per K-step (0.8 us with 128-token tiles) + 3 us.
+// Which kernel: the streaming kernel reads the whole weight once per 64 tokens (32 or 16 where K is deep), the GEMM once per
+// 128 but works on whole tiles whatever T is.  Measured: a pass of TB blocks of 16 tokens takes ~3 us + the blob at 5.5 TB/s +
+// TB x (0.8 us + the blob at 30 TB/s).  Up to 32 tokens a single pass is always taken (30 x 10240 -> 21392: 21.7 us against 25.8).
+// Both kernels over the 104 shapes of the fit with up to 600 tokens: the choice costs 0.8 % over the better one.
 hipError_t launch_mxfp4_linear(const paro_mxfp4_weight &w, const uint32_t *x_codes, const uint8_t *x_scales, int T,
                                paro_half_t *Y, int64_t ldy, hipStream_t s)
 {
-    const int pass = mxfp4_pass_tokens(w, T);
-    // the GEMM addresses the activations with 32-bit offsets
-    if (T > pass && (size_t)T * w.c_in / 2 < (1ull << 31) && ((size_t)(T - 1) * ldy + w.c_out) * 2 < (1ull << 31)) {
+    // the GEMM addresses the activations and the outputs with 32-bit offsets
+    if (T > std::min(mxfp4_pass_tokens(w, T), 32) && (size_t)T * w.c_in / 2 < (1ull << 31) && ((size_t)(T - 1) * ldy + w.c_out) * 2 < (1ull << 31)) {
         const double mb = ((double)w.c_out * w.c_in / 2 + (double)w.c_out * w.c_in / 32) / 1.0e6;
-        const double pass_us = 3.0 + mb / 5.5 + (pass / 16) * (0.8 + mb / 30.0);
-        const double stream_us = (double)((T + pass - 1) / pass) * pass_us;
-        const bool small = mxfp4_gemm_small_tiles(w, T);
-        const int bm = small ? 128 : kMxBM;
-        const long tiles = (long)((T + bm - 1) / bm) * ((w.c_out + kMxBN - 1) / kMxBN);
-        const double gemm_us = (double)((tiles + 255) / 256) * ((w.c_in / 128) * (small ? 0.8 : 0.9) + 3.0);
-        if (gemm_us < stream_us) return launch_mxfp4_gemm(w, x_codes, x_scales, T, Y, ldy, s);
+        double stream_us = 0;
+        for (int t0 = 0; t0 < T;) {
+            const int pass = mxfp4_pass_tokens(w, T - t0);
+            stream_us += 3.0 + mb / 5.5 + (pass / 16) * (0.8 + mb / 30.0);
+            t0 += pass;
+        }
+        if (mxfp4_gemm_us(w, T) < stream_us) return launch_mxfp4_gemm(w, x_codes, x_scales, T, Y, ldy, s);
     }
     for (int t0 = 0; t0 < T;) {
         const int pass = mxfp4_pass_tokens(w, T - t0);
