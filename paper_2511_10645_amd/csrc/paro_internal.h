@@ -186,7 +186,7 @@ hipError_t launch_mxfp4_linear(const paro_mxfp4_weight &w, const uint32_t *x_cod
 hipError_t launch_quantize_act_mxfp4(const paro_rotation &rot, const paro_half_t *X, int64_t ldx, int T, uint32_t *codes,
                                      uint8_t *scales, hipStream_t s);
 
-// Weights in the interchange layout, up to 32 tokens (linear_rows.hip).  scratch: room for the partial sums of K split
+// Weights in the interchange layout, up to 32 tokens (linear_ic.hip).  scratch: room for the partial sums of K split
 // between blocks (any contents before; after, those below `least` are zero: launch_splitk_reduce); without it the call
 // runs unsplit.
 bool linear_rows_supported(const paro_w4_weight &w, int64_t ldx, int T);

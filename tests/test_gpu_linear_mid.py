@@ -1,5 +1,5 @@
 """The W4A16 linear between the streaming decode kernels and the GEMM (linear_tile.hip) and on weights in the interchange
-layout (linear_rows.hip up to 32 tokens, linear_tile.hip above), against the oracle's contraction of the same fp16
+layout (linear_ic.hip up to 32 tokens, linear_tile.hip above), against the oracle's contraction of the same fp16
 activations.
 
 Both kernels multiply q - z exactly, apply the group's scale to fp32 sums and round once, so every output must lie within
@@ -43,6 +43,10 @@ CASES = [
     (1, 512, 528, "plain"), (1, 1152, 144, "plain"),       # one token, few short rows: a wave per row
     (1, 640, 48, "plain"), (1, 11008, 272, "plain"), (16, 128, 16, "plain"), (17, 1920, 80, "plain"), (32, 640, 528, "plain"),
     (24, 2176, 4112, "plain"), (33, 128, 16, "plain"), (33, 640, 144, "plain"), (64, 1152, 2064, "plain"),
+    # up to 32 tokens: fewer groups than a stage has, a last stage moved back, every split of the tokens into requests, 16 to 128
+    # outputs per block with tiles beyond the last output, K split (the last two)
+    (3, 384, 16, "plain"), (8, 896, 32064, "plain"), (4, 1664, 16400, "plain"), (9, 1152, 8240, "plain"), (16, 3712, 2064, "plain"), (25, 2688, 8208, "plain"),
+    (6, 2944, 9744, "plain"), (5, 896, 6080, "plain"), (14, 2176, 6096, "plain"), (29, 5760, 4144, "plain"), (21, 640, 20544, "plain"), (13, 11008, 272, "plain"), (24, 11008, 272, "plain"),
     (65, 1920, 272, "plain"), (129, 4096, 1040, "plain"), (200, 2176, 1296, "plain"), (5, 640, 80, "scales_odd"), (40, 640, 80, "scales_odd"),
     # repacked: 64-token tiles, K split and not, ragged tokens and outputs
     (33, 4096, 4112, "packed"), (64, 4096, 6144, "packed"), (64, 512, 16400, "packed"), (80, 2048, 2064, "packed"),
