@@ -203,6 +203,9 @@ hipError_t launch_plan_build(const paro_rotation &rot, void *plan_out, hipStream
 constexpr int kRotWaves = 4;   // waves per block
 constexpr int kRotTU = 4;      // tokens in flight per wave
 constexpr int kRotMaxBatches = 8;   // batches of kRotTU tokens per wave (the batch loop is unrolled)
+// Rows leave the L2 as they are written (sc1) instead of all at once when the launch ends.  Graph replay over 400 MB, us, plain
+// stores / these: 2048 x 4096 13.0 / 11.5, 1023 x 14336 20.2 / 18.5, 4096 x 27648 124 / 119; no difference at 16..256 tokens.
+constexpr int kAuxWriteThrough = 16;
 
 // f(0), f(1), ... while f returns true, at most N times; nested, so that stopping is one forward jump
 template <int N, class F, int I = 0>
@@ -319,7 +322,7 @@ __global__ __launch_bounds__(kRotWaves * 64) void rotate_planned_kernel(const ui
             __builtin_amdgcn_raw_buffer_store_b128(v, yr, t + (lane & 3) < n_tok ? off : (int)0x80000000u, 0, 0);
         } else {
 #pragma unroll
-            for (int u = 0; u < kRotTU; ++u) __builtin_amdgcn_raw_buffer_store_b32(o[u], yr, v4 + (t + u) * row_y, 0, 0);
+            for (int u = 0; u < kRotTU; ++u) __builtin_amdgcn_raw_buffer_store_b32(o[u], yr, v4 + (t + u) * row_y, 0, kAuxWriteThrough);
         }
         __builtin_amdgcn_wave_barrier();
 #pragma unroll
