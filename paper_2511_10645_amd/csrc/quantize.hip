@@ -18,19 +18,20 @@
 // One wavefront owns a channel group and a run of rows, four rows at a time (few rows: one each, kQuantFewRows), with the
 // lane plan and layer loop of the activation kernel (rotate_lane.h): the plan (7.4 KB at K = 8, 29 times a row's group) is
 // read once per run, the four rows' chains of multiply-adds and permutes are independent, and rows go through a
-// wave-private LDS area as [channel][4 rows].  What bounds it is the vector pipes (INT4 weights, counted: 101 instructions
-// per (row, group), at four cycles each the whole launch; LDS with its conflicts under half of it): 38 of rotation, and
-// the rest was made small against that -
+// wave-private LDS area as [channel][4 rows].  What bounds it is mostly the vector pipes (INT4 weights: some 88 instructions
+// per (row, group) at four cycles each, 38 of them rotation; taking 13 of 101 out gave 4 % with a rotation and 13 % without,
+// the rest is the permutes' LDS time) -
 //   - INT4: minimum and maximum of the four rows are reduced together, each swap of half waves merging two rows, so that
 //     every 16 lanes end up with one row's and the scale, its reciprocal and the zero point are computed once for all
 //     four; v / s is the correctly rounded quotient from the correctly rounded reciprocal and one residual (Markstein's
 //     theorem), which holds for finite v and s: rows with an infinite scale, and rows of infinities (whose range is NaN
-//     and whose scale is the floor), divide;
+//     and whose scale is the floor), divide; range / 15 and the zero point the same way; codes leave past the L2;
 //   - MXFP4: the rotated values are read back in channel order, 8 per lane, so that a block's maximum is two steps within
 //     four lanes and the codes are four instructions of the FP4 converter (equal to the thresholds of the format on every
 //     tie and its neighbours, probed over all exponents; the tests pin those that fp16 inputs and scales reach).
 // Measured over back-to-back calls (before: one row of INT4 weights per wave, plan re-read for each; MXFP4 one row at a
-// time, 14 instructions of thresholds per value): INT4 weight 28672 x 4096 414 -> 146 us, MXFP4 activations 2048 x 4096
+// time, 14 instructions of thresholds per value): INT4 weight 28672 x 4096 414 -> 146 us (137 with reciprocals in place of the
+// three divisions, bytes picked by permutes and the factor of one left out; without a rotation 97 -> 84), MXFP4 activations 2048 x 4096
 // 21.0 -> 12.8, 2048 x 14336 55.8 -> 36.4 us, INT4 activations 24.7 -> 14.8 and 78.3 -> 39.6 us; 1 x 4096 MXFP4
 // 3.0 -> 2.6, INT4 2.9 -> 2.8; the same bits throughout.
 #include "paro_internal.h"
@@ -94,6 +95,14 @@ constexpr int kRowLane[4] = {0, 32, 16, 48};         // a lane that holds row u'
 __device__ __forceinline__ int row_of_lane(int lane) { return ((lane >> 5) & 1) | ((lane >> 3) & 2); }
 __device__ __forceinline__ float from_lane(float v, int lane) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), lane)); }
 
+// 1 / s of an fp16 value s >= 2^-14, correctly rounded: the hardware's estimate and one Newton step (compared with the division
+// on all of them)
+__device__ __forceinline__ float quant_rcp(float s)
+{
+    const float r = __builtin_amdgcn_rcpf(s);
+    return fmaf(fmaf(-s, r, 1.0f), r, r);
+}
+
 // rotate_layers with the order of the two products of every sum written out (the one that is there first is rounded, the
 // later one joins it in a fused multiply-add): a code on a rounding tie must not depend on how the compiler schedules.
 template <int K, int U>
@@ -150,6 +159,8 @@ __global__ __launch_bounds__(kQuantWaves * 64) void quantize_kernel(QuantArgs a)
     auto lo_pair = [](uint32_t x, uint32_t y) { return (x & 0xffffu) | (y << 16); };
     auto hi_pair = [](uint32_t x, uint32_t y) { return (x >> 16) | (y & 0xffff0000u); };
     const int orow = lane >> 4, oword = lane & 15;       // the row of a batch and its 8 channels this lane writes out
+    const uint32_t pick_row = 0x0400u + 0x0101u * orow;  // byte orow of two dwords
+    const bool scales_out = K >= 0 && __any(oa != 1.f || ob != 1.f);             // multiplying by one is left out
 
     quant_while<U == 1 ? 1 : kQuantBatches>([&](auto I) {
         constexpr int t = I * U;
@@ -174,8 +185,9 @@ __global__ __launch_bounds__(kQuantWaves * 64) void quantize_kernel(QuantArgs a)
 #pragma unroll
             for (int u = 0; u < U; ++u) { va[u] = (float)ha[u] * ia; vb[u] = (float)hb[u] * ib; }
             quant_rotate<K, U>(P, va, vb);
+            if (scales_out)
 #pragma unroll
-            for (int u = 0; u < U; ++u) { va[u] *= oa; vb[u] *= ob; }
+                for (int u = 0; u < U; ++u) { va[u] *= oa; vb[u] *= ob; }
         } else {
 #pragma unroll
             for (int u = 0; u < U; ++u) {
@@ -196,12 +208,17 @@ __global__ __launch_bounds__(kQuantWaves * 64) void quantize_kernel(QuantArgs a)
                 mxv = wave_max4(mx); mnv = -wave_max4(nmn);
             }
             const float range = mxv - mnv;
-            float s32 = range / 15.0f;
+            // correctly rounded quotients by reciprocal and residual, as for the codes: range / 15 where the range is finite
+            constexpr float kR15 = 1.0f / 15.0f;
+            const float s15 = range * kR15;
+            float s32 = range < __builtin_inff() ? fmaf(fmaf(-15.0f, s15, range), kR15, s15) : range;
             if (!(s32 >= 6.103515625e-05f)) s32 = 6.103515625e-05f;
             const _Float16 s16 = (_Float16)s32;
-            const float s = (float)s16, rs = range == range ? 1.0f / s : 0.f;    // 0: infinite scale, or a group of infinities
-            float zf = -rintf(mnv / s);
-            zf = fminf(fmaxf(zf, 0.0f), 15.0f);
+            const float s = (float)s16, rs = range < __builtin_inff() && s < __builtin_inff() ? quant_rcp(s) : 0.f;  // 0: infinite scale, or a group of infinities
+            float zq = mnv * rs;
+            zq = fmaf(fmaf(-s, zq, mnv), rs, zq);
+            if (__any(!(rs > 0.f))) zq = rs > 0.f ? zq : mnv / s;
+            const float zf = __builtin_amdgcn_fmed3f(-rintf(zq), 0.0f, 15.0f);
             uint32_t ca = 0, cb = 0, zhalf = 0;
 #pragma unroll
             for (int u = 0; u < U; ++u) {
@@ -214,19 +231,21 @@ __global__ __launch_bounds__(kQuantWaves * 64) void quantize_kernel(QuantArgs a)
                 } else {
                     qa = va[u] / su; qb = vb[u] / su;
                 }
-                ca = __builtin_amdgcn_cvt_pk_u8_f32(fminf(fmaxf(rintf(qa) + zu, 0.0f), 15.0f), u, ca);
-                cb = __builtin_amdgcn_cvt_pk_u8_f32(fminf(fmaxf(rintf(qb) + zu, 0.0f), 15.0f), u, cb);
+                ca = __builtin_amdgcn_cvt_pk_u8_f32(__builtin_amdgcn_fmed3f(rintf(qa) + zu, 0.0f, 15.0f), u, ca);   // NaN: 0
+                cb = __builtin_amdgcn_cvt_pk_u8_f32(__builtin_amdgcn_fmed3f(rintf(qb) + zu, 0.0f, 15.0f), u, cb);
                 if constexpr (KIND == kW4Weight) zhalf |= (uint32_t)zu << (4 * u);
             }
             s_out[wave][ch_a] = ca;
             s_out[wave][ch_b] = cb;
             __builtin_amdgcn_wave_barrier();
-            uint32_t d[8], word = 0;
+            uint32_t d[8];
             *(u32x4v *)&d[0] = *(const u32x4v *)&s_out[wave][oword * 8];
             *(u32x4v *)&d[4] = *(const u32x4v *)&s_out[wave][oword * 8 + 4];
-#pragma unroll
-            for (int k = 0; k < 8; ++k) word |= ((d[k] >> (8 * orow)) & 15u) << (4 * k);
-            if (live) a.codes[(size_t)row * (a.C / 8) + (size_t)g * (kGroup / 8) + oword] = word;
+            // byte orow of every dword, two to a half, four to a dword, then the nibbles together
+            auto pick = [&](int k) { return __builtin_amdgcn_perm(d[k + 1], d[k], pick_row); };
+            const uint32_t c03 = __builtin_amdgcn_perm(pick(2), pick(0), 0x05040100u), c47 = __builtin_amdgcn_perm(pick(6), pick(4), 0x05040100u);
+            const uint32_t word = __builtin_amdgcn_perm(c47 | (c47 >> 4), c03 | (c03 >> 4), 0x06040200u);
+            if (live) __builtin_nontemporal_store(word, &a.codes[(size_t)row * (a.C / 8) + (size_t)g * (kGroup / 8) + oword]);
             const int64_t prow = t0 + t + row_of_lane(lane);         // the row whose scale this lane holds
             if (oword == 0 && row_of_lane(lane) < U && t + row_of_lane(lane) < n_rows) {
                 if constexpr (KIND == kW4Weight) a.scales[(size_t)g * a.T + prow] = s16;
@@ -267,7 +286,7 @@ __global__ __launch_bounds__(kQuantWaves * 64) void quantize_kernel(QuantArgs a)
             word = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(word, v[4], v[5], sc, 2);
             word = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(word, v[6], v[7], sc, 3);
             if (live) {
-                a.codes[(size_t)row * (a.C / 8) + (size_t)g * (kGroup / 8) + oword] = word;
+                __builtin_nontemporal_store(word, &a.codes[(size_t)row * (a.C / 8) + (size_t)g * (kGroup / 8) + oword]);
                 if ((lane & 3) == 0) a.bytes[(size_t)row * (a.C / 32) + (size_t)g * (kGroup / 32) + (oword >> 2)] = (uint8_t)(e + 127);
             }
         }
