@@ -3,27 +3,27 @@
 //
 // At these sizes neither of the other kernels fits.  The streaming kernel keeps a K-slice of activations in registers (32
 // tokens fill half the register file) and re-reads the weights for every further 32 tokens.  The GEMM's 128 x 256 tiles are
-// few, pay for rows that do not exist and carry every weight through LDS as fp16.  Here a block is 8 waves, each with 64
-// tokens x 32 outputs of 64 (or 128) tokens x 128 outputs:
-//   - activations (32 KB per step: 64 tokens x 2 groups, or 128 tokens x 1 group) go through LDS, whole 256-byte rows per
-//     request, the 16-byte chunk index XOR-ed with the row so that both directions are conflict-free; requested two
-//     steps ahead, written one step ahead, re-read into the fragment registers slot by slot as these fall free;
+// few, pay for rows that do not exist and carry every weight through LDS as fp16.  Here a block is 8 waves and 64 or 128
+// tokens x 128 outputs.  Of 64 tokens every wave has 32 outputs and one of a step's two groups (128 tokens: below):
+//   - activations (32 KB per step) go through LDS, whole 256-byte rows per request, the 16-byte chunk index XOR-ed with the row
+//     so that both directions are conflict-free; requested two steps ahead, written one step ahead, re-read into the fragment
+//     registers slot by slot as these fall free;
 //   - weights never touch LDS: a lane's 16 bytes of a 16 x 128 tile are its operand of four v_mfma_f32_16x16x32_f16 once
 //     the codes stand in registers as q - z (exact in fp16); the group's scale multiplies the fp32 sums of the group;
-//   - with 64 tokens the waves split the step's two groups and add their sums through LDS at the end.
+//   - the two halves of K are added through LDS at the end.
 // The step is written as slots, one MFMA each, with a piece of the next tile's dequantisation, a piece of the previous
 // tile's scaling and one load, LDS read or write in its shadow, pinned by scheduling barriers; one block barrier per step.
 // K is split between blocks where the tiles alone are too few (fp32 partial tiles, summed by the GEMM's second kernel).
 //
-// What bounds it: no single unit.  Taking out a part of the step (timing only, 1024 tokens, 1.38 us per step) gives
-// 1.01 without dequantisation, 1.15 without the scaling, 1.16 without LDS reads, 1.04 without staging: the parts add up, as
-// in the GEMM, because the chip's clock pays for every instruction.  That is 0.35 us per 64 x 64 x 128 of work against
-// the GEMM's 0.24 on full tiles, hence the line between the two (linear_tile_estimate_us).  Bare calls in a replayed graph
-// over 350 MB of weights, summing launch included, us, before (the cheaper of the other two) -> now: 64 tokens 4096 -> 28672
-// 37.8 -> 25.7, 14336 -> 4096 28.1 -> 20.9; 128 tokens 4096 -> 6144 22.9 -> 19.3, 4096 -> 4096 23.6 -> 16.9, 4096 -> 28672
-// 49.3 -> 43.6; 201 tokens 4096 -> 6144 27.5 -> 22.4, 4096 -> 4096 22.9 -> 18.1.  Interchange layout, 11008 -> 4096 at 48
-// tokens: rotated call 1874 -> 23.5 (K over 8 blocks); the bare call, which has no workspace and is not split, 1872 -> 52.3.
+// What bounds it: no single unit.  Taking out a part of the step (timing only) takes off what the part issues: the parts add
+// up, as in the GEMM, because the chip's clock pays for every instruction; at 64 tokens the weight stream is next (4096 -> 28672
+// without multiplication and scaling 18 of 25 us).  Bare calls in a replayed graph over 350 MB of weights, summing launch included,
+// us, the cheaper of the other two kernels -> this one: 64 tokens 4096 -> 28672 37.8 -> 25.4, 14336 -> 4096 28.1 -> 19.5;
+// 128 tokens 4096 -> 6144 22.9 -> 18.9, 4096 -> 4096 23.6 -> 15.7, 4096 -> 28672 49.3 -> 38.6; 201 tokens 4096 -> 6144 27.5 -> 21.2,
+// 4096 -> 4096 22.9 -> 17.9.  Interchange layout, 11008 -> 4096 at 48 tokens: rotated call 1874 -> 23.5 (K over 8 blocks); the
+// bare call, which has no workspace and is not split, 1872 -> 52.3.
 #include "paro_internal.h"
+#include <algorithm>
 #include <type_traits>
 
 namespace paro {
@@ -31,7 +31,9 @@ namespace paro {
 typedef _Float16 half8 __attribute__((ext_vector_type(8)));
 typedef _Float16 half2v __attribute__((ext_vector_type(2)));
 typedef float float4v __attribute__((ext_vector_type(4)));
+typedef float float16v __attribute__((ext_vector_type(16)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef __attribute__((address_space(3))) void tile_lds_t;
 
 constexpr uint32_t kOobT = 0x80000000u;             // beyond every buffer: reads as zero, is not written
 __device__ inline __amdgpu_buffer_rsrc_t tile_rsrc(const void *p, size_t bytes)
@@ -65,21 +67,33 @@ struct TileArgs {
 
 constexpr int kTileThreads = 512, kTileBuf = 32768;
 
+// Results leave the L2 as they are written (sc1) instead of all at once at the end of the launch; rows beyond a tile's are
+// beyond the buffer.  us, plain stores / these: 4096 -> 28672 at 128 tokens 38.8 / 37.6, 14336 -> 4096 at 64 (partial tiles)
+// 24.0 / 23.4 rotated; no difference on 1024 -> 12304.
+constexpr int kAuxThrough = 16;
+__device__ inline __amdgpu_buffer_rsrc_t tile_outputs(const TileArgs &a, int m0, int rows)
+{
+    return tile_rsrc(a.Y + (size_t)m0 * a.ldy, ((size_t)(rows - 1) * a.ldy + a.N) * 2);
+}
+__device__ inline __amdgpu_buffer_rsrc_t tile_partials(const TileArgs &a, int kslice, int m0, int rows)
+{
+    return tile_rsrc(a.partial ? a.partial + ((size_t)kslice * a.T + m0) * a.N : nullptr, a.partial ? (size_t)rows * a.N * 4 : 0);
+}
+
 // What the 16-byte chunk index of a row is XOR-ed with: the row, bit 3 flipped by bit 2.  A 16-byte LDS read serves lanes
 // 0-3, 12-15 and 20-27 together (then 4-11, 16-19 and 28-31): rows 0-3 and 12-15 of one quarter of the channels and rows
 // 4-11 of the next.  With the row itself the two sets of chunks coincide: 2.01 M conflict cycles over the chip at 64 tokens
 // 4096 -> 28672 (of 1.25 M instruction cycles of LDS), now 57 k; 1 to 4 % faster (LDS is not what bounds the kernel).
 __device__ inline int chunk_xor(int row) { return (row & 15) ^ ((row & 4) << 1); }
 
-template <int MW, int NW, int KW, bool IC>
+template <bool IC>
 __global__ __launch_bounds__(kTileThreads, 2) void linear_tile_kernel(TileArgs a)
 {
-    static_assert(MW * NW * KW == 8 && MW * KW == 2 && NW == 4, "");
-    constexpr int TB = 4, NT = 2, S = 16, TM = 64 * MW, TN = 32 * NW;
+    constexpr int NW = 4, KW = 2, TB = 4, NT = 2, S = 16, TM = 64, TN = 32 * NW;
     extern __shared__ __attribute__((aligned(16))) char s_x[];            // [2][KW][TM][256 B]
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int nw = wave % NW, mw = wave / NW % MW, kw = wave / (NW * MW);
+    const int nw = wave % NW, kw = wave / NW;
 
     // Consecutive tiles - token tiles first, then output tiles, then slices of K - on one XCD: its L2 serves a tile's
     // weights to the further token tiles and a slice's activations to the further output tiles, and every XCD has the
@@ -106,12 +120,12 @@ __global__ __launch_bounds__(kTileThreads, 2) void linear_tile_kernel(TileArgs a
     const int xw = srow * 256 + ((sc16 ^ chunk_xor(srow)) << 4);           // + 8192 i
     u32x4 xs[4];
     auto load_x = [&](int step, auto I) {
-        const int g = g0 + step * KW + (KW == 1 ? 0 : (int)I / 2);        // rows 0..63 of KW = 2: the step's first group
+        const int g = g0 + step * KW + (int)I / 2;                         // rows 0..63: the step's first group
         xs[I] = __builtin_amdgcn_raw_buffer_load_b128(xr, (int)(g < g_end ? xg[I] : kOobT), (int)tile_uniform(g * 256), 0);
     };
     auto store_x = [&](int buf, auto I) { *(u32x4 *)(s_x + buf * kTileBuf + xw + I * 8192) = xs[I]; };
     int xa_off[4];
-    tile_for<4>([&](auto J) { xa_off[J] = (kw * TM + mw * 64 + ft) * 256 + (((fkb * 4 + J) ^ chunk_xor(ft)) << 4); });
+    tile_for<4>([&](auto J) { xa_off[J] = (kw * TM + ft) * 256 + (((fkb * 4 + J) ^ chunk_xor(ft)) << 4); });
     half8 xa[TB][4];
     auto read_x = [&](int buf, auto B, auto J) { xa[B][J] = *(const half8 *)(s_x + buf * kTileBuf + xa_off[J] + B * 4096); };
 
@@ -228,7 +242,7 @@ __global__ __launch_bounds__(kTileThreads, 2) void linear_tile_kernel(TileArgs a
 
     // ---- epilogue: lane holds output ft of tokens 4 fkb .. + 3 of a 16 x 16 tile ------------------------------------
     __syncthreads();
-    if constexpr (KW == 2) {                         // the second half of K through LDS (the loop's buffers are free)
+    {                                                // the second half of K through LDS (the loop's buffers are free)
         float4v *sum = (float4v *)s_x + (size_t)(wave % 4) * TB * NT * 64;
         if (kw == 1) tile_for<TB>([&](auto B) { tile_for<NT>([&](auto N_) { sum[(B * NT + N_) * 64 + lane] = tot[B][N_]; }); });
         __syncthreads();
@@ -236,18 +250,19 @@ __global__ __launch_bounds__(kTileThreads, 2) void linear_tile_kernel(TileArgs a
         tile_for<TB>([&](auto B) { tile_for<NT>([&](auto N_) { tot[B][N_] += sum[(B * NT + N_) * 64 + lane]; }); });
     }
     if (n_rows <= 0) return;
-    const int mrow0 = m0 + mw * 64;
     if (a.partial) {
-        float *dst = a.partial + ((size_t)kslice * a.T + mrow0 + fkb * 4) * a.N + n0 + ft;
+        const __amdgpu_buffer_rsrc_t pr = tile_partials(a, kslice, m0, rows);
         tile_for<TB>([&](auto B) {
             tile_for<NT>([&](auto N_) {
 #pragma unroll
                 for (int r = 0; r < 4; ++r)
-                    if (mrow0 + B * 16 + fkb * 4 + r < a.T && N_ * 16 < n_rows) dst[(size_t)(B * 16 + r) * a.N + N_ * 16] = tot[B][N_][r];
+                    if (N_ * 16 < n_rows)
+                        __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(tot[B][N_][r]), pr, ((B * 16 + fkb * 4 + r) * a.N + n0 + ft + N_ * 16) * 4, 0, kAuxThrough);
             });
         });
         return;
     }
+    const __amdgpu_buffer_rsrc_t yr = tile_outputs(a, m0, rows);
     // a 16 x 32 strip through a wave-private kilobyte of LDS, out as one 16-byte store per lane
     _Float16 *strip = (_Float16 *)(s_x + 2 * kTileBuf - 8192 + wave * 1024);
     float bv[NT];
@@ -260,49 +275,299 @@ __global__ __launch_bounds__(kTileThreads, 2) void linear_tile_kernel(TileArgs a
         });
         __builtin_amdgcn_wave_barrier();
         const u32x4 v = *(const u32x4 *)(strip + orow * 32 + ocol);
-        if (ocol < n_rows && mrow0 + B * 16 + orow < a.T)
-            *(u32x4 *)(a.Y + (size_t)(mrow0 + B * 16 + orow) * a.ldy + n0 + ocol) = v;
+        if (ocol < n_rows) __builtin_amdgcn_raw_buffer_store_b128(v, yr, ((B * 16 + orow) * (int)a.ldy + n0 + ocol) * 2, 0, kAuxThrough);
         __builtin_amdgcn_wave_barrier();
     });
 }
 
-template <int MW, int NW, int KW, bool IC>
+constexpr int kTile2Stage = 65536, kTile2Lds = 2 * kTile2Stage;
+
+// 128 tokens x 128 outputs.  A wave has 64 x 64 of them and one of a step's two groups, so that an operand read from LDS serves
+// two tiles of v_mfma_f32_32x32x16_f16 (half the LDS reads and half the matrix instructions per product of the 64 x 32 tile above,
+// which bounded it: read, dequantised and scaled in phases that every wave went through together, the units took turns).
+// Activations go to LDS directly, 64 KB per step in a ring of two: behind the barrier that ends a step its buffer is requested
+// anew at once.  Weights are two groups ahead in registers; what is multiplied next is read and dequantised while this is.
+// The matrix pipes are busy 0.47 of a block's cycles (30 % of the launch at 4096 -> 28672, 128 tokens), issue the rest; without
+// activations' requests (timing only) 35 us of 39.8.  A launch begins and ends in 9 us, 4 of them launching 512 threads with this
+// much LDS, 2 the first requests, 2 to 4 the sums and the stores, and is therefore slower where a block has only two steps: 512 channels in
+// one round of blocks, 512 -> 17424 at 105 tokens 9.7 us against 9.0 for 64 x 32 tiles twice over the tokens.
+// us, those -> these: 4096 -> 28672 at 128 tokens 44.3 -> 37.6, rotated 49.2 -> 43.5; 14336 -> 4096 at 201 42.2 -> 38.5;
+// 512 -> 32656 at 289 rotated 27.4 -> 23.0; 75 random shapes of 65 to 1100 tokens 0.976 of the time (other kernels' among them).
+
+template <int N> __device__ __forceinline__ void tile_wait_vm() { __builtin_amdgcn_s_waitcnt(0x0f70 | (N & 15) | ((N >> 4) << 14)); }
+
+template <bool IC>
+__global__ __launch_bounds__(kTileThreads, 2) void linear_tile2_kernel(TileArgs a)
+{
+    constexpr int MW = 2, KW = 2, NW = 2, TB = 2, NT = 2, TM = 64 * MW, TN = 128, KK = 8;
+    extern __shared__ __attribute__((aligned(16))) char s_x[];            // [2][KW][TM][256 B]
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int nw = wave % NW, mw = wave / NW % MW, kw = wave / (NW * MW);
+
+    // Consecutive tiles - token tiles first, then output tiles, then slices of K - on one XCD: its L2 serves a tile's
+    // weights to the further token tiles and a slice's activations to the further output tiles, and every XCD has the
+    // same number of blocks (to one) whatever the counts are.  (The GEMM's patches of powers of two leave XCDs idle at 5
+    // token tiles: 8192 -> 16384 at 640 tokens 300 us against 212.)
+    const int tiles = a.m_tiles * a.n_tiles, all = tiles * a.k_split, per_xcd = (all + 7) / 8;
+    const int idx = (int)(blockIdx.x & 7) * per_xcd + (int)(blockIdx.x >> 3);
+    if (idx >= all) return;
+    const int kslice = idx / tiles, tile = idx % tiles, mt = tile % a.m_tiles, ntile = tile / a.m_tiles;
+    const int m0 = (int)tile_uniform(mt * TM), n0 = (int)tile_uniform(ntile * TN + nw * 64);
+    const int rows = min(a.T - m0, TM);
+    const int g0 = (int)tile_uniform(kslice * a.groups_per_split), g_end = min(a.G, g0 + a.groups_per_split);
+    const int n_steps = (g_end - g0 + KW - 1) / KW;
+    const int r32 = lane & 31, half = lane >> 5, ft = lane & 15;
+
+    // ---- activations: this wave requests 32 rows of one group of a step, 4 whole rows per request -------------------
+    const __amdgpu_buffer_rsrc_t xr = tile_rsrc(a.X + (size_t)m0 * a.ldx, ((size_t)(rows - 1) * a.ldx + a.C) * 2);
+    const int x_group = wave / (TM / 32), x_row = wave % (TM / 32) * 32;
+    uint32_t xg[4];                                  // rows beyond T are beyond the buffer; the last four are 16 rows on
+    tile_for<4>([&](auto I) {
+        const int t = x_row + 4 * I + (lane >> 4);
+        xg[I] = (uint32_t)((size_t)t * a.ldx * 2) + (((lane & 15) ^ (t & 15)) << 4);
+    });
+    const uint32_t x_next = tile_uniform((uint32_t)(a.ldx * 32));
+    auto request_x = [&](int step, int buf, auto I) {
+        const int g = g0 + step * KW + x_group;
+        char *dst = s_x + buf * kTile2Stage + wave * 8192 + I * 1024;
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(xr, (tile_lds_t *)dst, 16, (int)((g < g_end ? xg[I % 4] : kOobT) + (I / 4) * x_next), (int)tile_uniform(g * 256), 0, 0);
+    };
+    // operand kk = 4 i + j of a group: channels 64 i + 32 half + 8 j .. + 7, chunk 8 i + 4 half + j
+    const int x_off = (kw * TM + mw * 64 + r32) * 256 + (((half * 4) ^ ft) << 4);
+    half8 xa[2][TB];
+    auto read_x = [&](int buf, auto B, auto KK_) {
+        constexpr int kk = KK_;
+        xa[kk & 1][B] = *(const half8 *)(s_x + (x_off ^ (((kk / 4) * 8 + kk % 4) << 4)) + buf * kTile2Stage + B * 8192);
+    };
+
+    // ---- weights of the wave: two tiles of 32 rows, lane: row lane % 32, channels 32 half .. + 31 and 64 + 32 half .. + 31
+    const int n_rows = min(a.N - n0, 64);            // multiple of 16; <= 0: this wave's outputs do not exist
+    const __amdgpu_buffer_rsrc_t wr = IC ? tile_rsrc(a.w, n_rows > 0 ? (size_t)a.N * (a.C / 2) : 0)
+                                         : tile_rsrc(a.w, a.zeros_off + packed_zeros_bytes(a.C, a.N));
+    const __amdgpu_buffer_rsrc_t sr = tile_rsrc(a.scales, IC ? (size_t)a.G * a.N * 2 : 0);
+    const __amdgpu_buffer_rsrc_t zr = tile_rsrc(a.qzeros, IC ? (size_t)a.G * a.N / 2 : 0);
+    constexpr uint32_t kWGroup = IC ? 64 : 1024, kWHalf = IC ? 32 : 512;
+    const uint32_t z_sh = IC ? 4 * (ft & 7) : 16 * (ft & 1);
+    uint32_t wv[NT], sv[NT], zv[NT];
+    tile_for<NT>([&](auto N_) {
+        const int c = N_ * 32 + (lane & 16) < n_rows ? N_ * 32 + (lane & 16) : 0;      // rows beyond N read others: not stored
+        const uint32_t row = (uint32_t)max(n0 + c, 0), t16 = row / kTileN;
+        wv[N_] = IC ? (row + ft) * (uint32_t)(a.C / 2) + half * 16 : t16 * (uint32_t)a.G * 1024u + half * 256 + ft * 16;
+        sv[N_] = IC ? (row + (ft & 14)) * 2u : t16 * (uint32_t)(a.G / kSliceGroups) * 128u + ft * 8;
+        zv[N_] = IC ? row / 2 + (ft >> 3) * 4 : t16 * (uint32_t)(a.G / kSliceGroups) * 32u + (ft & 14) * 2;
+        if (n_rows <= 0) wv[N_] = sv[N_] = zv[N_] = kOobT;
+    });
+    u32x4 wq[2][NT][2];
+    uint32_t wsc[2][NT], wz[2][NT];
+    auto load_w = [&](int step, auto RING, auto N_, auto H) {
+        const int g = g0 + step * KW + kw;
+        wq[RING][N_][H] = __builtin_amdgcn_raw_buffer_load_b128(wr, (int)((g < g_end ? wv[N_] : kOobT) + H * kWHalf), (int)tile_uniform(g * kWGroup), 0);
+    };
+    auto load_sz = [&](int step, auto RING, auto N_) {
+        const int g = g0 + step * KW + kw;
+        const uint32_t gu = tile_uniform(g), so = g < g_end ? sv[N_] : kOobT, zo = g < g_end ? zv[N_] : kOobT;
+        if constexpr (IC) {
+            wsc[RING][N_] = (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(sr, (int)so, (int)(gu * (uint32_t)a.N * 2u), 0);
+            wz[RING][N_] = (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(zr, (int)zo, (int)(gu * (uint32_t)a.N / 2u), 0);
+        } else {
+            wsc[RING][N_] = (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(wr, (int)so, (int)(a.scales_off + (gu >> 2) * 128u + (gu & 2) * 2), 0);
+            wz[RING][N_] = (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(wr, (int)zo, (int)(a.zeros_off + (gu >> 2) * 32u), 0);
+        }
+    };
+    auto to_vgpr = [&](uint32_t v) { return (uint32_t)__builtin_amdgcn_ds_bpermute(lane << 2, (int)v); };
+    const uint32_t c_mlo = to_vgpr(a.m_lo), c_mhi = to_vgpr(a.m_hi), c_klo = to_vgpr(a.k_lo), c_khi = to_vgpr(a.k_hi);
+
+    const float16v zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    float16v tot[NT][TB], gacc[NT][TB];
+    union BFrag { u32x4 u; half8 h; } bf[2][NT];
+    float sc[NT];
+    half2v nlo[NT], nhi[NT];
+    uint32_t sp[NT];
+    tile_for<NT>([&](auto N_) {
+        sc[N_] = 0.f;
+        tile_for<TB>([&](auto B) { tot[N_][B] = gacc[N_][B] = zero; });
+    });
+    // two channels of operand kk of tile n: part 0..3
+    auto deq_piece = [&](int step, auto RING, auto N_, auto KK_, auto PART) {
+        constexpr int ring = RING, n = N_, kk = KK_, part = PART;
+        if constexpr (kk == 0 && part == 0) {
+            const uint32_t g = tile_uniform(g0 + step * KW + kw);
+            const uint32_t z = (wz[ring][n] >> (IC ? z_sh : z_sh + 4 * (g & 3))) & 15u;
+            nlo[n] = tile_h2((0xE400u + z) * 0x00010001u);              // -(1024 + z), twice
+            if constexpr (!IC) nhi[n] = tile_h2((0xD400u + (z << 4)) * 0x00010001u);    // -(64 + z), twice
+        }
+        const uint32_t u = wq[ring][n][kk / 4][kk % 4];
+        if constexpr (IC) {
+            if constexpr (part == 0) { const uint32_t x = u & 0xffffu; sp[n] = x | (x << 12); }
+            if constexpr (part == 2) { const uint32_t x = u >> 16; sp[n] = x | (x << 12); }
+            bf[kk & 1][n].u[part] = tile_u32(tile_h2(((part & 1 ? sp[n] >> 8 : sp[n]) & c_mlo) | c_klo) + nlo[n]);
+        } else {
+            const uint32_t v = part < 2 ? u : u >> 8;
+            if constexpr (part & 1) bf[kk & 1][n].u[part] = tile_u32(tile_h2((v & c_mhi) | c_khi) + nhi[n]);
+            else bf[kk & 1][n].u[part] = tile_u32(tile_h2((v & c_mlo) | c_klo) + nlo[n]);
+        }
+    };
+    auto take_scale = [&](int step, auto RING, auto N_) {
+        const uint32_t g = tile_uniform(g0 + step * KW + kw);
+        union { uint16_t u; _Float16 h; } c; c.u = (uint16_t)(wsc[RING][N_] >> (IC ? 16 * (ft & 1) : 16 * (g & 1)));
+        sc[N_] = (float)c.h;
+    };
+    using I0 = std::integral_constant<int, 0>;
+
+    // ---- prologue ----
+    tile_for<8>([&](auto I) { request_x(0, 0, I); __builtin_amdgcn_sched_barrier(0); });
+    tile_for<2>([&](auto U) {
+        tile_for<NT>([&](auto N_) { load_w(U, U, N_, I0{}); __builtin_amdgcn_sched_barrier(0); });
+        tile_for<NT>([&](auto N_) { load_w(U, U, N_, std::integral_constant<int, 1>{}); load_sz(U, U, N_); __builtin_amdgcn_sched_barrier(0); });
+    });
+    tile_wait_vm<8>();                               // the first step's
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    tile_for<3>([&](auto I) { request_x(1, 1, I); });
+    tile_for<TB>([&](auto B) { read_x(0, B, I0{}); });
+    tile_for<NT>([&](auto N_) { tile_for<4>([&](auto P) { deq_piece(0, I0{}, N_, I0{}, P); }); });
+
+    auto multiply = [&](int step, auto U) {
+        constexpr int ring = U;
+        tile_for<KK>([&](auto KK_) {
+            constexpr int kk = KK_, nk = (kk + 1) % KK, nring = kk == KK - 1 ? ring ^ 1 : ring;
+            using NK = std::integral_constant<int, nk>; using NRing = std::integral_constant<int, nring>;
+            tile_for<4>([&](auto SL) {
+                constexpr int s = SL, n = s / TB, tb = s % TB;
+                if constexpr (kk == 0) tot[n][tb] += sc[n] * gacc[n][tb];      // of the group before
+                gacc[n][tb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(xa[kk & 1][tb], bf[kk & 1][n].h, kk == 0 ? zero : gacc[n][tb], 0, 0, 0);
+                if constexpr (kk == KK - 1 && s == 1) {
+                    // the next step's rows are in LDS, this wave's by the count (two weight requests are younger),
+                    // the others' by the barrier, behind which this step's buffer is free, too
+                    __builtin_amdgcn_s_waitcnt(0xc07f);
+                    tile_wait_vm<2>();
+                    __builtin_amdgcn_s_barrier();
+                    asm volatile("" ::: "memory");
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+                constexpr int rs = kk == KK - 1 ? s - 1 : s;
+                if constexpr (rs >= 0 && rs < TB) read_x(nring, std::integral_constant<int, (rs >= 0 && rs < TB ? rs : 0)>{}, NK{});
+                tile_for<2>([&](auto P) { deq_piece(nk ? step : step + 1, NRing{}, std::integral_constant<int, s / 2>{}, NK{}, std::integral_constant<int, s % 2 * 2 + P>{}); });
+                constexpr int xi = kk == KK - 1 ? s - 1 : kk == 0 ? s + 3 : kk == 1 && s == 0 ? 7 : -1;      // (2 at kk = 7 of the step before)
+                if constexpr (xi >= 0) request_x(kk == KK - 1 ? step + 2 : step + 1, kk == KK - 1 ? ring : ring ^ 1, std::integral_constant<int, (xi >= 0 ? xi : 0)>{});
+                if constexpr (kk == 3 && s < NT) load_w(step + 2, U, std::integral_constant<int, s % NT>{}, I0{});
+                if constexpr (kk == KK - 2 && s < NT) take_scale(step, U, std::integral_constant<int, s % NT>{});
+                if constexpr (kk == KK - 1 && s >= 2) {
+                    load_w(step + 2, U, std::integral_constant<int, s % NT>{}, std::integral_constant<int, 1>{});
+                    load_sz(step + 2, U, std::integral_constant<int, s % NT>{});
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            });
+        });
+    };
+    // Whole pairs of steps (an exit inside the loop would join the requests of two histories at its head).  Requests beyond the
+    // last group or token are out of range: codes, scales and rows in LDS become zeros.
+    for (int step = 0; step < n_steps; step += 2) {
+        multiply(step, I0{});
+        multiply(step + 1, std::integral_constant<int, 1>{});
+    }
+    tile_for<NT>([&](auto N_) { tile_for<TB>([&](auto B) { tot[N_][B] += sc[N_] * gacc[N_][B]; }); });
+
+    // ---- epilogue: of the two waves of a 64 x 64 tile each gives away 32 tokens and finishes the others.  A lane holds output
+    // lane % 32 of tokens 8 (r / 4) + 4 half + r % 4 ------------------------------------------------------------------
+    tile_wait_vm<0>();                               // nothing is on its way into the ring any more
+    __syncthreads();
+    float16v own[NT];
+    float4v *const sums = (float4v *)s_x;
+    auto exchange = [&](auto OWN) {
+        tile_for<NT>([&](auto N_) {
+            own[N_] = tot[N_][OWN];
+            const float16v &v = tot[N_][1 - OWN];
+            tile_for<4>([&](auto R) { sums[((wave * NT + N_) * 4 + R) * 64 + lane] = float4v{v[(int)R * 4], v[(int)R * 4 + 1], v[(int)R * 4 + 2], v[(int)R * 4 + 3]}; });
+        });
+    };
+    if (kw == 0) exchange(I0{});
+    else exchange(std::integral_constant<int, 1>{});
+    __syncthreads();
+    if (n_rows <= 0) return;
+    const int r0 = mw * 64 + kw * 32, other = wave ^ (NW * MW);
+    tile_for<NT>([&](auto N_) {
+        tile_for<4>([&](auto R) {
+            const float4v v = sums[((other * NT + N_) * 4 + R) * 64 + lane];
+            tile_for<4>([&](auto E) { own[N_][(int)R * 4 + E] += v[(int)E]; });
+        });
+    });
+    if (a.partial) {
+        const __amdgpu_buffer_rsrc_t pr = tile_partials(a, kslice, m0, rows);
+        tile_for<NT>([&](auto N_) {
+            if (N_ * 32 + r32 < n_rows)
+                tile_for<16>([&](auto E) {
+                    __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(own[N_][(int)E]), pr, ((r0 + half * 4 + E / 4 * 8 + E % 4) * a.N + n0 + N_ * 32 + r32) * 4, 0, kAuxThrough);
+                });
+        });
+        return;
+    }
+    // 32 x 64 through a wave-private part of LDS (rows padded by 16 bytes), out as 16-byte stores, eight of them a line
+    constexpr int kRow = 72;
+    _Float16 *const strip = (_Float16 *)(s_x + kTile2Stage) + wave * (32 * kRow);
+    const __amdgpu_buffer_rsrc_t yr = tile_outputs(a, m0, rows);
+    tile_for<NT>([&](auto N_) {
+        const float bv = a.bias && N_ * 32 + r32 < n_rows ? (float)a.bias[n0 + N_ * 32 + r32] : 0.f;
+        tile_for<16>([&](auto E) { strip[(half * 4 + E / 4 * 8 + E % 4) * kRow + N_ * 32 + r32] = (_Float16)(own[N_][(int)E] + bv); });
+    });
+    __builtin_amdgcn_wave_barrier();
+    const int ocol = (lane & 7) * 8;
+    tile_for<4>([&](auto H) {
+        const int orow = H * 8 + (lane >> 3);
+        const u32x4 o = *(const u32x4 *)(strip + orow * kRow + ocol);
+        if (ocol < n_rows) __builtin_amdgcn_raw_buffer_store_b128(o, yr, ((r0 + orow) * (int)a.ldy + n0 + ocol) * 2, 0, kAuxThrough);
+    });
+}
+
+template <bool TWO, bool IC>
 static hipError_t launch_tile_cfg(TileArgs &a, hipStream_t s)
 {
-    a.m_tiles = (a.T + 64 * MW - 1) / (64 * MW); a.n_tiles = (a.N + 32 * NW - 1) / (32 * NW);
+    constexpr auto kernel = TWO ? linear_tile2_kernel<IC> : linear_tile_kernel<IC>;
+    constexpr int tm = TWO ? 128 : 64, lds = TWO ? kTile2Lds : 2 * kTileBuf;
+    a.m_tiles = (a.T + tm - 1) / tm; a.n_tiles = (a.N + 127) / 128;
     const unsigned blocks = (unsigned)(((size_t)a.m_tiles * a.n_tiles * a.k_split + 7) / 8 * 8);
     static std::atomic<uint64_t> attr_done{0};
     if (const int dev = once_pending(attr_done); dev >= 0) {
-        hipError_t e = hipFuncSetAttribute((const void *)linear_tile_kernel<MW, NW, KW, IC>, hipFuncAttributeMaxDynamicSharedMemorySize, 2 * kTileBuf);
+        hipError_t e = hipFuncSetAttribute((const void *)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
         if (e != hipSuccess) return e;
         once_done(attr_done, dev);
     }
-    hipLaunchKernelGGL((linear_tile_kernel<MW, NW, KW, IC>), dim3(blocks), dim3(kTileThreads), 2 * kTileBuf, s, a);
+    hipLaunchKernelGGL(kernel, dim3(blocks), dim3(kTileThreads), lds, s, a);
     return hipGetLastError();
 }
 
-
-// Which tile, and how many slices of K: the least of a cost model fitted to 4700 timings (58 shapes from 512 to 27648
-// channels and 512 to 55296 outputs, 33 to 2048 tokens; 7 % off in the mean): 1.6 us, per round of 256 blocks 3.5 us (first
-// requests, stores) and 0.96 us per step, 1.09 us where the blocks fill the chip, and for split K 1.7 us (the summing
-// launch's share of a graph; begin to end in a trace it is 4), 0.23 us per slice and the partial tiles at 6.9 TB/s.
+// Which tile, and how many slices of K: the least of a cost model fitted to 521 timings with either forced (13 shapes, 80 to 900
+// tokens; 4 and 5 % off in the mean, the choice costs 0.2 % over the best, 5 % at most): a fixed time, per round of 256 blocks
+// the first requests and the stores, and the steps, longer where the blocks fill the chip; for split K the summing launch and
+// the partial tiles.  128-token tiles take 0.8 of the time per token, but their blocks are longer and begin slower: 4096 -> 28672
+// at 128 tokens 39 us against 47, 4096 -> 4096 at 201 tokens 21.5 against 18.8.
 struct TilePlan { bool two_m; int k_split, groups_per_split; double est_us; };
 static TilePlan plan_tile(int c_in, int c_out, int T)
 {
+    struct Fit { double call, round, step, step_full, sum, slice, mb; };
+    // est_us stays the model that the lines to the other kernels were fitted with (low by up to 2 us on few steps, high by up to a
+    // fifth on 128-token tiles): the GEMM rounds the weights to fp16, and no call is to lose precision.
+    double lines_us = 1e30;
+    static const Fit fits[2] = {{1.7, 3.8, 0.94, 1.04, 1.3, 0.27, 0.151}, {3.0, 4.2, 1.49, 1.71, 0.5, 0.245, 0.189}};
     TilePlan best{false, 1, 0, 1e30};
     const int G = c_in / kGroup, n_tiles = (c_out + 127) / 128;
     for (int two = 0; two <= (T > 64 ? 1 : 0); ++two) {
+        const Fit &f = fits[two];
         const int m_tiles = (T + (two ? 127 : 63)) / (two ? 128 : 64);
         for (int ks = 1; ks <= 16 && (ks == 1 || (ks * 4 <= G && (long)m_tiles * n_tiles * ks <= 512)); ++ks) {
-            const int gps = ((G + ks - 1) / ks + 3) / 4 * 4;             // whole steps of either tile, an even number of them
+            const int gps = ((G + ks - 1) / ks + 3) / 4 * 4;             // whole steps, an even number of them
             if ((G + gps - 1) / gps != ks) continue;
             const long blocks = (long)m_tiles * n_tiles * ks, rounds = ((blocks + 7) / 8 + 31) / 32;
-            const double step_us = (blocks >= 160 ? 1.09 : 0.96) - (two ? 0.04 : 0.0);
-            double us = 1.6 + (double)rounds * (3.5 + (two ? gps : gps / 2) * step_us);
-            if (ks > 1) us += 1.7 + 0.23 * ks + (double)ks * T * c_out * 8.0 / 6.9e6;
+            double us = f.call + (double)rounds * (f.round + gps / 2 * (blocks >= 160 ? f.step_full : f.step));
+            if (ks > 1) us += f.sum + f.slice * ks + (double)ks * T * c_out * 8.0e-6 * f.mb;
             if (us < best.est_us) best = TilePlan{two != 0, ks, gps, us};
+            double line = 1.6 + (double)rounds * (3.5 + (two ? gps : gps / 2) * ((blocks >= 160 ? 1.09 : 0.96) - (two ? 0.04 : 0.0)));
+            if (ks > 1) line += 1.7 + 0.23 * ks + (double)ks * T * c_out * 8.0 / 6.9e6;
+            lines_us = std::min(lines_us, line);
         }
     }
+    best.est_us = lines_us;
     return best;
 }
 
@@ -345,8 +610,8 @@ hipError_t launch_linear_tile(const paro_w4_weight &w, bool interchange, const p
     }
     a.k_split = p.k_split; a.groups_per_split = p.groups_per_split;
     a.partial = p.k_split > 1 ? (float *)scratch : nullptr;
-    hipError_t e = interchange ? (p.two_m ? launch_tile_cfg<2, 4, 1, true>(a, s) : launch_tile_cfg<1, 4, 2, true>(a, s))
-                               : (p.two_m ? launch_tile_cfg<2, 4, 1, false>(a, s) : launch_tile_cfg<1, 4, 2, false>(a, s));
+    const hipError_t e = interchange ? (p.two_m ? launch_tile_cfg<true, true>(a, s) : launch_tile_cfg<false, true>(a, s))
+                                     : (p.two_m ? launch_tile_cfg<true, false>(a, s) : launch_tile_cfg<false, false>(a, s));
     if (e != hipSuccess || p.k_split == 1) return e;
     return launch_splitk_reduce(a.partial, p.k_split, T, 0, w.c_out, w.bias, Y, ldy, least, s);
 }

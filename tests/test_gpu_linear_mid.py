@@ -61,6 +61,8 @@ CASES = [
     # the last behind a rotation: operand order with 64 outputs per block and K split
     (65, 640, 16400, "plain"), (66, 2560, 6160, "plain"), (67, 512, 16400, "packed"), (66, 14336, 4112, "packed"), (64, 14336, 2064, "packed"),
     (127, 8704, 1040, "packed"),
+    # 128-token tiles, groups that do not come in whole pairs of steps, ragged last slices and tiles of 16 outputs
+    (66, 5248, 8208, "plain"), (129, 1152, 12304, "plain"), (66, 4608, 8208, "packed"), (129, 2560, 12304, "packed"), (383, 1536, 6160, "packed"),
 ]
 
 
