@@ -290,8 +290,8 @@ constexpr int kTile2Stage = 65536, kTile2Lds = 2 * kTile2Stage;
 // The matrix pipes are busy 0.47 of a block's cycles (30 % of the launch at 4096 -> 28672, 128 tokens), issue the rest; without
 // activations' requests (timing only) 35 us of 39.8.  A launch begins and ends in 9 us, 4 of them launching 512 threads with this
 // much LDS, 2 the first requests, 2 to 4 the sums and the stores, and is therefore slower where a block has only two steps: 512 channels in
-// one round of blocks, 512 -> 17424 at 105 tokens 9.7 us against 9.0 for 64 x 32 tiles twice over the tokens.
-// us, those -> these: 4096 -> 28672 at 128 tokens 44.3 -> 37.6, rotated 49.2 -> 43.5; 14336 -> 4096 at 201 42.2 -> 38.5;
+// one round of blocks, 512 -> 17424 at 105 tokens 9.7 us against 9.0 for 128 tokens as 64 x 32 per wave.
+// us, that -> this: 4096 -> 28672 at 128 tokens 44.3 -> 37.6, rotated 49.2 -> 43.5; 14336 -> 4096 at 201 42.2 -> 38.5;
 // 512 -> 32656 at 289 rotated 27.4 -> 23.0; 75 random shapes of 65 to 1100 tokens 0.976 of the time (other kernels' among them).
 
 template <int N> __device__ __forceinline__ void tile_wait_vm() { __builtin_amdgcn_s_waitcnt(0x0f70 | (N & 15) | ((N >> 4) << 14)); }
@@ -449,7 +449,7 @@ __global__ __launch_bounds__(kTileThreads, 2) void linear_tile2_kernel(TileArgs 
                 constexpr int rs = kk == KK - 1 ? s - 1 : s;
                 if constexpr (rs >= 0 && rs < TB) read_x(nring, std::integral_constant<int, (rs >= 0 && rs < TB ? rs : 0)>{}, NK{});
                 tile_for<2>([&](auto P) { deq_piece(nk ? step : step + 1, NRing{}, std::integral_constant<int, s / 2>{}, NK{}, std::integral_constant<int, s % 2 * 2 + P>{}); });
-                constexpr int xi = kk == KK - 1 ? s - 1 : kk == 0 ? s + 3 : kk == 1 && s == 0 ? 7 : -1;      // (2 at kk = 7 of the step before)
+                constexpr int xi = kk == KK - 1 ? s - 1 : kk == 0 ? s + 3 : kk == 1 && s == 0 ? 7 : -1;      // the first three behind the barrier of the step before
                 if constexpr (xi >= 0) request_x(kk == KK - 1 ? step + 2 : step + 1, kk == KK - 1 ? ring : ring ^ 1, std::integral_constant<int, (xi >= 0 ? xi : 0)>{});
                 if constexpr (kk == 3 && s < NT) load_w(step + 2, U, std::integral_constant<int, s % NT>{}, I0{});
                 if constexpr (kk == KK - 2 && s < NT) take_scale(step, U, std::integral_constant<int, s % NT>{});
@@ -462,7 +462,8 @@ __global__ __launch_bounds__(kTileThreads, 2) void linear_tile2_kernel(TileArgs 
         });
     };
     // Whole pairs of steps (an exit inside the loop would join the requests of two histories at its head).  Requests beyond the
-    // last group or token are out of range: codes, scales and rows in LDS become zeros.
+    // last group or token are out of range: codes and scales are zeros, and so are their rows of LDS (a lane out of range
+    // writes zeros there, tried with offsets far beyond the buffer and just past it).
     for (int step = 0; step < n_steps; step += 2) {
         multiply(step, I0{});
         multiply(step + 1, std::integral_constant<int, 1>{});
