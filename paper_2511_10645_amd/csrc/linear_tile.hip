@@ -544,12 +544,18 @@ static hipError_t launch_tile_cfg(TileArgs &a, hipStream_t s)
 // the partial tiles.  128-token tiles take 0.8 of the time per token, but their blocks are longer and begin slower: 4096 -> 28672
 // at 128 tokens 39 us against 47, 4096 -> 4096 at 201 tokens 21.5 against 18.8.
 struct TilePlan { bool two_m; int k_split, groups_per_split; double est_us; };
-static TilePlan plan_tile(int c_in, int c_out, int T)
+static size_t tile_partial_bytes(int k_split, int T, int c_out) { return k_split > 1 ? (size_t)k_split * T * c_out * sizeof(float) : 0; }
+// room: bytes for partial tiles; what needs more is not planned.  (Bare calls on interchange weights have none: unsplit with the
+// tile that was best for the split, 13696 -> 1936 at 757 tokens takes 106 us, with the one that is best unsplit 63; 18 such
+// calls 0.54 to 0.70 of the time.)
+static TilePlan plan_tile(int c_in, int c_out, int T, size_t room)
 {
     struct Fit { double call, round, step, step_full, sum, slice, mb; };
     // est_us stays the model that the lines to the other kernels were fitted with (low by up to 2 us on few steps, high by up to a
-    // fifth on 128-token tiles): the GEMM rounds the weights to fp16, and no call is to lose precision.
-    double lines_us = 1e30;
+    // fifth on 128-token tiles): the GEMM rounds the weights to fp16, and no call is to lose precision.  Where neither model's choice
+    // has room, the kernel with fewer slices is as slow as the others, and they stay.
+    double lines_us = 1e30, least_us = 1e30;
+    bool line_fits = false, least_fits = false;
     static const Fit fits[2] = {{1.7, 3.8, 0.94, 1.04, 1.3, 0.27, 0.151}, {3.0, 4.2, 1.49, 1.71, 0.5, 0.245, 0.189}};
     TilePlan best{false, 1, 0, 1e30};
     const int G = c_in / kGroup, n_tiles = (c_out + 127) / 128;
@@ -559,30 +565,31 @@ static TilePlan plan_tile(int c_in, int c_out, int T)
         for (int ks = 1; ks <= 16 && (ks == 1 || (ks * 4 <= G && (long)m_tiles * n_tiles * ks <= 512)); ++ks) {
             const int gps = ((G + ks - 1) / ks + 3) / 4 * 4;             // whole steps, an even number of them
             if ((G + gps - 1) / gps != ks) continue;
+            const bool fits_room = tile_partial_bytes(ks, T, c_out) <= room;
             const long blocks = (long)m_tiles * n_tiles * ks, rounds = ((blocks + 7) / 8 + 31) / 32;
             double us = f.call + (double)rounds * (f.round + gps / 2 * (blocks >= 160 ? f.step_full : f.step));
             if (ks > 1) us += f.sum + f.slice * ks + (double)ks * T * c_out * 8.0e-6 * f.mb;
-            if (us < best.est_us) best = TilePlan{two != 0, ks, gps, us};
+            if (us < least_us) { least_us = us; least_fits = fits_room; }
+            if (fits_room && us < best.est_us) best = TilePlan{two != 0, ks, gps, us};
             double line = 1.6 + (double)rounds * (3.5 + (two ? gps : gps / 2) * ((blocks >= 160 ? 1.09 : 0.96) - (two ? 0.04 : 0.0)));
             if (ks > 1) line += 1.7 + 0.23 * ks + (double)ks * T * c_out * 8.0 / 6.9e6;
-            lines_us = std::min(lines_us, line);
+            if (line < lines_us) { lines_us = line; line_fits = fits_room; }
         }
     }
-    best.est_us = lines_us;
+    best.est_us = line_fits || least_fits ? lines_us : 1e30;
     return best;
 }
 
-double linear_tile_estimate_us(const paro_w4_weight &w, int T) { return plan_tile(w.c_in, w.c_out, T).est_us; }
+double linear_tile_estimate_us(const paro_w4_weight &w, int T, size_t room) { return plan_tile(w.c_in, w.c_out, T, room).est_us; }
 
-size_t linear_tile_scratch_bytes(const paro_w4_weight &w, int T)
+size_t linear_tile_scratch_bytes(const paro_w4_weight &w, int T, size_t room)
 {
-    const TilePlan p = plan_tile(w.c_in, w.c_out, T);
-    return p.k_split > 1 ? (size_t)p.k_split * T * w.c_out * sizeof(float) : 0;
+    return tile_partial_bytes(plan_tile(w.c_in, w.c_out, T, room).k_split, T, w.c_out);
 }
 
-void linear_tile_plan(const paro_w4_weight &w, int T, int &tokens, int &k_slices)
+void linear_tile_plan(const paro_w4_weight &w, int T, size_t room, int &tokens, int &k_slices)
 {
-    const TilePlan p = plan_tile(w.c_in, w.c_out, T);
+    const TilePlan p = plan_tile(w.c_in, w.c_out, T, room);
     tokens = p.two_m ? 128 : 64; k_slices = p.k_split;
 }
 
@@ -596,7 +603,7 @@ bool linear_tile_supported(const paro_w4_weight &w, bool interchange)
 hipError_t launch_linear_tile(const paro_w4_weight &w, bool interchange, const paro_half_t *X, int64_t ldx, paro_half_t *Y,
                               int64_t ldy, int T, void *scratch, size_t scratch_bytes, const void *least, hipStream_t s)
 {
-    TilePlan p = plan_tile(w.c_in, w.c_out, T);
+    const TilePlan p = plan_tile(w.c_in, w.c_out, T, scratch && ((uintptr_t)scratch % 16) == 0 ? scratch_bytes : 0);
     TileArgs a;
     a.w = interchange ? (const char *)w.qweight : (const char *)w.packed;
     a.scales_off = (uint32_t)packed_tiles_bytes(w.c_in, w.c_out);
@@ -605,10 +612,6 @@ hipError_t launch_linear_tile(const paro_w4_weight &w, bool interchange, const p
     a.X = (const _Float16 *)X; a.ldx = ldx; a.Y = (_Float16 *)Y; a.ldy = ldy; a.bias = (const _Float16 *)w.bias;
     a.T = T; a.C = w.c_in; a.N = w.c_out; a.G = w.c_in / kGroup;
     a.m_lo = 0x000F000Fu; a.m_hi = 0x00F000F0u; a.k_lo = 0x64006400u; a.k_hi = 0x54005400u;
-    if (p.k_split > 1 && !(scratch && scratch_bytes >= (size_t)p.k_split * T * w.c_out * sizeof(float) && ((uintptr_t)scratch % 16) == 0)) {
-        if (!interchange) return hipErrorInvalidValue;                   // the caller takes another kernel then
-        p.k_split = 1; p.groups_per_split = (a.G + 3) / 4 * 4;           // no room for partial tiles
-    }
     a.k_split = p.k_split; a.groups_per_split = p.groups_per_split;
     a.partial = p.k_split > 1 ? (float *)scratch : nullptr;
     const hipError_t e = interchange ? (p.two_m ? launch_tile_cfg<true, true>(a, s) : launch_tile_cfg<false, true>(a, s))

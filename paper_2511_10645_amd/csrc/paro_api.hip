@@ -209,10 +209,9 @@ LinearRoute linear_route(const paro_w4_weight &w, int64_t ldx, int64_t ldy, int 
     // most per product.  The models are 6 to 15 % off, hence 0.9: over 5131 measured bare (shape, tokens) pairs (649 shapes,
     // 33 to 1024 tokens, every route forced) the choice loses more than 3 % on three (4 % there) and takes 1.32x less
     // time in the mean than the better of the other two, 1.34x being the best possible (8192 -> 16384 at 640 tokens, not
-    // among them, loses 6 %: 201 us against the GEMM's 189).  Above 1024 tokens it has no shape to itself.  Without room for its partial
-    // tiles it would run unsplit and as slow as the others.
-    if (T > kStreamPassTokens && T <= 1024 && linear_tile_supported(w, false) && linear_tile_scratch_bytes(w, T) <= scratch_bytes) {
-        const double tile_us = linear_tile_estimate_us(w, T);
+    // among them, loses 6 %: 201 us against the GEMM's 189).  Above 1024 tokens it has no shape to itself.
+    if (T > kStreamPassTokens && T <= 1024 && linear_tile_supported(w, false)) {
+        const double tile_us = linear_tile_estimate_us(w, T, scratch_bytes);
         if (tile_us < 0.9 * us) return {LinearRoute::kTile, tile_us};
     }
     return {gemm ? LinearRoute::kGemm : LinearRoute::kStream, us};
@@ -223,7 +222,7 @@ paro_status run_linear(const paro_w4_weight *w, const paro_half_t *X, int64_t ld
                        void *ws, const Scratch &scratch, hipStream_t s)
 {
     auto tile = [&](bool interchange) {
-        const size_t need = linear_tile_scratch_bytes(*w, T);
+        const size_t need = linear_tile_scratch_bytes(*w, T, scratch.bytes);
         return from_hip(launch_linear_tile(*w, interchange, X, ldx, Y, ldy, T, scratch.partials(need), need, scratch.least, s));
     };
     if (!fast_weight(w)) {
@@ -470,9 +469,11 @@ static paro_status rotated_linear(const paro_rotation *rot, const paro_w4_weight
     return run_linear(w, xr, w->c_in, Y, ldy, T, ws, scratch, s);
 }
 
-int paro_internal_linear_plan(const paro_rotation *rot, const paro_w4_weight *w, int32_t T, int32_t *tile, int32_t *k_slices)
+int paro_internal_linear_plan_in(const paro_rotation *rot, const paro_w4_weight *w, int32_t T, size_t ws_bytes, int32_t *tile, int32_t *k_slices)
 {
-    const WsLayout L = ws_layout(rot, w, T);
+    const WsLayout L = ws_layout_fit(rot, w, T, (const void *)256, ws_bytes);
+    *tile = -1; *k_slices = 0;
+    if (ws_bytes < L.total) return kPlanGeneric;
     const size_t scratch = L.extra_bytes + L.gemm_bytes;
     int t = 0, k = 0, kernel = kPlanGeneric;
     if (rot && fused_decode(rot, w, T)) kernel = kPlanHosted;
@@ -483,9 +484,14 @@ int paro_internal_linear_plan(const paro_rotation *rot, const paro_w4_weight *w,
         if (kernel == kPlanStream) t = rot && rot->plan && decode_wide_operand_pays(w->c_in, T);
     } else if (linear_rows_supported(*w, w->c_in, T)) { kernel = kPlanRows; k = scratch ? (int)(linear_rows_scratch_bytes(*w, T) / ((size_t)T * w->c_out * 4)) : 1; }
     else if (T > kStreamPassTokens && linear_tile_supported(*w, true)) kernel = kPlanTile;
-    if (kernel == kPlanTile) { linear_tile_plan(*w, T, t, k); if (linear_tile_scratch_bytes(*w, T) > scratch) k = 1; }
+    if (kernel == kPlanTile) linear_tile_plan(*w, T, scratch, t, k);
     *tile = t; *k_slices = k;
     return kernel;
+}
+
+int paro_internal_linear_plan(const paro_rotation *rot, const paro_w4_weight *w, int32_t T, int32_t *tile, int32_t *k_slices)
+{
+    return paro_internal_linear_plan_in(rot, w, T, ws_layout(rot, w, T).total, tile, k_slices);
 }
 
 paro_status paro_rotated_linear(const paro_rotation *rot, const paro_w4_weight *w, const paro_half_t *X, int64_t ldx,

@@ -204,9 +204,10 @@ hipError_t launch_linear_operand(const paro_w4_weight &w, const paro_half_t *Xop
 
 // Tiled linear with the weights in registers (linear_tile.hip), repacked or interchange layout; scratch as above.
 bool linear_tile_supported(const paro_w4_weight &w, bool interchange);
-double linear_tile_estimate_us(const paro_w4_weight &w, int T);
-void linear_tile_plan(const paro_w4_weight &w, int T, int &tokens, int &k_slices);
-size_t linear_tile_scratch_bytes(const paro_w4_weight &w, int T);
+// room: bytes there are for partial tiles; a call with less than the best split wants is planned with fewer slices, or none.
+double linear_tile_estimate_us(const paro_w4_weight &w, int T, size_t room);
+void linear_tile_plan(const paro_w4_weight &w, int T, size_t room, int &tokens, int &k_slices);
+size_t linear_tile_scratch_bytes(const paro_w4_weight &w, int T, size_t room = SIZE_MAX);
 hipError_t launch_linear_tile(const paro_w4_weight &w, bool interchange, const paro_half_t *X, int64_t ldx, paro_half_t *Y,
                               int64_t ldy, int T, void *scratch, size_t scratch_bytes, const void *least, hipStream_t s);
 
@@ -234,3 +235,5 @@ hipError_t launch_gemm(const paro_w4_weight &w, const paro_half_t *X, int64_t ld
 // Host only: the tests pin with it that a shape reaches the kernel it is there for.
 enum { kPlanHosted, kPlanStream, kPlanGemm, kPlanTile, kPlanOperand, kPlanRows, kPlanGeneric };
 extern "C" int paro_internal_linear_plan(const paro_rotation *rot, const paro_w4_weight *w, int32_t T, int32_t *tile, int32_t *k_slices);
+// The same with a workspace of ws_bytes (at least what the call cannot do without); kPlanGeneric with tile -1 if that is refused.
+extern "C" int paro_internal_linear_plan_in(const paro_rotation *rot, const paro_w4_weight *w, int32_t T, size_t ws_bytes, int32_t *tile, int32_t *k_slices);

@@ -76,6 +76,9 @@ def test_linear_against_oracle(P, T, c_in, c_out, form, rotated):
 # (exchange header in front for repacked weights) otherwise.  Partial tiles that only save time are not insisted on.
 @pytest.mark.parametrize("T,c_in,c_out,form,rotated,least", [
     (600, 2048, 528, "packed", False, 0), (24, 11008, 272, "plain", True, 24 * 11008 * 2), (600, 2048, 528, "packed", True, 256 + 600 * 2048 * 2),
+    # the tiled kernel with fewer slices than it would like, none or those that the GEMM's room holds (test_linear_plans.py)
+    (568, 1536, 672, "packed", False, 0), (568, 1536, 672, "packed", True, 256 + 568 * 1536 * 2), (901, 2048, 688, "packed", False, 0),
+    (655, 13312, 672, "packed", False, 7386880), (200, 2176, 1296, "plain", True, 200 * 2176 * 2), (129, 4096, 1040, "plain", True, 129 * 4096 * 2),
 ])
 def test_least_workspace(P, T, c_in, c_out, form, rotated, least):
     _check_linear(P, T, c_in, c_out, form, rotated, least)

@@ -21,6 +21,16 @@ def plan(T, c_in, c_out, form, rotated):
     return kernel, tile.value, k_slices.value
 
 
+def plan_in(T, c_in, c_out, form, rotated, ws_bytes):
+    f = paro.lib().paro_internal_linear_plan_in
+    f.restype, f.argtypes = ctypes.c_int, [ctypes.c_void_p, ctypes.c_void_p, ctypes.c_int32, ctypes.c_size_t, ctypes.c_void_p, ctypes.c_void_p]
+    w = _CW4Weight(c_in, c_out, 128, None, None, None, None, FAKE) if form == "packed" else _CW4Weight(c_in, c_out, 128, FAKE, FAKE, FAKE, None, None)
+    rot = _CRotation(c_in, 128, 8, 64, FAKE, FAKE, None, 0, FAKE)
+    tile, k_slices = ctypes.c_int32(), ctypes.c_int32()
+    kernel = f(ctypes.byref(rot) if rotated else None, ctypes.byref(w), T, ws_bytes, ctypes.byref(tile), ctypes.byref(k_slices))
+    return kernel, tile.value, k_slices.value
+
+
 def test_cases_reach_every_kernel():
     have = set()
     for T, c_in, c_out, form in CASES:
@@ -51,3 +61,22 @@ def test_long_rows_at_64_tokens_stay_on_the_tiled_kernel():
     """Rotated 14336 -> 4096 on weights that no cache holds: operand order 27.0 us, the tiled kernel 24.5."""
     assert plan(64, 14336, 4096, "packed", True)[0] == TILE
     assert plan(64, 4096, 4096, "packed", True)[0] == OPERAND
+
+
+def test_little_workspace_does_not_cost_precision():
+    """Calls without room for the slices of K that the tiled kernel would like run on it all the same, unsplit or with the slices
+    there is room for (the GEMM's own partial tiles), not on the GEMM, which rounds the weights to fp16."""
+    for T, c_in, c_out, least, k in ((568, 1536, 672, 0, 1), (901, 2048, 688, 0, 1), (666, 1536, 544, 0, 1), (959, 2048, 656, 0, 1),
+                                     (565, 20480, 976, 9447936, 3), (655, 13312, 672, 7386880, 3)):
+        assert plan_in(T, c_in, c_out, "packed", False, least) == (TILE, 64, k), (T, c_in, c_out)
+        header = 0 if least else 256                  # the bare call's least workspace has the exchange header, or is empty
+        assert plan_in(T, c_in, c_out, "packed", True, header + least + T * c_in * 2) == (TILE, 64, k), (T, c_in, c_out)
+        assert plan(T, c_in, c_out, "packed", False)[2] > k
+
+
+def test_calls_without_room_are_planned_unsplit():
+    """Bare calls on interchange weights have no room for partial tiles: the tile is the one that is faster unsplit (64 tokens;
+    measured 86, 63 and 93 us, with 128-token tiles 139, 106 and 158), not the one that would be with K split."""
+    for T, c_in, c_out in ((92, 17664, 14640), (757, 13696, 1936), (121, 20736, 9856)):
+        assert plan(T, c_in, c_out, "plain", False) == (TILE, 64, 1), (T, c_in, c_out)
+        assert plan(T, c_in, c_out, "plain", True)[1:] > (64, 1)
