@@ -455,21 +455,34 @@ __global__ __launch_bounds__(256, 2) void mxfp4_gemm_kernel(MxGemmArgs a)
 
     // ---- prologue ----
     using I0 = std::integral_constant<int, 0>; using I1 = std::integral_constant<int, 1>; using I2 = std::integral_constant<int, 2>;
+    // Requests leave in the order written, which the wait below counts on (the compiler moved the weights of K-steps 1 and 2 behind
+    // everything else, which was safe; in front of pair 0 they would not be).
+    auto in_order = [] { __builtin_amdgcn_sched_barrier(0); };
     load_xs(0);
     load_ws(0, I0{});
+    in_order();
     load_x(0);
+    in_order();
     mx_for<NTW>([&](auto NT) { load_w(0, I0{}, NT, I0{}); load_w(0, I0{}, NT, I1{}); });
+    in_order();
     load_x(1);
+    in_order();
     mx_for<NTW>([&](auto NT) { load_w(1, I1{}, NT, I0{}); load_w(1, I1{}, NT, I1{}); });
+    in_order();
     load_x(2);
+    in_order();
     mx_for<NTW>([&](auto NT) { load_w(2, I2{}, NT, I0{}); load_w(2, I2{}, NT, I1{}); });
+    in_order();
     store_xs(0);
+    in_order();
     load_xs(1);
     load_ws(1, I1{});
-    // activations of pair 0 are in LDS when at most the requests made after them are outstanding
+    in_order();
+    // activations of pair 0 are in LDS when at most the requests made after them are outstanding (8 NTW + 9)
     mx_wait_vm<8 * NTW>();
     __builtin_amdgcn_s_waitcnt(0xc07f);                      // LDS writes done
     __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
     mx_for<kAhead>([&](auto Q) { read_x(smem_mx, Q); });
     mx_for<MT>([&](auto M) { xsd[M] = *(const uint32_t *)(scales + fs + M * 128); });
 
@@ -492,6 +505,7 @@ __global__ __launch_bounds__(256, 2) void mxfp4_gemm_kernel(MxGemmArgs a)
                         mx_wait_vm<8 * NTW>();
                         __builtin_amdgcn_s_waitcnt(0xc07f);
                         __builtin_amdgcn_s_barrier();
+                        asm volatile("" ::: "memory");
                         load_x(pair + 3);
                     }
                     if constexpr (qa + kAhead < 4 * MT) read_x(cur, std::integral_constant<int, qa + kAhead>{});
