@@ -316,7 +316,7 @@ __global__ __launch_bounds__(kTileThreads, 2) void linear_tile2_kernel(TileArgs 
     const int m0 = (int)tile_uniform(mt * TM), n0 = (int)tile_uniform(ntile * TN + nw * 64);
     const int rows = min(a.T - m0, TM);
     const int g0 = (int)tile_uniform(kslice * a.groups_per_split), g_end = min(a.G, g0 + a.groups_per_split);
-    const int n_steps = (g_end - g0 + KW - 1) / KW;
+    const int n_steps = (g_end - g0 + KW - 1) / KW, n_own = (int)tile_uniform((g_end - g0 - kw + KW - 1) / KW);   // groups of this wave
     const int r32 = lane & 31, half = lane >> 5, ft = lane & 15;
 
     // ---- activations: this wave requests 32 rows of one group of a step, 4 whole rows per request -------------------
@@ -435,7 +435,8 @@ __global__ __launch_bounds__(kTileThreads, 2) void linear_tile2_kernel(TileArgs 
             using NK = std::integral_constant<int, nk>; using NRing = std::integral_constant<int, nring>;
             tile_for<4>([&](auto SL) {
                 constexpr int s = SL, n = s / TB, tb = s % TB;
-                if constexpr (kk == 0) tot[n][tb] += sc[n] * gacc[n][tb];      // of the group before
+                if constexpr (kk == 0)
+                    if (step <= n_own) tot[n][tb] += sc[n] * gacc[n][tb];      // of the group before
                 gacc[n][tb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(xa[kk & 1][tb], bf[kk & 1][n].h, kk == 0 ? zero : gacc[n][tb], 0, 0, 0);
                 if constexpr (kk == KK - 1 && s == 1) {
                     // the next step's rows are in LDS, this wave's by the count (two weight requests are younger),
@@ -462,13 +463,16 @@ __global__ __launch_bounds__(kTileThreads, 2) void linear_tile2_kernel(TileArgs 
         });
     };
     // Whole pairs of steps (an exit inside the loop would join the requests of two histories at its head).  Requests beyond the
-    // last group or token are out of range: codes and scales are zeros, and so are their rows of LDS (a lane out of range
-    // writes zeros there, tried with offsets far beyond the buffer and just past it).
+    // last group or token are out of range and fetch nothing.  What then stands in LDS is multiplied but reaches no stored sum:
+    // tokens are rows of the product, and the sums of a group that does not exist are not added.
+    int steps_run = 0;
     for (int step = 0; step < n_steps; step += 2) {
         multiply(step, I0{});
         multiply(step + 1, std::integral_constant<int, 1>{});
+        steps_run = step + 2;
     }
-    tile_for<NT>([&](auto N_) { tile_for<TB>([&](auto B) { tot[N_][B] += sc[N_] * gacc[N_][B]; }); });
+    if (steps_run <= n_own)
+        tile_for<NT>([&](auto N_) { tile_for<TB>([&](auto B) { tot[N_][B] += sc[N_] * gacc[N_][B]; }); });
 
     // ---- epilogue: of the two waves of a 64 x 64 tile each gives away 32 tokens and finishes the others.  A lane holds output
     // lane % 32 of tokens 8 (r / 4) + 4 half + r % 4 ------------------------------------------------------------------
