@@ -4,7 +4,8 @@
 // At these sizes neither of the other kernels fits.  The streaming kernel keeps a K-slice of activations in registers (32
 // tokens fill half the register file) and re-reads the weights for every further 32 tokens.  The GEMM's 128 x 256 tiles are
 // few, pay for rows that do not exist and carry every weight through LDS as fp16.  Here a block is 8 waves and 64 or 128
-// tokens x 128 outputs.  Of 64 tokens every wave has 32 outputs and one of a step's two groups (128 tokens: below):
+// tokens x 128 outputs.  Every wave has 64 tokens x 32 outputs, with 64 tokens of one of a step's two groups (128 tokens of
+// more groups: below):
 //   - activations (32 KB per step) go through LDS, whole 256-byte rows per request, the 16-byte chunk index XOR-ed with the row
 //     so that both directions are conflict-free; requested two steps ahead, written one step ahead, re-read into the fragment
 //     registers slot by slot as these fall free;
@@ -86,14 +87,15 @@ __device__ inline __amdgpu_buffer_rsrc_t tile_partials(const TileArgs &a, int ks
 // 4096 -> 28672 (of 1.25 M instruction cycles of LDS), now 57 k; 1 to 4 % faster (LDS is not what bounds the kernel).
 __device__ inline int chunk_xor(int row) { return (row & 15) ^ ((row & 4) << 1); }
 
-template <bool IC>
+// MW: 64-token parts of the block's tile; one: the waves split a step's two groups, two: a step is one group
+template <int MW, bool IC>
 __global__ __launch_bounds__(kTileThreads, 2) void linear_tile_kernel(TileArgs a)
 {
-    constexpr int NW = 4, KW = 2, TB = 4, NT = 2, S = 16, TM = 64, TN = 32 * NW;
+    constexpr int NW = 4, KW = 2 / MW, TB = 4, NT = 2, S = 16, TM = 64 * MW, TN = 32 * NW;
     extern __shared__ __attribute__((aligned(16))) char s_x[];            // [2][KW][TM][256 B]
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int nw = wave % NW, kw = wave / NW;
+    const int nw = wave % NW, mw = wave / NW % MW, kw = wave / (NW * MW);
 
     // Consecutive tiles - token tiles first, then output tiles, then slices of K - on one XCD: its L2 serves a tile's
     // weights to the further token tiles and a slice's activations to the further output tiles, and every XCD has the
@@ -120,12 +122,12 @@ __global__ __launch_bounds__(kTileThreads, 2) void linear_tile_kernel(TileArgs a
     const int xw = srow * 256 + ((sc16 ^ chunk_xor(srow)) << 4);           // + 8192 i
     u32x4 xs[4];
     auto load_x = [&](int step, auto I) {
-        const int g = g0 + step * KW + (int)I / 2;                         // rows 0..63: the step's first group
+        const int g = g0 + step * KW + (KW == 1 ? 0 : (int)I / 2);         // rows 0..63 of KW = 2: the step's first group
         xs[I] = __builtin_amdgcn_raw_buffer_load_b128(xr, (int)(g < g_end ? xg[I] : kOobT), (int)tile_uniform(g * 256), 0);
     };
     auto store_x = [&](int buf, auto I) { *(u32x4 *)(s_x + buf * kTileBuf + xw + I * 8192) = xs[I]; };
     int xa_off[4];
-    tile_for<4>([&](auto J) { xa_off[J] = (kw * TM + ft) * 256 + (((fkb * 4 + J) ^ chunk_xor(ft)) << 4); });
+    tile_for<4>([&](auto J) { xa_off[J] = (kw * TM + mw * 64 + ft) * 256 + (((fkb * 4 + J) ^ chunk_xor(ft)) << 4); });
     half8 xa[TB][4];
     auto read_x = [&](int buf, auto B, auto J) { xa[B][J] = *(const half8 *)(s_x + buf * kTileBuf + xa_off[J] + B * 4096); };
 
@@ -242,7 +244,7 @@ __global__ __launch_bounds__(kTileThreads, 2) void linear_tile_kernel(TileArgs a
 
     // ---- epilogue: lane holds output ft of tokens 4 fkb .. + 3 of a 16 x 16 tile ------------------------------------
     __syncthreads();
-    {                                                // the second half of K through LDS (the loop's buffers are free)
+    if constexpr (KW == 2) {                         // the second half of K through LDS (the loop's buffers are free)
         float4v *sum = (float4v *)s_x + (size_t)(wave % 4) * TB * NT * 64;
         if (kw == 1) tile_for<TB>([&](auto B) { tile_for<NT>([&](auto N_) { sum[(B * NT + N_) * 64 + lane] = tot[B][N_]; }); });
         __syncthreads();
@@ -257,7 +259,7 @@ __global__ __launch_bounds__(kTileThreads, 2) void linear_tile_kernel(TileArgs a
 #pragma unroll
                 for (int r = 0; r < 4; ++r)
                     if (N_ * 16 < n_rows)
-                        __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(tot[B][N_][r]), pr, ((B * 16 + fkb * 4 + r) * a.N + n0 + ft + N_ * 16) * 4, 0, kAuxThrough);
+                        __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(tot[B][N_][r]), pr, ((mw * 64 + B * 16 + fkb * 4 + r) * a.N + n0 + ft + N_ * 16) * 4, 0, kAuxThrough);
             });
         });
         return;
@@ -275,7 +277,7 @@ __global__ __launch_bounds__(kTileThreads, 2) void linear_tile_kernel(TileArgs a
         });
         __builtin_amdgcn_wave_barrier();
         const u32x4 v = *(const u32x4 *)(strip + orow * 32 + ocol);
-        if (ocol < n_rows) __builtin_amdgcn_raw_buffer_store_b128(v, yr, ((B * 16 + orow) * (int)a.ldy + n0 + ocol) * 2, 0, kAuxThrough);
+        if (ocol < n_rows) __builtin_amdgcn_raw_buffer_store_b128(v, yr, ((mw * 64 + B * 16 + orow) * (int)a.ldy + n0 + ocol) * 2, 0, kAuxThrough);
         __builtin_amdgcn_wave_barrier();
     });
 }
@@ -289,8 +291,7 @@ constexpr int kTile2Stage = 65536, kTile2Lds = 2 * kTile2Stage;
 // anew at once.  Weights are two groups ahead in registers; what is multiplied next is read and dequantised while this is.
 // The matrix pipes are busy 0.47 of a block's cycles (30 % of the launch at 4096 -> 28672, 128 tokens), issue the rest; without
 // activations' requests (timing only) 35 us of 39.8.  A launch begins and ends in 9 us, 4 of them launching 512 threads with this
-// much LDS, 2 the first requests, 2 to 4 the sums and the stores, and is therefore slower where a block has only two steps: 512 channels in
-// one round of blocks, 512 -> 17424 at 105 tokens 9.7 us against 9.0 for 128 tokens as 64 x 32 per wave.
+// much LDS, 2 the first requests, 2 to 4 the sums and the stores: not for few groups (kTileWideGroups).
 // us, that -> this: 4096 -> 28672 at 128 tokens 44.3 -> 37.6, rotated 49.2 -> 43.5; 14336 -> 4096 at 201 42.2 -> 38.5;
 // 512 -> 32656 at 289 rotated 27.4 -> 23.0; 75 random shapes of 65 to 1100 tokens 0.976 of the time (other kernels' among them).
 
@@ -525,11 +526,12 @@ __global__ __launch_bounds__(kTileThreads, 2) void linear_tile2_kernel(TileArgs 
     });
 }
 
-template <bool TWO, bool IC>
+// MW: 64-token parts of the tile; WIDE: 64 x 64 per wave (two parts)
+template <int MW, bool WIDE, bool IC>
 static hipError_t launch_tile_cfg(TileArgs &a, hipStream_t s)
 {
-    constexpr auto kernel = TWO ? linear_tile2_kernel<IC> : linear_tile_kernel<IC>;
-    constexpr int tm = TWO ? 128 : 64, lds = TWO ? kTile2Lds : 2 * kTileBuf;
+    constexpr auto kernel = WIDE ? linear_tile2_kernel<IC> : linear_tile_kernel<MW, IC>;
+    constexpr int tm = 64 * MW, lds = WIDE ? kTile2Lds : 2 * kTileBuf;
     a.m_tiles = (a.T + tm - 1) / tm; a.n_tiles = (a.N + 127) / 128;
     const unsigned blocks = (unsigned)(((size_t)a.m_tiles * a.n_tiles * a.k_split + 7) / 8 * 8);
     static std::atomic<uint64_t> attr_done{0};
@@ -542,11 +544,18 @@ static hipError_t launch_tile_cfg(TileArgs &a, hipStream_t s)
     return hipGetLastError();
 }
 
+// 128-token tiles with fewer groups per block than this keep 64 x 32 per wave: a block of the wide kernel begins slower and takes
+// groups in fours.  us, narrow / wide: 512 channels 9.1 / 10.2 (-> 16384 at 200 tokens), 1024 13.3 / 13.7, 1536 17.5 / 17.7 (but
+// 17.2 / 16.9 -> 17424 at 105, a tie over 12 shapes), 2048 21.9 / 21.6 (and 1 to 5 % on 7 of 8 others); interchange layout,
+// 256 -> 16400 at 300 tokens 13.3 / 18.7, 640 -> 16384 at 512 21.9 / 25.8, 1152 -> 12304 at 129 15.8 / 16.9, 1408 -> 17424 a tie.
+constexpr int kTileWideGroups = 12;
+
 // Which tile, and how many slices of K: the least of a cost model fitted to 521 timings with either forced (13 shapes, 80 to 900
 // tokens; 4 and 5 % off in the mean, the choice costs 0.2 % over the best, 5 % at most): a fixed time, per round of 256 blocks
 // the first requests and the stores, and the steps, longer where the blocks fill the chip; for split K the summing launch and
 // the partial tiles.  128-token tiles take 0.8 of the time per token, but their blocks are longer and begin slower: 4096 -> 28672
-// at 128 tokens 39 us against 47, 4096 -> 4096 at 201 tokens 21.5 against 18.8.
+// at 128 tokens 39 us against 47, 4096 -> 4096 at 201 tokens 21.5 against 18.8.  128-token tiles of few groups: 24 shapes of the
+// interchange layout in one to five rounds, 2 % off.
 struct TilePlan { bool two_m; int k_split, groups_per_split; double est_us; };
 static size_t tile_partial_bytes(int k_split, int T, int c_out) { return k_split > 1 ? (size_t)k_split * T * c_out * sizeof(float) : 0; }
 // room: bytes for partial tiles; what needs more is not planned.  (Bare calls on interchange weights have none: unsplit with the
@@ -571,7 +580,10 @@ static TilePlan plan_tile(int c_in, int c_out, int T, size_t room)
             if ((G + gps - 1) / gps != ks) continue;
             const bool fits_room = tile_partial_bytes(ks, T, c_out) <= room;
             const long blocks = (long)m_tiles * n_tiles * ks, rounds = ((blocks + 7) / 8 + 31) / 32;
-            double us = f.call + (double)rounds * (f.round + gps / 2 * (blocks >= 160 ? f.step_full : f.step));
+            const int groups = std::min(G, gps);
+            double us = two && groups < kTileWideGroups
+                            ? 1.6 + (double)rounds * (3.5 + (groups + 1) / 2 * 2 * (blocks >= 160 ? 1.08 : 0.97))
+                            : f.call + (double)rounds * (f.round + gps / 2 * (blocks >= 160 ? f.step_full : f.step));
             if (ks > 1) us += f.sum + f.slice * ks + (double)ks * T * c_out * 8.0e-6 * f.mb;
             if (us < least_us) { least_us = us; least_fits = fits_room; }
             if (fits_room && us < best.est_us) best = TilePlan{two != 0, ks, gps, us};
@@ -618,8 +630,13 @@ hipError_t launch_linear_tile(const paro_w4_weight &w, bool interchange, const p
     a.m_lo = 0x000F000Fu; a.m_hi = 0x00F000F0u; a.k_lo = 0x64006400u; a.k_hi = 0x54005400u;
     a.k_split = p.k_split; a.groups_per_split = p.groups_per_split;
     a.partial = p.k_split > 1 ? (float *)scratch : nullptr;
-    const hipError_t e = interchange ? (p.two_m ? launch_tile_cfg<true, true>(a, s) : launch_tile_cfg<false, true>(a, s))
-                                     : (p.two_m ? launch_tile_cfg<true, false>(a, s) : launch_tile_cfg<false, false>(a, s));
+    const bool wide = p.two_m && std::min(a.G, p.groups_per_split) >= kTileWideGroups;
+    const hipError_t e = interchange ? (wide      ? launch_tile_cfg<2, true, true>(a, s)
+                                        : p.two_m ? launch_tile_cfg<2, false, true>(a, s)
+                                                  : launch_tile_cfg<1, false, true>(a, s))
+                                     : (wide      ? launch_tile_cfg<2, true, false>(a, s)
+                                        : p.two_m ? launch_tile_cfg<2, false, false>(a, s)
+                                                  : launch_tile_cfg<1, false, false>(a, s));
     if (e != hipSuccess || p.k_split == 1) return e;
     return launch_splitk_reduce(a.partial, p.k_split, T, 0, w.c_out, w.bias, Y, ldy, least, s);
 }

@@ -63,6 +63,7 @@ CASES = [
     (127, 8704, 1040, "packed"),
     # 128-token tiles, groups that do not come in whole pairs of steps, ragged last slices and tiles of 16 outputs
     (66, 5248, 8208, "plain"), (129, 1152, 12304, "plain"), (66, 4608, 8208, "packed"), (129, 2560, 12304, "packed"), (383, 1536, 6160, "packed"),
+    (65, 1664, 18400, "plain"), (105, 512, 17424, "packed"),
 ]
 
 
