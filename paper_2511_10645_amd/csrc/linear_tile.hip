@@ -70,8 +70,15 @@ constexpr int kTileThreads = 512, kTileBuf = 32768;
 
 // Results leave the L2 as they are written (sc1) instead of all at once at the end of the launch; rows beyond a tile's are
 // beyond the buffer.  us, plain stores / these: 4096 -> 28672 at 128 tokens 38.8 / 37.6, 14336 -> 4096 at 64 (partial tiles)
-// 24.0 / 23.4 rotated; no difference on 1024 -> 12304.
+// 24.0 / 23.4 rotated.  Not outputs whose rows do not begin on a cache line: two tiles share the line there, and each would write
+// its piece (512 -> 32656 at 128 tokens 10.7 / 11.8, 640 -> 8208 at 1000 31.2 / 32.2); partial tiles gain even so (8192 -> 1552 at
+// 129 tokens 16.3 / 15.6).
 constexpr int kAuxThrough = 16;
+__device__ __forceinline__ void tile_store(bool through, u32x4 v, __amdgpu_buffer_rsrc_t r, int off)
+{
+    if (through) __builtin_amdgcn_raw_buffer_store_b128(v, r, off, 0, kAuxThrough);
+    else __builtin_amdgcn_raw_buffer_store_b128(v, r, off, 0, 0);
+}
 __device__ inline __amdgpu_buffer_rsrc_t tile_outputs(const TileArgs &a, int m0, int rows)
 {
     return tile_rsrc(a.Y + (size_t)m0 * a.ldy, ((size_t)(rows - 1) * a.ldy + a.N) * 2);
@@ -265,6 +272,7 @@ __global__ __launch_bounds__(kTileThreads, 2) void linear_tile_kernel(TileArgs a
         return;
     }
     const __amdgpu_buffer_rsrc_t yr = tile_outputs(a, m0, rows);
+    const bool through = (((uintptr_t)a.Y | (uintptr_t)(a.ldy * 2)) & 127) == 0;
     // a 16 x 32 strip through a wave-private kilobyte of LDS, out as one 16-byte store per lane
     _Float16 *strip = (_Float16 *)(s_x + 2 * kTileBuf - 8192 + wave * 1024);
     float bv[NT];
@@ -277,7 +285,7 @@ __global__ __launch_bounds__(kTileThreads, 2) void linear_tile_kernel(TileArgs a
         });
         __builtin_amdgcn_wave_barrier();
         const u32x4 v = *(const u32x4 *)(strip + orow * 32 + ocol);
-        if (ocol < n_rows) __builtin_amdgcn_raw_buffer_store_b128(v, yr, ((mw * 64 + B * 16 + orow) * (int)a.ldy + n0 + ocol) * 2, 0, kAuxThrough);
+        if (ocol < n_rows) tile_store(through, v, yr, ((mw * 64 + B * 16 + orow) * (int)a.ldy + n0 + ocol) * 2);
         __builtin_amdgcn_wave_barrier();
     });
 }
@@ -513,6 +521,7 @@ __global__ __launch_bounds__(kTileThreads, 2) void linear_tile2_kernel(TileArgs 
     constexpr int kRow = 72;
     _Float16 *const strip = (_Float16 *)(s_x + kTile2Stage) + wave * (32 * kRow);
     const __amdgpu_buffer_rsrc_t yr = tile_outputs(a, m0, rows);
+    const bool through = (((uintptr_t)a.Y | (uintptr_t)(a.ldy * 2)) & 127) == 0;
     tile_for<NT>([&](auto N_) {
         const float bv = a.bias && N_ * 32 + r32 < n_rows ? (float)a.bias[n0 + N_ * 32 + r32] : 0.f;
         tile_for<16>([&](auto E) { strip[(half * 4 + E / 4 * 8 + E % 4) * kRow + N_ * 32 + r32] = (_Float16)(own[N_][(int)E] + bv); });
@@ -522,7 +531,7 @@ __global__ __launch_bounds__(kTileThreads, 2) void linear_tile2_kernel(TileArgs 
     tile_for<4>([&](auto H) {
         const int orow = H * 8 + (lane >> 3);
         const u32x4 o = *(const u32x4 *)(strip + orow * kRow + ocol);
-        if (ocol < n_rows) __builtin_amdgcn_raw_buffer_store_b128(o, yr, ((r0 + orow) * (int)a.ldy + n0 + ocol) * 2, 0, kAuxThrough);
+        if (ocol < n_rows) tile_store(through, o, yr, ((r0 + orow) * (int)a.ldy + n0 + ocol) * 2);
     });
 }
 

@@ -1,5 +1,6 @@
 """128-token tiles of linear_tile.hip where a block's groups do not fill its steps: what LDS holds in place of the missing ones
-reaches no output, be it NaN from an earlier launch or infinities of the call's own earlier steps."""
+reaches no output, be it NaN from an earlier launch or infinities of the call's own earlier steps; and outputs whose rows begin
+anywhere."""
 import numpy as np
 import pytest
 
@@ -35,3 +36,18 @@ def test_infinite_activations_stay_infinite_beside_missing_groups(P):
     for row, c in at.items():
         q = li.codes.reshape(c_out, c_in)[:, c].astype(int) - li.zeros[c // 128].astype(int)
         assert np.isnan(y[row][q == 0]).all() and (y[row][q > 0] == np.inf).all() and (y[row][q < 0] == -np.inf).all(), row
+
+
+@pytest.mark.parametrize("T,c_in,c_out", [(64, 512, 16384), (200, 512, 16384), (383, 1536, 6144)])
+def test_outputs_are_the_same_wherever_their_rows_begin(P, T, c_in, c_out):
+    """Rows that are whole cache lines are stored another way than others: 64-token tiles, 128-token tiles of both widths."""
+    import torch
+    li = pin.make_custom(73, T, c_in, c_out, n_layers=0)
+    w = _weight(P, li, pin.make_bias(8, 8, c_out), "packed")
+    x = torch.as_tensor(li.x).cuda()
+    lines = P.paro_w4a16_linear(w, x)
+    buf = torch.full((T, c_out + 24), 7.0, dtype=torch.float16, device="cuda")
+    P.paro_w4a16_linear(w, x, Y=buf[:, 8:8 + c_out])
+    assert torch.equal(lines, buf[:, 8:8 + c_out])
+    assert (buf[:, :8] == 7.0).all() and (buf[:, 8 + c_out:] == 7.0).all()
+    _check_linear(P, T, c_in, c_out, "packed", False)
