@@ -94,3 +94,9 @@ def test_cases_reach_128_token_tiles_of_either_width():
                 have.add((form, groups >= 12, k > 1))
     want = {(form, wide, split) for form in ("plain", "packed") for wide in (False, True) for split in (False, True)}
     assert want - {("packed", False, True)} <= have, have
+
+
+def test_two_pairs_of_steps_are_not_split():
+    """1024 channels are two pairs of steps: in two slices, with a launch to sum them, slower but for very few outputs."""
+    for T, c_out, k in ((97, 128, 1), (126, 208, 1), (69, 144, 1), (80, 16, 2), (202, 48, 2)):
+        assert plan(T, 1024, c_out, "packed", False) == (TILE, 64, k), (T, c_out)
