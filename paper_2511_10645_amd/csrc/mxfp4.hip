@@ -333,7 +333,8 @@ static hipError_t launch_mxfp4_decode(const paro_mxfp4_weight &w, const uint32_t
 //   - Scale bytes: the weight's as one dword per lane and 512 channels from the blob; the activations' through LDS as
 //     [K-step][row] dwords, two slices of 512 channels deep.
 //   - Outputs leave past the L2 (non-temporal): a round's tiles finish together, and their 33 MB would push the operands out of
-//     the L2s (4096 tokens 5120 -> 55296: 636 us with plain stores, 581).
+//     the L2s (4096 tokens 5120 -> 55296: 636 us with plain stores, 581).  A ragged last tile does the same (in 2-byte stores
+//     it alone took 2 to 4 us: 168 tokens 1536 -> 19040 15.2 us with the quantiser, now 12.7).
 // What bounds it (counters, 4096 tokens 5120 -> 55296): the chip's power - 1.6 GHz with the matrix cores busy 55 % of the cycles -
 // and the operand traffic out of L2 (9 GB; with all-zero operands, which cost no switching, 431 us).
 // Measured, us, before (256 x 256 tiles of 8 waves, activations through registers, 16x16x128 instruction, one block per
@@ -533,7 +534,7 @@ __global__ __launch_bounds__(256, 2) void mxfp4_gemm_kernel(MxGemmArgs a)
     constexpr int kStrip = 64 * NTW + 16;                                            // bytes of a strip's row
     char *strip = smem_mx + wave * 32 * kStrip;
     const __amdgpu_buffer_rsrc_t yr = mx_rsrc(a.Y, (uint32_t)(((size_t)(a.T - 1) * a.ldy + a.N) * 2));
-    const bool row_wide = a.ldy % 8 == 0 && ((uintptr_t)a.Y % 16) == 0 && n0 + 32 * NTW <= a.N;
+    const bool row_wide = a.ldy % 8 == 0 && ((uintptr_t)a.Y % 16) == 0;             // 8 outputs are all there or none is
     if (a.bias) {
         const __amdgpu_buffer_rsrc_t bias = mx_rsrc(a.bias, (uint32_t)a.N * 2);      // outputs beyond N read as zero
 #pragma unroll
@@ -565,7 +566,7 @@ __global__ __launch_bounds__(256, 2) void mxfp4_gemm_kernel(MxGemmArgs a)
             for (int i = 0; i < 32 / kRows; ++i) {
                 const int row = i * kRows + lane / kLanes, col = (lane % kLanes) * 8, m = m0 + mt * 32 + row;
                 const u32x4 v = *(const u32x4 *)(strip + row * kStrip + col * 2);
-                const uint32_t off = m < a.T ? (uint32_t)(((size_t)m * a.ldy + n0 + col) * 2) : kOobM;
+                const uint32_t off = m < a.T && n0 + col < a.N ? (uint32_t)(((size_t)m * a.ldy + n0 + col) * 2) : kOobM;
                 __builtin_amdgcn_raw_buffer_store_b128(v, yr, (int)off, 0, 2);
             }
         } else {
