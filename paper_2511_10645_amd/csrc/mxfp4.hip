@@ -597,22 +597,36 @@ static hipError_t launch_mxfp4_gemm_cfg(MxGemmArgs &a, hipStream_t s)
     return hipGetLastError();
 }
 
-// 128 outputs per block while 256 would fill at most three quarters of a block per compute unit.  2048 tokens 4096 -> 4096 (256
-// tiles of 256 outputs) 21.1 us against 24.8 with 128; 512 tokens 4096 -> 6144 (96) 15.3 against 12.8.
+// 128 outputs per block while 256 would fill at most half of the compute units.  Both widths forced on 322 shapes, us with the
+// quantiser, 128 / 256 outputs: 4608 -> 13984 at 152 tokens (110 tiles of 256) 13.9 / 18.0 without it, 3072 -> 34736 at 67 (136)
+// 19.9 / 18.1, 2048 -> 18416 at 185 (144) 15.4 / 14.5; the choice costs 0.1 % over the better one, with the line at 192 tiles 0.3 %.
 static bool mxfp4_gemm_small_tiles(const paro_mxfp4_weight &w, int T)
 {
-    return (long)((T + kMxBM - 1) / kMxBM) * ((w.c_out + 255) / 256) <= 192;
+    return (long)((T + kMxBM - 1) / kMxBM) * ((w.c_out + 255) / 256) <= 128;
 }
 
-// Time of the GEMM, fitted to 152 random shapes from 17 tokens on (median 3 % off): a fixed part and a time per K-step that
-// grows with the blocks of a round (512 = two per compute unit).
+// Time of the GEMM behind the quantiser, up to 260 tokens and a round of blocks (512 = two per compute unit): a fixed part and a
+// time per K-step that grow with the blocks; 272 shapes, 4 % off.
 static double mxfp4_gemm_us(const paro_mxfp4_weight &w, int T)
 {
     const bool small = mxfp4_gemm_small_tiles(w, T);
     const int bn = small ? 128 : 256;
-    const double n = (double)((T + kMxBM - 1) / kMxBM) * ((w.c_out + bn - 1) / bn), k = w.c_in / 128, f = n / 512.0;
-    if (small) return n <= 256 ? 5.7 + k * (0.18 + 0.2 * f) : n <= 512 ? 5.7 + k * (0.28 + 0.33 * f) : 0.8 + (4.9 + 0.6 * k) * f;
-    return n <= 256 ? 8.9 + k * (0.286 + 0.38 * f) : n <= 512 ? 8.9 + k * (1.32 * f - 0.01) : (10.6 + k) * f - 1.7;
+    const double k = w.c_in / 128, f = (double)((T + kMxBM - 1) / kMxBM) * ((w.c_out + bn - 1) / bn) / 512.0;
+    return small ? 3.55 + k * (0.257 + 0.104 * f) + 3.3 * f : 4.38 + k * (0.356 + 0.248 * f) + 3.8 * f;
+}
+
+// Time of the streaming kernel: per pass and round of blocks the fragments of the activations, the waves' start, the sums of the
+// partial tiles and the units of the stream, and what the matrix cores take; 250 shapes of up to 5 passes, 4 % off.
+static double mxfp4_stream_us(const paro_mxfp4_weight &w, int T)
+{
+    const double mb = ((double)w.c_out * w.c_in / 2 + (double)w.c_out * w.c_in / 32) / 1.0e6;
+    double us = 0;
+    MxGeometry g;
+    for (int t0 = 0; t0 < T && mx_geometry(w.c_in, w.c_out, T - t0, g); t0 += 16 * g.tb) {
+        const double rows = std::min(T - t0, 16 * g.tb), rounds = (g.blocks + 255) / 256;
+        us += rounds * (0.48 * g.spw * g.tb + 0.464 * g.waves + 0.037 * g.tiles_per_block * rows / g.waves + 0.722 * g.tiles_per_block * g.spw) + 0.026 * mb * g.tb;
+    }
+    return us;
 }
 
 static hipError_t launch_mxfp4_gemm(const paro_mxfp4_weight &w, const uint32_t *xc, const uint8_t *xs, int T, paro_half_t *Y,
@@ -628,23 +642,25 @@ static hipError_t launch_mxfp4_gemm(const paro_mxfp4_weight &w, const uint32_t *
 }
 
 // Which kernel: the streaming kernel reads the whole weight once per 64 tokens (32 or 16 where K is deep), the GEMM once per
-// 128 but works on whole tiles whatever T is.  Measured: a pass of TB blocks of 16 tokens takes ~3 us + the blob at 5.5 TB/s +
-// TB x (0.8 us + the blob at 30 TB/s).  Up to 32 tokens a single pass is always taken (30 x 10240 -> 21392: 21.7 us against 25.8).
-// Both kernels over the 104 shapes of the fit with up to 600 tokens: the choice costs 0.8 % over the better one.
+// 128 but works on whole tiles whatever T is.  Up to 32 tokens a single pass is always taken (30 x 10240 -> 21392: 21.7 us against
+// 25.8).  Both kernels forced on 272 shapes of 33 to 420 tokens: the choice costs 0.3 % over the better one (the streaming kernel
+// stays where the models tie within 5 %; 48 tokens 19456 -> 3536: 34.0 us, the GEMM 45.8; 79 tokens 3584 -> 1088: 11.2 against 9.7).
+static bool mxfp4_gemm_route(const paro_mxfp4_weight &w, int T, int64_t ldy)
+{
+    // the GEMM addresses the activations and the outputs with 32-bit offsets
+    return T > std::min(mxfp4_pass_tokens(w, T), 32) && (size_t)T * w.c_in / 2 < (1ull << 31) && ((size_t)(T - 1) * ldy + w.c_out) * 2 < (1ull << 31) &&
+           1.05 * mxfp4_gemm_us(w, T) < mxfp4_stream_us(w, T);
+}
+
+int mxfp4_linear_plan(const paro_mxfp4_weight &w, int T)
+{
+    return !mxfp4_gemm_route(w, T, w.c_out) ? 0 : mxfp4_gemm_small_tiles(w, T) ? 128 : 256;
+}
+
 hipError_t launch_mxfp4_linear(const paro_mxfp4_weight &w, const uint32_t *x_codes, const uint8_t *x_scales, int T,
                                paro_half_t *Y, int64_t ldy, hipStream_t s)
 {
-    // the GEMM addresses the activations and the outputs with 32-bit offsets
-    if (T > std::min(mxfp4_pass_tokens(w, T), 32) && (size_t)T * w.c_in / 2 < (1ull << 31) && ((size_t)(T - 1) * ldy + w.c_out) * 2 < (1ull << 31)) {
-        const double mb = ((double)w.c_out * w.c_in / 2 + (double)w.c_out * w.c_in / 32) / 1.0e6;
-        double stream_us = 0;
-        for (int t0 = 0; t0 < T;) {
-            const int pass = mxfp4_pass_tokens(w, T - t0);
-            stream_us += 3.0 + mb / 5.5 + (pass / 16) * (0.8 + mb / 30.0);
-            t0 += pass;
-        }
-        if (mxfp4_gemm_us(w, T) < stream_us) return launch_mxfp4_gemm(w, x_codes, x_scales, T, Y, ldy, s);
-    }
+    if (mxfp4_gemm_route(w, T, ldy)) return launch_mxfp4_gemm(w, x_codes, x_scales, T, Y, ldy, s);
     for (int t0 = 0; t0 < T;) {
         const int pass = mxfp4_pass_tokens(w, T - t0);
         const int tp = T - t0 < pass ? T - t0 : pass;

@@ -489,6 +489,8 @@ int paro_internal_linear_plan_in(const paro_rotation *rot, const paro_w4_weight 
     return kernel;
 }
 
+int paro_internal_mxfp4_plan(const paro_mxfp4_weight *w, int32_t T) { return mxfp4_linear_plan(*w, T); }
+
 int paro_internal_linear_plan(const paro_rotation *rot, const paro_w4_weight *w, int32_t T, int32_t *tile, int32_t *k_slices)
 {
     return paro_internal_linear_plan_in(rot, w, T, ws_layout(rot, w, T).total, tile, k_slices);

@@ -181,6 +181,7 @@ void gemm_patches(int m_tiles, int n_tiles, int &patch_m, int &patch_n, int &blo
 hipError_t launch_mxfp4_repack(const paro_mxfp4_weight &w, void *packed_out, hipStream_t s);
 hipError_t launch_mxfp4_unpack(const paro_mxfp4_weight &w, uint8_t *codes, uint8_t *scales, hipStream_t s);
 bool mxfp4_linear_supported(const paro_mxfp4_weight &w);
+int mxfp4_linear_plan(const paro_mxfp4_weight &w, int T);
 hipError_t launch_mxfp4_linear(const paro_mxfp4_weight &w, const uint32_t *x_codes, const uint8_t *x_scales, int T,
                                paro_half_t *Y, int64_t ldy, hipStream_t s);
 hipError_t launch_quantize_act_mxfp4(const paro_rotation &rot, const paro_half_t *X, int64_t ldx, int T, uint32_t *codes,
@@ -237,3 +238,5 @@ enum { kPlanHosted, kPlanStream, kPlanGemm, kPlanTile, kPlanOperand, kPlanRows, 
 extern "C" int paro_internal_linear_plan(const paro_rotation *rot, const paro_w4_weight *w, int32_t T, int32_t *tile, int32_t *k_slices);
 // The same with a workspace of ws_bytes (at least what the call cannot do without); kPlanGeneric with tile -1 if that is refused.
 extern "C" int paro_internal_linear_plan_in(const paro_rotation *rot, const paro_w4_weight *w, int32_t T, size_t ws_bytes, int32_t *tile, int32_t *k_slices);
+// The MXFP4 linear with dense rows: 0 the streaming kernel, else the outputs per block of the GEMM.
+extern "C" int paro_internal_mxfp4_plan(const paro_mxfp4_weight *w, int32_t T);

@@ -88,13 +88,15 @@ def test_repack_and_unpack_are_bit_exact(P, shape):
     dict(seed=9210, T=300, C=1024, N=272, bias=True),         # ragged in tokens and in outputs
     dict(seed=9211, T=257, C=2048, N=528, bias=False),        # a second token tile of one row
     dict(seed=9212, T=1024, C=4096, N=1536, bias=True),       # 8 x 6 tiles of 128 tokens, 32 K-steps
-    dict(seed=9221, T=2100, C=512, N=3856, bias=True),        # 9 x 16 tiles of 256 tokens (more than half a round), ragged both ways
-    dict(seed=9222, T=2048, C=512, N=9216, bias=False),       # 8 x 36 = 288 tiles: one round of 256-token tiles, the last 4 output tiles as 128-token tiles
+    dict(seed=9221, T=2100, C=512, N=3856, bias=True),        # 17 x 16 tiles of 256 outputs, ragged both ways
+    dict(seed=9222, T=2048, C=512, N=9216, bias=False),       # 16 x 36 = 576 whole tiles of 256 outputs: more than two per compute unit
     dict(seed=9223, T=127, C=1536, N=112, bias=True),         # three slices: one whole period of the weight ring
     dict(seed=9224, T=128, C=2048, N=144, bias=False),        # four slices, a second output tile of 16
     dict(seed=9225, T=129, C=6656, N=4112, bias=True),        # 13 slices; a second token tile of one row
     dict(seed=9226, T=1537, C=1536, N=3856, bias=True, pad=8),# 13 x 16 tiles of 256 outputs: ragged both ways, padded rows
     dict(seed=9227, T=1537, C=2560, N=3856, bias=False, pad=4),   # the same with rows that are not 16-byte aligned
+    dict(seed=9228, T=1537, C=2048, N=2560, bias=True),       # 13 x 10 whole tiles of 256 outputs, four slices
+    dict(seed=9229, T=1537, C=2560, N=2576, bias=False),      # 13 x 11 tiles, the last of 16 outputs, five slices
     dict(seed=9215, T=64, C=4096, N=528, bias=True),          # 64 tokens in one pass: four token blocks per wave
     dict(seed=9216, T=40, C=5120, N=272, bias=False),         # 10 slices, three of four token blocks used
     dict(seed=9217, T=32, C=14336, N=96, bias=True),          # 28 slices: 4 per wave, two token blocks
