@@ -18,12 +18,14 @@
 // the 8 operand reads are most; more waves or deeper rings change nothing (11 groups per consumer and no barrier, each with a
 // ring of its own: 15.8 us for 11008 -> 4096 at 24 tokens against 14.6; requests two ahead instead of ten: the same).
 // Measured, us, before -> now (graph replay over 350 MB of weights): 11008 -> 4096 at 24 tokens bare 36.8 -> 14.0, rotated
-// 20.4 -> 17.4 (two slices of K), one token bare 19.3 -> 9.0; 2176 -> 4112 at 24 tokens bare 11.0 -> 6.3; 4224 -> 22016 32.3 -> 23;
-// 106 random shapes: bare 0.60 of the time, rotated 0.80 in the geometric mean, none more than 3 % slower.
+// 20.4 -> 17.4 (four slices of K), one token bare 19.3 -> 9.0; 2176 -> 4112 at 24 tokens bare 11.0 -> 6.3; 4224 -> 22016 32.3 -> 23;
+// 106 random shapes: bare 0.60 of the time, rotated 0.80 in the geometric mean; many outputs on few channels: ic_few_channels.
 #include "paro_internal.h"
 #include <algorithm>
 #include <cmath>
+#include <iterator>
 #include <type_traits>
+#include <utility>
 
 namespace paro {
 
@@ -294,27 +296,76 @@ bool linear_rows_supported(const paro_w4_weight &w, int64_t ldx, int T)
            (size_t)w.c_out * (w.c_in / 2) < (1ull << 31);
 }
 
-template <int TB, int RPW, int KG, int NCOL, int NTW, int XR, int RW>
+// Where the kernel of linear_rows.hip, whose small blocks share a compute unit, is the faster one: few channels and more outputs than
+// one round of blocks has, or two stages of which one is nearly empty.  us, it / this kernel, bare, 301 shapes: 512 -> 39280 at 2 tokens
+// 8.2 / 9.7, 1024 -> 43280 at 4 9.7 / 14.2, 128 -> 49216 at 10 6.8 / 11.8, 640 -> 19072 at 16 7.1 / 8.8, 768 -> 18240 at 4 6.7 / 7.3,
+// 384 -> 51168 at 25 13.7 / 15.1; but 256 -> 31184 at 3 (one round) 6.0 / 5.4, 1152 -> 26784 at 24 12.6 / 12.6; the choice costs 0.6 %
+// over the better one (at most 13 %: 1152 -> 24672 at 2 tokens 8.5 / 9.6, 3200 -> 24112 at 10 17.9 / 20.2).
+static bool ic_few_channels(const IcPlan &p, int c_in, int c_out, int T)
+{
+    const int G = c_in / kGroup;
+    const bool rounds = c_out > 256 * 16 * p.nt;
+    if (p.k_split > 1) return false;
+    if (T > 16) return G <= 3 && rounds;
+    return G <= 20 && (rounds || (T <= 8 && G > 4 && G <= 8 && c_out >= 8192));
+}
+
+// 16, 32, 64 outputs per block x up to 8, 16, 24, 32 tokens, and 128 outputs up to 8 tokens: the template's arguments
+struct IcConfig { int tb, rpw, kg, ncol, ntw, xr, rw; };
+constexpr IcConfig kIcConfigs[] = {
+    {1, 1, 8, 1, 1, 3, 7}, {1, 2, 8, 1, 1, 3, 6}, {2, 3, 8, 1, 1, 2, 6}, {2, 4, 8, 1, 1, 2, 3},
+    {1, 1, 4, 2, 1, 3, 6}, {1, 2, 4, 2, 1, 4, 7}, {2, 3, 4, 2, 1, 4, 6}, {2, 4, 4, 2, 1, 3, 6},
+    {1, 1, 4, 2, 2, 3, 3}, {1, 2, 4, 2, 2, 4, 5}, {2, 3, 4, 2, 2, 3, 4}, {2, 4, 4, 2, 2, 3, 3},
+    {1, 1, 4, 2, 4, 3, 3},
+};
+static int ic_config(int nt, int T) { return nt == 8 ? 12 : (nt == 4 ? 8 : nt == 2 ? 4 : 0) + (T - 1) / 8; }
+
+template <int I>
 static hipError_t launch_ic_cfg(const IcArgs &a, dim3 grid, hipStream_t s)
 {
-    constexpr int lds = ic_lds(KG, KG * NCOL, RPW, NCOL * NTW, XR, RW);
+    constexpr IcConfig c = kIcConfigs[I];
+    constexpr auto kernel = linear_ic_kernel<c.tb, c.rpw, c.kg, c.ncol, c.ntw, c.xr, c.rw>;
+    constexpr int lds = ic_lds(c.kg, c.kg * c.ncol, c.rpw, c.ncol * c.ntw, c.xr, c.rw);
     static_assert(lds <= 160 * 1024, "");
     static std::atomic<uint64_t> attr_done{0};
     if (const int dev = once_pending(attr_done); dev >= 0) {
-        hipError_t e = hipFuncSetAttribute((const void *)linear_ic_kernel<TB, RPW, KG, NCOL, NTW, XR, RW>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+        hipError_t e = hipFuncSetAttribute((const void *)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
         if (e != hipSuccess) return e;
         once_done(attr_done, dev);
     }
-    hipLaunchKernelGGL((linear_ic_kernel<TB, RPW, KG, NCOL, NTW, XR, RW>), grid, dim3((KG * NCOL + 1) * 64), lds, s, a);
+    hipLaunchKernelGGL(kernel, grid, dim3((c.kg * c.ncol + 1) * 64), lds, s, a);
     return hipGetLastError();
+}
+template <size_t... I>
+static hipError_t launch_ic(int config, const IcArgs &a, dim3 grid, hipStream_t s, std::index_sequence<I...>)
+{
+    static constexpr hipError_t (*launch[])(const IcArgs &, dim3, hipStream_t) = {launch_ic_cfg<I>...};
+    return launch[config](a, grid, s);
+}
+
+// the plan of a call with this much room for partial tiles
+static IcPlan ic_plan_in(const paro_w4_weight &w, int T, size_t room)
+{
+    const IcPlan p = ic_plan(w.c_in, w.c_out, T, true);
+    return p.k_split == 1 || (size_t)p.k_split * T * w.c_out * sizeof(float) <= room ? p : ic_plan(w.c_in, w.c_out, T, false);
+}
+
+void linear_rows_plan(const paro_w4_weight &w, int T, size_t room, int &outputs, int &k_slices, int &config, int &stages, int &ring)
+{
+    const IcPlan p = ic_plan_in(w, T, room);
+    k_slices = p.k_split; outputs = 0; config = -1; stages = ring = 0;
+    if (ic_few_channels(p, w.c_in, w.c_out, T)) return;
+    outputs = 16 * p.nt; config = ic_config(p.nt, T);
+    const IcConfig c = kIcConfigs[config];
+    stages = (p.groups_per_split + c.kg - 1) / c.kg; ring = std::max(c.xr, c.rw);
 }
 
 hipError_t launch_linear_rows(const paro_w4_weight &w, const paro_half_t *X, int64_t ldx, paro_half_t *Y, int64_t ldy, int T,
                               void *scratch, size_t scratch_bytes, const void *least, hipStream_t s)
 {
-    IcPlan p = ic_plan(w.c_in, w.c_out, T, true);
-    const bool split = p.k_split > 1 && scratch && scratch_bytes >= (size_t)p.k_split * T * w.c_out * sizeof(float) && ((uintptr_t)scratch % 16) == 0;
-    if (!split) p = ic_plan(w.c_in, w.c_out, T, false);
+    const IcPlan p = ic_plan_in(w, T, scratch && ((uintptr_t)scratch % 16) == 0 ? scratch_bytes : 0);
+    const bool split = p.k_split > 1;
+    if (ic_few_channels(p, w.c_in, w.c_out, T)) return launch_linear_direct(w, X, ldx, Y, ldy, T, s);
     IcArgs a;
     a.w = (const char *)w.qweight; a.scales = (const _Float16 *)w.scales; a.qzeros = w.qzeros;
     a.X = (const _Float16 *)X; a.ldx = ldx; a.Y = (_Float16 *)Y; a.ldy = ldy; a.bias = (const _Float16 *)w.bias;
@@ -322,24 +373,7 @@ hipError_t launch_linear_rows(const paro_w4_weight &w, const paro_half_t *X, int
     a.T = T; a.C = w.c_in; a.N = w.c_out; a.G = w.c_in / kGroup; a.groups_per_split = p.groups_per_split;
     a.m_lo = 0x000F000Fu; a.k_lo = 0x64006400u;
     const dim3 grid((w.c_out + 16 * p.nt - 1) / (16 * p.nt), p.k_split);
-    hipError_t e;
-    if (p.nt == 1)
-        e = T <= 8    ? launch_ic_cfg<1, 1, 8, 1, 1, 3, 7>(a, grid, s)
-            : T <= 16 ? launch_ic_cfg<1, 2, 8, 1, 1, 3, 6>(a, grid, s)
-            : T <= 24 ? launch_ic_cfg<2, 3, 8, 1, 1, 2, 6>(a, grid, s)
-                      : launch_ic_cfg<2, 4, 8, 1, 1, 2, 3>(a, grid, s);
-    else if (p.nt == 2)
-        e = T <= 8    ? launch_ic_cfg<1, 1, 4, 2, 1, 3, 6>(a, grid, s)
-            : T <= 16 ? launch_ic_cfg<1, 2, 4, 2, 1, 4, 7>(a, grid, s)
-            : T <= 24 ? launch_ic_cfg<2, 3, 4, 2, 1, 4, 6>(a, grid, s)
-                      : launch_ic_cfg<2, 4, 4, 2, 1, 3, 6>(a, grid, s);
-    else if (p.nt == 8)
-        e = launch_ic_cfg<1, 1, 4, 2, 4, 3, 3>(a, grid, s);
-    else
-        e = T <= 8    ? launch_ic_cfg<1, 1, 4, 2, 2, 3, 3>(a, grid, s)
-            : T <= 16 ? launch_ic_cfg<1, 2, 4, 2, 2, 4, 5>(a, grid, s)
-            : T <= 24 ? launch_ic_cfg<2, 3, 4, 2, 2, 3, 4>(a, grid, s)
-                      : launch_ic_cfg<2, 4, 4, 2, 2, 3, 3>(a, grid, s);
+    const hipError_t e = launch_ic(ic_config(p.nt, T), a, grid, s, std::make_index_sequence<std::size(kIcConfigs)>{});
     if (e != hipSuccess || !split) return e;
     return launch_splitk_reduce(a.partial, p.k_split, T, 0, w.c_out, w.bias, Y, ldy, least, s);
 }

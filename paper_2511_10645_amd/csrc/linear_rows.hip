@@ -1,19 +1,21 @@
-// W4A16 linear in which every wave is on its own until its sums are complete (Eq. 2): repacked weights with activations in
-// operand order, 33 to 256 tokens, where the outputs are few.  A rotation pass can write its result in any order, and writes it in
-// this one (rotate.hip) where this kernel follows.
+// W4A16 linear in which every wave is on its own until its sums are complete (Eq. 2), in two forms:
+//   - repacked weights with activations in operand order, 33 to 256 tokens, where the outputs are few: a rotation pass can
+//     write its result in any order, and writes it in this one (rotate.hip) where this kernel follows;
+//   - weights in the interchange layout on row-major activations, up to 32 tokens, where the outputs are many and the channels few
+//     (the others: linear_ic.hip, which chooses).
 //
-// A block is 4 waves and owns 32 tokens x (16 NT) outputs; its waves take the channel groups in turn (wave w: groups
+// A block is 4 waves and owns (16 TB tokens) x (16 NT outputs); its waves take the channel groups in turn (wave w: groups
 // w, w + 4, ...), so that every weight and every activation enters the compute unit once and the loop has no LDS, no
 // barrier and no hand-over:
 //   - weights: a lane's 16 bytes of a row's group are 32 channels of that row, which is the B operand of four
-//     v_mfma_f32_16x16x32_f16 once the codes stand in fp16 registers as q - z (exact; 9 vector instructions per 8 weights);
-//     the group's scale multiplies the fp32 sums;
-//   - activations straight into fragment registers: in operand order a fragment is one contiguous kilobyte (of row-major
-//     rows it would be 16-byte pieces of 32 cache lines, each a request of its own);
+//     v_mfma_f32_16x16x32_f16 once the codes stand in fp16 registers as q - z (exact; 14 vector instructions per 8
+//     weights in the natural code order, 9 in the repacked one); the group's scale multiplies the fp32 sums;
+//   - activations straight into fragment registers: in operand order a fragment is one contiguous kilobyte, of row-major
+//     rows it is 16-byte pieces of 32 cache lines, each a request of its own, which matters less the fewer the tokens are;
 //   - registers are a ring of two groups: a register is refilled for the group after next right after its last use.
 // The loop is written as slots, one MFMA each, with a piece of the next tile's dequantisation, a piece of the previous
 // tile's scaling and at most two loads in its shadow, pinned by scheduling barriers.  The 4 waves' sums meet in LDS once;
-// K is also split between blocks where the outputs alone are too few of them and the call has a scratch part.
+// K is also split between blocks where the outputs alone are too few of them (operand order).
 //
 // Bound by the weight stream and, at few groups per wave, by the chain load -> dequantise -> multiply -> sum; at more
 // tokens by what a compute unit takes in (a block reads all channels of its 32 tokens, 256 KB at 4096), hence
@@ -31,7 +33,7 @@ typedef _Float16 half2v __attribute__((ext_vector_type(2)));
 typedef float float4v __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
-constexpr int kRowsWaves = 4;                       // waves per block (K in turn)
+constexpr int kRowsWaves = 4, kRowsTiles = 4;       // waves per block (K in turn); 16-output tiles per block (interchange layout)
 constexpr uint32_t kOobR = 0x80000000u;             // beyond every buffer: reads as zero
 
 __device__ inline __amdgpu_buffer_rsrc_t rows_rsrc(const void *p, size_t bytes)
@@ -52,9 +54,11 @@ __device__ __forceinline__ void rows_for(F &&f)
 }
 
 struct RowsArgs {
-    const char *w;                                   // the repacked blob
-    uint32_t scales_off, zeros_off;
-    const _Float16 *X;                               // blocks of 16 tokens x 128 channels
+    const char *w;                                   // qweight, or the repacked blob
+    uint32_t scales_off, zeros_off;                  // of the blob
+    const _Float16 *scales;                          // interchange layout
+    const uint32_t *qzeros;
+    const _Float16 *X; int64_t ldx;                  // row-major, or (OPERAND) blocks of 16 tokens x 128 channels
     _Float16 *Y; int64_t ldy;
     const _Float16 *bias;
     float *partial;                                  // [k slices][T][N] where K is split between blocks, else NULL
@@ -62,11 +66,12 @@ struct RowsArgs {
     uint32_t m_lo, m_hi, k_lo, k_hi;                 // 0x000F000F, 0x00F000F0, 0x64006400, 0x54005400: arguments, so that
 };                                                   // (u & m) | k is one instruction
 
-// TB: blocks of 16 tokens per block; NT: tiles of 16 outputs.  Activations in operand order: a block of r = 16 tokens (the last one: of those that are left) x one group is [4 fragments j][4 kb][r tokens][16 B],
+// TB: blocks of 16 tokens per block; NT: tiles of 16 outputs; OPERAND: the second form above.  Activations in operand order:
+// a block of r = 16 tokens (the last one: of those that are left) x one group is [4 fragments j][4 kb][r tokens][16 B],
 // channels 32 kb + 8 j .. + 7.
 // WHOLE: every block of 16 tokens of this tile is whole, so that its strides are constants (with strides in registers, as a
 // ragged last tile has them, 4096 -> 4096 at 64 tokens takes 0.1 to 0.2 us more).
-template <int TB, int NT, bool WHOLE>
+template <int TB, int NT, bool OPERAND, bool WHOLE>
 __device__ __forceinline__ void linear_rows_tile(const RowsArgs &a, float *s_sum, int kslice, int mt, int ntile)
 {
     constexpr int R = 2;                             // ring of groups
@@ -85,29 +90,34 @@ __device__ __forceinline__ void linear_rows_tile(const RowsArgs &a, float *s_sum
 
     // ---- addresses: a per-lane offset that is fixed (or out of range) plus a wave-uniform one -----------------------
     const int n_tb = (m_rows + 15) / 16;
-    const __amdgpu_buffer_rsrc_t xr = rows_rsrc((const char *)a.X + (size_t)m0 * a.C * 2, (size_t)m_rows * 2 * a.C);
-    const __amdgpu_buffer_rsrc_t wr = rows_rsrc(a.w, a.zeros_off + packed_zeros_bytes(a.C, a.N));
+    const __amdgpu_buffer_rsrc_t xr = OPERAND ? rows_rsrc((const char *)a.X + (size_t)m0 * a.C * 2, (size_t)m_rows * 2 * a.C)
+                                              : rows_rsrc(a.X, ((size_t)(a.T - 1) * a.ldx + a.C) * 2);
+    const __amdgpu_buffer_rsrc_t wr = OPERAND ? rows_rsrc(a.w, a.zeros_off + packed_zeros_bytes(a.C, a.N))
+                                              : rows_rsrc(a.w + (size_t)n0 * (a.C / 2), (size_t)n_rows * (a.C / 2));
+    const __amdgpu_buffer_rsrc_t sr = rows_rsrc(a.scales, OPERAND ? 0 : (size_t)a.G * a.N * 2);
+    const __amdgpu_buffer_rsrc_t zr = rows_rsrc(a.qzeros, OPERAND ? 0 : (size_t)a.G * a.N / 2);
     uint32_t xv[TB], x_base[TB], x_rows[TB];         // per lane, and per block of 16 tokens (surplus blocks repeat the first)
     rows_for<TB>([&](auto B) {
-        x_base[B] = rows_uniform(B < n_tb ? B * 32u * (uint32_t)a.C : 0u);
-        x_rows[B] = WHOLE ? 16u : rows_uniform((uint32_t)min(16, B < n_tb ? m_rows - B * 16 : m_rows));
-        if constexpr (WHOLE) xv[B] = lane * 16u;
+        x_base[B] = OPERAND ? rows_uniform(B < n_tb ? B * 32u * (uint32_t)a.C : 0u) : 0u;
+        x_rows[B] = !OPERAND ? 1u : WHOLE ? 16u : rows_uniform((uint32_t)min(16, B < n_tb ? m_rows - B * 16 : m_rows));
+        if constexpr (!OPERAND) xv[B] = B * 16 + ft < a.T ? (uint32_t)(((size_t)(B * 16 + ft) * a.ldx + fkb * 32) * 2) : kOobR;
+        else if constexpr (WHOLE) xv[B] = lane * 16u;
         else xv[B] = (uint32_t)ft < x_rows[B] ? __umul24(fkb * 16u, x_rows[B]) + ft * 16u : kOobR;
     });
-    constexpr uint32_t kXGroup = kGroup * 2, kXFrag = 64;                            // per row of the block
-    const uint32_t wv = lane * 16u;
+    constexpr uint32_t kXGroup = kGroup * 2, kXFrag = OPERAND ? 64 : 16;             // per row of the block, or of the input
+    const uint32_t wv = OPERAND ? lane * 16u : (uint32_t)ft * (uint32_t)(a.C / 2) + fkb * 16;
     // Whole dwords, shifted where they are used: a 16-bit load's extension would be waited for where it is loaded.  (The
     // wave's groups share g % 4 in the blob: they are kRowsWaves = 4 apart, and a split begins at a multiple of 4.)
     static_assert(kRowsWaves == kSliceGroups, "");
     const int g4 = g_first & 3;
-    const uint32_t sv = ft * 8u + (g4 & 2) * 2, zv = (ft & 14) * 2u;
-    const uint32_t s_shift = 16 * (g4 & 1), z_shift = 16 * (ft & 1) + 4 * g4;
+    const uint32_t sv = OPERAND ? ft * 8u + (g4 & 2) * 2 : (ft & 14) * 2u, zv = OPERAND ? (ft & 14) * 2u : (ft >> 3) * 4u;
+    const uint32_t s_shift = OPERAND ? 16 * (g4 & 1) : 16 * (ft & 1), z_shift = OPERAND ? 16 * (ft & 1) + 4 * g4 : 4 * (ft & 7);
     // tiles beyond N read the last one again: their sums are not stored
     uint32_t w_tile[NT], s_tile[NT];
     rows_for<NT>([&](auto N_) {
         const int n = min((int)N_, n_rows / kTileN - 1), tile = n0 / kTileN + n;
-        w_tile[N_] = rows_uniform((uint32_t)tile * (uint32_t)a.G * 1024u);
-        s_tile[N_] = rows_uniform((uint32_t)tile * (uint32_t)(a.G / kSliceGroups));
+        w_tile[N_] = rows_uniform(OPERAND ? (uint32_t)tile * (uint32_t)a.G * 1024u : (uint32_t)n * 16u * (uint32_t)(a.C / 2));
+        s_tile[N_] = rows_uniform(OPERAND ? (uint32_t)tile * (uint32_t)(a.G / kSliceGroups) : (uint32_t)(n0 + n * kTileN));
     });
 
     half8 xa[R][TB][4];
@@ -124,15 +134,22 @@ __device__ __forceinline__ void linear_rows_tile(const RowsArgs &a, float *s_sum
     auto load_x = [&](int ring, int tb, int j) {
         union { u32x4 u; half8 h; } v;
         const uint32_t group = x_base[tb] + l_g * kXGroup * x_rows[tb], frag = j * kXFrag * x_rows[tb];
-        if constexpr (!WHOLE) v.u = __builtin_amdgcn_raw_buffer_load_b128(xr, (int)l_xv[tb], (int)(group + frag), 0);
+        if constexpr (OPERAND && !WHOLE) v.u = __builtin_amdgcn_raw_buffer_load_b128(xr, (int)l_xv[tb], (int)(group + frag), 0);
         else v.u = __builtin_amdgcn_raw_buffer_load_b128(xr, (int)(l_xv[tb] + frag), (int)group, 0);
         xa[ring][tb][j] = v.h;
     };
     auto load_w = [&](int ring, int n) {
-        const uint32_t sl = s_tile[n] + (l_g >> 2);
-        wq[ring][n] = __builtin_amdgcn_raw_buffer_load_b128(wr, (int)l_wv, (int)(w_tile[n] + l_g * 1024u), 0);
-        wsc[ring][n] = (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(wr, (int)l_sv, (int)(a.scales_off + sl * 128u), 0);
-        wz[ring][n] = (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(wr, (int)l_zv, (int)(a.zeros_off + sl * 32u), 0);
+        if constexpr (OPERAND) {
+            const uint32_t sl = s_tile[n] + (l_g >> 2);
+            wq[ring][n] = __builtin_amdgcn_raw_buffer_load_b128(wr, (int)l_wv, (int)(w_tile[n] + l_g * 1024u), 0);
+            wsc[ring][n] = (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(wr, (int)l_sv, (int)(a.scales_off + sl * 128u), 0);
+            wz[ring][n] = (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(wr, (int)l_zv, (int)(a.zeros_off + sl * 32u), 0);
+        } else {
+            const uint32_t first = l_g * (uint32_t)a.N + s_tile[n];
+            wq[ring][n] = __builtin_amdgcn_raw_buffer_load_b128(wr, (int)l_wv, (int)(w_tile[n] + l_g * 64u), 2);
+            wsc[ring][n] = (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(sr, (int)l_sv, (int)(first * 2u), 0);
+            wz[ring][n] = (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(zr, (int)l_zv, (int)(first / 2u), 0);
+        }
     };
 
     auto to_vgpr = [&](uint32_t v) { return (uint32_t)__builtin_amdgcn_ds_bpermute(lane << 2, (int)v); };
@@ -142,6 +159,7 @@ __device__ __forceinline__ void linear_rows_tile(const RowsArgs &a, float *s_sum
     union BFrag { u32x4 u; half8 h; } bf[2][4];
     float sc[2] = {0.f, 0.f};
     half2v nlo = rows_h2(0), nhi = rows_h2(0);
+    uint32_t sp = 0;                                 // codes 0, 2 (then 1, 3 eight bits higher) of a half word, spread
     rows_for<TB>([&](auto B) {
         rows_for<NT>([&](auto N_) { tot[B][N_] = float4v{0.f, 0.f, 0.f, 0.f}; });
         gacc[1][B] = float4v{0.f, 0.f, 0.f, 0.f};
@@ -153,12 +171,19 @@ __device__ __forceinline__ void linear_rows_tile(const RowsArgs &a, float *s_sum
         if constexpr (p == 0) {
             const uint32_t z = (wz[ring][n] >> z_shift) & 15u;
             nlo = rows_h2((0xE400u + z) * 0x00010001u);                      // -(1024 + z), twice
-            nhi = rows_h2((0xD400u + (z << 4)) * 0x00010001u);    // -(64 + z), twice
+            if constexpr (OPERAND) nhi = rows_h2((0xD400u + (z << 4)) * 0x00010001u);    // -(64 + z), twice
         }
         const uint32_t u = wq[ring][n][w4];
-        const uint32_t v = part < 2 ? u : u >> 8;
-        if constexpr (part & 1) bf[par][w4].u[part] = rows_u32(rows_h2((v & c_mhi) | c_khi) + nhi);
-        else bf[par][w4].u[part] = rows_u32(rows_h2((v & c_mlo) | c_klo) + nlo);
+        if constexpr (OPERAND) {
+            const uint32_t v = part < 2 ? u : u >> 8;
+            if constexpr (part & 1) bf[par][w4].u[part] = rows_u32(rows_h2((v & c_mhi) | c_khi) + nhi);
+            else bf[par][w4].u[part] = rows_u32(rows_h2((v & c_mlo) | c_klo) + nlo);
+        } else {
+            // codes 2 part and 2 part + 1 into the low nibbles of the two halves
+            if constexpr (part == 0) { const uint32_t x = u & 0xffffu; sp = x | (x << 12); }
+            if constexpr (part == 2) { const uint32_t x = u >> 16; sp = x | (x << 12); }
+            bf[par][w4].u[part] = rows_u32(rows_h2(((part & 1 ? sp >> 8 : sp) & c_mlo) | c_klo) + nlo);
+        }
         if constexpr (p == 15) {
             union { uint16_t u; _Float16 h; } c; c.u = (uint16_t)(wsc[ring][n] >> s_shift);
             sc[par] = (float)c.h;
@@ -232,20 +257,39 @@ __device__ __forceinline__ void linear_rows_tile(const RowsArgs &a, float *s_sum
     }
 }
 
-template <int TB, int NT>
+template <int TB, int NT, bool OPERAND>
 __global__ __launch_bounds__(kRowsWaves * 64, 2) void linear_rows_kernel(RowsArgs a)
 {
     __shared__ __attribute__((aligned(16))) float s_sum[kRowsWaves * TB * NT * 256];
-    // an XCD's blocks are a run of (K-slice, output tile, token tile), the last running fastest: its L2 serves a
-    // weight tile to the further token tiles, and every XCD gets the same number of blocks
-    const int tiles = a.m_tiles * a.n_tiles, all = tiles * a.k_split, per_xcd = (all + 7) / 8;
-    const int idx = (int)(blockIdx.x & 7) * per_xcd + (int)(blockIdx.x >> 3);
-    if (idx >= all) return;
-    const int mt = idx % tiles % a.m_tiles, ntile = idx % tiles / a.m_tiles;
-    if (a.T % 16 == 0 || mt + 1 < a.m_tiles) linear_rows_tile<TB, NT, true>(a, s_sum, idx / tiles, mt, ntile);
-    else linear_rows_tile<TB, NT, false>(a, s_sum, idx / tiles, mt, ntile);
+    if constexpr (OPERAND) {
+        // an XCD's blocks are a run of (K-slice, output tile, token tile), the last running fastest: its L2 serves a
+        // weight tile to the further token tiles, and every XCD gets the same number of blocks
+        const int tiles = a.m_tiles * a.n_tiles, all = tiles * a.k_split, per_xcd = (all + 7) / 8;
+        const int idx = (int)(blockIdx.x & 7) * per_xcd + (int)(blockIdx.x >> 3);
+        if (idx >= all) return;
+        const int mt = idx % tiles % a.m_tiles, ntile = idx % tiles / a.m_tiles;
+        if (a.T % 16 == 0 || mt + 1 < a.m_tiles) linear_rows_tile<TB, NT, true, true>(a, s_sum, idx / tiles, mt, ntile);
+        else linear_rows_tile<TB, NT, true, false>(a, s_sum, idx / tiles, mt, ntile);
+    } else {
+        linear_rows_tile<TB, NT, false, false>(a, s_sum, (int)blockIdx.y, 0, (int)blockIdx.x);
+    }
 }
 
+// ---- interchange layout ------------------------------------------------------------------------------------------------
+hipError_t launch_linear_direct(const paro_w4_weight &w, const paro_half_t *X, int64_t ldx, paro_half_t *Y, int64_t ldy, int T, hipStream_t s)
+{
+    RowsArgs a;
+    a.w = (const char *)w.qweight; a.scales_off = a.zeros_off = 0; a.m_tiles = a.n_tiles = a.k_split = 0; a.scales = (const _Float16 *)w.scales; a.qzeros = w.qzeros;
+    a.X = (const _Float16 *)X; a.ldx = ldx; a.Y = (_Float16 *)Y; a.ldy = ldy; a.bias = (const _Float16 *)w.bias;
+    a.T = T; a.C = w.c_in; a.N = w.c_out; a.G = w.c_in / kGroup; a.groups_per_split = a.G; a.partial = nullptr;
+    a.m_lo = 0x000F000Fu; a.m_hi = 0x00F000F0u; a.k_lo = 0x64006400u; a.k_hi = 0x54005400u;
+    const dim3 grid((w.c_out + 16 * kRowsTiles - 1) / (16 * kRowsTiles)), block(kRowsWaves * 64);
+    if (T <= 16) hipLaunchKernelGGL((linear_rows_kernel<1, kRowsTiles, false>), grid, block, 0, s, a);
+    else         hipLaunchKernelGGL((linear_rows_kernel<2, kRowsTiles, false>), grid, block, 0, s, a);
+    return hipGetLastError();
+}
+
+// ---- repacked weights, activations in operand order ---------------------------------------------------------------------
 // Outputs per block and K split from a cost model fitted to 4226 timings (140 shapes, 33 to 256 tokens, activations already in
 // operand order), 4 to 6 % off: per round of blocks over the chip a chain of steps (a group per wave each), the weight
 // stream, what further blocks of the same compute unit add, and for split K the summing launch and the partial tiles.
@@ -309,7 +353,7 @@ template <int NT>
 static hipError_t launch_operand_nt(RowsArgs &a, hipStream_t s)
 {
     a.m_tiles = (a.T + 31) / 32; a.n_tiles = (a.N + 16 * NT - 1) / (16 * NT);
-    hipLaunchKernelGGL((linear_rows_kernel<2, NT>), dim3((unsigned)(a.m_tiles * a.n_tiles * a.k_split + 7) / 8 * 8),
+    hipLaunchKernelGGL((linear_rows_kernel<2, NT, true>), dim3((unsigned)(a.m_tiles * a.n_tiles * a.k_split + 7) / 8 * 8),
                        dim3(kRowsWaves * 64), 0, s, a);
     return hipGetLastError();
 }
@@ -322,7 +366,8 @@ hipError_t launch_linear_operand(const paro_w4_weight &w, const paro_half_t *Xop
     a.w = (const char *)w.packed;
     a.scales_off = (uint32_t)packed_tiles_bytes(w.c_in, w.c_out);
     a.zeros_off = a.scales_off + (uint32_t)packed_scales_bytes(w.c_in, w.c_out);
-    a.X = (const _Float16 *)Xop; a.Y = (_Float16 *)Y; a.ldy = ldy; a.bias = (const _Float16 *)w.bias;
+    a.scales = nullptr; a.qzeros = nullptr;
+    a.X = (const _Float16 *)Xop; a.ldx = 0; a.Y = (_Float16 *)Y; a.ldy = ldy; a.bias = (const _Float16 *)w.bias;
     a.T = T; a.C = w.c_in; a.N = w.c_out; a.G = w.c_in / kGroup;
     a.m_lo = 0x000F000Fu; a.m_hi = 0x00F000F0u; a.k_lo = 0x64006400u; a.k_hi = 0x54005400u;
     // the caller takes this kernel only where its partial tiles have room

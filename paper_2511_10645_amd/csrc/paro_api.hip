@@ -489,6 +489,11 @@ int paro_internal_linear_plan_in(const paro_rotation *rot, const paro_w4_weight 
     return kernel;
 }
 
+void paro_internal_rows_plan(const paro_w4_weight *w, int32_t T, size_t room, int32_t out[5])
+{
+    linear_rows_plan(*w, T, room, out[0], out[1], out[2], out[3], out[4]);
+}
+
 int paro_internal_mxfp4_plan(const paro_mxfp4_weight *w, int32_t T) { return mxfp4_linear_plan(*w, T); }
 
 int paro_internal_linear_plan(const paro_rotation *rot, const paro_w4_weight *w, int32_t T, int32_t *tile, int32_t *k_slices)

@@ -191,9 +191,12 @@ hipError_t launch_quantize_act_mxfp4(const paro_rotation &rot, const paro_half_t
 // between blocks (any contents before; after, those below `least` are zero: launch_splitk_reduce); without it the call
 // runs unsplit.
 bool linear_rows_supported(const paro_w4_weight &w, int64_t ldx, int T);
+void linear_rows_plan(const paro_w4_weight &w, int T, size_t room, int &outputs, int &k_slices, int &config, int &stages, int &ring);
 size_t linear_rows_scratch_bytes(const paro_w4_weight &w, int T);
 hipError_t launch_linear_rows(const paro_w4_weight &w, const paro_half_t *X, int64_t ldx, paro_half_t *Y, int64_t ldy,
                               int T, void *scratch, size_t scratch_bytes, const void *least, hipStream_t s);
+// The same with activations and weights straight in registers (linear_rows.hip), never split.
+hipError_t launch_linear_direct(const paro_w4_weight &w, const paro_half_t *X, int64_t ldx, paro_half_t *Y, int64_t ldy, int T, hipStream_t s);
 
 // Repacked weights on activations in operand order (linear_rows.hip); scratch as above.
 bool linear_operand_supported(const paro_w4_weight &w, int T);
@@ -240,3 +243,6 @@ extern "C" int paro_internal_linear_plan(const paro_rotation *rot, const paro_w4
 extern "C" int paro_internal_linear_plan_in(const paro_rotation *rot, const paro_w4_weight *w, int32_t T, size_t ws_bytes, int32_t *tile, int32_t *k_slices);
 // The MXFP4 linear with dense rows: 0 the streaming kernel, else the outputs per block of the GEMM.
 extern "C" int paro_internal_mxfp4_plan(const paro_mxfp4_weight *w, int32_t T);
+// kPlanRows with `room` bytes for partial tiles: outputs per block (0: launch_linear_direct), slices of K, which instantiation, the
+// stages of a slice and the deeper of its rings.
+extern "C" void paro_internal_rows_plan(const paro_w4_weight *w, int32_t T, size_t room, int32_t out[5]);

@@ -43,10 +43,16 @@ CASES = [
     (1, 512, 528, "plain"), (1, 1152, 144, "plain"),       # one token, few short rows: a wave per row
     (1, 640, 48, "plain"), (1, 11008, 272, "plain"), (16, 128, 16, "plain"), (17, 1920, 80, "plain"), (32, 640, 528, "plain"),
     (24, 2176, 4112, "plain"), (33, 128, 16, "plain"), (33, 640, 144, "plain"), (64, 1152, 2064, "plain"),
-    # up to 32 tokens: fewer groups than a stage has, a last stage moved back, every split of the tokens into requests, 16 to 128
-    # outputs per block with tiles beyond the last output, K split (the last two)
+    # up to 32 tokens: fewer groups than a stage has, a last stage moved back, every split of the tokens into requests, 16 to 64
+    # outputs per block with tiles beyond the last output, K split (the last two, rotated)
     (3, 384, 16, "plain"), (8, 896, 32064, "plain"), (4, 1664, 16400, "plain"), (9, 1152, 8240, "plain"), (16, 3712, 2064, "plain"), (25, 2688, 8208, "plain"),
     (6, 2944, 9744, "plain"), (5, 896, 6080, "plain"), (14, 2176, 6096, "plain"), (29, 5760, 4144, "plain"), (21, 640, 20544, "plain"), (13, 11008, 272, "plain"), (24, 11008, 272, "plain"),
+    # every instantiation with more stages than its rings hold, the last one moved back (test_linear_plans.py), and the split of 11008 -> 4096
+    (4, 7296, 16, "plain"), (12, 6272, 16, "plain"), (23, 6272, 16, "plain"), (29, 3200, 16, "plain"), (4, 3200, 4112, "plain"), (15, 3712, 4192, "plain"),
+    (22, 3200, 4128, "plain"), (27, 3200, 4144, "plain"), (2, 1664, 8304, "plain"), (9, 2688, 8208, "plain"), (19, 2176, 8208, "plain"), (28, 1664, 8288, "plain"),
+    (1, 1664, 16688, "plain"), (24, 11008, 4096, "plain"),
+    # many outputs on few channels: every wave on its own, one and two blocks of 16 tokens, waves with no, one and many groups, ragged tokens and outputs
+    (2, 128, 39280, "plain"), (16, 640, 19088, "plain"), (5, 640, 8208, "plain"), (1, 2432, 17424, "plain"), (13, 2560, 16400, "plain"), (25, 384, 51168, "plain"), (32, 128, 27312, "plain"),
     (65, 1920, 272, "plain"), (129, 4096, 1040, "plain"), (200, 2176, 1296, "plain"), (5, 640, 80, "scales_odd"), (40, 640, 80, "scales_odd"),
     # repacked: 64-token tiles, K split and not, ragged tokens and outputs
     (33, 4096, 4112, "packed"), (64, 4096, 6144, "packed"), (64, 512, 16400, "packed"), (80, 2048, 2064, "packed"),

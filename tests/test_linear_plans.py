@@ -100,3 +100,41 @@ def test_two_pairs_of_steps_are_not_split():
     """1024 channels are two pairs of steps: in two slices, with a launch to sum them, slower but for very few outputs."""
     for T, c_out, k in ((97, 128, 1), (126, 208, 1), (69, 144, 1), (80, 16, 2), (202, 48, 2)):
         assert plan(T, 1024, c_out, "packed", False) == (TILE, 64, k), (T, c_out)
+
+
+def rows_plan(T, c_in, c_out, room):
+    """outputs per block (0: every wave on its own), slices of K, instantiation, stages of a slice, the deeper of its rings"""
+    f = paro.lib().paro_internal_rows_plan
+    f.restype, f.argtypes = None, [ctypes.c_void_p, ctypes.c_int32, ctypes.c_size_t, ctypes.c_void_p]
+    out = (ctypes.c_int32 * 5)()
+    f(ctypes.byref(_CW4Weight(c_in, c_out, 128, FAKE, FAKE, FAKE, None, None)), T, room, out)
+    return tuple(out)
+
+
+def test_cases_refill_the_rings_of_every_interchange_instantiation():
+    wrap, split, direct = set(), set(), set()
+    for T, c_in, c_out, form in CASES:
+        for rotated in (False, True):
+            if plan(T, c_in, c_out, form, rotated)[0] != ROWS:
+                continue
+            outputs, k, config, stages, ring = rows_plan(T, c_in, c_out, 1 << 40 if rotated else 0)
+            if not outputs:
+                direct.add(T > 16)
+                continue
+            groups = -(-(c_in // 128) // k)
+            if stages > ring and groups % (8 if outputs == 16 else 4):
+                wrap.add(config)                      # a slot is requested anew, and the last stage is moved back
+            if k > 1 and stages > ring:
+                split.add(outputs)
+    assert wrap == set(range(13)), sorted(wrap)
+    assert split >= {64} and direct == {False, True}, (split, direct)
+    assert rows_plan(24, 11008, 4096, 1 << 40) == (64, 4, 10, 6, 4)
+
+
+def test_many_outputs_on_few_channels_leave_the_staged_kernel():
+    """Bare interchange calls, every wave on its own against staged through LDS, us: 9.7 / 14.2, 6.8 / 11.8, 7.1 / 8.8, 13.7 / 15.1;
+    6.0 / 5.4, 6.8 / 6.3, 12.6 / 12.6, 9.0 / 8.5."""
+    for T, c_in, c_out in ((4, 1024, 43280), (10, 128, 49216), (16, 640, 19072), (25, 384, 51168)):
+        assert rows_plan(T, c_in, c_out, 0)[0] == 0, (T, c_in, c_out)
+    for T, c_in, c_out in ((3, 256, 31184), (8, 1536, 12160), (24, 1152, 26784), (20, 512, 22304)):
+        assert rows_plan(T, c_in, c_out, 0)[0] > 0, (T, c_in, c_out)
