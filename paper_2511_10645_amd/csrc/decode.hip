@@ -398,8 +398,8 @@ hipError_t launch_decode_multi(int n_parts, const paro_rotation *const *rot, con
 
 // ------------------------------------------------------------------------------------------
 // Generic linear on the interchange layout: one wave per output row, plain fp32 FMAs.
-// For one token on few short rows (linear_rows_supported), and for what linear_ic.hip and linear_tile.hip cannot address (scales
-// not 4-byte aligned, 2 GiB of codes or rows and more), where it is slow.
+// For what linear_ic.hip and linear_tile.hip cannot address (scales not 4-byte aligned, 2 GiB of codes or rows and more), where it
+// is slow.  (One token on few short rows took it, too, while the other kernel was slower there: 512 -> 1040 3.4 us, now 3.0.)
 // ------------------------------------------------------------------------------------------
 __global__ __launch_bounds__(256) void linear_generic_kernel(const uint32_t *__restrict__ qweight,
                                                              const _Float16 *__restrict__ scales,

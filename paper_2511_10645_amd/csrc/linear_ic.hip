@@ -286,12 +286,9 @@ size_t linear_rows_scratch_bytes(const paro_w4_weight &w, int T)
     return p.k_split > 1 ? (size_t)p.k_split * T * w.c_out * sizeof(float) : 0;
 }
 
-// scales as dwords; row offsets of a block and the whole code array in 31 bits; up to 32 tokens.  Not one token on few
-// short rows: this kernel runs whole rounds of 8 groups, the generic one (a wave per row, 512 channels a step) just what is
-// there.
+// scales as dwords; row offsets of a block and the whole code array in 31 bits; up to 32 tokens
 bool linear_rows_supported(const paro_w4_weight &w, int64_t ldx, int T)
 {
-    if (T == 1 && ((w.c_in <= 512 && w.c_out <= 2048) || (w.c_in > 1024 && w.c_in <= 1536 && w.c_out <= 640))) return false;
     return w.qweight && w.scales && w.qzeros && ((uintptr_t)w.scales % 4) == 0 && T <= 32 && (size_t)T * ldx * 2 < (1ull << 31) &&
            (size_t)w.c_out * (w.c_in / 2) < (1ull << 31);
 }

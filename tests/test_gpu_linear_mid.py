@@ -40,7 +40,7 @@ def _weight(P, li, bias, form):
 
 CASES = [
     # interchange layout: blocks of 16 tokens, the last group of a round missing, outputs that end inside a block
-    (1, 512, 528, "plain"), (1, 1152, 144, "plain"),       # one token, few short rows: a wave per row
+    (1, 512, 528, "plain"), (1, 1152, 144, "plain"),       # one token, few short rows
     (1, 640, 48, "plain"), (1, 11008, 272, "plain"), (16, 128, 16, "plain"), (17, 1920, 80, "plain"), (32, 640, 528, "plain"),
     (24, 2176, 4112, "plain"), (33, 128, 16, "plain"), (33, 640, 144, "plain"), (64, 1152, 2064, "plain"),
     # up to 32 tokens: fewer groups than a stage has, a last stage moved back, every split of the tokens into requests, 16 to 64
