@@ -335,12 +335,13 @@ static hipError_t launch_mxfp4_decode(const paro_mxfp4_weight &w, const uint32_t
 //   - Outputs leave past the L2 (non-temporal): a round's tiles finish together, and their 33 MB would push the operands out of
 //     the L2s (4096 tokens 5120 -> 55296: 636 us with plain stores, 581).  A ragged last tile does the same (in 2-byte stores
 //     it alone took 2 to 4 us: 168 tokens 1536 -> 19040 15.2 us with the quantiser, now 12.7).
-// What bounds it (counters, 4096 tokens 5120 -> 55296): the chip's power - 1.6 GHz with the matrix cores busy 55 % of the cycles -
-// and the operand traffic out of L2 (9 GB; with all-zero operands, which cost no switching, 431 us).
+// What bounds it (counters, 4096 tokens 5120 -> 55296): the chip's power - 1.6 GHz with the matrix cores busy 61 % of the cycles -
+// and the operand traffic out of L2 (9 GB; with all-zero operands, which cost no switching, 431 us).  2048 tokens 4096 -> 28672: 2.3
+// GHz, busy 44 %.  NTW = 2 takes all 256 registers and spills one, in the prologue and back behind the loop.
 // Measured, us, before (256 x 256 tiles of 8 waves, activations through registers, 16x16x128 instruction, one block per
 // compute unit) -> now: 2048 tokens 4096 -> 6144 42.3 -> 36.0, 4096 -> 4096 26.9 -> 21.1, 4096 -> 28672 168.7 -> 143.1 (3.4
-// PFLOP/s), 14336 -> 4096 74.6 -> 65.9; 4096 tokens 5120 -> 55296 698 -> 579 (4.0); 256 tokens 14336 -> 4096 53.8 -> 27.9; the
-// 152 shapes of the fit below: 0.76 of the time in the geometric mean.
+// PFLOP/s), 14336 -> 4096 74.6 -> 65.9; 4096 tokens 5120 -> 55296 698 -> 579 (4.0); 256 tokens 14336 -> 4096 53.8 -> 27.9;
+// with the quantiser, 111 random shapes of 33 to 2048 tokens: 0.77 of the time in the geometric mean, none more than 1.5 % slower.
 // ------------------------------------------------------------------------------------------
 struct MxGemmArgs {
     const void *blob; uint32_t blob_bytes, scales_off;

@@ -18,9 +18,9 @@
 // One wavefront owns a channel group and a run of rows, four rows at a time (few rows: one each, kQuantFewRows), with the
 // lane plan and layer loop of the activation kernel (rotate_lane.h): the plan (7.4 KB at K = 8, 29 times a row's group) is
 // read once per run, the four rows' chains of multiply-adds and permutes are independent, and rows go through a
-// wave-private LDS area as [channel][4 rows].  What bounds it is mostly the vector pipes (INT4 weights: some 88 instructions
-// per (row, group) at four cycles each, 38 of them rotation; taking 13 of 101 out gave 4 % with a rotation and 13 % without,
-// the rest is the permutes' LDS time) -
+// wave-private LDS area as [channel][4 rows].  No single unit bounds it: the vector pipes (INT4 weights: some 88
+// instructions per (row, group), 38 of them rotation; taking 13 of 101 out gave 4 % with a rotation and 13 % without), the
+// permutes' LDS time, and 6 waves per SIMD (77 registers) to overlap the two -
 //   - INT4: minimum and maximum of the four rows are reduced together, each swap of half waves merging two rows, so that
 //     every 16 lanes end up with one row's and the scale, its reciprocal and the zero point are computed once for all
 //     four; v / s is the correctly rounded quotient from the correctly rounded reciprocal and one residual (Markstein's
@@ -32,8 +32,9 @@
 // Measured over back-to-back calls (before: one row of INT4 weights per wave, plan re-read for each; MXFP4 one row at a
 // time, 14 instructions of thresholds per value): INT4 weight 28672 x 4096 414 -> 146 us (137 with reciprocals in place of the
 // three divisions, bytes picked by permutes and the factor of one left out; without a rotation 97 -> 84), MXFP4 activations 2048 x 4096
-// 21.0 -> 12.8, 2048 x 14336 55.8 -> 36.4 us, INT4 activations 24.7 -> 14.8 and 78.3 -> 39.6 us; 1 x 4096 MXFP4
-// 3.0 -> 2.6, INT4 2.9 -> 2.8; the same bits throughout.
+// 21.0 -> 12.2, 2048 x 14336 55.8 -> 35.2 us (11.8 and 35.5 with codes past the L2, as INT4 codes leave it: weights 1 to 7 % faster
+// alone, a GEMM behind as fast over 36 shapes), INT4 activations 24.7 -> 14.3 and 78.3 -> 39.6 us (now 13.9 on the former); 1 x 4096
+// MXFP4 3.0 -> 2.6, INT4 2.9 -> 2.8; the same bits throughout.
 #include "paro_internal.h"
 #include "rotate_lane.h"
 #include <type_traits>

@@ -203,8 +203,9 @@ hipError_t launch_plan_build(const paro_rotation &rot, void *plan_out, hipStream
 constexpr int kRotWaves = 4;   // waves per block
 constexpr int kRotTU = 4;      // tokens in flight per wave
 constexpr int kRotMaxBatches = 8;   // batches of kRotTU tokens per wave (the batch loop is unrolled)
-// Rows leave the L2 as they are written (sc1) instead of all at once when the launch ends.  Graph replay over 400 MB, us, plain
-// stores / these: 2048 x 4096 13.0 / 11.5, 1023 x 14336 20.2 / 18.5, 4096 x 27648 124 / 119; no difference at 16..256 tokens.
+// Rows leave the L2 as they are written (sc1) instead of all at once when the launch ends.  Graph replay over 350 MB of rows, us,
+// plain stores / these: 2048 x 4096 12.4 / 11.2, 1023 x 14336 19.6 / 18.1, 2048 x 14336 33.0 / 32.0, also where rows begin anywhere in
+// a cache line (13.2 / 12.1 and 20.2 / 18.6 on the first two); 4096 x 27648 124 / 119; no difference at 16..256 tokens.
 constexpr int kAuxWriteThrough = 16;
 
 // f(0), f(1), ... while f returns true, at most N times; nested, so that stopping is one forward jump
