@@ -570,7 +570,7 @@ static size_t tile_partial_bytes(int k_split, int T, int c_out) { return k_split
 // room: bytes for partial tiles; what needs more is not planned.  (Bare calls on interchange weights have none: unsplit with the
 // tile that was best for the split, 13696 -> 1936 at 757 tokens takes 106 us, with the one that is best unsplit 63; 18 such
 // calls 0.54 to 0.70 of the time.)
-static TilePlan plan_tile(int c_in, int c_out, int T, size_t room)
+static TilePlan plan_tile(int c_in, int c_out, int T, bool interchange, size_t room)
 {
     struct Fit { double call, round, step, step_full, sum, slice, mb; };
     // est_us stays the model that the lines to the other kernels were fitted with (low by up to 2 us on few steps, high by up to a
@@ -578,11 +578,14 @@ static TilePlan plan_tile(int c_in, int c_out, int T, size_t room)
     // has room, the kernel with fewer slices is as slow as the others, and they stay.
     double lines_us = 1e30, least_us = 1e30;
     bool line_fits = false, least_fits = false;
-    static const Fit fits[2] = {{1.7, 3.8, 0.94, 1.04, 1.3, 0.27, 0.151}, {3.0, 4.2, 1.49, 1.71, 0.5, 0.245, 0.189}};
+    // The interchange layout costs 14 instead of 9 instructions per 8 weights, more of a step of the wide kernel (80 shapes with either
+    // forced, 3 % off; priced as repacked weights 5888 -> 16944 at 464 tokens took 162 us in 128-token tiles instead of 152).
+    static const Fit fits[2][2] = {{{1.7, 3.8, 0.94, 1.04, 1.3, 0.27, 0.151}, {3.0, 4.2, 1.49, 1.71, 0.5, 0.245, 0.189}},
+                                   {{2.0, 3.36, 1.04, 1.12, 1.3, 0.27, 0.151}, {0.5, 4.9, 1.88, 1.96, 0.5, 0.245, 0.189}}};
     TilePlan best{false, 1, 0, 1e30};
     const int G = c_in / kGroup, n_tiles = (c_out + 127) / 128;
     for (int two = 0; two <= (T > 64 ? 1 : 0); ++two) {
-        const Fit &f = fits[two];
+        const Fit &f = fits[interchange][two];
         const int m_tiles = (T + (two ? 127 : 63)) / (two ? 128 : 64);
         for (int ks = 1; ks <= 16 && (ks == 1 || (ks * 4 <= G && (long)m_tiles * n_tiles * ks <= 512)); ++ks) {
             const int gps = ((G + ks - 1) / ks + 3) / 4 * 4;             // whole steps, an even number of them
@@ -608,16 +611,16 @@ static TilePlan plan_tile(int c_in, int c_out, int T, size_t room)
     return best;
 }
 
-double linear_tile_estimate_us(const paro_w4_weight &w, int T, size_t room) { return plan_tile(w.c_in, w.c_out, T, room).est_us; }
+double linear_tile_estimate_us(const paro_w4_weight &w, int T, size_t room) { return plan_tile(w.c_in, w.c_out, T, false, room).est_us; }
 
-size_t linear_tile_scratch_bytes(const paro_w4_weight &w, int T, size_t room)
+size_t linear_tile_scratch_bytes(const paro_w4_weight &w, int T, bool interchange, size_t room)
 {
-    return tile_partial_bytes(plan_tile(w.c_in, w.c_out, T, room).k_split, T, w.c_out);
+    return tile_partial_bytes(plan_tile(w.c_in, w.c_out, T, interchange, room).k_split, T, w.c_out);
 }
 
-void linear_tile_plan(const paro_w4_weight &w, int T, size_t room, int &tokens, int &k_slices)
+void linear_tile_plan(const paro_w4_weight &w, int T, bool interchange, size_t room, int &tokens, int &k_slices)
 {
-    const TilePlan p = plan_tile(w.c_in, w.c_out, T, room);
+    const TilePlan p = plan_tile(w.c_in, w.c_out, T, interchange, room);
     tokens = p.two_m ? 128 : 64; k_slices = p.k_split;
 }
 
@@ -631,7 +634,7 @@ bool linear_tile_supported(const paro_w4_weight &w, bool interchange)
 hipError_t launch_linear_tile(const paro_w4_weight &w, bool interchange, const paro_half_t *X, int64_t ldx, paro_half_t *Y,
                               int64_t ldy, int T, void *scratch, size_t scratch_bytes, const void *least, hipStream_t s)
 {
-    const TilePlan p = plan_tile(w.c_in, w.c_out, T, scratch && ((uintptr_t)scratch % 16) == 0 ? scratch_bytes : 0);
+    const TilePlan p = plan_tile(w.c_in, w.c_out, T, interchange, scratch && ((uintptr_t)scratch % 16) == 0 ? scratch_bytes : 0);
     TileArgs a;
     a.w = interchange ? (const char *)w.qweight : (const char *)w.packed;
     a.scales_off = (uint32_t)packed_tiles_bytes(w.c_in, w.c_out);

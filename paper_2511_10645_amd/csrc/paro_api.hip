@@ -117,12 +117,12 @@ WsLayout ws_layout(const paro_rotation *rot, const paro_w4_weight *w, int T, boo
         L.exchange_bytes = (rot || part) ? kWsPartialOff + round_up(part, 256) : 0;
         if (T > kDecodeMaxTokens) {
             L.gemm_bytes = round_up(gemm_scratch_bytes(*w, T), 256);
-            if (T > kStreamPassTokens && T <= 1024) faster = linear_tile_scratch_bytes(*w, T);
+            if (T > kStreamPassTokens && T <= 1024) faster = linear_tile_scratch_bytes(*w, T, false);
             if (rot && rot->plan && linear_operand_supported(*w, T)) faster = std::max(faster, linear_operand_scratch_bytes(*w, T));
         }
     } else if (rot) {
         // weights in the interchange layout; the bare call needs no workspace and runs without the split
-        faster = T <= kStreamPassTokens ? linear_rows_scratch_bytes(*w, T) : linear_tile_scratch_bytes(*w, T);
+        faster = T <= kStreamPassTokens ? linear_rows_scratch_bytes(*w, T) : linear_tile_scratch_bytes(*w, T, true);
     }
     faster = round_up(faster, 256);
     if (!lean && faster > L.gemm_bytes) L.extra_bytes = faster - L.gemm_bytes;
@@ -222,7 +222,7 @@ paro_status run_linear(const paro_w4_weight *w, const paro_half_t *X, int64_t ld
                        void *ws, const Scratch &scratch, hipStream_t s)
 {
     auto tile = [&](bool interchange) {
-        const size_t need = linear_tile_scratch_bytes(*w, T, scratch.bytes);
+        const size_t need = linear_tile_scratch_bytes(*w, T, interchange, scratch.bytes);
         return from_hip(launch_linear_tile(*w, interchange, X, ldx, Y, ldy, T, scratch.partials(need), need, scratch.least, s));
     };
     if (!fast_weight(w)) {
@@ -484,7 +484,7 @@ int paro_internal_linear_plan_in(const paro_rotation *rot, const paro_w4_weight 
         if (kernel == kPlanStream) t = rot && rot->plan && decode_wide_operand_pays(w->c_in, T);
     } else if (linear_rows_supported(*w, w->c_in, T)) { kernel = kPlanRows; k = scratch ? (int)(linear_rows_scratch_bytes(*w, T) / ((size_t)T * w->c_out * 4)) : 1; }
     else if (T > kStreamPassTokens && linear_tile_supported(*w, true)) kernel = kPlanTile;
-    if (kernel == kPlanTile) linear_tile_plan(*w, T, scratch, t, k);
+    if (kernel == kPlanTile) linear_tile_plan(*w, T, !fast_weight(w), scratch, t, k);
     *tile = t; *k_slices = k;
     return kernel;
 }

@@ -210,8 +210,8 @@ hipError_t launch_linear_operand(const paro_w4_weight &w, const paro_half_t *Xop
 bool linear_tile_supported(const paro_w4_weight &w, bool interchange);
 // room: bytes there are for partial tiles; a call with less than the best split wants is planned with fewer slices, or none.
 double linear_tile_estimate_us(const paro_w4_weight &w, int T, size_t room);
-void linear_tile_plan(const paro_w4_weight &w, int T, size_t room, int &tokens, int &k_slices);
-size_t linear_tile_scratch_bytes(const paro_w4_weight &w, int T, size_t room = SIZE_MAX);
+void linear_tile_plan(const paro_w4_weight &w, int T, bool interchange, size_t room, int &tokens, int &k_slices);
+size_t linear_tile_scratch_bytes(const paro_w4_weight &w, int T, bool interchange, size_t room = SIZE_MAX);
 hipError_t launch_linear_tile(const paro_w4_weight &w, bool interchange, const paro_half_t *X, int64_t ldx, paro_half_t *Y,
                               int64_t ldy, int T, void *scratch, size_t scratch_bytes, const void *least, hipStream_t s);
 

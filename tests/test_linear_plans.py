@@ -138,3 +138,10 @@ def test_many_outputs_on_few_channels_leave_the_staged_kernel():
         assert rows_plan(T, c_in, c_out, 0)[0] == 0, (T, c_in, c_out)
     for T, c_in, c_out in ((3, 256, 31184), (8, 1536, 12160), (24, 1152, 26784), (20, 512, 22304)):
         assert rows_plan(T, c_in, c_out, 0)[0] > 0, (T, c_in, c_out)
+
+
+def test_interchange_weights_are_planned_with_their_own_times():
+    """Several rounds of blocks, where the wide kernel's step costs more on interchange weights (64- / 128-token tiles, us: 157 / 162,
+    240 / 249, 319 / 333; 356 / 338)."""
+    for T, c_in, c_out, tokens in ((464, 5888, 16944, 64), (414, 5376, 36048, 64), (731, 13184, 11728, 64), (952, 4480, 29152, 128)):
+        assert plan(T, c_in, c_out, "plain", False) == (TILE, tokens, 1), (T, c_in, c_out)
