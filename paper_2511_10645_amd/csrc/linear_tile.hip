@@ -567,6 +567,7 @@ constexpr int kTileWideGroups = 12;
 // interchange layout in one to five rounds, 2 % off.
 struct TilePlan { bool two_m; int k_split, groups_per_split; double est_us; };
 static size_t tile_partial_bytes(int k_split, int T, int c_out) { return k_split > 1 ? (size_t)k_split * T * c_out * sizeof(float) : 0; }
+
 // room: bytes for partial tiles; what needs more is not planned.  (Bare calls on interchange weights have none: unsplit with the
 // tile that was best for the split, 13696 -> 1936 at 757 tokens takes 106 us, with the one that is best unsplit 63; 18 such
 // calls 0.54 to 0.70 of the time.)
@@ -579,7 +580,7 @@ static TilePlan plan_tile(int c_in, int c_out, int T, bool interchange, size_t r
     double lines_us = 1e30, least_us = 1e30;
     bool line_fits = false, least_fits = false;
     // The interchange layout costs 14 instead of 9 instructions per 8 weights, more of a step of the wide kernel (80 shapes with either
-    // forced, 3 % off; priced as repacked weights 5888 -> 16944 at 464 tokens took 162 us in 128-token tiles instead of 152).
+    // forced, 3 % off; priced as repacked weights 5888 -> 16944 at 464 tokens took 162 us in 128-token tiles instead of 157).
     static const Fit fits[2][2] = {{{1.7, 3.8, 0.94, 1.04, 1.3, 0.27, 0.151}, {3.0, 4.2, 1.49, 1.71, 0.5, 0.245, 0.189}},
                                    {{2.0, 3.36, 1.04, 1.12, 1.3, 0.27, 0.151}, {0.5, 4.9, 1.88, 1.96, 0.5, 0.245, 0.189}}};
     TilePlan best{false, 1, 0, 1e30};
