@@ -13,6 +13,7 @@
 //   MXFP4        32 consecutive channels share 2^e, e = floor(log2(max |v|)) - 2 (>= -127), stored as e + 127; every value
 //                becomes the E2M1 code of v / 2^e, to nearest, ties to the even code, saturated at 6.  A block that is
 //                NaN throughout has e = 126 and codes +-6: what is multiplied with it overflows.
+// (large dense weights: quantize_weight.hip)
 // so that  sum_c (q - z) s . x'_c  ~  w_n . x  for the activations x' that paro_rotate_scale produces (Eq. 2).
 //
 // One wavefront owns a channel group and a run of rows, four rows at a time (few rows: one each, kQuantFewRows), with the
@@ -36,7 +37,7 @@
 // alone, a GEMM behind as fast over 36 shapes), INT4 activations 24.7 -> 14.3 and 78.3 -> 39.6 us (now 13.9 on the former); 1 x 4096
 // MXFP4 3.0 -> 2.6, INT4 2.9 -> 2.8; the same bits throughout.
 #include "paro_internal.h"
-#include "rotate_lane.h"
+#include "quantize_common.h"
 #include <type_traits>
 
 namespace paro {
@@ -69,14 +70,6 @@ __device__ __forceinline__ void quant_while(F &&f)
     }
 }
 
-// v of another lane of the same 16 (DPP control word CTRL)
-template <int CTRL>
-__device__ __forceinline__ float dpp(float v)
-{
-    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, true));
-}
-constexpr int kQuadXor1 = 0xB1, kQuadXor2 = 0x4E, kHalfMirror = 0x141, kMirror = 0x140;
-
 // Maximum over the wave of four values per lane; lanes 0-15 return that of v[0], 16-31 of v[2], 32-47 of v[1], 48-63 of v[3].
 __device__ __forceinline__ float wave_max4(const float (&v)[4])
 {
@@ -95,30 +88,6 @@ __device__ __forceinline__ float wave_max4(const float (&v)[4])
 constexpr int kRowLane[4] = {0, 32, 16, 48};         // a lane that holds row u's maximum
 __device__ __forceinline__ int row_of_lane(int lane) { return ((lane >> 5) & 1) | ((lane >> 3) & 2); }
 __device__ __forceinline__ float from_lane(float v, int lane) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), lane)); }
-
-// 1 / s of an fp16 value s >= 2^-14, correctly rounded: the hardware's estimate and one Newton step (compared with the division
-// on all of them)
-__device__ __forceinline__ float quant_rcp(float s)
-{
-    const float r = __builtin_amdgcn_rcpf(s);
-    return fmaf(fmaf(-s, r, 1.0f), r, r);
-}
-
-// rotate_layers with the order of the two products of every sum written out (the one that is there first is rounded, the
-// later one joins it in a fused multiply-add): a code on a rounding tie must not depend on how the compiler schedules.
-template <int K, int U>
-__device__ __forceinline__ void quant_rotate(const LanePlan<K> &P, float (&a)[U], float (&b)[U])
-{
-#pragma unroll
-    for (int l = 0; l < K; ++l)
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const float na = l == 0 ? fmaf(P.m00[l], a[u], P.m01[l] * b[u]) : fmaf(P.m01[l], b[u], P.m00[l] * a[u]);
-            const float nb = l == 0 ? fmaf(P.m10[l], a[u], P.m11[l] * b[u]) : fmaf(P.m11[l], b[u], P.m10[l] * a[u]);
-            a[u] = na;
-            b[u] = (l + 1 < K) ? __int_as_float(__builtin_amdgcn_ds_bpermute(P.src[l], __float_as_int(nb))) : nb;
-        }
-}
 
 // K < 0: no transform (rows quantised as they are).  U: rows side by side, kQuantRows, or one where the rows do not fill the
 // chip: four rows then only lengthen the chain of one wave.
@@ -346,6 +315,7 @@ static hipError_t launch_quant(const paro_rotation *rot, QuantArgs &a, hipStream
 hipError_t launch_quantize(const paro_rotation *rot, const paro_half_t *W, int64_t ldw, int N, int C, uint32_t *qweight,
                            paro_half_t *scales, uint32_t *qzeros, hipStream_t s)
 {
+    if (quantize_tiles_pay(rot, false, N, C)) return launch_quantize_tiles(rot, false, W, ldw, N, C, qweight, scales, qzeros, nullptr, s);
     QuantArgs a{nullptr, (const _Float16 *)W, ldw, N, C, 0, qweight, (_Float16 *)scales, (uint16_t *)qzeros, nullptr};
     return launch_quant<kW4Weight>(rot, a, s);
 }
@@ -368,6 +338,7 @@ hipError_t launch_quantize_act_mxfp4(const paro_rotation &rot, const paro_half_t
 hipError_t launch_quantize_weight_mxfp4(const paro_rotation *rot, const paro_half_t *W, int64_t ldw, int N, int C,
                                         uint32_t *codes, uint8_t *scales, hipStream_t s)
 {
+    if (quantize_tiles_pay(rot, true, N, C)) return launch_quantize_tiles(rot, true, W, ldw, N, C, codes, nullptr, nullptr, scales, s);
     QuantArgs a{nullptr, (const _Float16 *)W, ldw, N, C, 0, codes, nullptr, nullptr, scales};
     return launch_quant<kMxWeight>(rot, a, s);
 }
