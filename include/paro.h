@@ -216,8 +216,9 @@ paro_status paro_rotated_linear_noalloc(const paro_rotation *rot, const paro_w4_
  * (or gate / up) of a decoder layer need three (two) transforms of one X.  Part p computes
  * Y[p] = W^_p . (R_p . S_p . x) (+ b_p) exactly as paro_rotated_linear(rots[p], weights[p], X, Y[p]).
  * n_parts in 1..4; all parts share c_in.  With T <= 4, every rotation planned, every weight
- * repacked and equal layer counts the parts run as ONE launch (results are bit-identical to the
- * separate calls); otherwise the call is the sequence of separate calls.  rots, weights, Y and
+ * repacked and equal layer counts the parts run as ONE launch, or one for the transforms and one
+ * for the products (results are bit-identical to the separate calls where these take the same
+ * kernel, and agree to rounding elsewhere); otherwise the call is the sequence of separate calls.  rots, weights, Y and
  * ldy are HOST arrays of n_parts entries (device pointers inside, as in the single call).
  * ws: device, >= paro_workspace_bytes_multi(...) bytes, 256-byte aligned, in the two parts
  * described at paro_workspace_bytes() (exchange part: paro_workspace_exchange_bytes_multi()). */

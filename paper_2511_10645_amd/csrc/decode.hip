@@ -204,13 +204,6 @@ __global__ __launch_bounds__(W * 64) void decode_kernel(DecodeArgs a)
 // the method has its own pairs, angles and scales - q / k / v or gate / up of a decoder layer),
 // in one launch: the block rows (blockIdx.y) are divided among the parts, and a block runs the
 // single-linear body on its part's arguments.
-constexpr int kMaxParts = 4;
-struct MultiArgs {
-    DecodeArgs part[kMaxParts];
-    int nb_end[kMaxParts];      // block rows [nb_end[p-1], nb_end[p]) belong to part p
-    int n_parts;
-};
-
 template <int K, bool SPLIT, bool T1>
 __global__ __launch_bounds__(kDecThreads) void decode_multi_kernel(MultiArgs m)
 {

@@ -36,6 +36,14 @@ struct DecodeArgs {
     uint32_t m_lo, m_hi, k_lo, k_hi;     // dequant constants, see DequantConsts
 };
 
+// Several linears in one launch.
+constexpr int kMaxParts = 4;
+struct MultiArgs {
+    DecodeArgs part[kMaxParts];
+    int nb_end[kMaxParts];      // block rows [nb_end[p-1], nb_end[p]) belong to part p
+    int n_parts;
+};
+
 // Raw buffer resources (stride 0): an access whose byte offset lies beyond num_records returns 0
 // (loads) or is dropped (stores).  Predication by offset keeps every memory instruction of the
 // stream loop unconditional, so the outstanding-load count is static and the compiler can wait

@@ -125,14 +125,27 @@ __device__ __forceinline__ void load_x_fragments(const DecodeArgs &a, int ks, bo
 // MAXW: most waves per block (8: two waves per SIMD and 256 registers; otherwise kWideWaves).
 constexpr int kRotStageWords = kSliceCh / 2;     // the slice's 512 fp16 activations of one token, in floats
 
-template <bool SPLIT, bool T1, int ROTK = 0, int MAXW = kWideWaves>
-__global__ __launch_bounds__(MAXW * 64) void decode_wide_kernel(DecodeArgs a)
+// ARGS: MultiArgs for several linears of the same width in, in one launch: the block rows are divided among the parts, every
+// part has as many tiles per block, and a block runs on its part's arguments.
+__device__ __forceinline__ const DecodeArgs &part_of(const DecodeArgs &a, int &) { return a; }
+__device__ __forceinline__ const DecodeArgs &part_of(const MultiArgs &m, int &nb)
+{
+    int p = 0;
+    while (p + 1 < m.n_parts && nb >= m.nb_end[p]) ++p;
+    if (p) nb -= m.nb_end[p - 1];
+    return m.part[p];
+}
+
+template <bool SPLIT, bool T1, int ROTK = 0, int MAXW = kWideWaves, class ARGS = DecodeArgs>
+__global__ __launch_bounds__(MAXW * 64) void decode_wide_kernel(ARGS args)
 {
     static_assert(ROTK == 0 || T1, "the hosted transform is for one token");
     constexpr int NS = kWideStages;
     // [waves][tiles per block] partial tiles | kReduceWords reduce scratch
     extern __shared__ __attribute__((aligned(16))) float s_wide[];
-    const int kb = blockIdx.x, nb = blockIdx.y;
+    const int kb = blockIdx.x;
+    int nb = blockIdx.y;
+    const DecodeArgs &a = part_of(args, nb);
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int nw = blockDim.x >> 6;                                        // K-slices (waves) per block
@@ -399,7 +412,7 @@ __global__ __launch_bounds__(kWide2Waves * 64) void decode_wide2_kernel(DecodeAr
 }
 
 struct WideGeometry { int kb, nb, waves, tiles_per_block; size_t lds; };
-static WideGeometry wide_geometry(int c_in, int c_out, int T, bool hosted = false)
+static WideGeometry wide_geometry(int c_in, int c_out, int T, bool hosted = false, int n_parts = 1, const paro_w4_weight *const *w = nullptr)
 {
     const bool two = T > 16;                                 // two blocks of 16 tokens per wave (decode_wide2_kernel)
     WideGeometry g;
@@ -418,8 +431,14 @@ static WideGeometry wide_geometry(int c_in, int c_out, int T, bool hosted = fals
         const int fit = (int)((kWideLdsBytes - kReduceWords * sizeof(float)) / ((size_t)g.waves * 1024));
         if (tpb > fit) tpb = fit;
     }
-    g.tiles_per_block = tpb;
     g.nb = (NT + tpb - 1) / tpb;
+    if (w) {                                                 // c_out is that of all parts: their last blocks may be short, too
+        auto blocks = [&] { int b = 0; for (int p = 0; p < n_parts; ++p) b += (w[p]->c_out / kTileN + tpb - 1) / tpb; return b; };
+        const int most = two ? kWide2MaxTiles : std::min(wide_max_tiles(T == 1), T == 1 ? 16 : (int)((kWideLdsBytes - kReduceWords * sizeof(float)) / ((size_t)g.waves * 1024)));
+        while (tpb < most && blocks() > nb) ++tpb;
+        g.nb = blocks();
+    }
+    g.tiles_per_block = tpb;
     const int tile_words = two ? 512 : T == 1 ? kTileN : 256;
     const int wstride = hosted ? std::max(tpb * tile_words, kRotStageWords)                // as in the kernels
                         : T == 1 ? tpb * tile_words : std::max(tpb * tile_words, kXsWords);
@@ -461,6 +480,49 @@ bool decode_wide_operand_pays(int c_in, int T)
     return T > 16 && T <= kWideMaxTokens && c_in <= 2 * kWide2Waves * kSliceCh;
 }
 
+static DecodeArgs wide_args(const paro_w4_weight &w, const paro_half_t *X, int64_t ldx, paro_half_t *Y, int64_t ldy, int T, void *ws,
+                            size_t partial_off, const paro_rotation *rot, const WideGeometry &g)
+{
+    DecodeArgs a;
+    a.blob = w.packed;
+    a.scales_off = (uint32_t)packed_tiles_bytes(w.c_in, w.c_out);
+    a.zeros_off = a.scales_off + (uint32_t)packed_scales_bytes(w.c_in, w.c_out);
+    a.blob_bytes = a.zeros_off + (uint32_t)packed_zeros_bytes(w.c_in, w.c_out);
+    a.X = (const _Float16 *)X; a.ldx = ldx; a.Y = (_Float16 *)Y; a.ldy = ldy;
+    a.bias = (const _Float16 *)w.bias;
+    a.plan = rot ? (const uint32_t *)rot->plan + plan_compact_offset_dwords(rot->c_in / kGroup, rot->n_layers) : nullptr;
+    a.err = ws ? (uint32_t *)ws + kWsErrorWord : nullptr;
+    a.partial = ws ? (float *)((char *)ws + kWsPartialOff + partial_off) : nullptr;
+    a.T = T; a.C = w.c_in; a.N = w.c_out; a.G = w.c_in / kGroup; a.NT = w.c_out / kTileN;
+    a.KS = a.G / kSliceGroups;
+    a.tiles_per_block = g.tiles_per_block;
+    a.m_lo = 0x000F000Fu; a.m_hi = 0x00F000F0u; a.k_lo = 0x64006400u; a.k_hi = 0x54005400u;
+    return a;
+}
+
+static hipError_t wide_attributes()
+{
+    static std::atomic<uint64_t> attr_done{0};
+    if (const int dev = once_pending(attr_done); dev >= 0) {
+        const void *fns[] = {(const void *)decode_wide_kernel<false, false>, (const void *)decode_wide_kernel<false, true>,
+                             (const void *)decode_wide_kernel<true, false>, (const void *)decode_wide_kernel<true, true>,
+                             (const void *)decode_wide2_kernel<false, false>, (const void *)decode_wide2_kernel<true, false>,
+                             (const void *)decode_wide2_kernel<false, true>, (const void *)decode_wide2_kernel<true, true>,
+                             (const void *)decode_wide_kernel<false, true, 8, 8>, (const void *)decode_wide_kernel<true, true, 8, 8>,
+                             (const void *)decode_wide_kernel<false, true, 8>,
+                             (const void *)decode_wide_kernel<false, false, 0, kWideWaves, MultiArgs>, (const void *)decode_wide_kernel<true, false, 0, 8, MultiArgs>,
+                             (const void *)decode_wide_kernel<false, true, 8, 8, MultiArgs>, (const void *)decode_wide_kernel<true, true, 8, 8, MultiArgs>,
+                             (const void *)decode_wide_kernel<false, true, 8, kWideWaves, MultiArgs>,
+                             (const void *)decode_wide_kernel<false, true, 0, kWideWaves, MultiArgs>, (const void *)decode_wide_kernel<true, true, 0, 8, MultiArgs>};
+        for (const void *f : fns) {
+            hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+            if (e != hipSuccess) return e;
+        }
+        once_done(attr_done, dev);
+    }
+    return hipSuccess;
+}
+
 // ws: the exchange part of the workspace (may be NULL where no partial sums are exchanged).
 // rot: NULL for the bare linear; otherwise a transform decode_wide_hosts() accepts, applied to X by the kernel itself.
 // x_operand: X is in operand order (17..32 tokens).
@@ -472,34 +534,8 @@ hipError_t launch_decode_wide(const paro_w4_weight &w, const paro_half_t *X, int
     if (rot && (!decode_wide_hosts(*rot, T) || rot->c_in != w.c_in)) return hipErrorInvalidValue;
     const WideGeometry g = wide_geometry(w.c_in, w.c_out, T, rot != nullptr);
     if (g.kb > 64 || g.lds > kWideLdsBytes || (g.kb > 1 && !ws)) return hipErrorInvalidValue;
-    DecodeArgs a;
-    a.blob = w.packed;
-    a.scales_off = (uint32_t)packed_tiles_bytes(w.c_in, w.c_out);
-    a.zeros_off = a.scales_off + (uint32_t)packed_scales_bytes(w.c_in, w.c_out);
-    a.blob_bytes = a.zeros_off + (uint32_t)packed_zeros_bytes(w.c_in, w.c_out);
-    a.X = (const _Float16 *)X; a.ldx = ldx; a.Y = (_Float16 *)Y; a.ldy = ldy;
-    a.bias = (const _Float16 *)w.bias;
-    a.plan = rot ? (const uint32_t *)rot->plan + plan_compact_offset_dwords(rot->c_in / kGroup, rot->n_layers) : nullptr;
-    a.err = ws ? (uint32_t *)ws + kWsErrorWord : nullptr;
-    a.partial = ws ? (float *)((char *)ws + kWsPartialOff) : nullptr;
-    a.T = T; a.C = w.c_in; a.N = w.c_out; a.G = w.c_in / kGroup; a.NT = w.c_out / kTileN;
-    a.KS = a.G / kSliceGroups;
-    a.tiles_per_block = g.tiles_per_block;
-    a.m_lo = 0x000F000Fu; a.m_hi = 0x00F000F0u; a.k_lo = 0x64006400u; a.k_hi = 0x54005400u;
-    static std::atomic<uint64_t> attr_done{0};
-    if (const int dev = once_pending(attr_done); dev >= 0) {
-        const void *fns[] = {(const void *)decode_wide_kernel<false, false>, (const void *)decode_wide_kernel<false, true>,
-                             (const void *)decode_wide_kernel<true, false>, (const void *)decode_wide_kernel<true, true>,
-                             (const void *)decode_wide2_kernel<false, false>, (const void *)decode_wide2_kernel<true, false>,
-                             (const void *)decode_wide2_kernel<false, true>, (const void *)decode_wide2_kernel<true, true>,
-                             (const void *)decode_wide_kernel<false, true, 8, 8>, (const void *)decode_wide_kernel<true, true, 8, 8>,
-                             (const void *)decode_wide_kernel<false, true, 8>};
-        for (const void *f : fns) {
-            hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
-            if (e != hipSuccess) return e;
-        }
-        once_done(attr_done, dev);
-    }
+    const DecodeArgs a = wide_args(w, X, ldx, Y, ldy, T, ws, 0, rot, g);
+    if (hipError_t e = wide_attributes(); e != hipSuccess) return e;
     const dim3 grid(g.kb, g.nb), block(g.waves * 64);
     if (rot) {
         // blocks of more than 8 waves hold all K-slices of their rows (wide_geometry): only the 8-wave form is split
@@ -519,6 +555,74 @@ hipError_t launch_decode_wide(const paro_w4_weight &w, const paro_half_t *X, int
     } else {
         if (g.kb > 1) hipLaunchKernelGGL((decode_wide_kernel<true, false>), grid, block, g.lds, s, a);
         else          hipLaunchKernelGGL((decode_wide_kernel<false, false>), grid, block, g.lds, s, a);
+    }
+    return hipGetLastError();
+}
+
+// Several parts, 1..4 tokens.  X: [part][T][ldx] activations of each part where `rot` is NULL (a rotation pass wrote them),
+// otherwise the one input of transforms that decode_wide_hosts() accepts.
+size_t decode_wide_multi_bytes(int n_parts, const paro_w4_weight *const *w, int T)
+{
+    const int KS = w[0]->c_in / kGroup / kSliceGroups, kb = KS <= kWideWaves ? 1 : (KS + 7) / 8;
+    size_t total = 0;
+    if (kb > 1)
+        for (int p = 0; p < n_parts; ++p) total += ((size_t)kb * T * w[p]->c_out * sizeof(float) + 255) / 256 * 256;
+    return total;
+}
+
+// As decode_wide_hosting_pays, of the sum of the outputs, by whole tiles: a last tile per wave that few blocks have does not hide it
+// (nor do two waves per block hide anything: 1024 -> 19232 6.8 us K-major, 7.2).  All blocks in one round.
+bool decode_wide_multi_hosting_pays(int c_in, int64_t c_out_sum)
+{
+    const int KS = c_in / kGroup / kSliceGroups, kb = KS <= kWideWaves ? 1 : (KS + 7) / 8, waves = (KS + kb - 1) / kb;
+    const int64_t tiles = c_out_sum / kTileN, blocks = 256 / kb;
+    return KS > 2 && kb <= 64 && tiles >= blocks * (waves <= 8 ? 4 : 6) && tiles + 4 * wide_max_tiles(true) <= blocks * wide_max_tiles(true);
+}
+
+bool decode_wide_multi_fits(int n_parts, const paro_w4_weight *const *w, int T)
+{
+    int64_t n_all = 0;
+    for (int p = 0; p < n_parts; ++p) n_all += w[p]->c_out;
+    if (n_all > (1 << 30)) return false;
+    const WideGeometry g = wide_geometry(w[0]->c_in, (int)n_all, T, false, n_parts, w);
+    return g.kb * g.nb <= 256 && g.lds <= kWideLdsBytes && (g.kb == 1 || g.waves <= 8);
+}
+
+hipError_t launch_decode_wide_multi(int n_parts, const paro_rotation *const *rot, const paro_w4_weight *const *w,
+                                    const paro_half_t *const *X, int64_t ldx, paro_half_t *const *Y, const int64_t *ldy, int T, void *ws, hipStream_t s)
+{
+    if (n_parts < 1 || n_parts > kMaxParts || T < 1 || T > 4) return hipErrorInvalidValue;
+    int n_all = 0;
+    for (int p = 0; p < n_parts; ++p) {
+        if (packed_blob_bytes(w[p]->c_in, w[p]->c_out) >= (1ull << 31) || w[p]->c_in != w[0]->c_in) return hipErrorInvalidValue;
+        if (rot && (!decode_wide_hosts(*rot[p], T) || rot[p]->c_in != w[p]->c_in)) return hipErrorInvalidValue;
+        n_all += w[p]->c_out;
+    }
+    const WideGeometry g = wide_geometry(w[0]->c_in, n_all, T, rot != nullptr, n_parts, w);
+    if (g.kb > 64 || g.lds > kWideLdsBytes || (g.kb > 1 && (!ws || g.waves > 8))) return hipErrorInvalidValue;
+    MultiArgs m;
+    m.n_parts = n_parts;
+    size_t off = 0;
+    int nb = 0;
+    for (int p = 0; p < n_parts; ++p) {
+        m.part[p] = wide_args(*w[p], X[p], ldx, Y[p], ldy[p], T, ws, off, rot ? rot[p] : nullptr, g);
+        nb += (w[p]->c_out / kTileN + g.tiles_per_block - 1) / g.tiles_per_block;
+        m.nb_end[p] = nb;
+        if (g.kb > 1) off += ((size_t)g.kb * T * w[p]->c_out * sizeof(float) + 255) / 256 * 256;
+    }
+    for (int p = n_parts; p < kMaxParts; ++p) { m.part[p] = m.part[0]; m.nb_end[p] = nb; }
+    if (hipError_t e = wide_attributes(); e != hipSuccess) return e;
+    const dim3 grid(g.kb, nb), block(g.waves * 64);
+    if (rot) {
+        if (g.kb > 1)          hipLaunchKernelGGL((decode_wide_kernel<true, true, 8, 8, MultiArgs>), grid, block, g.lds, s, m);
+        else if (g.waves <= 8) hipLaunchKernelGGL((decode_wide_kernel<false, true, 8, 8, MultiArgs>), grid, block, g.lds, s, m);
+        else                   hipLaunchKernelGGL((decode_wide_kernel<false, true, 8, kWideWaves, MultiArgs>), grid, block, g.lds, s, m);
+    } else if (T == 1) {
+        if (g.kb > 1) hipLaunchKernelGGL((decode_wide_kernel<true, true, 0, 8, MultiArgs>), grid, block, g.lds, s, m);
+        else          hipLaunchKernelGGL((decode_wide_kernel<false, true, 0, kWideWaves, MultiArgs>), grid, block, g.lds, s, m);
+    } else {
+        if (g.kb > 1) hipLaunchKernelGGL((decode_wide_kernel<true, false, 0, 8, MultiArgs>), grid, block, g.lds, s, m);
+        else          hipLaunchKernelGGL((decode_wide_kernel<false, false, 0, kWideWaves, MultiArgs>), grid, block, g.lds, s, m);
     }
     return hipGetLastError();
 }

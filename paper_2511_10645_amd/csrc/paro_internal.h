@@ -124,7 +124,10 @@ inline void once_done(std::atomic<uint64_t> &done, int dev)
 hipError_t launch_plan_build(const paro_rotation &rot, void *plan_out, hipStream_t s);
 hipError_t launch_rotate_planned(const paro_rotation &rot, const paro_half_t *X, int64_t ldx,
                                  paro_half_t *Xr, int64_t ldxr, int T, hipStream_t s);
-// The same in operand order (linear_rows.hip).
+// Several transforms of the same rows in one launch: same c_in and layer count.
+hipError_t launch_rotate_multi(int n_parts, const paro_rotation *const *rot, const paro_half_t *X, int64_t ldx, paro_half_t *const *Xr,
+                               int64_t ldxr, int T, hipStream_t s);
+// The same as launch_rotate_planned in operand order (linear_rows.hip).
 hipError_t launch_rotate_operand(const paro_rotation &rot, const paro_half_t *X, int64_t ldx, paro_half_t *Xop, int T, hipStream_t s);
 hipError_t launch_rotate_generic(const paro_rotation &rot, const paro_half_t *X, int64_t ldx,
                                  paro_half_t *Xr, int64_t ldxr, int T, hipStream_t s);
@@ -161,6 +164,14 @@ bool decode_wide_hosting_pays(int c_in, int c_out);
 bool decode_wide_operand_pays(int c_in, int T);
 hipError_t launch_decode_wide(const paro_w4_weight &w, const paro_half_t *X, int64_t ldx, paro_half_t *Y, int64_t ldy,
                               int T, void *ws, hipStream_t s, const paro_rotation *rot = nullptr, bool x_operand = false);
+// The wide kernel for several weights of one c_in, up to 4 tokens, in one launch.  X: activations of every part (rot NULL: transformed
+// already).  Workspace: decode_wide_multi_bytes of partial sums.
+bool decode_wide_multi_hosting_pays(int c_in, int64_t c_out_sum);
+bool decode_wide_multi_fits(int n_parts, const paro_w4_weight *const *w, int T);
+size_t decode_wide_multi_bytes(int n_parts, const paro_w4_weight *const *w, int T);
+hipError_t launch_decode_wide_multi(int n_parts, const paro_rotation *const *rot, const paro_w4_weight *const *w,
+                                    const paro_half_t *const *X, int64_t ldx, paro_half_t *const *Y, const int64_t *ldy, int T,
+                                    void *ws, hipStream_t s);
 hipError_t launch_linear_generic(const paro_w4_weight &w, const paro_half_t *X, int64_t ldx,
                                  paro_half_t *Y, int64_t ldy, int T, hipStream_t s);
 

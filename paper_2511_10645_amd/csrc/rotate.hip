@@ -376,6 +376,78 @@ hipError_t launch_rotate_operand(const paro_rotation &rot, const paro_half_t *X,
     return launch_rotate<true>(rot, X, ldx, Xop, 0, T, s);
 }
 
+// Several transforms of up to kRotTU rows (blockIdx.y), each to rows of its own: a wave has one group of all rows.
+struct RotateMultiArgs {
+    const uint32_t *plan[4];
+    _Float16 *Xr[4];
+};
+template <int K>
+__global__ __launch_bounds__(64) void rotate_multi_kernel(RotateMultiArgs m, const _Float16 *X, int64_t ldx, int64_t ldxr, int T)
+{
+    typedef _Float16 half4v __attribute__((ext_vector_type(4)));
+    __shared__ half4v s_stage[kGroup];                      // [channel][row]
+    const int g = blockIdx.x, lane = threadIdx.x;
+    uint32_t x[kRotTU];
+#pragma unroll
+    for (int u = 0; u < kRotTU; ++u) x[u] = *(const uint32_t *)(X + (size_t)min(u, T - 1) * ldx + (size_t)g * kGroup + 2 * lane);
+    LanePlan<K> P;
+    load_lane_plan<K>(m.plan[blockIdx.y] + (size_t)g * plan_group_dwords(K), lane, P);
+    union { uint32_t u; _Float16 h[2]; } c;
+    half4v lo, hi;
+#pragma unroll
+    for (int u = 0; u < kRotTU; ++u) { c.u = x[u]; lo[u] = c.h[0]; hi[u] = c.h[1]; }
+    s_stage[2 * lane] = lo; s_stage[2 * lane + 1] = hi;
+    __builtin_amdgcn_wave_barrier();
+    lo = s_stage[P.in_a]; hi = s_stage[P.in_b];
+    float a[kRotTU], b[kRotTU];
+#pragma unroll
+    for (int u = 0; u < kRotTU; ++u) { a[u] = (float)lo[u] * P.sia; b[u] = (float)hi[u] * P.sib; }
+    rotate_layers<K, kRotTU>(P, a, b);
+    __builtin_amdgcn_wave_barrier();
+#pragma unroll
+    for (int u = 0; u < kRotTU; ++u) { lo[u] = (_Float16)(a[u] * P.soa); hi[u] = (_Float16)(b[u] * P.sob); }
+    s_stage[P.out_a] = lo; s_stage[P.out_b] = hi;
+    __builtin_amdgcn_wave_barrier();
+    lo = s_stage[2 * lane]; hi = s_stage[2 * lane + 1];
+#pragma unroll
+    for (int u = 0; u < kRotTU; ++u) {
+        c.h[0] = lo[u]; c.h[1] = hi[u];
+        if (u < T) *(uint32_t *)(m.Xr[blockIdx.y] + (size_t)u * ldxr + (size_t)g * kGroup + 2 * lane) = c.u;
+    }
+}
+
+template <int K>
+static hipError_t launch_rotate_multi_k(int n_parts, const RotateMultiArgs &m, int G, const paro_half_t *X, int64_t ldx, int64_t ldxr,
+                                        int T, hipStream_t s)
+{
+    hipLaunchKernelGGL((rotate_multi_kernel<K>), dim3(G, n_parts), dim3(64), 0, s, m, (const _Float16 *)X, ldx, ldxr, T);
+    return hipGetLastError();
+}
+
+// All transforms: same c_in and layer count, with plans; T <= kRotTU.
+hipError_t launch_rotate_multi(int n_parts, const paro_rotation *const *rot, const paro_half_t *X, int64_t ldx, paro_half_t *const *Xr,
+                               int64_t ldxr, int T, hipStream_t s)
+{
+    if (n_parts < 1 || n_parts > 4 || T < 1 || T > kRotTU) return hipErrorInvalidValue;
+    RotateMultiArgs m;
+    for (int p = 0; p < 4; ++p) {
+        m.plan[p] = (const uint32_t *)rot[p < n_parts ? p : 0]->plan;
+        m.Xr[p] = (_Float16 *)Xr[p < n_parts ? p : 0];
+    }
+    const int G = rot[0]->c_in / kGroup;
+    switch (rot[0]->n_layers) {
+    case 0: return launch_rotate_multi_k<0>(n_parts, m, G, X, ldx, ldxr, T, s);
+    case 1: return launch_rotate_multi_k<1>(n_parts, m, G, X, ldx, ldxr, T, s);
+    case 2: return launch_rotate_multi_k<2>(n_parts, m, G, X, ldx, ldxr, T, s);
+    case 3: return launch_rotate_multi_k<3>(n_parts, m, G, X, ldx, ldxr, T, s);
+    case 4: return launch_rotate_multi_k<4>(n_parts, m, G, X, ldx, ldxr, T, s);
+    case 5: return launch_rotate_multi_k<5>(n_parts, m, G, X, ldx, ldxr, T, s);
+    case 6: return launch_rotate_multi_k<6>(n_parts, m, G, X, ldx, ldxr, T, s);
+    case 7: return launch_rotate_multi_k<7>(n_parts, m, G, X, ldx, ldxr, T, s);
+    default: return launch_rotate_multi_k<8>(n_parts, m, G, X, ldx, ldxr, T, s);
+    }
+}
+
 // ------------------------------------------------------------------------------------------
 // Generic rotation kernel: reads pairs/theta directly (no plan).  One wave per block; the
 // group's 128 channels of one token live in LDS as fp32, each lane updates the pair of its

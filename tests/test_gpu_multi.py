@@ -90,3 +90,30 @@ def test_multi_qkv_shape_of_the_8b_layer(P):
     torch.cuda.synchronize()
     for k, (y, allowed) in enumerate(refs):
         assert float((np.abs(ys[k].cpu().numpy().astype(np.float64) - y) / allowed).max()) <= 1.0
+
+
+@pytest.mark.parametrize("T,c_in,c_outs,n_layers", [
+    (1, 1024, (16 * 700, 16 * 331), 8),                             # transforms per wave, one block per row of tiles, ragged shares
+    (1, 6656, (16 * 260, 16 * 256), 8),                             # the same with K over two blocks
+    (1, 4608, (16 * 800, 16 * 740), 8),                             # and with nine waves per block
+    (1, 5120, (16 * 1100, 16 * 1100), 3),                           # one token, layers that the kernel cannot host: two launches
+    (3, 4096, (16 * 513, 16 * 5, 16 * 510), 8),                     # two launches, a part of one block
+    (4, 3072, (16 * 640, 16 * 900), 5),
+    (2, 6656, (16 * 1200, 16 * 31), 8),                             # two launches, K over two blocks
+])
+def test_multi_on_the_wide_kernel(P, T, c_in, c_outs, n_layers):
+    """Against the oracle, with the workspace that the query gives and with the smaller one that the K-major kernel takes."""
+    import torch
+    say(f"multi, wide kernel T={T} {c_in} -> {c_outs}")
+    x, rots, ws, refs = _parts(P, 2200 + T + c_in, T, c_in, c_outs, n_layers=n_layers, bias_on=0)
+    total, exchange = P.paro_workspace_bytes_multi(rots, ws, T), P.paro_workspace_exchange_bytes_multi(rots, ws, T)
+    for nbytes in sorted({total, exchange}):
+        wsp = P.Workspace(nbytes)
+        ys = P.paro_rotated_linear_multi(rots, ws, x, wsp)
+        again = P.paro_rotated_linear_multi(rots, ws, x, wsp)
+        assert all(torch.equal(a, b) for a, b in zip(ys, again))
+        assert wsp.partials_clean(exchange) and wsp.error_word() == 0
+        for k, (y, allowed) in enumerate(refs):
+            worst = float((np.abs(ys[k].cpu().numpy().astype(np.float64) - y) / allowed).max())
+            say(f"  part {k}, {nbytes} bytes: worst err/allowed = {worst:.3f}")
+            assert worst <= 1.0
