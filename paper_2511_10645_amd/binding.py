@@ -9,7 +9,9 @@ import torch
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 _LIB_PATH = os.path.join(_HERE, "libparo.so")
+_HOST_PATH = os.path.join(_HERE, "paro_host.so")
 _lib = None
+_host = None
 
 PARO_OK = 0
 
@@ -52,7 +54,7 @@ def lib():
     """Load libparo.so, building it first only if nothing has been built yet."""
     global _lib
     if _lib is None:
-        if not os.path.exists(_LIB_PATH):
+        if not (os.path.exists(_LIB_PATH) and os.path.exists(_HOST_PATH)):
             from . import build as _build
             _build.build()
         L = ctypes.CDLL(_LIB_PATH)
@@ -118,6 +120,23 @@ def lib():
             getattr(L, name).restype = ctypes.c_int
         _lib = L
     return _lib
+
+
+def _native():
+    """The native half of the linear calls (csrc/host_call.cpp), over the same libparo.so."""
+    global _host
+    if _host is None:
+        lib()
+        from . import paro_host
+        paro_host.types(_CRotation, _CW4Weight)
+        _host = paro_host
+    return _host
+
+
+def _output(out, where: str):
+    if type(out) is int:                # a status: the call was refused
+        raise ParoError(out, where)
+    return out
 
 
 def _check(st: int, where: str):
@@ -335,35 +354,16 @@ def _rows(x: torch.Tensor):
 
 
 def paro_rotate_scale(rot: Rotation, X: torch.Tensor, Xr: torch.Tensor | None = None) -> torch.Tensor:
-    T, ldx = _rows(X)
-    if Xr is None:
-        Xr = torch.empty((T, rot.c_in), dtype=torch.float16, device=X.device)
-    _, ldxr = _rows(Xr)
-    _check(lib().paro_rotate_scale(rot.ref(), X.data_ptr(), ldx, Xr.data_ptr(), ldxr, T, _stream()), "paro_rotate_scale")
-    return Xr
+    return _output((_host or _native()).rotate(rot.c, rot.c_in, X, Xr), "paro_rotate_scale")
 
 
 def paro_w4a16_linear(w: W4Weight, X: torch.Tensor, ws: Workspace | None = None, Y: torch.Tensor | None = None):
-    T, ldx = _rows(X)
-    if Y is None:
-        Y, ldy = torch.empty((T, w.c_out), dtype=torch.float16, device=X.device), w.c_out
-    else:
-        _, ldy = _rows(Y)
-    _check(lib().paro_w4a16_linear(w.ref(), X.data_ptr(), ldx, Y.data_ptr(), ldy, T,
-                                   ws.buf.data_ptr() if ws else None, ws.nbytes if ws else 0, _stream()),
-           "paro_w4a16_linear")
-    return Y
+    buf, nbytes = (ws.buf, ws.nbytes) if ws else (None, 0)
+    return _output((_host or _native()).linear(None, w.c, w.c_out, X, Y, buf, nbytes), "paro_w4a16_linear")
 
 
 def paro_rotated_linear(rot: Rotation, w: W4Weight, X: torch.Tensor, ws: Workspace, Y: torch.Tensor | None = None):
-    T, ldx = _rows(X)
-    if Y is None:
-        Y, ldy = torch.empty((T, w.c_out), dtype=torch.float16, device=X.device), w.c_out
-    else:
-        _, ldy = _rows(Y)
-    _check(lib().paro_rotated_linear(rot.ref(), w.ref(), X.data_ptr(), ldx, Y.data_ptr(), ldy, T,
-                                     ws.buf.data_ptr(), ws.nbytes, _stream()), "paro_rotated_linear")
-    return Y
+    return _output((_host or _native()).linear(rot.c, w.c, w.c_out, X, Y, ws.buf, ws.nbytes), "paro_rotated_linear")
 
 
 def paro_rotated_linear_noalloc(rot: Rotation, w: W4Weight, X: torch.Tensor, Y: torch.Tensor):
