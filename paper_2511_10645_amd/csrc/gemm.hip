@@ -25,14 +25,15 @@
 // LDS rows are padded by 16 bytes so that the 16-byte fragment reads of 32 consecutive rows
 // spread over all banks.
 //
-// Blocks are numbered so that the 32 blocks resident on one XCD (block id mod 8) form an
-// 8 (token tiles) x 4 (output tiles) patch that walks K in step: they share activation and
-// weight panels through that XCD's L2.  With fewer than 8 token tiles the patch is narrower
-// in tokens and wider in outputs, so that no block id of a patch is left without work, and
-// with fewer than 256 tiles the patches shrink so that all 8 XCDs still get one.
+// Blocks are numbered so that the 32 blocks resident on one XCD (block id mod 8) form a patch of 8 (token tiles) x 4 (output
+// tiles) that walks K in step: tiles are counted in bands of 8 token tiles, output tile by output tile, dealt to the XCDs 32 at
+// a time, and what does not fill a round of 256 in eight equal runs, so that every XCD has the same number of tiles to one.
+// (Patches of powers of two throughout left some XCDs with a second round and others idle.  us, before / after, rotated:
+// 16896 -> 8480 at 647 tokens 444 / 251, 4096 -> 6144 at 1100 121 / 72, 4096 -> 16000 at 1500 313 / 198, 7168 -> 9216 at 3000
+// 541 / 404; one run per XCD of all tiles is 2 % slower on many rounds: 5120 -> 55296 at 4096 1973 / 2017.)
 //
 // Split K.  Some tens to hundreds of tokens give only a handful of tiles, each walking all of K on
-// one compute unit.  Then K is cut into slices (blockIdx.y), as many as fit one round of blocks;
+// one compute unit.  Then K is cut into slices, as many as fit one round of blocks;
 // every slice stores its fp32 tile to scratch memory and a second kernel sums the slices in index
 // order, adds the bias and rounds once (deterministic; no atomics).
 #include "paro_internal.h"
@@ -47,7 +48,7 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kBN = 256, kBK = 64;
 constexpr int kLdsRow = kBK + 8;                    // halfs per padded LDS row
-constexpr int kPatchBlocks = 32;                    // most blocks of one XCD patch (8 x 4 token x output tiles)
+constexpr int kBandTiles = 8;                       // token tiles of a band that is walked output tile by output tile
 
 constexpr uint32_t kOobG = 0x80000000u;
 __device__ inline __amdgpu_buffer_rsrc_t make_rsrc_g(const void *p, uint32_t bytes)
@@ -74,10 +75,9 @@ struct GemmArgs {
     int T, C, N, G, S;          // S = G / 4 K-slices of the scales/zeros tiling
     int m_tiles, n_tiles;       // tiles of this launch
     int n_tile0;                // first 256-output tile of this launch
-    int k_split, k_steps;       // blockIdx.y walks K-steps [y k_steps, (y+1) k_steps); k_split > 1: fp32 partial tiles
+    int k_split, k_steps;       // slice y has K-steps [y k_steps, (y+1) k_steps); k_split > 1: fp32 partial tiles
     float *partial;             //   [k_split][T][part_w] instead of Y (outputs part_n0 .. part_n0 + part_w), summed
     int part_n0, part_w;        //   by gemm_splitk_reduce_kernel
-    int patch_m, patch_n;       // token tiles x output tiles of the patch of blocks one XCD works on
     uint32_t m_lo, m_hi, k_lo, k_hi;   // 0x000F000F, 0x00F000F0, 0x64006400, 0x54005400: passed as arguments and
                                        // moved to VGPRs so that (u & mask) | magic becomes one v_and_or_b32
 };
@@ -107,7 +107,7 @@ constexpr int kAuxNt = 2;                             // non-temporal
 
 // MI x NI: 32x32 MFMA tiles per wave (tokens x outputs); WM x WN: waves per block.
 // Block tile = (WM MI 32) tokens x (WN NI 32 = 256 or 192) outputs.
-// SPLITK: blockIdx.y selects a slice of K and the block stores fp32 partial tiles.
+// SPLITK: a block has one slice of K and stores fp32 partial tiles.
 template <int MI, int NI, int WM, int WN, bool SPLITK = false>
 __global__ __launch_bounds__(WM * WN * 64) void gemm_w4a16_kernel(GemmArgs a)
 {
@@ -130,16 +130,17 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_w4a16_kernel(GemmArgs a)
     _Float16 *As = smem;                                   // [2][BM][kLdsRow]
     _Float16 *Bs = smem + 2 * BM * kLdsRow;                // [2][kBN][kLdsRow]
 
-    // ---- block -> (m tile, n tile), XCD-aware --------------------------------------------------
-    const int bid = blockIdx.x;
-    const int xcd = bid & 7, j = bid >> 3;
-    const int pb = a.patch_m * a.patch_n;
-    const int patch = j / pb, q = j % pb;
-    const int m_patches = (a.m_tiles + a.patch_m - 1) / a.patch_m;
-    const int gp = patch * 8 + xcd;                        // global patch index
-    const int pm = gp % m_patches, pn = gp / m_patches;
-    const int mt = pm * a.patch_m + q % a.patch_m, ntile = pn * a.patch_n + q / a.patch_m;
-    if (mt >= a.m_tiles || ntile >= a.n_tiles) return;
+    // ---- block -> (slice of K, m tile, n tile): whole rounds of 256 in patches of 32, the rest in equal runs ------------
+    const int tiles = a.m_tiles * a.n_tiles, all = tiles * (SPLITK ? a.k_split : 1);
+    const int xcd = blockIdx.x & 7, j = blockIdx.x >> 3, j_rest = all / 256 * 32;          // of this XCD; the first of its run
+    const int idx = j < j_rest ? (j / 32 * 8 + xcd) * 32 + j % 32 : j_rest * 8 + xcd * ((int)(gridDim.x >> 3) - j_rest) + j - j_rest;
+    if (idx >= all) return;
+    const int kslice = SPLITK ? idx / tiles : 0;
+    const int tile = SPLITK ? idx % tiles : idx;
+    const int whole = a.m_tiles / kBandTiles * kBandTiles * a.n_tiles;              // tiles of whole bands
+    const int high = tile < whole ? kBandTiles : a.m_tiles % kBandTiles, first = tile < whole ? 0 : whole;
+    const int column = (tile - first) / high, mt0 = tile < whole ? column / a.n_tiles * kBandTiles : a.m_tiles - high;
+    const int mt = mt0 + (tile - first) % high, ntile = column % a.n_tiles;
     const int m0 = mt * BM, n0 = (a.n_tile0 + ntile) * BN;
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -180,7 +181,7 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_w4a16_kernel(GemmArgs a)
     typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
     u32x2 bsc[PB];                  // the 4 fp16 group scales of the thread's row in the current 512-channel slice
     uint16_t bzq[PB];               // its 4 zero points; widened where it is used: no ALU op (hence no wait) at the load
-    const int k_begin = SPLITK ? blockIdx.y * a.k_steps : 0;             // this block's K-steps (split K: a slice)
+    const int k_begin = SPLITK ? kslice * a.k_steps : 0;             // this block's K-steps (split K: a slice)
     const int k_end = SPLITK ? min(a.C / kBK, k_begin + a.k_steps) : a.C / kBK;
     auto load_a = [&](int r, int ks) {
         areg[r] = __builtin_amdgcn_raw_buffer_load_b128(xr, (int)a_voff[r], ks * (kBK * 2), 0);
@@ -308,7 +309,7 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_w4a16_kernel(GemmArgs a)
     if constexpr (SPLITK) {
         // split K: this slice's fp32 sums; bias and rounding happen once, in the reduction
         const __amdgpu_buffer_rsrc_t pr =
-            make_rsrc_g(a.partial + (size_t)blockIdx.y * a.T * a.part_w, (uint32_t)((size_t)a.T * a.part_w * 4));
+            make_rsrc_g(a.partial + (size_t)kslice * a.T * a.part_w, (uint32_t)((size_t)a.T * a.part_w * 4));
 #pragma unroll
         for (int jn = 0; jn < NI; ++jn) {
             const int n = n0 + wn * NI * 32 + jn * 32 + fr;
@@ -406,11 +407,11 @@ hipError_t launch_splitk_reduce(float *partial, int k_split, int T, int n0, int 
     return hipGetLastError();
 }
 
-// Block slots of a launch over m_tiles x n_tiles tiles: the XCD patches are rounded up to whole
-// rounds of 8 (see the kernel's block numbering); slots without a tile exit at once.
+// Block slots of a launch over m_tiles x n_tiles tiles in XCD patches of powers of two, rounded up to whole rounds of 8: the
+// numbering of the MXFP4 GEMM, and what the plans below count (slots without a tile exit at once).
 void gemm_patches(int m_tiles, int n_tiles, int &patch_m, int &patch_n, int &blocks)
 {
-    int pb = kPatchBlocks;
+    int pb = 32;                                     // most blocks of a patch (8 x 4 token x output tiles)
     while (pb > 1 && (long)m_tiles * n_tiles < 8L * pb) pb >>= 1;
     patch_m = 1;
     while (patch_m * 2 <= pb && patch_m * 2 <= 8 && patch_m * 2 <= m_tiles) patch_m <<= 1;
@@ -428,7 +429,7 @@ void gemm_patches(int m_tiles, int n_tiles, int &patch_m, int &patch_n, int &blo
 //   of output tiles, the "tail") is launched separately with 128-token tiles: e.g. 896 tiles =
 //   3 rounds of 256-token tiles + one round of 256 half-size tiles instead of 4.
 //   Split K: a launch of 128-token tiles that fills at most half of the block slots (the whole
-//   call at some tens to hundreds of tokens, or the tail) cuts K into slices over blockIdx.y, as
+//   call at some tens to hundreds of tokens, or the tail) cuts K into slices, as
 //   many as fit one round of slots with at least 4 K-steps each; the slices' fp32 tiles go to
 //   scratch memory and are summed by a second kernel.  The number of slices minimises a measured
 //   cost model: ~0.95 us per K-step of a block in a long launch, ~5 us + 1.2 us per K-step for the
@@ -561,10 +562,7 @@ static hipError_t launch_gemm_cfg(GemmArgs &a, int n_tile0, int n_count, hipStre
 {
     constexpr int BM = WM * MI * 32;
     a.m_tiles = (a.T + BM - 1) / BM; a.n_tiles = n_count; a.n_tile0 = n_tile0;
-    // 32 blocks per patch when there is work for all 8 XCDs at that size; smaller patches
-    // otherwise, so that a small grid is still spread over every XCD's L2 and memory channels
-    int blocks;
-    gemm_patches(a.m_tiles, a.n_tiles, a.patch_m, a.patch_n, blocks);
+    const unsigned blocks = (unsigned)(((size_t)a.m_tiles * a.n_tiles * (SPLITK ? a.k_split : 1) + 7) / 8 * 8);
     const size_t lds = (size_t)2 * (BM + kBN) * kLdsRow * sizeof(_Float16);
     static std::atomic<uint64_t> attr_done{0};
     if (const int dev = once_pending(attr_done); dev >= 0) {
@@ -573,7 +571,7 @@ static hipError_t launch_gemm_cfg(GemmArgs &a, int n_tile0, int n_count, hipStre
         if (e != hipSuccess) return e;
         once_done(attr_done, dev);
     }
-    hipLaunchKernelGGL((gemm_w4a16_kernel<MI, NI, WM, WN, SPLITK>), dim3(blocks, SPLITK ? a.k_split : 1),
+    hipLaunchKernelGGL((gemm_w4a16_kernel<MI, NI, WM, WN, SPLITK>), dim3(blocks),
                        dim3(WM * WN * 64), lds, s, a);
     return hipGetLastError();
 }
