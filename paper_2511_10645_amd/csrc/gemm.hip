@@ -25,10 +25,7 @@
 // LDS rows are padded by 16 bytes so that the 16-byte fragment reads of 32 consecutive rows
 // spread over all banks.
 //
-// Blocks are numbered so that the 32 blocks resident on one XCD (block id mod 8) form a patch of 8 (token tiles) x 4 (output
-// tiles) that walks K in step: tiles are counted in bands of 8 token tiles, output tile by output tile, dealt to the XCDs 32 at
-// a time, and what does not fill a round of 256 in eight equal runs, so that every XCD has the same number of tiles to one.
-// (Patches of powers of two throughout left some XCDs with a second round and others idle.  us, before / after, rotated:
+// The order of the blocks is that of tile_order.h.  (Patches of powers of two throughout left some XCDs with a second round and others idle.  us, before / after, rotated:
 // 16896 -> 8480 at 647 tokens 444 / 251, 4096 -> 6144 at 1100 121 / 72, 4096 -> 16000 at 1500 313 / 198, 7168 -> 9216 at 3000
 // 541 / 404; one run per XCD of all tiles is 2 % slower on many rounds: 5120 -> 55296 at 4096 1973 / 2017.)
 //
@@ -37,6 +34,7 @@
 // every slice stores its fp32 tile to scratch memory and a second kernel sums the slices in index
 // order, adds the bias and rounds once (deterministic; no atomics).
 #include "paro_internal.h"
+#include "tile_order.h"
 #include <type_traits>
 
 namespace paro {
@@ -48,7 +46,6 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kBN = 256, kBK = 64;
 constexpr int kLdsRow = kBK + 8;                    // halfs per padded LDS row
-constexpr int kBandTiles = 8;                       // token tiles of a band that is walked output tile by output tile
 
 constexpr uint32_t kOobG = 0x80000000u;
 __device__ inline __amdgpu_buffer_rsrc_t make_rsrc_g(const void *p, uint32_t bytes)
@@ -131,16 +128,11 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_w4a16_kernel(GemmArgs a)
     _Float16 *Bs = smem + 2 * BM * kLdsRow;                // [2][kBN][kLdsRow]
 
     // ---- block -> (slice of K, m tile, n tile): whole rounds of 256 in patches of 32, the rest in equal runs ------------
-    const int tiles = a.m_tiles * a.n_tiles, all = tiles * (SPLITK ? a.k_split : 1);
-    const int xcd = blockIdx.x & 7, j = blockIdx.x >> 3, j_rest = all / 256 * 32;          // of this XCD; the first of its run
-    const int idx = j < j_rest ? (j / 32 * 8 + xcd) * 32 + j % 32 : j_rest * 8 + xcd * ((int)(gridDim.x >> 3) - j_rest) + j - j_rest;
-    if (idx >= all) return;
+    const int tiles = a.m_tiles * a.n_tiles;
+    int idx, mt, ntile;
+    if (!tile_index(tiles * (SPLITK ? a.k_split : 1), idx)) return;
     const int kslice = SPLITK ? idx / tiles : 0;
-    const int tile = SPLITK ? idx % tiles : idx;
-    const int whole = a.m_tiles / kBandTiles * kBandTiles * a.n_tiles;              // tiles of whole bands
-    const int high = tile < whole ? kBandTiles : a.m_tiles % kBandTiles, first = tile < whole ? 0 : whole;
-    const int column = (tile - first) / high, mt0 = tile < whole ? column / a.n_tiles * kBandTiles : a.m_tiles - high;
-    const int mt = mt0 + (tile - first) % high, ntile = column % a.n_tiles;
+    tile_place(SPLITK ? idx % tiles : idx, a.m_tiles, a.n_tiles, mt, ntile);
     const int m0 = mt * BM, n0 = (a.n_tile0 + ntile) * BN;
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -407,8 +399,8 @@ hipError_t launch_splitk_reduce(float *partial, int k_split, int T, int n0, int 
     return hipGetLastError();
 }
 
-// Block slots of a launch over m_tiles x n_tiles tiles in XCD patches of powers of two, rounded up to whole rounds of 8: the
-// numbering of the MXFP4 GEMM, and what the plans below count (slots without a tile exit at once).
+// Block slots of a launch over m_tiles x n_tiles tiles in XCD patches of powers of two, rounded up to whole rounds of 8: what
+// the plans below count.
 void gemm_patches(int m_tiles, int n_tiles, int &patch_m, int &patch_n, int &blocks)
 {
     int pb = 32;                                     // most blocks of a patch (8 x 4 token x output tiles)

@@ -20,6 +20,7 @@
 // there are more than 12), partial tiles summed through LDS; no exchange between blocks.  More tokens:
 // a tiled GEMM (see below).
 #include "paro_internal.h"
+#include "tile_order.h"
 #include <algorithm>
 #include <type_traits>
 
@@ -349,7 +350,7 @@ struct MxGemmArgs {
     _Float16 *Y; int64_t ldy;
     const _Float16 *bias;
     int T, C, N, K128, KS;
-    int m_tiles, n_tiles, patch_m, patch_n;
+    int m_tiles, n_tiles;
 };
 
 typedef float float16v __attribute__((ext_vector_type(16)));
@@ -367,15 +368,9 @@ __global__ __launch_bounds__(256, 2) void mxfp4_gemm_kernel(MxGemmArgs a)
 {
     extern __shared__ __attribute__((aligned(16))) char smem_mx[];
     constexpr int BN = 128 * NTW, MT = kMxBM / 32, XR = 4;   // XR: activation requests of a wave per 256 channels
-    const int bid = blockIdx.x;
-    const int xcd = bid & 7, j = bid >> 3;
-    const int pb = a.patch_m * a.patch_n;
-    const int patch = j / pb, q = j % pb;
-    const int m_patches = (a.m_tiles + a.patch_m - 1) / a.patch_m;
-    const int gp = patch * 8 + xcd;
-    const int pm = gp % m_patches, pn = gp / m_patches;
-    const int mt0 = pm * a.patch_m + q % a.patch_m, ntile = pn * a.patch_n + q / a.patch_m;
-    if (mt0 >= a.m_tiles || ntile >= a.n_tiles) return;
+    int idx, mt0, ntile;
+    if (!tile_index(a.m_tiles * a.n_tiles, idx)) return;
+    tile_place(idx, a.m_tiles, a.n_tiles, mt0, ntile);
     const int m0 = mt0 * kMxBM;
 
     const int tid = threadIdx.x, lane = tid & 63;
@@ -586,8 +581,7 @@ template <int NTW>
 static hipError_t launch_mxfp4_gemm_cfg(MxGemmArgs &a, hipStream_t s)
 {
     a.m_tiles = (a.T + kMxBM - 1) / kMxBM; a.n_tiles = (a.N + 128 * NTW - 1) / (128 * NTW);
-    int blocks;
-    gemm_patches(a.m_tiles, a.n_tiles, a.patch_m, a.patch_n, blocks);
+    const unsigned blocks = (unsigned)(((size_t)a.m_tiles * a.n_tiles + 7) / 8 * 8);
     static std::atomic<uint64_t> attr_done{0};
     if (const int dev = once_pending(attr_done); dev >= 0) {
         hipError_t e = hipFuncSetAttribute((const void *)mxfp4_gemm_kernel<NTW>, hipFuncAttributeMaxDynamicSharedMemorySize, kMxGemmLds);
