@@ -12,6 +12,11 @@ constexpr int kFuseMaxTokens = 4;            // the K-major decode kernel hosts 
 constexpr int64_t kMaxRowStride = 1 << 22;   // elements; the kernels address a run of up to 256 rows with 31-bit byte offsets
 constexpr int kDecodeMaxTokens = 16;         // above this the MFMA GEMM competes with passes of the streaming decode kernel
 constexpr int kStreamPassTokens = 32;        // tokens of one pass of the streaming kernel (two blocks of 16)
+// Most tokens that the kernel between streaming and GEMM is considered for.  Above 1024 it is the few outputs whose GEMM tiles
+// leave most of the chip idle that it serves (70 random shapes of 1026 to 4096 tokens and up to 8300 outputs, every route forced:
+// 0.79 of the time in the mean of the 33 that it takes, none slower).  us, GEMM / tiled: 3584 -> 736 at 1250 tokens 55.8 / 25.2,
+// 4096 -> 512 at 4096 70.1 / 43.2, 14336 -> 1024 at 2048 124 / 98, 8192 -> 8240 at 1283 stays (211 / 219).
+constexpr int kTileMaxTokens = 4096;
 
 inline bool aligned(const void *p, size_t a) { return ((uintptr_t)p % a) == 0; }
 inline size_t round_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
@@ -117,7 +122,7 @@ WsLayout ws_layout(const paro_rotation *rot, const paro_w4_weight *w, int T, boo
         L.exchange_bytes = (rot || part) ? kWsPartialOff + round_up(part, 256) : 0;
         if (T > kDecodeMaxTokens) {
             L.gemm_bytes = round_up(gemm_scratch_bytes(*w, T), 256);
-            if (T > kStreamPassTokens && T <= 1024) faster = linear_tile_scratch_bytes(*w, T, false);
+            if (T > kStreamPassTokens && T <= kTileMaxTokens) faster = linear_tile_scratch_bytes(*w, T, false);
             if (rot && rot->plan && linear_operand_supported(*w, T)) faster = std::max(faster, linear_operand_scratch_bytes(*w, T));
         }
     } else if (rot) {
@@ -209,8 +214,8 @@ LinearRoute linear_route(const paro_w4_weight &w, int64_t ldx, int64_t ldy, int 
     // most per product.  The models are 6 to 15 % off, hence 0.9: over 5131 measured bare (shape, tokens) pairs (649 shapes,
     // 33 to 1024 tokens, every route forced) the choice loses more than 3 % on three (4 % there) and takes 1.32x less
     // time in the mean than the better of the other two, 1.34x being the best possible (8192 -> 16384 at 640 tokens, not
-    // among them, loses 6 %: 201 us against the GEMM's 189).  Above 1024 tokens it has no shape to itself.
-    if (T > kStreamPassTokens && T <= 1024 && linear_tile_supported(w, false)) {
+    // among them, loses 6 %: 201 us against the GEMM's 189).
+    if (T > kStreamPassTokens && T <= kTileMaxTokens && linear_tile_supported(w, false)) {
         const double tile_us = linear_tile_estimate_us(w, T, scratch_bytes);
         if (tile_us < 0.9 * us) return {LinearRoute::kTile, tile_us};
     }

@@ -17,7 +17,9 @@ def P():
                                           (2100, 512, 8208),        # 9 x 33 of 256: a round, a second band
                                           (4100, 512, 5136),        # 17 x 21: a tail of half-size tiles behind
                                           (700, 4096, 3088),        # 256-token tiles, K in two
-                                          (513, 1024, 16)])         # one output tile
+                                          (513, 1024, 16),          # one output tile
+                                          (1250, 3584, 736),        # few outputs: the kernel beside the GEMM, K split
+                                          (4096, 512, 528)])        # at its largest number of tokens
 def test_every_tile(P, T, c_in, c_out):
     """Bound: half an fp16 ulp of the result and one fp32 rounding per product of the fp16 weights that the GEMM multiplies."""
     import torch
