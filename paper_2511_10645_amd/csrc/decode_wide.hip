@@ -456,14 +456,36 @@ size_t decode_wide_partial_bytes(int c_in, int c_out, int T)
 // Whether the one-token kernel can host this transform (instantiated for the paper's 8 layers)
 bool decode_wide_hosts(const paro_rotation &rot, int T) { return T == 1 && rot.plan && rot.n_layers == 8; }
 
-// Whether it pays: every wave spends ~1.5 us on its 4 groups before it consumes its first tile, which its weight
-// stream hides from about 4 tiles per wave on (6 where a block has more than 8 waves, three per SIMD).  Measured on
-// MI355X, this kernel against the K-major kernel (or rotation pass + bare kernel where that is faster), us:
-// 4096 -> 12288 (3 tiles per wave) 8.7 / 8.9, 4096 -> 16384 (4) 9.7 / 10.3, 4096 -> 28672 (7) 12.8 / 14.8,
-// 2048 -> 28672 (7) 8.3 / 10.2, 14336 -> 4096 (4) 10.3 / 10.5, 14336 -> 8192 (8) 14.1 / 17.4, 8192 -> 8192 (4)
-// 11.0 / 10.9, 27648 -> 5120 (9) 15.5 / 18.9, 5120 -> 55296 (14, 10 waves) 26.1 / 28.8; but 4096 -> 6144 (2)
-// 7.5 / 6.8, 5120 -> 7168 (2) 9.1 / 7.9, 6144 -> 12288 (3, 12 waves) 11.9 / 11.5.
+// Whether it pays against the K-major kernel.  Every wave spends ~1.5 us on its 4 groups before it consumes its first tile,
+// which a long weight stream hides; the K-major kernel spreads that over 4 waves, but its blocks exchange one fp32 partial tile
+// per K-slice and end ~1 us later for it.  Measured on MI355X in a replayed graph, K-major / this kernel, us:
+//   1 slice: nothing is exchanged, and 4 waves stream where this kernel has one: 512 -> 4096 4.46 / 4.35, 512 -> 8192 4.57 / 4.69,
+//     512 -> 16384 4.73 / 5.35, 512 -> 38864 5.99 / 7.83.  Never.
+//   2 to 4 slices: the exchange is most of what the launch pays for: 1024 -> 1024 5.5 / 4.4, 1024 -> 8192 5.8 / 4.9, 1536 -> 4096 5.7 / 4.7,
+//     2048 -> 2048 5.7 / 4.95, 2048 -> 12288 7.0 / 6.0.  Always (1024 -> 32768 7.6 / 8.0).
+//   5 to 8: from 4 tiles per wave: 2560 -> 12288 (3) 7.65 / 7.94, 2560 -> 16384 9.1 / 8.6, 4096 -> 12288 9.5 / 9.5, 4096 -> 16384 11.1 / 10.7,
+//     4096 -> 28672 (7) 14.8 / 12.8.
+//   9 to 12 (three waves per SIMD): by the K-slices of tiles per compute unit, 44: 4608 -> 16384 (36) 12.5 / 12.6, 5120 -> 17600 (43) 14.1 / 14.2,
+//     5632 -> 16384 (44) 14.1 / 13.7, 4608 -> 20480 (45) 14.5 / 14.3, 6144 -> 20480 (60) 19.1 / 16.6, 5120 -> 55296 28.8 / 26.1.
+//   2 or 3 blocks along K, which exchange as well: 33, or 31 where every block has 8 slices: 9216 -> 4752 (21) 9.6 / 10.3, 7168 -> 8192 (28)
+//     10.9 / 11.2, 10240 -> 6800 (33) 12.4 / 12.2, 8192 -> 9216 (36) 12.6 / 12.4, 12288 -> 5440 (32) 12.4 / 12.1, 12288 -> 9520 (56) 19.2 / 15.4.
+//   4 and more: 25, beyond 5 blocks, where the K-major kernel sums over 40 words and more, 19: 14336 -> 3264 (22) 10.2 / 10.7, 14336 -> 4096 (28) 11.3 / 11.3,
+//     16384 -> 3264 (25) 11.5 / 11.2, 27648 -> 1440 (19) 10.9 / 10.4, 27648 -> 5120 (68) 18.9 / 15.5.
 bool decode_wide_hosting_pays(int c_in, int c_out)
+{
+    const WideGeometry g = wide_geometry(c_in, c_out, 1, true);
+    const int KS = c_in / kGroup / kSliceGroups, NT = c_out / kTileN;
+    const int64_t slices = (int64_t)KS * NT / 256;           // per compute unit
+    if (KS == 1) return false;
+    if (KS <= 4) return true;
+    if (g.waves > 8) return slices >= 44;
+    if (g.kb == 1) return g.tiles_per_block >= 4;
+    return slices >= (g.kb > 5 ? 19 : g.kb > 3 ? 25 : g.waves * g.kb == KS ? 31 : 33);
+}
+
+// Whether it stands in for a K-major call whose buffer has no room for the partial sums of all K-slices: from 4 tiles per wave
+// (6 where a block has more than 8) it costs at most 1 us more.
+bool decode_wide_hosting_stands_in(int c_in, int c_out)
 {
     const WideGeometry g = wide_geometry(c_in, c_out, 1, true);
     return g.tiles_per_block >= (g.waves <= 8 ? 4 : 6);

@@ -67,12 +67,16 @@ inline bool can_fuse_decode(const paro_rotation *rot, const paro_w4_weight *w, i
 // (4096 / 5120 / 14336 / 27648 input channels, 4096 .. 55296 outputs): 1 - 2 MB of partial sums
 // for one token, 0.75 MB for 2..4 tokens.  `always`: for callers without a scratch part.
 constexpr size_t kFusePartialOne = 3u << 19, kFusePartialFew = 3u << 18;
-// One token, the paper's 8 layers, a weight stream of some length per wave: the kernel in which every wave transforms
-// its own K-slice (decode_wide.hip) - nothing is exchanged between blocks that the bare linear would not exchange, and
-// the stream hides the transform (decode_wide_hosting_pays has the measurements behind the rule).
+// One token, the paper's 8 layers, few K-slices or a weight stream of some length per wave: the kernel in which every wave
+// transforms its own K-slice (decode_wide.hip) - nothing is exchanged between blocks that the bare linear would not exchange
+// (decode_wide_hosting_pays has the measurements behind the rule).
 inline bool fused_wide(const paro_rotation *rot, const paro_w4_weight *w, int T)
 {
     return can_fuse_decode(rot, w, T) && decode_wide_hosts(*rot, T) && decode_wide_hosting_pays(w->c_in, w->c_out);
+}
+inline bool wide_stands_in(const paro_rotation *rot, const paro_w4_weight *w, int T)
+{
+    return can_fuse_decode(rot, w, T) && decode_wide_hosts(*rot, T) && decode_wide_hosting_stands_in(w->c_in, w->c_out);
 }
 inline bool fused_decode(const paro_rotation *rot, const paro_w4_weight *w, int T, bool always = false)
 {
@@ -114,10 +118,10 @@ WsLayout ws_layout(const paro_rotation *rot, const paro_w4_weight *w, int T, boo
     size_t faster = 0;
     const bool fused = fused_decode(rot, w, T, always_fuse);
     if (fast_weight(w)) {
-        // partial sums of the kernel this call launches: the K-major one (one part per K-slice) or the bare one
-        // (parts only beyond 6144 channels)
-        const size_t part = fused && !fused_wide(rot, w, T) ? decode_geometry(w->c_in, w->c_out, T).partial_bytes
-                                                            : decode_wide_partial_bytes(w->c_in, w->c_out, T);
+        // partial sums of the K-major kernel (one part per K-slice) or of the wide one (parts only beyond 6144 channels), which
+        // stands in on a buffer without room for the former.  Short streams ask for the K-major kernel's whichever runs.
+        const bool wide = !fused || (wide_stands_in(rot, w, T) && (lean || fused_wide(rot, w, T)));
+        const size_t part = wide ? decode_wide_partial_bytes(w->c_in, w->c_out, T) : decode_geometry(w->c_in, w->c_out, T).partial_bytes;
         // the bare linear without partial sums to exchange needs no workspace at all
         L.exchange_bytes = (rot || part) ? kWsPartialOff + round_up(part, 256) : 0;
         if (T > kDecodeMaxTokens) {
@@ -452,7 +456,9 @@ static paro_status rotated_linear(const paro_rotation *rot, const paro_w4_weight
     if (L.total && !aligned(ws, 256)) return PARO_ERR_ALIGN;
     hipStream_t s = (hipStream_t)stream;
 
-    if (fused_wide(rot, w, T)) return from_hip(launch_decode_wide(*w, X, ldx, Y, ldy, T, ws, s, rot));
+    const bool wide = fused_wide(rot, w, T) ||
+                      (wide_stands_in(rot, w, T) && L.exchange_bytes < kWsPartialOff + decode_geometry(w->c_in, w->c_out, T).partial_bytes);
+    if (wide) return from_hip(launch_decode_wide(*w, X, ldx, Y, ldy, T, ws, s, rot));
     if (fused_decode(rot, w, T, always_fuse)) return from_hip(launch_decode(rot, *w, X, ldx, Y, ldy, T, ws, s));
 
     // two passes: transform into the workspace, then the bare linear

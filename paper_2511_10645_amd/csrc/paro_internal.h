@@ -161,6 +161,7 @@ hipError_t launch_decode_multi(int n_parts, const paro_rotation *const *rot, con
 size_t decode_wide_partial_bytes(int c_in, int c_out, int T);
 bool decode_wide_hosts(const paro_rotation &rot, int T);
 bool decode_wide_hosting_pays(int c_in, int c_out);
+bool decode_wide_hosting_stands_in(int c_in, int c_out);
 bool decode_wide_operand_pays(int c_in, int T);
 hipError_t launch_decode_wide(const paro_w4_weight &w, const paro_half_t *X, int64_t ldx, paro_half_t *Y, int64_t ldy,
                               int T, void *ws, hipStream_t s, const paro_rotation *rot = nullptr, bool x_operand = false);
