@@ -126,13 +126,16 @@ __device__ __forceinline__ void load_x_fragments(const DecodeArgs &a, int ks, bo
 constexpr int kRotStageWords = kSliceCh / 2;     // the slice's 512 fp16 activations of one token, in floats
 
 // ARGS: MultiArgs for several linears of the same width in, in one launch: the block rows are divided among the parts, every
-// part has as many tiles per block, and a block runs on its part's arguments.
+// part has as many tiles per block, and a block runs on its part's arguments.  (All bounds in one load: asked one after the
+// other, as a loop does, they cost the launch 0.1 us.)
 __device__ __forceinline__ const DecodeArgs &part_of(const DecodeArgs &a, int &) { return a; }
 __device__ __forceinline__ const DecodeArgs &part_of(const MultiArgs &m, int &nb)
 {
-    int p = 0;
-    while (p + 1 < m.n_parts && nb >= m.nb_end[p]) ++p;
-    if (p) nb -= m.nb_end[p - 1];
+    int p = 0, lo = 0;
+#pragma unroll
+    for (int q = 0; q + 1 < kMaxParts; ++q)
+        if (q + 1 < m.n_parts && nb >= m.nb_end[q]) { p = q + 1; lo = m.nb_end[q]; }
+    nb -= lo;
     return m.part[p];
 }
 
@@ -592,13 +595,17 @@ size_t decode_wide_multi_bytes(int n_parts, const paro_w4_weight *const *w, int 
     return total;
 }
 
-// As decode_wide_hosting_pays, of the sum of the outputs, by whole tiles: a last tile per wave that few blocks have does not hide it
-// (nor do two waves per block hide anything: 1024 -> 19232 6.8 us K-major, 7.2).  All blocks in one round.
+// As decode_wide_hosting_pays, of the sum of the outputs, by whole tiles: a last tile per wave that few blocks have does not hide it.
+// 2 to 4 slices always, but for 2 on a long stream.  Three parts, K-major / this kernel, us: 1024 -> 1536 in all 5.7 / 5.0, 1024 -> 6144
+// 5.8 / 5.4, 1024 -> 11264 6.3 / 5.9, 1024 -> 16384 6.4 / 6.35, 1024 -> 28672 7.45 / 7.6, 1536 -> 6144 6.3 / 5.6, 2048 -> 1536 5.8 / 5.3, 2048 -> 8192 6.5 / 6.0.
+// All blocks in one round.
 bool decode_wide_multi_hosting_pays(int c_in, int64_t c_out_sum)
 {
     const int KS = c_in / kGroup / kSliceGroups, kb = KS <= kWideWaves ? 1 : (KS + 7) / 8, waves = (KS + kb - 1) / kb;
     const int64_t tiles = c_out_sum / kTileN, blocks = 256 / kb;
-    return KS > 2 && kb <= 64 && tiles >= blocks * (waves <= 8 ? 4 : 6) && tiles + 4 * wide_max_tiles(true) <= blocks * wide_max_tiles(true);
+    if (KS == 1 || kb > 64 || tiles + 4 * wide_max_tiles(true) > blocks * wide_max_tiles(true)) return false;
+    if (KS <= 4) return KS > 2 || tiles < blocks * 4;
+    return tiles >= blocks * (waves <= 8 ? 4 : 6);
 }
 
 bool decode_wide_multi_fits(int n_parts, const paro_w4_weight *const *w, int T)

@@ -94,6 +94,7 @@ def test_multi_qkv_shape_of_the_8b_layer(P):
 
 @pytest.mark.parametrize("T,c_in,c_outs,n_layers", [
     (1, 1024, (16 * 700, 16 * 331), 8),                             # transforms per wave, one block per row of tiles, ragged shares
+    (1, 1024, (16 * 130, 16 * 9), 8), (1, 1536, (16 * 13, 16 * 5, 48), 8), (1, 2048, (16 * 300, 64), 8),     # 2 to 4 slices, few tiles per wave
     (1, 6656, (16 * 260, 16 * 256), 8),                             # the same with K over two blocks
     (1, 4608, (16 * 800, 16 * 740), 8),                             # and with nine waves per block
     (1, 5120, (16 * 1100, 16 * 1100), 3),                           # one token, layers that the kernel cannot host: two launches
