@@ -1,5 +1,5 @@
-// W4A16 linear, tiled, with the weights straight in registers (Eq. 2): from 33 tokens to some hundreds (a thousand on the
-// narrower outputs), and weights in the interchange layout above 32 tokens.
+// W4A16 linear, tiled, with the weights straight in registers (Eq. 2): from 33 tokens to some hundreds (thousands where
+// the outputs are few), and weights in the interchange layout above 32 tokens.
 //
 // At these sizes neither of the other kernels fits.  The streaming kernel keeps a K-slice of activations in registers (32
 // tokens fill half the register file) and re-reads the weights for every further 32 tokens.  The GEMM's 128 x 256 tiles are
@@ -298,8 +298,8 @@ constexpr int kTile2Stage = 65536, kTile2Lds = 2 * kTile2Stage;
 // Activations go to LDS directly, 64 KB per step in a ring of two: behind the barrier that ends a step its buffer is requested
 // anew at once.  Weights are two groups ahead in registers; what is multiplied next is read and dequantised while this is.
 // The matrix pipes are busy 0.47 of a block's cycles (30 % of the launch at 4096 -> 28672, 128 tokens), issue the rest; without
-// activations' requests (timing only) 35 us of 39.8.  A launch begins and ends in 9 us, 4 of them launching 512 threads with this
-// much LDS, 2 the first requests, 2 to 4 the sums and the stores: not for few groups (kTileWideGroups).
+// activations' requests (timing only) 35 us of 39.8.  A launch begins and ends in 9 us, 2 of them the first requests, 2 to 4 the sums and the
+// stores (an empty kernel takes 1.7 us whatever its LDS and threads): not for few groups (kTileWideGroups).
 // us, that -> this: 4096 -> 28672 at 128 tokens 44.3 -> 37.6, rotated 49.2 -> 43.5; 14336 -> 4096 at 201 42.2 -> 38.5;
 // 512 -> 32656 at 289 rotated 27.4 -> 23.0; 75 random shapes of 65 to 1100 tokens 0.976 of the time (other kernels' among them).
 

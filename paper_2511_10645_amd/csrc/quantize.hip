@@ -13,7 +13,6 @@
 //   MXFP4        32 consecutive channels share 2^e, e = floor(log2(max |v|)) - 2 (>= -127), stored as e + 127; every value
 //                becomes the E2M1 code of v / 2^e, to nearest, ties to the even code, saturated at 6.  A block that is
 //                NaN throughout has e = 126 and codes +-6: what is multiplied with it overflows.
-// (large dense weights: quantize_weight.hip)
 // so that  sum_c (q - z) s . x'_c  ~  w_n . x  for the activations x' that paro_rotate_scale produces (Eq. 2).
 //
 // One wavefront owns a channel group and a run of rows, four rows at a time (few rows: one each, kQuantFewRows), with the
@@ -32,7 +31,8 @@
 //     tie and its neighbours, probed over all exponents; the tests pin those that fp16 inputs and scales reach).
 // Measured over back-to-back calls (before: one row of INT4 weights per wave, plan re-read for each; MXFP4 one row at a
 // time, 14 instructions of thresholds per value): INT4 weight 28672 x 4096 414 -> 146 us (137 with reciprocals in place of the
-// three divisions, bytes picked by permutes and the factor of one left out; without a rotation 97 -> 84), MXFP4 activations 2048 x 4096
+// three divisions, bytes picked by permutes and the factor of one left out; without a rotation 97 -> 84; weights of this size
+// now go through the matrix cores, quantize_weight.hip, 84 to 94), MXFP4 activations 2048 x 4096
 // 21.0 -> 12.2, 2048 x 14336 55.8 -> 35.2 us (11.8 and 35.5 with codes past the L2, as INT4 codes leave it: weights 1 to 7 % faster
 // alone, a GEMM behind as fast over 36 shapes), INT4 activations 24.7 -> 14.3 and 78.3 -> 39.6 us (now 13.9 on the former); 1 x 4096
 // MXFP4 3.0 -> 2.6, INT4 2.9 -> 2.8; the same bits throughout.
