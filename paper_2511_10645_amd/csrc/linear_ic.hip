@@ -1,7 +1,8 @@
-// W4A16 linear on weights in the interchange layout, up to 32 tokens (Eq. 2): what a call runs on when the weight was not
-// repacked, or has no repacked form because its input width is no multiple of 512 channels.  (More tokens: linear_tile.hip.)
+// W4A16 linear on weights in the interchange layout, up to 32 tokens, and up to 256 where that is the faster (Eq. 2): what a call
+// runs on when the weight was not repacked, or has no repacked form because its input width is no multiple of 512 channels.
+// (More: linear_tile.hip.)
 //
-// A block owns 16 NT outputs and all tokens.  It walks its channels in stages of KG groups; KG consumer waves (times NCOL columns
+// A block owns 16 NT outputs and all tokens (more than 32: up to 32 of them, as many blocks as it takes, all at once).  It walks its channels in stages of KG groups; KG consumer waves (times NCOL columns
 // of NTW output tiles) take one group each, and their sums meet in LDS once at the end.  Everything goes from memory to LDS
 // without passing through registers, and who requests what is split by latency, because a wave's requests complete in order:
 // the producer wave requests only what comes from memory (codes, scales and zero points, RW stages deep), the consumers the
@@ -20,6 +21,8 @@
 // Measured, us, before -> now (graph replay over 350 MB of weights): 11008 -> 4096 at 24 tokens bare 36.8 -> 14.0, rotated
 // 20.4 -> 17.4 (four slices of K), one token bare 19.3 -> 9.0; 2176 -> 4112 at 24 tokens bare 11.0 -> 6.3; 4224 -> 22016 32.3 -> 23;
 // 106 random shapes: bare 0.60 of the time, rotated 0.80 in the geometric mean; many outputs on few channels: ic_few_channels.
+// 33 tokens and more, tiled kernel -> this one: 9600 -> 2272 at 48 bare 45.9 -> 15.5, 11008 -> 4096 at 48 bare 53.0 -> 18.1, 4096 -> 4096 at 64
+// bare 22.8 -> 9.2, rotated 18.2 -> 13.1, 1024 -> 208 at 128 bare 9.4 -> 4.3, 2816 -> 3440 at 256 bare 18.8 -> 18.3: linear_rows_pay.
 #include "paro_internal.h"
 #include <algorithm>
 #include <cmath>
@@ -73,6 +76,7 @@ struct IcArgs {
     float *partial;                                  // [k slices][T][N] where K is split between blocks, else NULL
     int T, C, N, G, groups_per_split;
     uint32_t m_lo, k_lo;                             // 0x000F000F, 0x64006400: arguments, so that (u & m) | k is one instruction
+    int pass_tokens;                                 // of a block where there are more than 32
 };
 
 constexpr int ic_wstage(int kg, int nt) { return kg * nt * 1024 + (kg * nt * 32 + 255) / 256 * 256 + 256; }  // codes | scales | zero points
@@ -80,7 +84,8 @@ constexpr int ic_lds(int kg, int consumers, int rpw, int nt, int xr, int rw) { r
 
 // TB: blocks of 16 tokens; RPW: token rows that a consumer wave requests per stage; NCOL, NTW: see above; XR, RW: stages in the
 // rings of activations and weights
-template <int TB, int RPW, int KG, int NCOL, int NTW, int XR, int RW>
+// PASSES: more than 32 tokens, blockIdx.z has pass_tokens of them each (as a condition at run time it costs the others 0.1 us).
+template <int TB, int RPW, int KG, int NCOL, int NTW, int XR, int RW, bool PASSES>
 __global__ __launch_bounds__((KG * NCOL + 1) * 64) void linear_ic_kernel(IcArgs a)
 {
     constexpr int NC = KG * NCOL, NT = NCOL * NTW, kXRow = KG * 256, kXStage = NC * RPW * kXRow, kWTile = KG * 1024, kWStage = ic_wstage(KG, NT);
@@ -94,6 +99,7 @@ __global__ __launch_bounds__((KG * NCOL + 1) * 64) void linear_ic_kernel(IcArgs 
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int n0 = blockIdx.x * 16 * NT, n_rows = min(a.N - n0, 16 * NT);          // multiple of 16
     const int g_lo = (int)blockIdx.y * a.groups_per_split, g_hi = min(a.G, g_lo + a.groups_per_split);
+    const int t_lo = PASSES ? (int)blockIdx.z * a.pass_tokens : 0, T = PASSES ? min(a.T - t_lo, a.pass_tokens) : a.T;      // tokens of this block
     // Stage st is groups g_lo + KG st .. + KG - 1; a last stage of fewer is moved back to the last KG (those that were there
     // already are not multiplied again).
     const int n_grp = g_hi - g_lo, n_st = (n_grp + KG - 1) / KG, g_last = n_grp < KG ? 0 : n_grp - KG;
@@ -148,11 +154,11 @@ __global__ __launch_bounds__((KG * NCOL + 1) * 64) void linear_ic_kernel(IcArgs 
             if (st + RW < n_st) request(st + RW);            // into the slot of stage st, which every wave has read
         }
     } else {
-        const __amdgpu_buffer_rsrc_t xr = ic_rsrc(a.X, ((size_t)(a.T - 1) * a.ldx + a.C) * 2);
+        const __amdgpu_buffer_rsrc_t xr = ic_rsrc(a.X + (size_t)t_lo * a.ldx, ((size_t)(T - 1) * a.ldx + a.C) * 2);
         uint32_t xv[kXReq];
         ic_for<kXReq>([&](auto I) {
             const int row = wave * RPW + I / (KG / 4), c = (I % (KG / 4) * 64 + lane) ^ swz(row);
-            xv[I] = row < a.T && c < 16 * n_grp ? (uint32_t)(((size_t)row * a.ldx) * 2) + g_lo * 256 + (c << 4) : kOobI;
+            xv[I] = row < T && c < 16 * n_grp ? (uint32_t)(((size_t)row * a.ldx) * 2) + g_lo * 256 + (c << 4) : kOobI;
         });
         uint32_t slot = 0;
         auto request = [&](int st) {
@@ -239,16 +245,16 @@ __global__ __launch_bounds__((KG * NCOL + 1) * 64) void linear_ic_kernel(IcArgs 
         for (int w = 1; w < KG; ++w) sum += *(const float4v *)(s_sum + w * TB * NT * 256 + u * 4);
         const int o = n0 + n * 16 + (l & 15);
         if (a.partial) {
-            float *dst = a.partial + ((size_t)blockIdx.y * a.T + t0) * a.N + o;
+            float *dst = a.partial + ((size_t)blockIdx.y * a.T + t_lo + t0) * a.N + o;
 #pragma unroll
             for (int r = 0; r < 4; ++r)
-                if (t0 + r < a.T) dst[(size_t)r * a.N] = sum[r];
+                if (t0 + r < T) dst[(size_t)r * a.N] = sum[r];
         } else {
             const float bv = a.bias ? (float)a.bias[o] : 0.f;
-            _Float16 *dst = a.Y + (size_t)t0 * a.ldy + o;
+            _Float16 *dst = a.Y + (size_t)(t_lo + t0) * a.ldy + o;
 #pragma unroll
             for (int r = 0; r < 4; ++r)
-                if (t0 + r < a.T) dst[(size_t)r * a.ldy] = (_Float16)(sum[r] + bv);
+                if (t0 + r < T) dst[(size_t)r * a.ldy] = (_Float16)(sum[r] + bv);
         }
     }
 }
@@ -256,9 +262,13 @@ __global__ __launch_bounds__((KG * NCOL + 1) * 64) void linear_ic_kernel(IcArgs 
 // Tiles per block and slices of K by a model fitted to 106 random shapes (2 % off; the choice costs 0.3 % over the best): a block
 // per compute unit and round, a fixed time and one per stage, which grows with the blocks that share the memory.  At 24 tokens,
 // 4096 outputs, a stage of 8 groups of one tile takes 1.0 us, of 4 groups of two tiles 0.7, of four tiles 1.1.
-struct IcPlan { int nt, k_split, groups_per_split; };
+struct IcPlan { int nt, k_split, groups_per_split; double us; };
+constexpr int kIcMaxTokens = 256;
+static int ic_passes(int T) { return (T + 31) / 32; }
+static int ic_pass_tokens(int T) { return T <= 32 ? T : ((T + ic_passes(T) - 1) / ic_passes(T) + 7) / 8 * 8; }
 static IcPlan ic_plan(int c_in, int c_out, int T, bool may_split)
 {
+    const int pass = ic_pass_tokens(T);
     struct Fit { int nt; double first, round, stage, busy; };
     static const Fit fits[3][4] = {                          // up to 8, 16, 32 tokens
         {{1, 1.13, 1.76, 0.476, 0.115}, {2, 1.84, 1.06, 0.480, -0.008}, {4, 0.65, 2.41, 0.721, 0.130}, {8, 1.94, 1.74, 1.249, 0.454}},
@@ -266,16 +276,15 @@ static IcPlan ic_plan(int c_in, int c_out, int T, bool may_split)
         {{1, 1.71, 1.44, 0.604, 0.418}, {2, 1.33, 2.01, 0.525, 0.192}, {4, 1.17, 2.42, 0.809, 0.258}, {0, 0, 0, 0, 0}},
     };
     const int G = c_in / kGroup;
-    IcPlan best{1, 1, G};
-    double best_us = 1e30;
-    for (const Fit &f : fits[T <= 8 ? 0 : T <= 16 ? 1 : 2])
+    IcPlan best{1, 1, G, 1e30};
+    for (const Fit &f : fits[pass <= 8 ? 0 : pass <= 16 ? 1 : 2])
         for (int ks = 1; f.nt && ks <= (may_split ? 4 : 1); ++ks) {
             const int gps = (G + ks - 1) / ks, kg = f.nt == 1 ? 8 : 4, stages = (gps + kg - 1) / kg;
             if ((G + gps - 1) / gps != ks) continue;
-            const double blocks = (double)((c_out + 16 * f.nt - 1) / (16 * f.nt)) * ks;
+            const double blocks = (double)((c_out + 16 * f.nt - 1) / (16 * f.nt)) * ks * ic_passes(T);
             double us = f.first + std::ceil(blocks / 256) * (f.round + stages * (f.stage + f.busy * std::min(blocks, 256.0) / 256));
             if (ks > 1) us += 2.0 + 0.14e-6 * 8.0 * ks * T * c_out;          // the summing launch; partial tiles written and read
-            if (us < best_us) { best = IcPlan{f.nt, ks, gps}; best_us = us; }
+            if (us < best.us) best = IcPlan{f.nt, ks, gps, us};
         }
     return best;
 }
@@ -286,10 +295,10 @@ size_t linear_rows_scratch_bytes(const paro_w4_weight &w, int T)
     return p.k_split > 1 ? (size_t)p.k_split * T * w.c_out * sizeof(float) : 0;
 }
 
-// scales as dwords; row offsets of a block and the whole code array in 31 bits; up to 32 tokens
+// scales as dwords; row offsets of a block and the whole code array in 31 bits
 bool linear_rows_supported(const paro_w4_weight &w, int64_t ldx, int T)
 {
-    return w.qweight && w.scales && w.qzeros && ((uintptr_t)w.scales % 4) == 0 && T <= 32 && (size_t)T * ldx * 2 < (1ull << 31) &&
+    return w.qweight && w.scales && w.qzeros && ((uintptr_t)w.scales % 4) == 0 && T <= kIcMaxTokens && (size_t)T * ldx * 2 < (1ull << 31) &&
            (size_t)w.c_out * (w.c_in / 2) < (1ull << 31);
 }
 
@@ -317,11 +326,11 @@ constexpr IcConfig kIcConfigs[] = {
 };
 static int ic_config(int nt, int T) { return nt == 8 ? 12 : (nt == 4 ? 8 : nt == 2 ? 4 : 0) + (T - 1) / 8; }
 
-template <int I>
+template <int I, bool PASSES>
 static hipError_t launch_ic_cfg(const IcArgs &a, dim3 grid, hipStream_t s)
 {
     constexpr IcConfig c = kIcConfigs[I];
-    constexpr auto kernel = linear_ic_kernel<c.tb, c.rpw, c.kg, c.ncol, c.ntw, c.xr, c.rw>;
+    constexpr auto kernel = linear_ic_kernel<c.tb, c.rpw, c.kg, c.ncol, c.ntw, c.xr, c.rw, PASSES>;
     constexpr int lds = ic_lds(c.kg, c.kg * c.ncol, c.rpw, c.ncol * c.ntw, c.xr, c.rw);
     static_assert(lds <= 160 * 1024, "");
     static std::atomic<uint64_t> attr_done{0};
@@ -336,8 +345,9 @@ static hipError_t launch_ic_cfg(const IcArgs &a, dim3 grid, hipStream_t s)
 template <size_t... I>
 static hipError_t launch_ic(int config, const IcArgs &a, dim3 grid, hipStream_t s, std::index_sequence<I...>)
 {
-    static constexpr hipError_t (*launch[])(const IcArgs &, dim3, hipStream_t) = {launch_ic_cfg<I>...};
-    return launch[config](a, grid, s);
+    static constexpr hipError_t (*launch[])(const IcArgs &, dim3, hipStream_t) = {launch_ic_cfg<I, false>...};
+    static constexpr hipError_t (*passes[])(const IcArgs &, dim3, hipStream_t) = {launch_ic_cfg<I, kIcConfigs[I].tb == 2>...};      // 17..32 tokens each
+    return a.T > 32 ? passes[config](a, grid, s) : launch[config](a, grid, s);
 }
 
 // the plan of a call with this much room for partial tiles
@@ -347,12 +357,22 @@ static IcPlan ic_plan_in(const paro_w4_weight &w, int T, size_t room)
     return p.k_split == 1 || (size_t)p.k_split * T * w.c_out * sizeof(float) <= room ? p : ic_plan(w.c_in, w.c_out, T, false);
 }
 
+// More than 32 tokens: where blocks of up to 32 tokens, all at once, take less than the tiled kernel in the room there is for partial tiles.
+// That one's blocks are 64 tokens x 128 outputs, few where the outputs are, and walk all of K one after the other; here every 32 tokens read the
+// weights once more and the codes are unpacked again, which loses where the blocks fill several rounds: 256 -> 5840 at 256 tokens bare
+// 7.6 / 11.3 us, 4224 -> 9408 at 200 42 / 56.  Both by their models, with a margin of 5 % (15 % where the tiled kernel splits K): 309 calls of
+// 33 to 256 tokens, 256 to 15000 channels, 16 to 24000 outputs take 0.64 of the time, within 1 % of the better of the two in the mean; none slower.
+bool linear_rows_pay(const paro_w4_weight &w, int64_t ldx, int T, size_t room)
+{
+    return linear_rows_supported(w, ldx, T) && (T <= 32 || !linear_tile_supported(w, true) || linear_tile_loses(w, T, room, ic_plan_in(w, T, room).us));
+}
+
 void linear_rows_plan(const paro_w4_weight &w, int T, size_t room, int &outputs, int &k_slices, int &config, int &stages, int &ring)
 {
     const IcPlan p = ic_plan_in(w, T, room);
     k_slices = p.k_split; outputs = 0; config = -1; stages = ring = 0;
-    if (ic_few_channels(p, w.c_in, w.c_out, T)) return;
-    outputs = 16 * p.nt; config = ic_config(p.nt, T);
+    if (T <= 32 && ic_few_channels(p, w.c_in, w.c_out, T)) return;
+    outputs = 16 * p.nt; config = ic_config(p.nt, ic_pass_tokens(T));
     const IcConfig c = kIcConfigs[config];
     stages = (p.groups_per_split + c.kg - 1) / c.kg; ring = std::max(c.xr, c.rw);
 }
@@ -362,15 +382,16 @@ hipError_t launch_linear_rows(const paro_w4_weight &w, const paro_half_t *X, int
 {
     const IcPlan p = ic_plan_in(w, T, scratch && ((uintptr_t)scratch % 16) == 0 ? scratch_bytes : 0);
     const bool split = p.k_split > 1;
-    if (ic_few_channels(p, w.c_in, w.c_out, T)) return launch_linear_direct(w, X, ldx, Y, ldy, T, s);
+    if (T <= 32 && ic_few_channels(p, w.c_in, w.c_out, T)) return launch_linear_direct(w, X, ldx, Y, ldy, T, s);
     IcArgs a;
     a.w = (const char *)w.qweight; a.scales = (const _Float16 *)w.scales; a.qzeros = w.qzeros;
     a.X = (const _Float16 *)X; a.ldx = ldx; a.Y = (_Float16 *)Y; a.ldy = ldy; a.bias = (const _Float16 *)w.bias;
     a.partial = split ? (float *)scratch : nullptr;
     a.T = T; a.C = w.c_in; a.N = w.c_out; a.G = w.c_in / kGroup; a.groups_per_split = p.groups_per_split;
+    a.pass_tokens = ic_pass_tokens(T);
     a.m_lo = 0x000F000Fu; a.k_lo = 0x64006400u;
-    const dim3 grid((w.c_out + 16 * p.nt - 1) / (16 * p.nt), p.k_split);
-    const hipError_t e = launch_ic(ic_config(p.nt, T), a, grid, s, std::make_index_sequence<std::size(kIcConfigs)>{});
+    const dim3 grid((w.c_out + 16 * p.nt - 1) / (16 * p.nt), p.k_split, ic_passes(T));
+    const hipError_t e = launch_ic(ic_config(p.nt, a.pass_tokens), a, grid, s, std::make_index_sequence<std::size(kIcConfigs)>{});
     if (e != hipSuccess || !split) return e;
     return launch_splitk_reduce(a.partial, p.k_split, T, 0, w.c_out, w.bias, Y, ldy, least, s);
 }

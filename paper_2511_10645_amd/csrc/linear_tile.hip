@@ -1,5 +1,5 @@
 // W4A16 linear, tiled, with the weights straight in registers (Eq. 2): from 33 tokens to some hundreds (thousands where
-// the outputs are few), and weights in the interchange layout above 32 tokens.
+// the outputs are few), and weights in the interchange layout above 32 tokens where linear_ic.hip is not the faster.
 //
 // At these sizes neither of the other kernels fits.  The streaming kernel keeps a K-slice of activations in registers (32
 // tokens fill half the register file) and re-reads the weights for every further 32 tokens.  The GEMM's 128 x 256 tiles are
@@ -565,7 +565,7 @@ constexpr int kTileWideGroups = 12;
 // the partial tiles.  128-token tiles take 0.8 of the time per token, but their blocks are longer and begin slower: 4096 -> 28672
 // at 128 tokens 39 us against 47, 4096 -> 4096 at 201 tokens 21.5 against 18.8.  128-token tiles of few groups: 24 shapes of the
 // interchange layout in one to five rounds, 2 % off.
-struct TilePlan { bool two_m; int k_split, groups_per_split; double est_us; };
+struct TilePlan { bool two_m; int k_split, groups_per_split; double est_us, fit_us; };
 static size_t tile_partial_bytes(int k_split, int T, int c_out) { return k_split > 1 ? (size_t)k_split * T * c_out * sizeof(float) : 0; }
 
 // room: bytes for partial tiles; what needs more is not planned.  (Bare calls on interchange weights have none: unsplit with the
@@ -583,7 +583,7 @@ static TilePlan plan_tile(int c_in, int c_out, int T, bool interchange, size_t r
     // forced, 3 % off; priced as repacked weights 5888 -> 16944 at 464 tokens took 162 us in 128-token tiles instead of 157).
     static const Fit fits[2][2] = {{{1.7, 3.8, 0.94, 1.04, 1.3, 0.27, 0.151}, {3.0, 4.2, 1.49, 1.71, 0.5, 0.245, 0.189}},
                                    {{2.0, 3.36, 1.04, 1.12, 1.3, 0.27, 0.151}, {0.5, 4.9, 1.88, 1.96, 0.5, 0.245, 0.189}}};
-    TilePlan best{false, 1, 0, 1e30};
+    TilePlan best{false, 1, 0, 1e30, 1e30};
     const int G = c_in / kGroup, n_tiles = (c_out + 127) / 128;
     for (int two = 0; two <= (T > 64 ? 1 : 0); ++two) {
         const Fit &f = fits[interchange][two];
@@ -602,7 +602,7 @@ static TilePlan plan_tile(int c_in, int c_out, int T, bool interchange, size_t r
                             : f.call + (double)rounds * (f.round + gps / 2 * (blocks >= 160 ? f.step_full : f.step));
             if (ks > 1) us += f.sum + f.slice * ks + (double)ks * T * c_out * 8.0e-6 * f.mb;
             if (us < least_us) { least_us = us; least_fits = fits_room; }
-            if (fits_room && us < best.est_us) best = TilePlan{two != 0, ks, gps, us};
+            if (fits_room && us < best.fit_us) best = TilePlan{two != 0, ks, gps, us, us};
             double line = 1.6 + (double)rounds * (3.5 + (two ? gps : gps / 2) * ((blocks >= 160 ? 1.09 : 0.96) - (two ? 0.04 : 0.0)));
             if (ks > 1) line += 1.7 + 0.23 * ks + (double)ks * T * c_out * 8.0 / 6.9e6;
             if (line < lines_us) { lines_us = line; line_fits = fits_room; }
@@ -613,6 +613,12 @@ static TilePlan plan_tile(int c_in, int c_out, int T, bool interchange, size_t r
 }
 
 double linear_tile_estimate_us(const paro_w4_weight &w, int T, size_t room) { return plan_tile(w.c_in, w.c_out, T, false, room).est_us; }
+// whether a call on interchange weights that takes `us` elsewhere is faster there, by more than the two models are off
+bool linear_tile_loses(const paro_w4_weight &w, int T, size_t room, double us)
+{
+    const TilePlan p = plan_tile(w.c_in, w.c_out, T, true, room);
+    return us < (p.k_split > 1 ? 0.85 : 0.95) * p.fit_us;
+}
 
 size_t linear_tile_scratch_bytes(const paro_w4_weight &w, int T, bool interchange, size_t room)
 {

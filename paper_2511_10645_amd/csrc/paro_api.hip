@@ -236,7 +236,7 @@ paro_status run_linear(const paro_w4_weight *w, const paro_half_t *X, int64_t ld
     };
     if (!fast_weight(w)) {
         if (!(w->qweight && w->scales && w->qzeros)) return PARO_ERR_UNSUPPORTED;
-        if (linear_rows_supported(*w, ldx, T)) {
+        if (linear_rows_pay(*w, ldx, T, scratch.bytes)) {
             const size_t need = linear_rows_scratch_bytes(*w, T);
             return from_hip(launch_linear_rows(*w, X, ldx, Y, ldy, T, scratch.partials(need), need, scratch.least, s));
         }
@@ -493,7 +493,7 @@ int paro_internal_linear_plan_in(const paro_rotation *rot, const paro_w4_weight 
         const LinearRoute::Kernel r = linear_route(*w, w->c_in, w->c_out, T, scratch).kernel;
         kernel = r == LinearRoute::kTile ? kPlanTile : r == LinearRoute::kGemm ? kPlanGemm : kPlanStream;
         if (kernel == kPlanStream) t = rot && rot->plan && decode_wide_operand_pays(w->c_in, T);
-    } else if (linear_rows_supported(*w, w->c_in, T)) { kernel = kPlanRows; k = scratch ? (int)(linear_rows_scratch_bytes(*w, T) / ((size_t)T * w->c_out * 4)) : 1; }
+    } else if (linear_rows_pay(*w, w->c_in, T, scratch)) { kernel = kPlanRows; k = scratch ? (int)(linear_rows_scratch_bytes(*w, T) / ((size_t)T * w->c_out * 4)) : 1; }
     else if (T > kStreamPassTokens && linear_tile_supported(*w, true)) kernel = kPlanTile;
     if (kernel == kPlanTile) linear_tile_plan(*w, T, !fast_weight(w), scratch, t, k);
     *tile = t; *k_slices = k;

@@ -205,10 +205,11 @@ hipError_t launch_mxfp4_linear(const paro_mxfp4_weight &w, const uint32_t *x_cod
 hipError_t launch_quantize_act_mxfp4(const paro_rotation &rot, const paro_half_t *X, int64_t ldx, int T, uint32_t *codes,
                                      uint8_t *scales, hipStream_t s);
 
-// Weights in the interchange layout, up to 32 tokens (linear_ic.hip).  scratch: room for the partial sums of K split
-// between blocks (any contents before; after, those below `least` are zero: launch_splitk_reduce); without it the call
-// runs unsplit.
+// Weights in the interchange layout, up to 32 tokens, and more where that pays (linear_ic.hip).  scratch: room for the partial sums
+// of K split between blocks (any contents before; after, those below `least` are zero: launch_splitk_reduce); without it the
+// call runs unsplit.
 bool linear_rows_supported(const paro_w4_weight &w, int64_t ldx, int T);
+bool linear_rows_pay(const paro_w4_weight &w, int64_t ldx, int T, size_t room);
 void linear_rows_plan(const paro_w4_weight &w, int T, size_t room, int &outputs, int &k_slices, int &config, int &stages, int &ring);
 size_t linear_rows_scratch_bytes(const paro_w4_weight &w, int T);
 hipError_t launch_linear_rows(const paro_w4_weight &w, const paro_half_t *X, int64_t ldx, paro_half_t *Y, int64_t ldy,
@@ -228,6 +229,7 @@ hipError_t launch_linear_operand(const paro_w4_weight &w, const paro_half_t *Xop
 bool linear_tile_supported(const paro_w4_weight &w, bool interchange);
 // room: bytes there are for partial tiles; a call with less than the best split wants is planned with fewer slices, or none.
 double linear_tile_estimate_us(const paro_w4_weight &w, int T, size_t room);
+bool linear_tile_loses(const paro_w4_weight &w, int T, size_t room, double us);
 void linear_tile_plan(const paro_w4_weight &w, int T, bool interchange, size_t room, int &tokens, int &k_slices);
 size_t linear_tile_scratch_bytes(const paro_w4_weight &w, int T, bool interchange, size_t room = SIZE_MAX);
 hipError_t launch_linear_tile(const paro_w4_weight &w, bool interchange, const paro_half_t *X, int64_t ldx, paro_half_t *Y,

@@ -70,6 +70,10 @@ CASES = [
     # 128-token tiles, groups that do not come in whole pairs of steps, ragged last slices and tiles of 16 outputs
     (66, 5248, 8208, "plain"), (129, 1152, 12304, "plain"), (66, 4608, 8208, "packed"), (129, 2560, 12304, "packed"), (383, 1536, 6160, "packed"),
     (65, 1664, 18400, "plain"), (105, 512, 17424, "packed"),
+    # interchange layout above 32 tokens: blocks of 17..32 tokens at once, the last with one token and with all, K split and not, outputs that end inside a
+    # block; and 64-token tiles with K split
+    (33, 256, 400, "plain"), (97, 2944, 80, "plain"), (129, 1280, 1040, "plain"), (256, 384, 2064, "plain"), (65, 13824, 144, "plain"), (225, 896, 4112, "plain"),
+    (64, 5248, 4112, "plain"),
 ]
 
 

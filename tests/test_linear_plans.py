@@ -154,3 +154,9 @@ def test_many_tokens_on_few_outputs():
         assert plan(T, c_in, c_out, "packed", False)[0] == plan(T, c_in, c_out, "packed", True)[0] == TILE
     for T, c_in, c_out in ((1283, 8192, 8240), (1229, 3584, 5296), (2048, 4096, 4096), (4097, 4096, 512)):
         assert plan(T, c_in, c_out, "packed", False)[0] == plan(T, c_in, c_out, "packed", True)[0] == GEMM
+
+
+def test_few_outputs_on_interchange_weights_take_the_staged_kernel():
+    """Above 32 tokens; bare, this against the tiled kernel, us: 15.5 / 45.9, 9.2 / 22.8, 4.3 / 9.4; but 56 / 42, 11.3 / 7.6, and it ends at 256."""
+    for T, c_in, c_out, want in ((48, 9600, 2272, ROWS), (64, 4096, 4096, ROWS), (128, 1024, 208, ROWS), (200, 4224, 9408, TILE), (256, 256, 5840, TILE), (257, 1024, 208, TILE)):
+        assert plan(T, c_in, c_out, "plain", False)[0] == want, (T, c_in, c_out)
