@@ -143,9 +143,10 @@ paro_status paro_w4_repack(const paro_w4_weight *w, void *packed_out, void *stre
  *        bytes [0, 256)   header.  Bytes 8..11 (paro_workspace_error_offset()) hold an error
  *                         word: it stays 0 unless a bounded wait between blocks of a launch ran
  *                         out (the outputs that depended on it are then NaN);
- *        from paro_workspace_partials_offset() on: fp32 partial sums of split-K launches; every
- *                         word is reset by its reader, so this range is all zero again after
- *                         every call.
+ *        from paro_workspace_partials_offset() on: fp32 partial sums of split-K launches (and
+ *                         the transformed activations of a paro_rotated_linear_multi() in two
+ *                         launches); every word is reset by its last reader, so this range is
+ *                         all zero again after every call.
  *     The blocks that exchange data must be resident at the same time: do not run other long
  *     kernels concurrently with these calls.  After a non-zero error word (or after a call that
  *     was cancelled or faulted) zero-fill the exchange part again before the next call.

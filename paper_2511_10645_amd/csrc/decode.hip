@@ -360,7 +360,7 @@ hipError_t launch_decode_multi(int n_parts, const paro_rotation *const *rot, con
                                void *ws, hipStream_t s)
 {
     if (n_parts < 1 || n_parts > kMaxParts) return hipErrorInvalidValue;
-    MultiArgs m;
+    MultiArgs m{};
     m.n_parts = n_parts;
     int nb_total = 0, ks = 0;
     size_t off = 0;

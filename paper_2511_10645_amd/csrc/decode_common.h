@@ -42,6 +42,7 @@ struct MultiArgs {
     DecodeArgs part[kMaxParts];
     int nb_end[kMaxParts];      // block rows [nb_end[p-1], nb_end[p]) belong to part p
     int n_parts;
+    uint32_t *seen[kMaxParts];  // decode_wide_kernel on rows in the exchange part: a word per K-slice and block of the part
 };
 
 // Raw buffer resources (stride 0): an access whose byte offset lies beyond num_records returns 0

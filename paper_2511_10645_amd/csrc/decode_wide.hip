@@ -128,16 +128,24 @@ constexpr int kRotStageWords = kSliceCh / 2;     // the slice's 512 fp16 activat
 // ARGS: MultiArgs for several linears of the same width in, in one launch: the block rows are divided among the parts, every
 // part has as many tiles per block, and a block runs on its part's arguments.  (All bounds in one load: asked one after the
 // other, as a loop does, they cost the launch 0.1 us.)
-__device__ __forceinline__ const DecodeArgs &part_of(const DecodeArgs &a, int &) { return a; }
-__device__ __forceinline__ const DecodeArgs &part_of(const MultiArgs &m, int &nb)
+__device__ __forceinline__ const DecodeArgs &part_of(const DecodeArgs &a, int &, int &) { return a; }
+__device__ __forceinline__ const DecodeArgs &part_of(const MultiArgs &m, int &nb, int &p)
 {
-    int p = 0, lo = 0;
+    int lo = 0;
 #pragma unroll
     for (int q = 0; q + 1 < kMaxParts; ++q)
         if (q + 1 < m.n_parts && nb >= m.nb_end[q]) { p = q + 1; lo = m.nb_end[q]; }
     nb -= lo;
     return m.part[p];
 }
+
+// Several linears whose transforms ran before (ROTK 0): their rows lie in the exchange part, which has to be zero again after the
+// call.  The slice of a part's rows that a wave reads is read by the same wave of each of the part's blocks: every one of them sets a
+// word of its own once its rows are in registers, and the part's last block, behind its outputs, clears the slice and the
+// words where all are set (they are long since; the wait is bounded, and for blocks that were dispatched before).  It costs the launch
+// 0.1 to 0.9 us of 11 to 25, 3 % in the mean of 32 shapes; a counter per slice instead of words costs up to 1.7, its
+// adds coming one after the other, and a launch of its own 1.7.
+constexpr int kMaxMultiBlocks = 256;            // of such a launch, over all parts
 
 template <bool SPLIT, bool T1, int ROTK = 0, int MAXW = kWideWaves, class ARGS = DecodeArgs>
 __global__ __launch_bounds__(MAXW * 64) void decode_wide_kernel(ARGS args)
@@ -147,8 +155,9 @@ __global__ __launch_bounds__(MAXW * 64) void decode_wide_kernel(ARGS args)
     // [waves][tiles per block] partial tiles | kReduceWords reduce scratch
     extern __shared__ __attribute__((aligned(16))) float s_wide[];
     const int kb = blockIdx.x;
-    int nb = blockIdx.y;
-    const DecodeArgs &a = part_of(args, nb);
+    int nb = blockIdx.y, part = 0;
+    const DecodeArgs &a = part_of(args, nb, part);
+    constexpr bool CLEARS = ROTK == 0 && !std::is_same_v<ARGS, DecodeArgs>;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int nw = blockDim.x >> 6;                                        // K-slices (waves) per block
@@ -270,6 +279,15 @@ __global__ __launch_bounds__(MAXW * 64) void decode_wide_kernel(ARGS args)
             nb1[g2] = s1; nb2[g2] = s2;
         }
     }
+    int n_blocks = 0;                                    // of this part
+    uint32_t *seen = nullptr;                            // [n_blocks] of this slice
+    if constexpr (CLEARS) {
+        n_blocks = args.nb_end[part] - (part ? args.nb_end[part - 1] : 0);
+        seen = args.seen[part] + ks * n_blocks;
+        uint32_t one = 1;
+        asm volatile("" : "+v"(one) : "v"(nb2[0]), "v"(nb2[1]), "v"(nb2[2]), "v"(nb2[3]));      // behind the sums over all of the wave's rows
+        if (slice_ok && lane == 0) __hip_atomic_store(seen + nb, one, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
     auto to_vgpr = [&](uint32_t v) { return (uint32_t)__builtin_amdgcn_ds_bpermute(lane << 2, (int)v); };
     const DequantConsts dq = {to_vgpr(a.m_lo), to_vgpr(a.m_hi), to_vgpr(a.k_lo), to_vgpr(a.k_hi)};
 
@@ -295,6 +313,14 @@ __global__ __launch_bounds__(MAXW * 64) void decode_wide_kernel(ARGS args)
         emit(st[i % NS], i);
         return true;
     });
+    const bool clears = CLEARS && slice_ok && nb == n_blocks - 1;
+    uint32_t set[kMaxMultiBlocks / 64];
+    auto look = [&] {
+#pragma unroll
+        for (int u = 0; u < kMaxMultiBlocks / 64; ++u)
+            set[u] = lane + 64 * u < n_blocks ? __hip_atomic_load(seen + lane + 64 * u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 1u;
+    };
+    if constexpr (CLEARS) { if (clears) look(); }            // (asked ahead of the outputs, examined behind them)
     __syncthreads();
     // ---- sum the K-slices; outputs indexed (i, t, n) with n fastest for coalesced stores -----
     const int per_tile = a.T * kTileN;
@@ -316,6 +342,16 @@ __global__ __launch_bounds__(MAXW * 64) void decode_wide_kernel(ARGS args)
         }
     }
     if constexpr (SPLIT) splitk_reduce(a, gridDim.x, kb, tile_lo, tile_hi, s_red);
+    if constexpr (CLEARS) {
+        if (clears) {
+            auto all_set = [&] { return __all(set[0] && set[1] && set[2] && set[3]); };
+            for (int spin = 0; spin < kSpinLimit && !all_set(); ++spin) look();
+            if (!all_set() && lane == 0) __hip_atomic_store(a.err, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            for (int b = lane; b < n_blocks; b += 64) __hip_atomic_store(seen + b, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            _Float16 *row = const_cast<_Float16 *>(a.X) + (size_t)ks * kSliceCh + lane * 8;
+            for (int t = 0; t < a.T; ++t) *(u32x4 *)(row + (size_t)t * a.ldx) = u32x4{0, 0, 0, 0};
+        }
+    }
 }
 
 // ------------------------------------------------------------------------------------------
@@ -584,15 +620,26 @@ hipError_t launch_decode_wide(const paro_w4_weight &w, const paro_half_t *X, int
     return hipGetLastError();
 }
 
-// Several parts, 1..4 tokens.  X: [part][T][ldx] activations of each part where `rot` is NULL (a rotation pass wrote them),
-// otherwise the one input of transforms that decode_wide_hosts() accepts.
+// Several parts, 1..4 tokens, behind the header of the exchange part: partial sums, and where the transforms run before, the rows of
+// each part and a word per K-slice and block of those that have read them (kMaxMultiBlocks in all).
 size_t decode_wide_multi_bytes(int n_parts, const paro_w4_weight *const *w, int T)
 {
-    const int KS = w[0]->c_in / kGroup / kSliceGroups, kb = KS <= kWideWaves ? 1 : (KS + 7) / 8;
+    const int kb = wide_geometry(w[0]->c_in, kTileN, T).kb;
     size_t total = 0;
     if (kb > 1)
         for (int p = 0; p < n_parts; ++p) total += ((size_t)kb * T * w[p]->c_out * sizeof(float) + 255) / 256 * 256;
     return total;
+}
+
+static size_t multi_seen_bytes(int c_in) { return (size_t)kMaxMultiBlocks * (c_in / kSliceCh) * 4; }
+static size_t multi_row_bytes(int c_in, int T) { return ((size_t)T * c_in * 2 + 255) / 256 * 256; }
+size_t decode_wide_multi_pass_bytes(int n_parts, const paro_w4_weight *const *w, int T)
+{
+    return decode_wide_multi_bytes(n_parts, w, T) + multi_seen_bytes(w[0]->c_in) + n_parts * multi_row_bytes(w[0]->c_in, T);
+}
+paro_half_t *decode_wide_multi_rows(int n_parts, const paro_w4_weight *const *w, int T, void *ws, int part)
+{
+    return (paro_half_t *)((char *)ws + kWsPartialOff + decode_wide_multi_pass_bytes(n_parts, w, T) - (n_parts - part) * multi_row_bytes(w[0]->c_in, T));
 }
 
 // As decode_wide_hosting_pays, of the sum of the outputs, by whole tiles: a last tile per wave that few blocks have does not hide it.
@@ -617,6 +664,8 @@ bool decode_wide_multi_fits(int n_parts, const paro_w4_weight *const *w, int T)
     return g.kb * g.nb <= 256 && g.lds <= kWideLdsBytes && (g.kb == 1 || g.waves <= 8);
 }
 
+// rot NULL: X has the transformed rows of each part, at decode_wide_multi_rows; otherwise the one input of transforms that
+// decode_wide_hosts() accepts.
 hipError_t launch_decode_wide_multi(int n_parts, const paro_rotation *const *rot, const paro_w4_weight *const *w,
                                     const paro_half_t *const *X, int64_t ldx, paro_half_t *const *Y, const int64_t *ldy, int T, void *ws, hipStream_t s)
 {
@@ -628,18 +677,24 @@ hipError_t launch_decode_wide_multi(int n_parts, const paro_rotation *const *rot
         n_all += w[p]->c_out;
     }
     const WideGeometry g = wide_geometry(w[0]->c_in, n_all, T, rot != nullptr, n_parts, w);
-    if (g.kb > 64 || g.lds > kWideLdsBytes || (g.kb > 1 && (!ws || g.waves > 8))) return hipErrorInvalidValue;
+    if (g.kb > 64 || g.lds > kWideLdsBytes || !ws || (g.kb > 1 && g.waves > 8)) return hipErrorInvalidValue;
+    if (!rot)
+        for (int p = 0; p < n_parts; ++p)
+            if (X[p] != decode_wide_multi_rows(n_parts, w, T, ws, p) || ldx != w[0]->c_in) return hipErrorInvalidValue;
+    uint32_t *seen = (uint32_t *)((char *)ws + kWsPartialOff + decode_wide_multi_bytes(n_parts, w, T));
     MultiArgs m;
     m.n_parts = n_parts;
     size_t off = 0;
     int nb = 0;
     for (int p = 0; p < n_parts; ++p) {
         m.part[p] = wide_args(*w[p], X[p], ldx, Y[p], ldy[p], T, ws, off, rot ? rot[p] : nullptr, g);
+        m.seen[p] = rot ? nullptr : seen + (size_t)nb * (w[0]->c_in / kSliceCh);
         nb += (w[p]->c_out / kTileN + g.tiles_per_block - 1) / g.tiles_per_block;
         m.nb_end[p] = nb;
         if (g.kb > 1) off += ((size_t)g.kb * T * w[p]->c_out * sizeof(float) + 255) / 256 * 256;
     }
-    for (int p = n_parts; p < kMaxParts; ++p) { m.part[p] = m.part[0]; m.nb_end[p] = nb; }
+    for (int p = n_parts; p < kMaxParts; ++p) { m.part[p] = m.part[0]; m.nb_end[p] = nb; m.seen[p] = nullptr; }
+    if (!rot && nb > kMaxMultiBlocks) return hipErrorInvalidValue;
     if (hipError_t e = wide_attributes(); e != hipSuccess) return e;
     const dim3 grid(g.kb, nb), block(g.waves * 64);
     if (rot) {

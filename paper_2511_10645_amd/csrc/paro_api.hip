@@ -594,12 +594,13 @@ static paro_status check_multi(int32_t n, const paro_rotation *const *rots, cons
 // on the wide kernel with the transforms per wave (one token); or as one launch for the transforms and the wide kernel behind it.
 // Replayed graphs over 600 MB of weights, us, K-major / the other (110 random shapes, every route forced; sum of the outputs):
 // per wave 4096 -> 28672 16.4 / 14.0, 8192 -> 24784 28.6 / 23.0, but 6656 -> 6288 (3 tiles per wave) 9.1 / 10.6;
-// two launches at 3 and 4 tokens 4096 -> 28672 19.4 / 17.3 and 19.9 / 17.4, 8192 -> 19520 37.0 / 23.9, 6144 -> 8192 14.8 / 12.0
-// (K-major exchanges 2.8, 3.7, 5.0 and 1.6 MB), but 4096 -> 6144 9.4 / 10.1 (0.6 MB), 3072 -> 24576 14.4 / 15.4 (1.8 MB),
-// 2048 -> 40960 17.2 / 18.8 (2.6 MB; few waves per block), 8192 -> 9216 14.5 / 15.6 (1.8 MB; the wide kernel exchanges, too).
+// two launches at 3 and 4 tokens 4096 -> 21760 17.0 / 15.0, 6144 -> 8544 15.0 / 12.6, 5632 -> 15072 18.4 / 15.3, 8192 -> 17280 22.7 / 21.0, at 2
+// 8192 -> 22048 34.7 / 24.6 (K-major exchanges 2.1, 1.6, 2.7, 3.3 and 2.8 MB), but, without what keeps the rows out of the buffer,
+// 4096 -> 6144 9.4 / 10.1 (0.6 MB), 3072 -> 24576 14.4 / 15.4 (1.8 MB), 2048 -> 40960 17.2 / 18.8 (2.6 MB; few waves per block),
+// 8192 -> 9216 14.5 / 15.6 (1.8 MB; the wide kernel exchanges, too).  Nearest to the line: 5632 -> 14656 at 2 tokens 15.6 / 14.9 (1.3 MB),
+// 6144 -> 7040 at 3 12.7 / 11.7 (1.0 MB).
 // Hence the volume from which on they pay: 12 MB over the number of K-slices, seven and more of them, or 2 MB; and the blocks have
 // to fit one round (8192 -> 28656 at 2 tokens 40.1 / 44.7).
-enum MultiRoute { kMultiSeparate, kMultiKMajor, kMultiHosted, kMultiPass };
 static MultiRoute multi_route(int32_t n, const paro_rotation *const *rots, const paro_w4_weight *const *ws_, int32_t T)
 {
     if (!multi_one_launch(n, rots, ws_, T)) return kMultiSeparate;
@@ -610,7 +611,8 @@ static MultiRoute multi_route(int32_t n, const paro_rotation *const *rots, const
     if (hosts && decode_wide_multi_hosting_pays(c_in, n_all)) return kMultiHosted;
     const double volume = (double)slices * T * (double)n_all * 4.0;
     const double most = T == 1 ? (double)kFusePartialOne : slices > 12 ? 2.0e6 : slices >= 7 ? 12.0e6 / slices : 1.0e18;
-    return volume >= most && decode_wide_multi_fits(n, ws_, T) ? kMultiPass : kMultiKMajor;
+    // (the rows that the transforms hand on lie where the K-major kernel's partial sums would)
+    return volume >= most && decode_wide_multi_fits(n, ws_, T) && decode_wide_multi_pass_bytes(n, ws_, T) <= decode_multi_bytes(n, ws_, T) ? kMultiPass : kMultiKMajor;
 }
 
 static WsLayout ws_layout_multi(int32_t n_parts, const paro_rotation *const *rots, const paro_w4_weight *const *weights,
@@ -623,11 +625,10 @@ static WsLayout ws_layout_multi(int32_t n_parts, const paro_rotation *const *rot
         if (one.scratch_bytes > M.scratch_bytes) M.scratch_bytes = one.scratch_bytes;
     }
     if (multi_one_launch(n_parts, rots, weights, T)) {
+        // the K-major kernel's partial sums, of which every other route needs a part only
         size_t m = kWsPartialOff + round_up(paro::decode_multi_bytes(n_parts, weights, T), 256);
-        m = std::max(m, kWsPartialOff + paro::decode_wide_multi_bytes(n_parts, weights, T));
         if (m > M.exchange_bytes) M.exchange_bytes = m;
-        // (lean: without room for the transformed activations of kMultiPass, which then runs as kMultiKMajor)
-        M.scratch_bytes = lean || multi_route(n_parts, rots, weights, T) != kMultiPass ? 0 : n_parts * round_up((size_t)T * weights[0]->c_in * 2, 256);
+        M.scratch_bytes = 0;
     }
     M.total = M.exchange_bytes + M.scratch_bytes;
     return M;
@@ -645,6 +646,11 @@ size_t paro_workspace_exchange_bytes_multi(int32_t n_parts, const paro_rotation 
 {
     if (check_multi(n_parts, rots, weights) != PARO_OK || T <= 0) return 0;
     return ws_layout_multi(n_parts, rots, weights, T).exchange_bytes;
+}
+
+int paro_internal_multi_plan(int32_t n_parts, const paro_rotation *const *rots, const paro_w4_weight *const *weights, int32_t T)
+{
+    return multi_route(n_parts, rots, weights, T);
 }
 
 paro_status paro_rotated_linear_multi(int32_t n_parts, const paro_rotation *const *rots,
@@ -667,11 +673,9 @@ paro_status paro_rotated_linear_multi(int32_t n_parts, const paro_rotation *cons
         const paro_half_t *x[4] = {X, X, X, X};
         return from_hip(paro::launch_decode_wide_multi(n_parts, rots, weights, x, ldx, Y, ldy, T, ws, (hipStream_t)stream));
     }
-    const WsLayout M = ws_layout_multi(n_parts, rots, weights, T);
-    if (route == kMultiPass && ws_bytes >= M.total) {
-        const size_t one = M.scratch_bytes / n_parts;
+    if (route == kMultiPass) {
         paro_half_t *xr[4] = {};
-        for (int p = 0; p < n_parts; ++p) xr[p] = (paro_half_t *)((char *)ws + (ws_bytes - M.scratch_bytes) / 256 * 256 + p * one);
+        for (int p = 0; p < n_parts; ++p) xr[p] = paro::decode_wide_multi_rows(n_parts, weights, T, ws, p);
         const int c_in = weights[0]->c_in;
         if (paro::launch_rotate_multi(n_parts, rots, X, ldx, xr, c_in, T, (hipStream_t)stream) != hipSuccess) return PARO_ERR_HIP;
         return from_hip(paro::launch_decode_wide_multi(n_parts, nullptr, weights, xr, c_in, Y, ldy, T, ws, (hipStream_t)stream));

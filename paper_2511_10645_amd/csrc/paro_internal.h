@@ -166,10 +166,13 @@ bool decode_wide_operand_pays(int c_in, int T);
 hipError_t launch_decode_wide(const paro_w4_weight &w, const paro_half_t *X, int64_t ldx, paro_half_t *Y, int64_t ldy,
                               int T, void *ws, hipStream_t s, const paro_rotation *rot = nullptr, bool x_operand = false);
 // The wide kernel for several weights of one c_in, up to 4 tokens, in one launch.  X: activations of every part (rot NULL: transformed
-// already).  Workspace: decode_wide_multi_bytes of partial sums.
+// already, at decode_wide_multi_rows).  Workspace: decode_wide_multi_bytes of partial sums, or decode_wide_multi_pass_bytes where rot is
+// NULL; all of it is zero again afterwards, the rows too.
 bool decode_wide_multi_hosting_pays(int c_in, int64_t c_out_sum);
 bool decode_wide_multi_fits(int n_parts, const paro_w4_weight *const *w, int T);
 size_t decode_wide_multi_bytes(int n_parts, const paro_w4_weight *const *w, int T);
+size_t decode_wide_multi_pass_bytes(int n_parts, const paro_w4_weight *const *w, int T);
+paro_half_t *decode_wide_multi_rows(int n_parts, const paro_w4_weight *const *w, int T, void *ws, int part);
 hipError_t launch_decode_wide_multi(int n_parts, const paro_rotation *const *rot, const paro_w4_weight *const *w,
                                     const paro_half_t *const *X, int64_t ldx, paro_half_t *const *Y, const int64_t *ldy, int T,
                                     void *ws, hipStream_t s);
@@ -266,3 +269,6 @@ extern "C" int paro_internal_mxfp4_plan(const paro_mxfp4_weight *w, int32_t T);
 // kPlanRows with `room` bytes for partial tiles: outputs per block (0: launch_linear_direct), slices of K, which instantiation, the
 // stages of a slice and the deeper of its rings.
 extern "C" void paro_internal_rows_plan(const paro_w4_weight *w, int32_t T, size_t room, int32_t out[5]);
+// How paro_rotated_linear_multi runs these parts.
+enum MultiRoute { kMultiSeparate, kMultiKMajor, kMultiHosted, kMultiPass };
+extern "C" int paro_internal_multi_plan(int32_t n_parts, const paro_rotation *const *rots, const paro_w4_weight *const *weights, int32_t T);

@@ -11,6 +11,7 @@ import pytest
 import oracle
 import paro_inputs as pin
 from paro_tol import linear_allowed
+from test_linear_plans import TWO_LAUNCHES, multi_plan
 
 pytestmark = pytest.mark.gpu
 
@@ -112,3 +113,45 @@ def test_nothing_is_written_behind_a_ragged_last_block(P, T, c_in, c_out):
     ws.nbytes = need
     _close(P.paro_rotated_linear(rot, w, torch.as_tensor(x).cuda(), ws), _want(li, x), "guarded")
     assert bool((ws.buf[need:] == 0x5A).all())
+
+
+def _random_part(P, seed, c_in, c_out, n_layers=8):
+    import torch
+    g = torch.Generator(device="cuda").manual_seed(seed)
+    words = lambda *s: torch.randint(-(1 << 31), 1 << 31, s, generator=g, device="cuda", dtype=torch.int32)
+    w = P.W4Weight.from_device(words(c_out, c_in // 8), (0.005 + 0.015 * torch.rand((c_in // 128, c_out), generator=g, device="cuda")).half(),
+                               words(c_in // 128, c_out // 8))
+    P.paro_w4_repack(w)
+    li = pin.make_custom(seed, 1, c_in, 16, n_layers=n_layers)
+    rot = P.Rotation(li.pairs, li.theta, li.ch_scale)
+    P.paro_rotation_plan_build(rot)
+    return rot, w
+
+
+# several transforms of 1..4 tokens that run as one launch for the transforms and one for the products (K in one block and in two, one token
+# and several), beside a call whose exchange part is the larger
+@pytest.mark.parametrize("T,c_in,outs,n_layers", [(3, 4096, (8192, 8208), 8), (4, 4096, (6160, 4096, 4112), 5), (2, 7168, (16384, 2064), 8),
+                                                  (1, 7168, (14336, 14352), 3)])
+def test_transforms_of_several_linears_leave_nothing_behind(P, T, c_in, outs, n_layers):
+    """The rows that the first launch hands to the second lie in the buffer: none of their words may be left in the exchange part
+    of another call, whatever the buffer's size."""
+    import torch
+    print(f"multi in two launches T={T} {c_in} -> {outs}", flush=True)
+    assert multi_plan(T, c_in, outs, n_layers)[0] == TWO_LAUNCHES
+    parts = [_random_part(P, 9400 + 10 * k + T, c_in, n, n_layers) for k, n in enumerate(outs)]
+    rots, weights = [p[0] for p in parts], [p[1] for p in parts]
+    x = torch.as_tensor(_x(9450 + T, T, c_in)).cuda()
+    total, exchange = P.paro_workspace_bytes_multi(rots, weights, T), P.paro_workspace_exchange_bytes_multi(rots, weights, T)
+    want = P.paro_rotated_linear_multi(rots, weights, x, P.Workspace(total))
+    _, other = _random_part(P, 9490, 27648, 5120)
+    xo = torch.as_tensor(_x(9491, 16, 27648)).cuda()
+    larger = P.paro_workspace_exchange_bytes(None, other, 16)
+    assert larger > max(total, exchange)
+    for nbytes in (larger, larger + 4096):
+        ws = P.Workspace(nbytes)
+        first = P.paro_w4a16_linear(other, xo, ws)
+        for _ in range(2):
+            ys = P.paro_rotated_linear_multi(rots, weights, x, ws)
+            assert ws.partials_clean(nbytes) and ws.error_word() == 0
+            assert all(torch.equal(a, b) for a, b in zip(ys, want))
+            assert torch.equal(P.paro_w4a16_linear(other, xo, ws), first)

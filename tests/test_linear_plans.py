@@ -8,6 +8,7 @@ from test_gpu_linear_mid import CASES
 
 FAKE = 0x10000                                        # never dereferenced
 HOSTED, STREAM, GEMM, TILE, OPERAND, ROWS, GENERIC = range(7)
+SEPARATE, K_MAJOR, PER_WAVE, TWO_LAUNCHES = range(4)
 
 
 def plan(T, c_in, c_out, form, rotated):
@@ -29,6 +30,18 @@ def plan_in(T, c_in, c_out, form, rotated, ws_bytes):
     tile, k_slices = ctypes.c_int32(), ctypes.c_int32()
     kernel = f(ctypes.byref(rot) if rotated else None, ctypes.byref(w), T, ws_bytes, ctypes.byref(tile), ctypes.byref(k_slices))
     return kernel, tile.value, k_slices.value
+
+
+def multi_plan(T, c_in, outs, n_layers=8):
+    """The route, and what the two workspace queries give."""
+    L = paro.lib()
+    f = L.paro_internal_multi_plan
+    f.restype, f.argtypes = ctypes.c_int, [ctypes.c_int32, ctypes.c_void_p, ctypes.c_void_p, ctypes.c_int32]
+    rot = _CRotation(c_in, 128, n_layers, 64, FAKE, FAKE, None, 0, FAKE)
+    ws = [_CW4Weight(c_in, n, 128, None, None, None, None, FAKE) for n in outs]
+    rots = (ctypes.c_void_p * len(outs))(*[ctypes.addressof(rot)] * len(outs))
+    weights = (ctypes.c_void_p * len(outs))(*[ctypes.addressof(w) for w in ws])
+    return f(len(outs), rots, weights, T), L.paro_workspace_bytes_multi(len(outs), rots, weights, T), L.paro_workspace_exchange_bytes_multi(len(outs), rots, weights, T)
 
 
 def test_cases_reach_every_kernel():
@@ -160,3 +173,18 @@ def test_few_outputs_on_interchange_weights_take_the_staged_kernel():
     """Above 32 tokens; bare, this against the tiled kernel, us: 15.5 / 45.9, 9.2 / 22.8, 4.3 / 9.4; but 56 / 42, 11.3 / 7.6, and it ends at 256."""
     for T, c_in, c_out, want in ((48, 9600, 2272, ROWS), (64, 4096, 4096, ROWS), (128, 1024, 208, ROWS), (200, 4224, 9408, TILE), (256, 256, 5840, TILE), (257, 1024, 208, TILE)):
         assert plan(T, c_in, c_out, "plain", False)[0] == want, (T, c_in, c_out)
+
+
+def test_several_transforms_need_no_scratch():
+    """1..4 tokens: whatever the route, the workspace is the exchange part of the K-major kernel, which the other routes share."""
+    seen = set()
+    for T in (1, 2, 3, 4):
+        for c_in in (512, 1024, 3584, 4096, 6144, 6656, 8192, 27648):
+            for outs in ((64,), (4096, 1024, 1024), (14336, 14336), (16 * 900, 16 * 899, 16 * 31, 48)):
+                for layers in (8, 3):
+                    route, total, exchange = multi_plan(T, c_in, outs, layers)
+                    seen.add(route)
+                    slices = c_in // 512
+                    k_major = sum((slices * T * n * 4 + 255) // 256 * 256 for n in outs) if slices > 1 else 0
+                    assert total == exchange == 256 + k_major, (T, c_in, outs, layers)
+    assert seen == {K_MAJOR, PER_WAVE, TWO_LAUNCHES}
