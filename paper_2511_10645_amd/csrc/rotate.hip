@@ -34,6 +34,7 @@ __global__ __launch_bounds__(64) void plan_build_kernel(const int16_t *__restric
     __shared__ uint8_t s_keep[kMaxLayers][64], s_send[kMaxLayers][64];
     __shared__ uint8_t s_tmp[3][128];
     __shared__ int s_bad;                                             // the table violates Def. 1 (or an index is out of range)
+    __shared__ int s_wild;                                            // an angle is not finite
 
     const int g = blockIdx.x;
     const int lane = threadIdx.x;
@@ -44,7 +45,7 @@ __global__ __launch_bounds__(64) void plan_build_kernel(const int16_t *__restric
     // no pair of the layer names are paired among themselves with the identity rotation.
     if (lane == 0) {
         uint8_t *used = s_tmp[0];
-        s_bad = 0;
+        s_bad = s_wild = 0;
         for (int l = 0; l < n_layers; ++l) {
             for (int c = 0; c < kGroup; ++c) used[c] = 0;
             int cnt = 0;
@@ -77,6 +78,7 @@ __global__ __launch_bounds__(64) void plan_build_kernel(const int16_t *__restric
             c = (float)cd; s = (float)sd;
             double turns = th * 0.15915494309189535;                  // 1 / (2 pi)
             turns -= floor(turns);
+            if (!(turns >= 0.0)) { s_wild = 1; turns = 0.0; }
             rev = (uint32_t)llrint(turns * 16777216.0) & 0xFFFFFFu;
         }
         s_c[l][lane] = c; s_s[l][lane] = s; s_rev[l][lane] = rev;
@@ -184,6 +186,9 @@ __global__ __launch_bounds__(64) void plan_build_kernel(const int16_t *__restric
         if (l + 1 < n_layers) eps_b = s_eps[s_src[l][lane]];
         else eps_out = eps_send;
     }
+    // An angle in 2^-24 revolutions has no NaN: where one of the group's is not finite (and so are its sine and cosine above), the
+    // scales are.
+    if (s_wild) sia = sib = soa = sob = __builtin_nanf("");
     cout[0 * 64 + lane] = out[0 * 64 + lane];
     cout[1 * 64 + lane] = h16(sia) | (h16(sib) << 16);
     cout[2 * 64 + lane] = h16(soa) | (h16(eps_out > 0 ? sob : -sob) << 16);

@@ -47,3 +47,27 @@ def test_one_token_against_oracle(c_in, c_out):
 @pytest.mark.parametrize("c_in,c_out,blocks", TIGHT)
 def test_no_room_for_all_partial_sums(c_in, c_out, blocks):
     _check(c_in, c_out, 256 + (blocks * c_out * 4 + 255) // 256 * 256)
+
+
+# K-major; transforms per wave, K in one block (8 and 10 waves) and in several; two launches
+@pytest.mark.parametrize("T,c_in,c_out", [(1, 512, 64), (1, 4096, 4096), (1, 1024, 64), (1, 4096, 28672), (1, 5120, 40960), (1, 14336, 4112), (7, 1024, 64)])
+@pytest.mark.parametrize("angle", [float("nan"), float("inf"), float("-inf")])
+def test_angles_that_are_not_finite(T, c_in, c_out, angle):
+    """Cosine and sine of such an angle are NaN, hence every output of the call, whichever kernel it takes; an empty slot's angle counts for
+    nothing."""
+    import torch
+    import paper_2511_10645_amd as P
+    print(f"angle {angle}, T={T} {c_in} -> {c_out}", flush=True)
+    li = pin.make_custom(760, T, c_in, 16)
+    words = lambda *s: torch.randint(-(1 << 31), 1 << 31, s, generator=torch.Generator(device="cuda").manual_seed(c_out), device="cuda", dtype=torch.int32)
+    w = P.W4Weight.from_device(words(c_out, c_in // 8), torch.full((c_in // 128, c_out), 0.01, dtype=torch.float16, device="cuda"), words(c_in // 128, c_out // 8))
+    P.paro_w4_repack(w)
+    for empty in (False, True):
+        pairs, theta = li.pairs.copy(), li.theta.copy()
+        theta[c_in // 128 - 1, 3, 9] = angle
+        if empty:
+            pairs[c_in // 128 - 1, 3, 9] = 0
+        rot = P.Rotation(pairs, theta, li.ch_scale)
+        P.paro_rotation_plan_build(rot)
+        y = P.paro_rotated_linear(rot, w, torch.as_tensor(li.x).cuda(), P.Workspace(P.paro_workspace_bytes(rot, w, T)))
+        assert (torch.isfinite(y) if empty else torch.isnan(y)).all()
