@@ -242,7 +242,8 @@ paro_status paro_rotated_linear_multi(int32_t n_parts, const paro_rotation *cons
  *                                        q = clamp(round(w'/s) + z, 0, 15)          (Eq. 1, b = 4)
  * rot == NULL quantises W as it is.  A rotation needs its plan (PARO_ERR_UNSUPPORTED otherwise).
  * Arithmetic: rotation in fp32; s, z, q decided in fp32 with the fp16-rounded scale that is
- * stored, round-half-to-even; s >= 2^-14; z clamped to 0..15.
+ * stored, round-half-to-even; s >= 2^-14; z clamped to 0..15.  No result of a row depends on the
+ * other rows or on their number: shards of a weight quantise to what the whole does.
  * Outputs (device, written completely): qweight [c_out][c_in/8], scales [c_in/128][c_out],
  * qzeros [c_in/128][c_out/8].  c_in % 128 == 0, c_out % 8 == 0, ldw >= c_in and even, W 4-byte
  * aligned.  Enqueues on `stream`; no workspace. */

@@ -183,11 +183,9 @@ hipError_t launch_linear_generic(const paro_w4_weight &w, const paro_half_t *X, 
 hipError_t launch_quantize(const paro_rotation *rot, const paro_half_t *W, int64_t ldw, int N, int C, uint32_t *qweight,
                            paro_half_t *scales, uint32_t *qzeros, hipStream_t s);
 
-// The same for many rows, 32 to a wave and a transform on the matrix cores (quantize_weight.hip); mx: MXFP4 codes and `bytes`,
-// else INT4 codes, `scales` and `qzeros`.
-bool quantize_tiles_pay(const paro_rotation *rot, bool mx, int N, int C);
-hipError_t launch_quantize_tiles(const paro_rotation *rot, bool mx, const paro_half_t *W, int64_t ldw, int N, int C, uint32_t *codes,
-                                 paro_half_t *scales, uint32_t *qzeros, uint8_t *bytes, hipStream_t s);
+// The same without a transform for many rows, 32 to a wave (quantize_weight.hip).
+bool quantize_plain_pays(int N, int C);
+hipError_t launch_quantize_plain(const paro_half_t *W, int64_t ldw, int N, int C, uint32_t *codes, paro_half_t *scales, uint32_t *qzeros, hipStream_t s);
 
 // Transformed activations quantised to INT4 per (token, group) right after the rotation (rot.plan set).
 hipError_t launch_quantize_act(const paro_rotation &rot, const paro_half_t *X, int64_t ldx, int T, uint32_t *codes,

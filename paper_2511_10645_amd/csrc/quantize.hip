@@ -31,13 +31,14 @@
 //     tie and its neighbours, probed over all exponents; the tests pin those that fp16 inputs and scales reach).
 // Measured over back-to-back calls (before: one row of INT4 weights per wave, plan re-read for each; MXFP4 one row at a
 // time, 14 instructions of thresholds per value): INT4 weight 28672 x 4096 414 -> 146 us (137 with reciprocals in place of the
-// three divisions, bytes picked by permutes and the factor of one left out; without a rotation 97 -> 84; weights of this size
-// now go through the matrix cores, quantize_weight.hip, 84 to 94), MXFP4 activations 2048 x 4096
+// three divisions, bytes picked by permutes and the factor of one left out; without a rotation 97 -> 84, large
+// ones now in quantize_weight.hip), MXFP4 activations 2048 x 4096
 // 21.0 -> 12.2, 2048 x 14336 55.8 -> 35.2 us (11.8 and 35.5 with codes past the L2, as INT4 codes leave it: weights 1 to 7 % faster
 // alone, a GEMM behind as fast over 36 shapes), INT4 activations 24.7 -> 14.3 and 78.3 -> 39.6 us (now 13.9 on the former); 1 x 4096
 // MXFP4 3.0 -> 2.6, INT4 2.9 -> 2.8; the same bits throughout.
 #include "paro_internal.h"
 #include "quantize_common.h"
+#include "rotate_lane.h"
 #include <type_traits>
 
 namespace paro {
@@ -88,6 +89,22 @@ __device__ __forceinline__ float wave_max4(const float (&v)[4])
 constexpr int kRowLane[4] = {0, 32, 16, 48};         // a lane that holds row u's maximum
 __device__ __forceinline__ int row_of_lane(int lane) { return ((lane >> 5) & 1) | ((lane >> 3) & 2); }
 __device__ __forceinline__ float from_lane(float v, int lane) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), lane)); }
+
+// rotate_layers with the order of the two products of every sum written out (the one that is there first is rounded, the
+// later one joins it in a fused multiply-add): a code on a rounding tie must not depend on how the compiler schedules.
+template <int K, int U>
+__device__ __forceinline__ void quant_rotate(const LanePlan<K> &P, float (&a)[U], float (&b)[U])
+{
+#pragma unroll
+    for (int l = 0; l < K; ++l)
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const float na = l == 0 ? fmaf(P.m00[l], a[u], P.m01[l] * b[u]) : fmaf(P.m01[l], b[u], P.m00[l] * a[u]);
+            const float nb = l == 0 ? fmaf(P.m10[l], a[u], P.m11[l] * b[u]) : fmaf(P.m11[l], b[u], P.m10[l] * a[u]);
+            a[u] = na;
+            b[u] = (l + 1 < K) ? __int_as_float(__builtin_amdgcn_ds_bpermute(P.src[l], __float_as_int(nb))) : nb;
+        }
+}
 
 // K < 0: no transform (rows quantised as they are).  U: rows side by side, kQuantRows, or one where the rows do not fill the
 // chip: four rows then only lengthen the chain of one wave.
@@ -315,7 +332,7 @@ static hipError_t launch_quant(const paro_rotation *rot, QuantArgs &a, hipStream
 hipError_t launch_quantize(const paro_rotation *rot, const paro_half_t *W, int64_t ldw, int N, int C, uint32_t *qweight,
                            paro_half_t *scales, uint32_t *qzeros, hipStream_t s)
 {
-    if (quantize_tiles_pay(rot, false, N, C)) return launch_quantize_tiles(rot, false, W, ldw, N, C, qweight, scales, qzeros, nullptr, s);
+    if (!rot && quantize_plain_pays(N, C)) return launch_quantize_plain(W, ldw, N, C, qweight, scales, qzeros, s);
     QuantArgs a{nullptr, (const _Float16 *)W, ldw, N, C, 0, qweight, (_Float16 *)scales, (uint16_t *)qzeros, nullptr};
     return launch_quant<kW4Weight>(rot, a, s);
 }
@@ -338,7 +355,6 @@ hipError_t launch_quantize_act_mxfp4(const paro_rotation &rot, const paro_half_t
 hipError_t launch_quantize_weight_mxfp4(const paro_rotation *rot, const paro_half_t *W, int64_t ldw, int N, int C,
                                         uint32_t *codes, uint8_t *scales, hipStream_t s)
 {
-    if (quantize_tiles_pay(rot, true, N, C)) return launch_quantize_tiles(rot, true, W, ldw, N, C, codes, nullptr, nullptr, scales, s);
     QuantArgs a{nullptr, (const _Float16 *)W, ldw, N, C, 0, codes, nullptr, nullptr, scales};
     return launch_quant<kMxWeight>(rot, a, s);
 }

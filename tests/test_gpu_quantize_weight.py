@@ -1,5 +1,5 @@
-"""Weight-side quantisers on the matrix cores (240000 (row, group) pairs and more): numbers of rows at the edges of a wave's 32 and
-a block's run, few and many layers, both scale orders, and the rows and groups that are transformed pair by pair instead."""
+"""Weight-side quantisers on large weights: numbers of rows that no run or tile divides, few and many layers, both scale orders, special
+values, and a row's independence of the others."""
 import numpy as np
 import pytest
 
@@ -63,11 +63,11 @@ def _tiled(a, rows, cols):
 
 @pytest.mark.parametrize("span", [10, 11, 29])
 @pytest.mark.parametrize("order", [0, 1])
-def test_rows_and_groups_that_go_pair_by_pair(P, span, order):
-    """Layers that name no channel and factors that are powers of two: exact on either way, whose border lies at factors 2^10
-    apart; a NaN stays in its filler pair and must not reach the other channels or rows."""
+def test_a_nan_stays_in_its_pair(P, span, order):
+    """Layers that name no channel and factors that are powers of two, up to 2^29 apart: exact; a NaN stays in its filler pair and must not
+    reach the other channels or rows."""
     import torch
-    print(f"weight quantiser, pairwise rows, factors 2^{span} apart, order={order}", flush=True)
+    print(f"weight quantiser, NaN in a pair, factors 2^{span} apart, order={order}", flush=True)
     R, G = 16, 108                                         # the pattern of 72 rows x 256 channels, repeated
     rng = np.random.default_rng(span)
     W = rng.integers(-60, 61, (72, 256)).astype(np.float16)
@@ -110,7 +110,7 @@ def test_infinities_and_broken_tables(P):
     assert torch.equal(a.qweight[others], b.qweight[others]) and torch.equal(a.scales[:, others], b.scales[:, others])
     assert torch.equal(c.codes[others], d.codes[others]) and torch.equal(c.scales[others], d.scales[others])
     assert torch.equal(a.qweight[5, 16:], b.qweight[5, 16:])              # the row's other groups
-    few = P.paro_w4_quantize(good, bad[:8].contiguous())                  # few rows go pair by pair altogether
+    few = P.paro_w4_quantize(good, bad[:8].contiguous())
     assert torch.equal(b.qweight[5, :16], few.qweight[5, :16]) and torch.equal(b.scales[0, 5:6], few.scales[0, 5:6])
     m = P.paro_mxfp4_quantize_weight(broken, W)
     assert (m.scales[:, 4:8] == 253).all() and torch.equal(m.codes[:, :16], c.codes[:, :16])
@@ -132,3 +132,22 @@ def test_rows_without_a_transform(P):
     codes, scales, zeros = int4_definition(special_rows())
     for r in (4096, 12320):
         assert np.array_equal(_nibbles(whole.qweight[r:r + 8]), codes) and np.array_equal(whole.scales[:, r:r + 8].cpu().numpy().view(np.uint16), scales.T.view(np.uint16))
+
+
+@pytest.mark.parametrize("n_layers,slots", [(8, 64), (1, 64), (8, 8), (1, 8)])
+@pytest.mark.parametrize("order", [0, 1])
+def test_a_row_does_not_depend_on_how_many_there_are(P, n_layers, slots, order):
+    """A weight quantised whole and in shards of rows, as ranks of a parallel layer do it: the same bits, which also says that
+    the whole is decided with the rounding errors of a shard."""
+    import torch
+    print(f"weight quantiser in shards, {n_layers} layers of {slots} pairs, order={order}", flush=True)
+    li = pin.make_custom(6700 + n_layers, 1, 4096, 16, n_layers=n_layers, pairs_per_layer=slots)
+    rot = _rot(P, li.pairs, li.theta, li.ch_scale, order)
+    W = 0.02 * torch.randn((8192, 4096), generator=torch.Generator(device="cuda").manual_seed(slots), device="cuda")
+    W = W.half()
+    whole, mx = P.paro_w4_quantize(rot, W), P.paro_mxfp4_quantize_weight(rot, W)
+    for lo in range(0, 8192, 1024):
+        part, mpart = P.paro_w4_quantize(rot, W[lo:lo + 1024]), P.paro_mxfp4_quantize_weight(rot, W[lo:lo + 1024])
+        assert torch.equal(whole.qweight[lo:lo + 1024], part.qweight) and torch.equal(whole.scales[:, lo:lo + 1024], part.scales)
+        assert torch.equal(whole.qzeros[:, lo // 8:lo // 8 + 128], part.qzeros)
+        assert torch.equal(mx.codes[lo:lo + 1024], mpart.codes) and torch.equal(mx.scales[lo:lo + 1024], mpart.scales)
