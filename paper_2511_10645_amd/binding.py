@@ -3,6 +3,7 @@ from __future__ import annotations
 
 import ctypes
 import os
+import warnings
 
 import numpy as np
 import torch
@@ -54,7 +55,7 @@ def lib():
     """Load libparo.so, building it first only if nothing has been built yet."""
     global _lib
     if _lib is None:
-        if not (os.path.exists(_LIB_PATH) and os.path.exists(_HOST_PATH)):
+        if not os.path.exists(_LIB_PATH):
             from . import build as _build
             _build.build()
         L = ctypes.CDLL(_LIB_PATH)
@@ -122,14 +123,44 @@ def lib():
     return _lib
 
 
+class _CtypesCalls:
+    """The steps of csrc/host_call.cpp without it: the same checks, kernels and results, 2 us of host time a call more."""
+
+    @staticmethod
+    def linear(rot, w, c_out: int, X, Y, buf, nbytes: int):
+        T, ldx = _rows(X)
+        if Y is None:
+            Y, ldy = torch.empty((T, c_out), dtype=torch.float16, device=X.device), c_out
+        else:
+            _, ldy = _rows(Y)
+        args = (ctypes.byref(w), X.data_ptr(), ldx, Y.data_ptr(), ldy, T, _ptr(buf), nbytes, _stream())
+        st = lib().paro_w4a16_linear(*args) if rot is None else lib().paro_rotated_linear(ctypes.byref(rot), *args)
+        return Y if st == PARO_OK else st
+
+    @staticmethod
+    def rotate(rot, c_in: int, X, Xr):
+        T, ldx = _rows(X)
+        if Xr is None:
+            Xr = torch.empty((T, c_in), dtype=torch.float16, device=X.device)
+        _, ldxr = _rows(Xr)
+        st = lib().paro_rotate_scale(ctypes.byref(rot), X.data_ptr(), ldx, Xr.data_ptr(), ldxr, T, _stream())
+        return Xr if st == PARO_OK else st
+
+
 def _native():
-    """The native half of the linear calls (csrc/host_call.cpp), over the same libparo.so."""
+    """The native half of the linear calls (csrc/host_call.cpp), over the same libparo.so; where it is not built, or was built
+    against another torch and does not load, the calls need no more than libparo.so."""
     global _host
     if _host is None:
         lib()
-        from . import paro_host
-        paro_host.types(_CRotation, _CW4Weight)
-        _host = paro_host
+        try:
+            from . import paro_host
+            paro_host.types(_CRotation, _CW4Weight)
+            _host = paro_host
+        except ImportError as e:
+            if os.path.exists(_HOST_PATH):
+                warnings.warn(f"paro_host.so does not load, calls go through ctypes: {e}")
+            _host = _CtypesCalls
     return _host
 
 

@@ -1,5 +1,9 @@
-"""The native half of the Python linear calls: what it refuses without a GPU, and that outputs, streams, strides and errors are
-those of the call."""
+"""The native half of the Python linear calls, and the same steps through ctypes: what they refuse without a GPU, and that outputs, streams,
+strides and errors are those of the call."""
+import os
+import shutil
+import subprocess
+import sys
 import threading
 
 import numpy as np
@@ -35,11 +39,41 @@ def test_refusals_need_no_gpu(P):
         P.paro_rotated_linear(w, rot, x, ws)
 
 
+def test_libparo_alone_is_enough(P, tmp_path):
+    """Without paro_host.so, or with one that does not load, and without any compiler: the library loads and the calls take the same
+    steps through ctypes."""
+    package = os.path.dirname(P.binding.__file__)
+    for broken in (False, True):
+        copy = tmp_path / str(broken) / "paper_2511_10645_amd"
+        copy.mkdir(parents=True)
+        for name in os.listdir(package):
+            if name.endswith(".py") or name == "libparo.so":
+                shutil.copy(os.path.join(package, name), copy / name)
+        if broken:
+            (copy / "paro_host.so").write_bytes(b"not a library")
+        code = """
+import torch, paper_2511_10645_amd as P
+assert P.paro_version() == 110
+w = P.W4Weight.from_device(torch.zeros((64, 64), dtype=torch.int32), torch.zeros((4, 64), dtype=torch.float16), torch.zeros((4, 8), dtype=torch.int32))
+try:
+    P.paro_w4a16_linear(w, torch.zeros((1, 512)))
+except AssertionError:
+    print("refused")
+"""
+        env = {**{k: v for k, v in os.environ.items() if k != "PYTHONPATH"}, "PATH": "/nonexistent", "HIPCC": "/nonexistent"}
+        r = subprocess.run([sys.executable, "-W", "ignore", "-c", code], cwd=tmp_path / str(broken), env=env, capture_output=True, text=True)
+        assert r.returncode == 0 and r.stdout == "refused\n", r.stderr
+
+
 @pytest.mark.gpu
+@pytest.mark.parametrize("native", [True, False])
 @pytest.mark.parametrize("T", [1, 5, 40])
-def test_calls(P, T):
+def test_calls(P, T, native, monkeypatch):
     import torch
-    print(f"host call T={T}", flush=True)
+    print(f"host call T={T} native={native}", flush=True)
+    if not native:
+        monkeypatch.setattr(P.binding, "_host", P.binding._CtypesCalls)
+    assert (P.binding._native().__name__ == "paper_2511_10645_amd.paro_host") == native
     li = pin.make_custom(6910 + T, T, 1024, 272)
     rot, w = P.Rotation(li.pairs, li.theta, li.ch_scale), P.W4Weight(li.qweight, li.scales, li.qzeros)
     P.paro_rotation_plan_build(rot)
