@@ -648,6 +648,8 @@ size_t paro_workspace_exchange_bytes_multi(int32_t n_parts, const paro_rotation 
     return ws_layout_multi(n_parts, rots, weights, T).exchange_bytes;
 }
 
+int paro_internal_quantize_plan(int32_t c_out, int32_t c_in) { return paro::quantize_plain_pays(c_out, c_in); }
+
 int paro_internal_multi_plan(int32_t n_parts, const paro_rotation *const *rots, const paro_w4_weight *const *weights, int32_t T)
 {
     return multi_route(n_parts, rots, weights, T);

@@ -267,6 +267,8 @@ extern "C" int paro_internal_mxfp4_plan(const paro_mxfp4_weight *w, int32_t T);
 // kPlanRows with `room` bytes for partial tiles: outputs per block (0: launch_linear_direct), slices of K, which instantiation, the
 // stages of a slice and the deeper of its rings.
 extern "C" void paro_internal_rows_plan(const paro_w4_weight *w, int32_t T, size_t room, int32_t out[5]);
+// Whether untransformed INT4 rows are quantised 32 to a wave (quantize_weight.hip).
+extern "C" int paro_internal_quantize_plan(int32_t c_out, int32_t c_in);
 // How paro_rotated_linear_multi runs these parts.
 enum MultiRoute { kMultiSeparate, kMultiKMajor, kMultiHosted, kMultiPass };
 extern "C" int paro_internal_multi_plan(int32_t n_parts, const paro_rotation *const *rots, const paro_w4_weight *const *weights, int32_t T);

@@ -92,18 +92,26 @@ def test_multi_qkv_shape_of_the_8b_layer(P):
         assert float((np.abs(ys[k].cpu().numpy().astype(np.float64) - y) / allowed).max()) <= 1.0
 
 
-@pytest.mark.parametrize("T,c_in,c_outs,n_layers", [
-    (1, 1024, (16 * 700, 16 * 331), 8),                             # transforms per wave, one block per row of tiles, ragged shares
+# T, c_in, outputs, layers: on the wide kernel, and short of its lines (test_linear_plans.py asks the library's own choice)
+PER_WAVE = [
+    (1, 1024, (16 * 700, 16 * 315), 8),                             # one block per row of tiles, ragged shares
     (1, 1024, (16 * 130, 16 * 9), 8), (1, 1536, (16 * 13, 16 * 5, 48), 8), (1, 2048, (16 * 300, 64), 8),     # 2 to 4 slices, few tiles per wave
     (1, 6656, (16 * 260, 16 * 256), 8),                             # the same with K over two blocks
     (1, 4608, (16 * 800, 16 * 740), 8),                             # and with nine waves per block
-    (1, 5120, (16 * 1100, 16 * 1100), 3),                           # one token, layers that the kernel cannot host: two launches
-    (3, 4096, (16 * 513, 16 * 5, 16 * 510), 8),                     # two launches, a part of one block
-    (4, 3072, (16 * 640, 16 * 900), 5),
-    (2, 6656, (16 * 1200, 16 * 31), 8),                             # two launches, K over two blocks
-])
+]
+TWO_LAUNCHES = [
+    (1, 5120, (16 * 1240, 16 * 1240), 3),                           # one token, layers that the kernel cannot host
+    (1, 7168, (16 * 900, 16 * 870), 7),                             # the same with K over two blocks
+    (3, 4096, (16 * 513, 16 * 5, 16 * 510), 8),                     # a part of one block
+    (4, 3584, (16 * 640, 16 * 330), 5), (3, 6144, (16 * 220, 16 * 216), 1),
+    (2, 6656, (16 * 1200, 16 * 31), 8),                             # K over two blocks
+]
+SHORT_OF_IT = [(1, 1024, (16 * 700, 16 * 331), 8), (1, 5120, (16 * 1100, 16 * 1100), 3), (4, 3072, (16 * 640, 16 * 900), 5)]
+
+
+@pytest.mark.parametrize("T,c_in,c_outs,n_layers", PER_WAVE + TWO_LAUNCHES + SHORT_OF_IT)
 def test_multi_on_the_wide_kernel(P, T, c_in, c_outs, n_layers):
-    """Against the oracle, with the workspace that the query gives and with the smaller one that the K-major kernel takes."""
+    """Against the oracle, with the workspace that the query gives (all of it exchange part) and nothing left in it."""
     import torch
     say(f"multi, wide kernel T={T} {c_in} -> {c_outs}")
     x, rots, ws, refs = _parts(P, 2200 + T + c_in, T, c_in, c_outs, n_layers=n_layers, bias_on=0)

@@ -4,6 +4,7 @@ import ctypes
 
 import paper_2511_10645_amd as paro
 from paper_2511_10645_amd.binding import _CRotation, _CW4Weight
+import test_gpu_multi
 from test_gpu_linear_mid import CASES
 
 FAKE = 0x10000                                        # never dereferenced
@@ -182,6 +183,23 @@ def test_one_token_on_two_slices():
         w, rot = _CW4Weight(1024, c_out, 128, None, None, None, None, FAKE), _CRotation(1024, 128, 8, 64, FAKE, FAKE, None, 0, FAKE)
         exchange = paro.lib().paro_workspace_exchange_bytes(ctypes.byref(rot), ctypes.byref(w), 1)
         assert exchange == 256 + k_major * (2 * c_out * 4 + 255) // 256 * 256, c_out
+
+
+def test_several_transforms_reach_the_wide_kernel():
+    """Every case that test_gpu_multi.py has there, and with them every form of the two launches: K in one block and in several, one token
+    and more."""
+    assert all(multi_plan(*case)[0] == PER_WAVE for case in test_gpu_multi.PER_WAVE)
+    assert all(multi_plan(*case)[0] == TWO_LAUNCHES for case in test_gpu_multi.TWO_LAUNCHES)
+    assert all(multi_plan(*case)[0] == K_MAJOR for case in test_gpu_multi.SHORT_OF_IT)
+    for cases, forms in ((test_gpu_multi.PER_WAVE, {(True, True), (True, False)}),
+                         (test_gpu_multi.TWO_LAUNCHES, {(one, split) for one in (True, False) for split in (True, False)})):
+        assert forms <= {(case[0] == 1, case[1] > 6144) for case in cases}
+
+
+def test_rows_of_weights_that_are_quantised_32_to_a_wave():
+    """The sizes of test_gpu_quantize_weight.test_rows_without_a_transform, whole and in parts."""
+    pays = paro.lib().paro_internal_quantize_plan
+    assert pays(12328, 256) == 1 and pays(8, 256) == 0
 
 
 def test_several_transforms_need_no_scratch():
