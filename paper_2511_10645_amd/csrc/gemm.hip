@@ -127,12 +127,14 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_w4a16_kernel(GemmArgs a)
     _Float16 *As = smem;                                   // [2][BM][kLdsRow]
     _Float16 *Bs = smem + 2 * BM * kLdsRow;                // [2][kBN][kLdsRow]
 
-    // ---- block -> (slice of K, m tile, n tile): whole rounds of 256 in patches of 32, the rest in equal runs ------------
+    // block -> (slice of K, m tile, n tile): whole rounds of 256 in patches of 32, the rest in equal runs.  Slices of a tile
+    // are neighbours, so that an XCD has all of K of few tiles (slice by slice it reads a part of every row of codes: 4096 -> 4096
+    // at 256 tokens 25.8 us, this 22.5; 5120 -> 8192 at 35 23.1 / 20.2; 8192 -> 1024 at 512 25.4 / 23.1).
     const int tiles = a.m_tiles * a.n_tiles;
     int idx, mt, ntile;
     if (!tile_index(tiles * (SPLITK ? a.k_split : 1), idx)) return;
-    const int kslice = SPLITK ? idx / tiles : 0;
-    tile_place(SPLITK ? idx % tiles : idx, a.m_tiles, a.n_tiles, mt, ntile);
+    const int kslice = SPLITK ? idx % a.k_split : 0;
+    tile_place(SPLITK ? idx / a.k_split : idx, a.m_tiles, a.n_tiles, mt, ntile);
     const int m0 = mt * BM, n0 = (a.n_tile0 + ntile) * BN;
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
