@@ -401,17 +401,17 @@ hipError_t launch_splitk_reduce(float *partial, int k_split, int T, int n0, int 
     return hipGetLastError();
 }
 
-// Block slots of a launch over m_tiles x n_tiles tiles in XCD patches of powers of two, rounded up to whole rounds of 8: what
-// the plans below count.
-void gemm_patches(int m_tiles, int n_tiles, int &patch_m, int &patch_n, int &blocks)
+// What the plans below count a launch over m_tiles x n_tiles tiles as when they bound its slices of K: the tiles in patches of powers of
+// two, the patches rounded up to 8.  A launch has as many blocks as tiles (tile_order.h); this is up to 2.5 times as
+// many (3 x 20 tiles: 96 for 60, 9 x 17: 384 for 153), and fewer slices than fit one round follow from it.  The plans' constants and
+// gemm_fitted_us were fitted with it, so it stays until both are fitted anew.
+static int plan_slots(int m_tiles, int n_tiles)
 {
-    int pb = 32;                                     // most blocks of a patch (8 x 4 token x output tiles)
+    int pb = 32, patch_m = 1;                        // most tiles of a patch (8 x 4 token x output tiles)
     while (pb > 1 && (long)m_tiles * n_tiles < 8L * pb) pb >>= 1;
-    patch_m = 1;
     while (patch_m * 2 <= pb && patch_m * 2 <= 8 && patch_m * 2 <= m_tiles) patch_m <<= 1;
-    patch_n = pb / patch_m;
-    const int m_patches = (m_tiles + patch_m - 1) / patch_m, n_patches = (n_tiles + patch_n - 1) / patch_n;
-    blocks = (m_patches * n_patches + 7) / 8 * 8 * pb;
+    const int patch_n = pb / patch_m, m_patches = (m_tiles + patch_m - 1) / patch_m, n_patches = (n_tiles + patch_n - 1) / patch_n;
+    return (m_patches * n_patches + 7) / 8 * 8 * pb;
 }
 
 // How a (weight, T) pair is launched.
@@ -445,8 +445,7 @@ static void plan_split(GemmPlan &p, int T, int n_ks, int width, double base_us, 
     p.k_split = 1; p.k_steps = n_ks; p.scratch = 0;
     const int m_tiles = (T + 127) / 128;
     if ((long)m_tiles * p.n_small > 128 || n_ks < 8 || (size_t)T * width * 4 >= (1ull << 31)) return;
-    int pm, pn, slots;
-    gemm_patches(m_tiles, p.n_small, pm, pn, slots);
+    const int slots = plan_slots(m_tiles, p.n_small);
     double best = base_us;
     for (int ks = 2; ks <= n_ks / 4 && (long)slots * ks <= 256; ++ks) {
         const int steps = (n_ks + ks - 1) / ks, split = (n_ks + steps - 1) / steps;
@@ -476,8 +475,7 @@ static GemmPlan plan_gemm(const paro_w4_weight &w, int T)
         // partial tiles cost about their bytes at 9 TB/s (they overlap the tail of the main kernel).
         // 254 -> 236 us on that shape; not worth it for K = 4096.
         if (p.k_split == 1 && T > 512 && (size_t)T * w.c_out * 4 < (1ull << 31)) {
-            int pm, pn, slots;
-            gemm_patches(p.m_big, p.n_all, pm, pn, slots);
+            const int slots = plan_slots(p.m_big, p.n_all);
             double best = (double)n_ks * 1.1 * (double)((tiles + 255) / 256);
             for (int ks = 2; ks <= 4 && (long)slots * ks <= 256 && n_ks / ks >= 32; ++ks) {
                 const int steps = (n_ks + ks - 1) / ks;
@@ -533,7 +531,8 @@ double gemm_estimate_us(const paro_w4_weight &w, int T) { return plan_gemm(w, T)
 // tokens), 6 % off in the mean for unsplit launches, 8 and 14 % for split ones.  (plan_gemm's model ranks its own
 // choices, but is 24 % off as a time.)  Calls with a tail: 3144 timings (393 shapes, 129 to 1024 tokens), 13 % off; 6 % below
 // that fit on purpose, so that none of them runs more than 3 % slower than the GEMM does (a tail charged 0.6 of a round,
-// whatever its size, made that 229: 6144 -> 16496 at 946 tokens 246 us instead of 198).
+// whatever its size, made that 229: 6144 -> 16496 at 946 tokens 246 us instead of 198).  All of these with tiles in patches of
+// powers of two; 635 timings (79 shapes, 33 to 1024 tokens) with tiles dealt evenly: 8 % off unsplit, 6 % split.
 double gemm_fitted_us(const paro_w4_weight &w, int T)
 {
     const GemmPlan p = plan_gemm(w, T);

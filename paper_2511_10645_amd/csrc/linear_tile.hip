@@ -106,8 +106,8 @@ __global__ __launch_bounds__(kTileThreads, 2) void linear_tile_kernel(TileArgs a
 
     // Consecutive tiles - token tiles first, then output tiles, then slices of K - on one XCD: its L2 serves a tile's
     // weights to the further token tiles and a slice's activations to the further output tiles, and every XCD has the
-    // same number of blocks (to one) whatever the counts are.  (The GEMM's patches of powers of two leave XCDs idle at 5
-    // token tiles: 8192 -> 16384 at 640 tokens 300 us against 212.)
+    // same number of blocks (to one) whatever the counts are.  (Patches of powers of two leave XCDs idle at 5 token tiles:
+    // 8192 -> 16384 at 640 tokens 300 us against 212.)
     const int tiles = a.m_tiles * a.n_tiles, all = tiles * a.k_split, per_xcd = (all + 7) / 8;
     const int idx = (int)(blockIdx.x & 7) * per_xcd + (int)(blockIdx.x >> 3);
     if (idx >= all) return;
@@ -316,8 +316,8 @@ __global__ __launch_bounds__(kTileThreads, 2) void linear_tile2_kernel(TileArgs 
 
     // Consecutive tiles - token tiles first, then output tiles, then slices of K - on one XCD: its L2 serves a tile's
     // weights to the further token tiles and a slice's activations to the further output tiles, and every XCD has the
-    // same number of blocks (to one) whatever the counts are.  (The GEMM's patches of powers of two leave XCDs idle at 5
-    // token tiles: 8192 -> 16384 at 640 tokens 300 us against 212.)
+    // same number of blocks (to one) whatever the counts are.  (Patches of powers of two leave XCDs idle at 5 token tiles:
+    // 8192 -> 16384 at 640 tokens 300 us against 212.)
     const int tiles = a.m_tiles * a.n_tiles, all = tiles * a.k_split, per_xcd = (all + 7) / 8;
     const int idx = (int)(blockIdx.x & 7) * per_xcd + (int)(blockIdx.x >> 3);
     if (idx >= all) return;

@@ -215,10 +215,10 @@ LinearRoute linear_route(const paro_w4_weight &w, int64_t ldx, int64_t ldy, int 
                            : (double)(T / kStreamPassTokens + (rem > 16)) * (4.6 + 0.37 * mb + 1.34 * part32) +
                                  (rem > 0 && rem <= 16 ? 3.5 + 0.25 * mb + 1.34 * part16 : 0.0);
     // The kernel between the two (linear_tile.hip) neither walks whole GEMM tiles nor re-reads the weights, but costs
-    // most per product.  The models are 6 to 15 % off, hence 0.9: over 5131 measured bare (shape, tokens) pairs (649 shapes,
-    // 33 to 1024 tokens, every route forced) the choice loses more than 3 % on three (4 % there) and takes 1.32x less
-    // time in the mean than the better of the other two, 1.34x being the best possible (8192 -> 16384 at 640 tokens, not
-    // among them, loses 6 %: 201 us against the GEMM's 189).
+    // most per product.  The models are 6 to 15 % off, hence 0.9: over 635 measured bare (shape, tokens) pairs (79 shapes,
+    // 33 to 1024 tokens, every route forced) it is taken nowhere where it loses 3 %, and the choice takes 1.34x less time in the mean than the
+    // better of the other two, 1.35x being the best possible (8192 -> 16384 at 640 tokens, not among them, loses 7 %: 220 us
+    // against the GEMM's 206; on the other side 15872 -> 560 at 70 stays on the GEMM, 23.0 / 15.5).
     if (T > kStreamPassTokens && T <= kTileMaxTokens && linear_tile_supported(w, false)) {
         const double tile_us = linear_tile_estimate_us(w, T, scratch_bytes);
         if (tile_us < 0.9 * us) return {LinearRoute::kTile, tile_us};

@@ -3,7 +3,7 @@
 // quantize_kernel holds two values of a row per lane and reduces over the wave, 28672 x 4096 84 us; here a wave has 32 rows of one
 // group and lanes r and r + 32 the two halves of row r: a row's extrema are one exchange between the two, its scale and zero point
 // are computed once for the 32 rows, and eight codes of consecutive channels are in one lane.  63 us (295 MB read and written: 60 at
-// the rate of a large copy).  The same bits: no result of a row depends on other rows.
+// the rate of a large copy; 50 where the weight is still in the last-level cache).  The same bits: no result of a row depends on other rows.
 //
 // A transform stays with quantize_kernel.  One matrix per group through the matrix cores, kept as two fp16 parts (22 bits), was built: 139 -> 101
 // us, but it is further off from 64 bits than fp32 coefficients where layers or pairs are few (one layer of 8 pairs 1.4 times), and a
