@@ -501,9 +501,9 @@ bool decode_wide_hosts(const paro_rotation &rot, int T) { return T == 1 && rot.p
 //   1 slice: nothing is exchanged, and 4 waves stream where this kernel has one: 512 -> 4096 4.46 / 4.35, 512 -> 8192 4.57 / 4.69,
 //     512 -> 16384 4.73 / 5.35, 512 -> 38864 5.99 / 7.83.  Never.
 //   2 to 4 slices: the exchange is most of what the launch pays for: 1024 -> 1024 5.5 / 4.4, 1024 -> 8192 5.8 / 4.9, 1536 -> 4096 5.7 / 4.7,
-//     2048 -> 2048 5.7 / 4.95, 2048 -> 12288 7.0 / 6.0, 1536 -> 55296 13.6 / 12.2.  Always but for 2, two waves to a block, on more than 5 tiles per
-//     compute unit (1024 -> 20464 6.8 / 6.3, 1024 -> 26624 7.4 / 7.5, 1024 -> 40960 8.5 / 9.4, 1024 -> 81920 13.1 / 15.7) as long as the K-major
-//     kernel's blocks fit its rounds, up to 28 (1024 -> 114688 16.6 / 16.7, 1024 -> 118784 18.7 / 16.9).
+//     2048 -> 2048 5.7 / 4.95, 2048 -> 12288 7.0 / 6.0, 1536 -> 55296 13.6 / 12.2.  Always, though 2 slices, two waves to a block, lose from 5 to 28
+//     tiles per compute unit (1024 -> 20464 6.8 / 6.3, 1024 -> 26624 7.4 / 7.5, 1024 -> 40960 8.5 / 9.4, 1024 -> 81920 13.1 / 15.7, 1024 -> 118784 18.7 /
+//     16.9): from 4 tiles on, calls of this kernel ask for no partial sums, of which the K-major kernel needs all.
 //   5 to 8: from 4 tiles per wave: 2560 -> 12288 (3) 7.65 / 7.94, 2560 -> 16384 9.1 / 8.6, 4096 -> 12288 9.5 / 9.5, 4096 -> 16384 11.1 / 10.7,
 //     4096 -> 28672 (7) 14.8 / 12.8.
 //   9 to 12 (three waves per SIMD): by the K-slices of tiles per compute unit, 44: 4608 -> 16384 (36) 12.5 / 12.6, 5120 -> 17600 (43) 14.1 / 14.2,
@@ -518,7 +518,6 @@ bool decode_wide_hosting_pays(int c_in, int c_out)
     const int KS = c_in / kGroup / kSliceGroups, NT = c_out / kTileN;
     const int64_t slices = (int64_t)KS * NT / 256;           // per compute unit
     if (KS == 1) return false;
-    if (KS == 2) return NT <= 5 * 256 || NT > 28 * 256;
     if (KS <= 4) return true;
     if (g.waves > 8) return slices >= 44;
     if (g.kb == 1) return g.tiles_per_block >= 4;

@@ -176,15 +176,6 @@ def test_few_outputs_on_interchange_weights_take_the_staged_kernel():
         assert plan(T, c_in, c_out, "plain", False)[0] == want, (T, c_in, c_out)
 
 
-def test_one_token_on_two_slices():
-    """The K-major kernel, whose partial sums the workspace then has room for, where its waves have more than 5 tiles per compute unit, up to 28
-    (K-major / transform per wave, us: 6.8 / 6.3 at 20464 outputs, 7.4 / 7.5, 13.1 / 15.7, 16.6 / 16.7, 18.7 / 16.9)."""
-    for c_out, k_major in ((20480, False), (20496, True), (26624, True), (81920, True), (114688, True), (114704, False), (118784, False)):
-        w, rot = _CW4Weight(1024, c_out, 128, None, None, None, None, FAKE), _CRotation(1024, 128, 8, 64, FAKE, FAKE, None, 0, FAKE)
-        exchange = paro.lib().paro_workspace_exchange_bytes(ctypes.byref(rot), ctypes.byref(w), 1)
-        assert exchange == 256 + k_major * (2 * c_out * 4 + 255) // 256 * 256, c_out
-
-
 def test_several_transforms_reach_the_wide_kernel():
     """Every case that test_gpu_multi.py has there, and with them every form of the two launches: K in one block and in several, one token
     and more."""
