@@ -117,7 +117,8 @@ size_t paro_rotation_plan_bytes(const paro_rotation *rot);
  * (rounded from an fp64 evaluation) and the folded channel scales used by the fast
  * rotation kernels, followed by a compact copy (one angle in 2^-24 revolutions per lane
  * and layer, fp16 scales) for the one-token linear whose waves each transform their own
- * slice of the input channels (Eq. 4, 5 with the sine and cosine taken at run time).
+ * slice of the input channels (Eq. 4, 5 with the sine and cosine taken at run time).  A group
+ * with an angle that is not finite yields NaN outputs.
  * plan_out: device buffer of paro_rotation_plan_bytes(), 256-byte aligned.  rot->plan is
  * ignored. */
 paro_status paro_rotation_plan_build(const paro_rotation *rot, void *plan_out, void *stream);

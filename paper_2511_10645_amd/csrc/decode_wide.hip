@@ -143,7 +143,7 @@ __device__ __forceinline__ const DecodeArgs &part_of(const MultiArgs &m, int &nb
 // call.  The slice of a part's rows that a wave reads is read by the same wave of each of the part's blocks: every one of them sets a
 // word of its own once its rows are in registers, and the part's last block, behind its outputs, clears the slice and the
 // words where all are set (they are long since; the wait is bounded, and for blocks that were dispatched before).  It costs the launch
-// 0.1 to 0.9 us of 11 to 25, 3 % in the mean of 32 shapes; a counter per slice instead of words costs up to 1.7, its
+// 0.1 to 1.0 us of 11 to 25, 2 to 3 % in the mean of 32 shapes; a counter per slice instead of words costs up to 1.7, its
 // adds coming one after the other, and a launch of its own 1.7.
 constexpr int kMaxMultiBlocks = 256;            // of such a launch, over all parts
 
@@ -346,10 +346,13 @@ __global__ __launch_bounds__(MAXW * 64) void decode_wide_kernel(ARGS args)
         if (clears) {
             auto all_set = [&] { return __all(set[0] && set[1] && set[2] && set[3]); };
             for (int spin = 0; spin < kSpinLimit && !all_set(); ++spin) look();
-            if (!all_set() && lane == 0) __hip_atomic_store(a.err, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            for (int b = lane; b < n_blocks; b += 64) __hip_atomic_store(seen + b, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            _Float16 *row = const_cast<_Float16 *>(a.X) + (size_t)ks * kSliceCh + lane * 8;
-            for (int t = 0; t < a.T; ++t) *(u32x4 *)(row + (size_t)t * a.ldx) = u32x4{0, 0, 0, 0};
+            if (all_set()) {
+                for (int b = lane; b < n_blocks; b += 64) __hip_atomic_store(seen + b, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                _Float16 *row = const_cast<_Float16 *>(a.X) + (size_t)ks * kSliceCh + lane * 8;
+                for (int t = 0; t < a.T; ++t) *(u32x4 *)(row + (size_t)t * a.ldx) = u32x4{0, 0, 0, 0};
+            } else if (lane == 0) {                          // left to the readers; the error word asks for the part to be cleared
+                __hip_atomic_store(a.err, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
         }
     }
 }

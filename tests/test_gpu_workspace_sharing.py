@@ -155,3 +155,12 @@ def test_transforms_of_several_linears_leave_nothing_behind(P, T, c_in, outs, n_
             assert ws.partials_clean(nbytes) and ws.error_word() == 0
             assert all(torch.equal(a, b) for a, b in zip(ys, want))
             assert torch.equal(P.paro_w4a16_linear(other, xo, ws), first)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        ys = P.paro_rotated_linear_multi(rots, weights, x, ws)
+    for _ in range(3):                                     # replays, with eager calls on the same buffer between them
+        for y in ys:
+            y.fill_(float("nan"))
+        graph.replay()
+        assert torch.equal(P.paro_w4a16_linear(other, xo, ws), first)
+        assert all(torch.equal(a, b) for a, b in zip(ys, want)) and ws.partials_clean(larger) and ws.error_word() == 0
